@@ -63,3 +63,55 @@ def test_a_fault_in_one_fibre_stays_there(n, D):
     for a, b in zip(clean, got):
         assert torch.equal(a[:, others], b[:, others])
     assert not torch.isfinite(got[0][:, n:2 * n]).all() and not torch.isfinite(got[1][:, 2 * n:3 * n]).all()
+
+
+def chain(a, b, steps):
+    """fp32 sum over `steps` of outer products a(i) * b(i), one multiply-add after the other (products exact, every sum rounded once)."""
+    acc = np.float32(0)
+    for i in steps:
+        acc = (a(i).astype(np.float64) * b(i) + acc).astype(np.float32)
+    return acc
+
+
+def halves(x, y):
+    """x [F, n, D] times y^T, every row of products summed in two halves: what the vector kernels do."""
+    D = x.shape[-1]
+    return sum(chain(lambda d: x[:, :, None, d], lambda d: y[:, None, :, d], range(i * D // 2, (i + 1) * D // 2)) for i in (0, 1))
+
+
+@pytest.mark.parametrize("n,D,fibres", [(16, 64, 96), (11, 128, 96), (32, 128, 48), (24, 100, 48), (64, 128, 24), (40, 64, 24)])
+def test_scores_lose_no_more_than_sums_over_half_rows(n, D, fibres):
+    """Rounding error (2-norm against 64 bits) of one hop and its gradients, against the same hop in fp32 with scores and dP summed over
+    half rows: a longer chain of sums per score, e.g. one over the whole row, gives a larger error (1.3 times and more in o)."""
+    N = n * fibres
+    q, k, v, g = make_inputs(1, N, 1, 1, D, seed=8200 + n + D, dtype="f32", with_grad=True)
+    f = [x.reshape(fibres, n, D) for x in (q, k, v, g)]
+    scale = np.float32(1 / np.sqrt(D))
+
+    s = halves(f[0], f[1]) * scale
+    w = np.exp(s - s.max(-1, keepdims=True))
+    inv = np.float32(1) / w.sum(-1, keepdims=True)
+    p, dp = w * inv, halves(f[3], f[2])
+    ds = p * (dp - (p * dp).sum(-1, keepdims=True))
+    low = [chain(lambda c: w[:, :, c, None], lambda c: f[2][:, c, None], range(n)) * inv,
+           chain(lambda c: p[:, c, :, None], lambda c: f[3][:, c, None], range(n)),
+           chain(lambda c: ds[:, :, c, None], lambda c: f[1][:, c, None], range(n)) * scale]
+
+    q64, k64, v64, g64 = (x.astype(np.float64) for x in f)
+    s = q64 @ k64.swapaxes(1, 2) / np.sqrt(D)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    dp = g64 @ v64.swapaxes(1, 2)
+    ds = p * (dp - (p * dp).sum(-1, keepdims=True))
+    exact = [p @ v64, p.swapaxes(1, 2) @ g64, ds @ k64 / np.sqrt(D)]
+
+    dev = [torch.from_numpy(x).cuda() for x in (q, k, v, g)]
+    plan = ta.ta_plan_create(1, 1, 1, D, (fibres, n), ta.TA_F32, False)
+    o, dx, dq, dk = (torch.zeros_like(dev[0]) for _ in range(4))
+    ta.ta_axis_attn_forward(plan, 1, *dev[:3], ta.TA_VIN_O, o)
+    ta.ta_axis_attn_backward(plan, 1, *dev[:3], ta.TA_VIN_O, dev[3], dx, dq, dk, False)
+    for name, got, ref, low_one in zip(("o", "dx", "dq"), (o, dx, dq), exact, low):
+        got = got.cpu().numpy().reshape(fibres, n, D).astype(np.float64)
+        size = np.linalg.norm(ref)
+        err, bound = np.linalg.norm(got - ref) / size, np.linalg.norm(low_one - ref) / size
+        assert err <= bound, f"{name}: {err:.3e}, with half rows {bound:.3e}"
