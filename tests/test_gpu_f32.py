@@ -115,3 +115,31 @@ def test_scores_lose_no_more_than_sums_over_half_rows(n, D, fibres):
         size = np.linalg.norm(ref)
         err, bound = np.linalg.norm(got - ref) / size, np.linalg.norm(low_one - ref) / size
         assert err <= bound, f"{name}: {err:.3e}, with half rows {bound:.3e}"
+
+
+@pytest.mark.parametrize("n", [7, 16, 25, 32, 45])
+def test_turned_rows_are_rounded_once(n):
+    """With an upstream gradient on one row a of a fibre only, dK of position 0 (which is not turned back) is a multiple of the turned
+    query row a: two roundings, one of the turned row and one of the product, each 2.5e-8 in the 2-norm on average (an error evenly
+    spread up to half a unit in the last place of mantissas of every size), 3.5e-8 together; a row turned in fp32 arithmetic
+    carries 4.2e-8 and gives 4.9e-8."""
+    H, D, fibres = 4, 64, 64
+    N = n * fibres
+    q, k, v, g = make_inputs(1, N, H, H, D, seed=8250 + n, dtype="f32", with_grad=True)
+    rows = np.arange(fibres) % (n - 1) + 1                     # the row of each fibre that has a gradient
+    keep = np.zeros((fibres, n, 1, 1), np.float32)
+    keep[np.arange(fibres), rows] = 1
+    g = (g.reshape(fibres, n, H, D) * keep).reshape(1, N, H, D)
+    dev = [torch.from_numpy(x).cuda() for x in (q, k, v, g)]
+    plan = ta.ta_plan_create(1, H, H, D, (fibres, n), ta.TA_F32, False, rope_base=8192.0)      # (a base whose logarithm, kept in fp32, is exact)
+    dx, dq, dk = (torch.zeros_like(dev[0]) for _ in range(3))
+    ta.ta_axis_attn_backward(plan, 1, *dev[:3], ta.TA_VIN_O, dev[3], dx, dq, dk, False)
+    got = dk.cpu().numpy().astype(np.float64).reshape(fibres, n, H, D)[:, 0]
+    x = q.astype(np.float64).reshape(fibres, n, H, D)[np.arange(fibres), rows]
+    ang = rows[:, None, None] * 8192.0 ** (-np.arange(0, D, 2) / D)
+    turned = np.empty_like(x)
+    turned[..., 0::2] = x[..., 0::2] * np.cos(ang) - x[..., 1::2] * np.sin(ang)
+    turned[..., 1::2] = x[..., 0::2] * np.sin(ang) + x[..., 1::2] * np.cos(ang)
+    turned *= (got * turned).sum(-1, keepdims=True) / (turned * turned).sum(-1, keepdims=True)
+    err = np.sqrt((((got - turned) ** 2).sum(-1) / (turned ** 2).sum(-1)).mean())
+    assert err <= 1.15 * 3.5e-8, f"{err:.3e}"
