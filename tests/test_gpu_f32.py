@@ -143,3 +143,55 @@ def test_turned_rows_are_rounded_once(n):
     turned *= (got * turned).sum(-1, keepdims=True) / (turned * turned).sum(-1, keepdims=True)
     err = np.sqrt((((got - turned) ** 2).sum(-1) / (turned ** 2).sum(-1)).mean())
     assert err <= 1.15 * 3.5e-8, f"{err:.3e}"
+
+
+@pytest.mark.parametrize("n,fibres", [(12, 96), (32, 48), (70, 24)])
+def test_weights_lose_no_more_than_expf_of_scaled_scores(n, fibres):
+    """Whole-numbered queries and keys: every score is exact, and the error left is that of the softmax and of the sums after it.  The
+    scale is one whose product with log2(e) loses 7e-8 of itself when it is rounded to fp32."""
+    D, scale = 64, np.float32(0.1813800036907196)
+    N = n * fibres
+    rng = np.random.default_rng(n)
+    q, k = (rng.integers(-2, 3, (1, N, 1, D)).astype(np.float32) for _ in range(2))
+    _, _, v, g = make_inputs(1, N, 1, 1, D, seed=8270 + n, dtype="f32", with_grad=True)
+    f = [x.reshape(fibres, n, D) for x in (q, k, v, g)]
+
+    s = (f[0] @ f[1].swapaxes(1, 2)) * scale
+    w = np.exp(s - s.max(-1, keepdims=True))
+    inv = np.float32(1) / w.sum(-1, keepdims=True)
+    low = [chain(lambda c: w[:, :, c, None], lambda c: f[2][:, c, None], range(n)) * inv,
+           chain(lambda c: (w * inv)[:, c, :, None], lambda c: f[3][:, c, None], range(n))]
+    q64, k64, v64, g64 = (x.astype(np.float64) for x in f)
+    s = q64 @ k64.swapaxes(1, 2) * np.float64(scale)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+
+    dev = [torch.from_numpy(x).cuda() for x in (q, k, v, g)]
+    plan = ta.ta_plan_create(1, 1, 1, D, (fibres, n), ta.TA_F32, False, scale=float(scale))
+    o, dx, dq, dk = (torch.zeros_like(dev[0]) for _ in range(4))
+    ta.ta_axis_attn_forward(plan, 1, *dev[:3], ta.TA_VIN_O, o)
+    ta.ta_axis_attn_backward(plan, 1, *dev[:3], ta.TA_VIN_O, dev[3], dx, dq, dk, False)
+    for name, got, ref, low_one in zip(("o", "dx"), (o, dx), (p @ v64, p.swapaxes(1, 2) @ g64), low):
+        got = got.cpu().numpy().reshape(fibres, n, D).astype(np.float64)
+        size = np.linalg.norm(ref)
+        err, bound = np.linalg.norm(got - ref) / size, np.linalg.norm(low_one - ref) / size
+        assert err <= bound, f"{name}: {err:.3e}, with expf {bound:.3e}"
+
+
+def test_scores_at_the_ends_of_the_range():
+    """A score of -inf weighs nothing, a row of such scores gives zeros, and NaN and +inf scores give NaN in their own row only."""
+    D, n = 64, 40
+    for rows in (n, 16, 24):                                   # streaming, and tiles of 16 and of 32 rows
+        q, k, v = (torch.ones(1, rows, 1, D, device="cuda") for _ in range(3))
+        v[0, :, 0, :] = torch.arange(rows, device="cuda", dtype=torch.float32)[:, None]
+        q[0, 1], q[0, 2], q[0, 3] = -3e38, 3e38, float("nan")
+        k[0, 0] = 2.0                                          # scores of row 0: key 0 ahead
+        plan = ta.ta_plan_create(1, 1, 1, D, (rows,), ta.TA_F32, False)
+        o = torch.zeros_like(q)
+        ta.ta_axis_attn_forward(plan, 0, q, k, v, ta.TA_VIN_O, o)
+        o = o.cpu()
+        assert (o[0, 1] == 0).all() and torch.isnan(o[0, 2:4]).all()
+        w = torch.exp((k[0, :, 0].double() @ q[0, :, 0].double().T / 8).T.cpu())
+        ref = (w / w.sum(-1, keepdim=True)) @ v[0, :, 0].double().cpu()
+        keep = [r for r in range(rows) if r not in (1, 2, 3)]
+        assert (o[0, keep, 0] - ref[keep]).abs().max() <= TOL["f32"] * rows      # values up to `rows`
