@@ -1,4 +1,4 @@
-"""GPU parity of the fp32 matrix kernels at the sizes where they can go wrong: one fibre and many per 32-row tile,
+"""GPU parity of the fp32 matrix kernels at the sizes where they can go wrong: one fibre and many per tile,
 axes on both sides of a tile, row widths on both sides of the 32-, 64- and 128-wide tiles, grouped heads, every mask, the
 encoding; and a fault (infinity) in one fibre that must not reach the fibres that share its tile."""
 import numpy as np
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # dims, B, Hq, Hkv, D, causal, window, valid_len, rope base
-    ((1, 5, 16), 1, 3, 3, 64, False, None, None, None),        # unit axis: 32 fibres per tile; a last tile that is part full
+    ((1, 5, 16), 1, 3, 3, 64, False, None, None, None),        # unit axis: 16 fibres per tile; a last tile that is part full
     ((17, 31), 2, 2, 1, 32, True, None, None, None),           # one fibre per tile
     ((32, 33), 1, 4, 2, 36, True, (0, 9), 1000, None),         # a whole tile; one row more than a tile
     ((9, 64), 1, 1, 1, 128, False, None, None, None),
@@ -39,30 +39,71 @@ def test_fp32_hops_match_oracle(dims, B, Hq, Hkv, D, causal, window, valid_len, 
     check_backward(grads, q, k, v, d_o, dims, causal, "f32", valid_len=valid_len, **kw)
 
 
-@pytest.mark.parametrize("n,D", [(8, 64), (5, 128), (16, 32)])
+@pytest.mark.parametrize("n,D", [(8, 64), (5, 128), (4, 32)])
 def test_a_fault_in_one_fibre_stays_there(n, D):
-    """Fibres of the last axis share tiles: an infinity in one fibre's values or upstream gradient leaves the results of
+    """Fibres of the last axis share tiles: an infinity or NaN in one fibre's rows of any input leaves the results of
     every other fibre what they are without it (same bits: the same sums in the same order, with zeros beside them)."""
     dims, H = (9, n), 2
     N = 9 * n
     q, k, v, d_o = (torch.from_numpy(x).cuda() for x in make_inputs(1, N, H, H, D, seed=811, dtype="f32", with_grad=True))
     plan = ta.ta_plan_create(1, H, H, D, dims, ta.TA_F32, False)
 
-    def run(v, g):
+    def run(q, k, v, g):
         o, dx, dq, dk = (torch.zeros_like(q) for _ in range(4))
         ta.ta_axis_attn_forward(plan, 1, q, k, v, ta.TA_VIN_O, o)
         ta.ta_axis_attn_backward(plan, 1, q, k, v, ta.TA_VIN_O, g, dx, dq, dk, False)
         return [t.cpu() for t in (o, dx, dq, dk)]
 
-    clean = run(v, d_o)
-    bad_v, bad_g = v.clone(), d_o.clone()
-    bad_v[0, n + 1, :, 3] = float("inf")                       # fibre 1
-    bad_g[0, 2 * n, :, 0] = float("nan")                       # fibre 2
-    got = run(bad_v, bad_g)
-    others = [t for t in range(N) if t // n not in (1, 2)]
+    clean = run(q, k, v, d_o)
+    bad = [x.clone() for x in (q, k, v, d_o)]
+    bad[2][0, n + 1, :, 3] = float("inf")                      # fibre 1
+    bad[3][0, 2 * n, :, 0] = float("nan")                      # fibre 2
+    bad[0][0, 4 * n + 1, :, 2] = float("nan")                  # fibre 4
+    bad[1][0, 6 * n, :, 1] = float("inf")                      # fibre 6
+    got = run(*bad)
+    others = [t for t in range(N) if t // n not in (1, 2, 4, 6)]
     for a, b in zip(clean, got):
         assert torch.equal(a[:, others], b[:, others])
-    assert not torch.isfinite(got[0][:, n:2 * n]).all() and not torch.isfinite(got[1][:, 2 * n:3 * n]).all()
+    for result, fibre in ((0, 1), (1, 2), (0, 4), (2, 4), (0, 6), (3, 6)):
+        assert not torch.isfinite(got[result][:, fibre * n:(fibre + 1) * n]).all()
+
+
+@pytest.mark.parametrize("n,D,causal,window,valid", [
+    (6, 64, False, 0, 20), (12, 128, True, 0, 17), (24, 64, False, 0, 40), (30, 100, True, 5, 70), (100, 64, False, 0, 37), (100, 128, True, 0, 150),
+    (130, 36, False, 9, 300), (65, 128, False, 0, 64)])
+def test_values_that_no_row_sees_reach_none(n, D, causal, window, valid):
+    """Padding is never attended to and gives zeros, whatever its rows hold: with infinities and NaN in the padding of K and the
+    values, every output is what it is with zeros there (same bits).  The same for keys that a row does not see for any other reason:
+    an infinity in one value row reaches the rows that see it, and no others."""
+    for dims, axis in (((4, n), 1), ((n, 3), 0)):
+        N, H = int(np.prod(dims)), 2
+        q, k, v = (torch.from_numpy(x).cuda() for x in make_inputs(1, N, H, H, D, seed=812, dtype="f32"))
+        valid = min(valid, N)
+        plan = ta.ta_plan_create(1, H, H, D, dims, ta.TA_F32, causal, window=tuple(window if i == axis else 0 for i in range(2)), valid_len=valid)
+
+        def run(k, v):
+            o = torch.full_like(q, 7.0)
+            ta.ta_axis_attn_forward(plan, axis, q, k, v, ta.TA_VIN_O, o)
+            return o.cpu()
+
+        k[:, valid:], v[:, valid:] = 0.0, 0.0
+        clean = run(k, v)
+        bad_k, bad_v = k.clone(), v.clone()
+        bad_k[:, valid:], bad_v[:, valid:] = float("nan"), float("inf")
+        bad_v[:, valid::2] = float("nan")
+        got = run(bad_k, bad_v)
+        assert torch.equal(got, clean) and (got[:, valid:] == 0).all()
+
+        stride = N // n if axis == 0 else 1
+        c = min(n - 1, (valid - 1) // stride if axis == 0 else valid - 1) // 2      # a real key of the first fibre
+        bad_v = v.clone()
+        bad_v[:, c * stride, :, 1] = float("inf")
+        got = run(k, bad_v)
+        for a in range(n):
+            sees = a * stride < valid and (not causal or c <= a) and (not window or abs(a - c) < window)
+            row, ref = got[0, a * stride], clean[0, a * stride]
+            assert torch.equal(row[:, 0], ref[:, 0]) or sees            # (another order of sums where it is seen)
+            assert torch.isinf(row[:, 1]).all() if sees else torch.equal(row, ref)
 
 
 def chain(a, b, steps):
