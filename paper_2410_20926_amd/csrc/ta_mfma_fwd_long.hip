@@ -6,16 +6,18 @@
 // wave fetches its share of a block's K and value rows, which enter LDS once for all of them (two buffers, one barrier
 // per block; the block after next is requested when a block is written, so its rows have a whole block's work to
 // arrive).  Per block a wave forms S^T = K Q^T for two 32-key tiles, the softmax of 64 keys at once, O^T += V^T P^T.
-//   The reference value of a row's weights moves only when the row's maximum passes it by more than 2^kSlack (weights up to 2^kSlack
-// keep their relative precision in bf16 and the sums are fp32), so that the accumulators are rarely rescaled; the sum of the
-// ROUNDED weights is one dot product per pair of weights.
-//   What bounds it: for long axes the matrix, vector and LDS pipes about equally (per 64-key block a wave needs 32 matrix instructions
-// of 32 cycles, some 900 cycles of vector work and 256 of the CU's LDS), on short ones memory and the wait for the first rows.
-// The kernel it replaces took 32 keys per barrier, rescaled the accumulators for every tile and, without groups of four heads, fetched
-// every K and V row once per query tile.  32 / 8 heads of width 128, causal: 32,768 keys 10.8 -> 8.75 ms (1.0 PFLOP/s; a large bf16
-// matrix product reaches 1.15 on this card), 4,096 x 8 (per-head value input) 1.81 -> 1.24 ms, 128 x 128 (per-head value input) 117 -> 84 us;
-// 8 heads of 1,024 x 16: 119 -> 76 us, of width 64, 512 x 64: 72 -> 55 us.
+//   The weights of each 32-key tile are rounded relative to the row's maximum up to that tile (see below), and the accumulators are
+// rescaled only when some row's maximum has grown; the sum of the ROUNDED weights is one dot product per pair of weights.  A tile that
+// no row of the query tile sees (half of a diagonal block, padding) is left out.
+//   What bounds it: for long axes the matrix pipe (per 64-key block a wave needs 32 matrix instructions of 32 cycles) and the vector
+// pipe (32 exponentials of 16 cycles, as much again for the rest, 256 cycles for each rescaling), on short ones memory and the wait for the
+// first rows.  The kernel it replaces took 32 keys per barrier, rescaled the accumulators for every tile and, without groups of four heads,
+// fetched every K and V row once per query tile.  32 / 8 heads of width 128: 32,768 keys, causal, 10.9 -> 9.9 ms (0.9 PFLOP/s; a
+// large bf16 matrix product reaches 1.15 on this card), 4,096 keys, not causal, 405 -> 375 us; with the second hop, 128 x 128, 200 -> 184 us;
+// 8 heads of 1,024 x 16: 140 -> 116 us, of width 64, 512 x 64: 101 -> 86 us.  (A reference that moved only when the maximum had passed
+// it by 2^6 took 8.7 ms, with 3 per cent more error.)
 #include "ta_mfma_common.h"
+#include <type_traits>
 
 namespace ta {
 namespace {
@@ -23,7 +25,12 @@ namespace {
 using namespace mfma;
 
 constexpr int kKeys = 64;                                 // keys of a block
-constexpr float kSlack = 6.f;
+
+// Maximum of a lane's and lane ^ 32's value, without a trip through LDS.
+__device__ inline float both_halves_max(float x) {
+    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(y[0]), __uint_as_float(y[1]));
+}
 
 struct LongParams {
     uint32_t heads;                                       // query heads of a group per workgroup: 1 or 4
@@ -80,18 +87,18 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
         visible_range(qrow, 0, n, p.causal, p.window, klo, khi);
         khi = min(khi, nreal);
     }
-    // key blocks that some row of the workgroup sees, and that some row of this wave's tile sees
-    auto blocks = [&](int first, int last, int& jb, int& je) {
+    // key blocks that some row of the workgroup sees, and key tiles (half blocks) that some row of this wave's tile sees
+    auto keys = [&](int first, int last, int size, int& begin, int& end) {
         int lo, hi, lo2, hi2;
         visible_range(min(first, n - 1), 0, n, p.causal, p.window, lo, hi);
         visible_range(min(last, n - 1), 0, n, p.causal, p.window, lo2, hi2);
-        jb = max(lo, 0) / kKeys;
-        je = (min(hi2, n) + kKeys - 1) / kKeys;
+        begin = max(lo, 0) / size;
+        end = (min(hi2, nreal) + size - 1) / size;
     };
     int jb, je, wb, we;
-    blocks(qb * tiles * kTile, (qb + 1) * tiles * kTile - 1, jb, je);
-    blocks(qt * kTile, qt * kTile + kTile - 1, wb, we);
-    if (qt * kTile >= n) we = wb;
+    keys(qb * tiles * kTile, (qb + 1) * tiles * kTile - 1, kKeys, jb, je);
+    keys(qt * kTile, qt * kTile + kTile - 1, kTile, wb, we);
+    if (qt * kTile >= nreal) we = wb;
 
     // this wave's share of block j: rows w * kRowsPerPass + lrow + i * kRows
     struct Raw { u32x4 v[kMine]; uint32_t mis; };
@@ -155,6 +162,7 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
     const uint32_t nat = (uint32_t)(r32 * G::kPitch + hf * 16);
     const uint32_t trn = (uint32_t)((4 * hf + ((lane & 15) >> 2)) * G::kPitch + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2);
     const float sl2 = p.scale * kLog2e;
+    const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
     float m = -INFINITY, l = 0.f;                         // reference value (log2 domain); sum of this lane's weights
     f32x16 ot[G::kDTiles];
 #pragma unroll
@@ -171,69 +179,84 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
             request(kbase, lp.k_row, j + 2, kr);
             request(vbase, lp.v_row, j + 2, vr);
         }
-        if (j >= wb && j < we) {
-            const char* kt = sK + slot * kBlock + nat;
-            f32x16 st[2] = {};
+        // key tiles of the block that some row of the query tile sees: the other half of a diagonal block and padding are left out
+        const int first = max(2 * j, wb) - 2 * j, end = min(2 * j + 2, we) - 2 * j;
+        if (first < end) {
+            // weights of TILES tiles from `first` on, sums and maxima moved on; the first tile's value operands are on their way meanwhile
+            u32x4 vop[G::kDTiles][2], pop[2][2];
+            float corr[2] = {1.f, 1.f};
+            bool grows[2] = {false, false};
+            auto values = [&](int t) { read_transposed<D>(sV + slot * kBlock + t * (kTile * G::kPitch) + trn, vop); };
+            auto weights = [&](auto tag) {
+                constexpr int TILES = decltype(tag)::value;
+                const char* kt = sK + slot * kBlock + first * (kTile * G::kPitch) + nat;
+                f32x16 st[TILES] = {};
 #pragma unroll
-            for (int s = 0; s < G::kKSteps; ++s)
+                for (int s = 0; s < G::kKSteps; ++s)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) st[t] = mma(*reinterpret_cast<const u32x4*>(kt + t * (kTile * G::kPitch) + 32 * s), qop[s], st[t]);
-            // masked keys; a block that every row of the tile sees whole skips this
-            const int lo = klo - kKeys * j, hi = khi - kKeys * j;
-            uint32_t vis[2];
+                    for (int t = 0; t < TILES; ++t) st[t] = mma(*reinterpret_cast<const u32x4*>(kt + t * (kTile * G::kPitch) + 32 * s), qop[s], st[t]);
+                values(first);
+                // masked keys; tiles that every row sees whole skip this
+                uint32_t vis[TILES], all = 0xffffffffu;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                vis[t] = range_mask(min(max(lo - kTile * t, 0), kTile), min(max(hi - kTile * t, 0), kTile));
-                if (p.mask && 2 * j + t < p.mask_words && qrow < nreal) vis[t] &= table_word(p, (uint32_t)f, qrow, 2 * j + t);
-            }
-            if (!__all((vis[0] & vis[1]) == 0xffffffffu)) {
+                for (int t = 0; t < TILES; ++t) {
+                    const int c = 2 * j + first + t;
+                    vis[t] = range_mask(min(max(klo - kTile * c, 0), kTile), min(max(khi - kTile * c, 0), kTile));
+                    if (p.mask && qrow < nreal) vis[t] &= table_word(p, (uint32_t)f, qrow, c);
+                    all &= vis[t];
+                }
+                if (!__all(all == 0xffffffffu)) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < TILES; ++t)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        st[t][r] = ((vis[t] >> (4 * hf + 8 * (r / 4) + (r % 4))) & 1u) ? st[t][r] : -INFINITY;
-            }
-            float mx = fmaxf(st[0][0], st[1][0]);
+                        for (int r = 0; r < 16; ++r) st[t][r] = ((vis[t] >> (4 * hf + 8 * (r / 4) + (r % 4))) & 1u) ? st[t][r] : -INFINITY;
+                }
+                // Each tile's weights are relative to the row's maximum up to and including that tile, so that the largest is exactly 1:
+                // relative to the maximum of both tiles, or to one that lags behind, more of them are rounded (3 per cent more error at
+                // 4,096 keys).
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(st[0][r], st[1][r]));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            mx = mx == -INFINITY ? mx : mx * sl2;
-            if (__any(mx > m + kSlack || (m == -INFINITY && mx != -INFINITY))) {
-                const float top = mx > m + kSlack ? mx : m;   // (m = -inf: any finite maximum passes it)
-                const float corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top);
-                m = top;
-                l *= corr;
+                for (int t = 0; t < TILES; ++t) {
+                    float mx = st[t][0];
 #pragma unroll
-                for (int t = 0; t < G::kDTiles; ++t)
+                    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[t][r]);
+                    mx = both_halves_max(mx);
+                    mx = mx == -INFINITY ? mx : mx * sl2;
+                    grows[t] = __any(mx > m);             // (m = -inf: any finite maximum passes it)
+                    const float top = mx > m ? mx : m;
+                    corr[t] = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top);
+                    m = top;
+                    l *= corr[t];
+                    const float ref = m == -INFINITY ? 0.f : m;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) ot[t][r] *= corr;
-            }
-            const float ref = m == -INFINITY ? 0.f : m;
-            u32x4 pop[2][2];
-            const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+                    for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+                        for (int e = 0; e < 4; ++e) {
+                            const int r = 8 * s2 + 2 * e;
+                            const uint32_t pk = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(st[t][r], sl2, -ref)), __builtin_amdgcn_exp2f(fmaf(st[t][r + 1], sl2, -ref)));
+                            l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, l, false);
+                            pop[t][s2][e] = pk;
+                        }
+                }
+            };
+            if (end - first == 2) weights(std::integral_constant<int, 2>{});
+            else weights(std::integral_constant<int, 1>{});
+#pragma unroll 1
+            for (int t = first; t < end; ++t) {           // one body: two would copy the accumulators from one to the other
+                if (grows[0]) {
+#pragma unroll
+                    for (int d = 0; d < G::kDTiles; ++d)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) ot[d][r] *= corr[0];
+                }
 #pragma unroll
                 for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int r = 8 * s2 + 2 * e;
-                        const uint32_t pk = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(st[t][r], sl2, -ref)), __builtin_amdgcn_exp2f(fmaf(st[t][r + 1], sl2, -ref)));
-                        l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, l, false);
-                        pop[t][s2][e] = pk;
-                    }
-            const char* vt = sV + slot * kBlock + trn;
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-                    for (int d = 0; d < G::kDTiles; ++d) {
-                        const char* a0 = vt + (32 * t + 16 * s2) * G::kPitch + 64 * d;
-                        const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a0)));
-                        const u32x2 y = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a0 + 8 * G::kPitch)));
-                        ot[d] = mma(u32x4{x.x, x.y, y.x, y.y}, pop[t][s2], ot[d]);
-                    }
+                    for (int d = 0; d < G::kDTiles; ++d) ot[d] = mma(vop[d][s2], pop[0][s2], ot[d]);
+                if (t + 1 < end) {
+                    values(t + 1);
+                    pop[0][0] = pop[1][0]; pop[0][1] = pop[1][1]; corr[0] = corr[1]; grows[0] = grows[1];
+                }
+            }
         }
         if (!SHORT) __syncthreads();                      // block j has been read, block j + 1 is complete
     }
@@ -250,6 +273,7 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
             u32x2 v;
             v.x = pack_bf16x2(ot[t][4 * q4] * inv, ot[t][4 * q4 + 1] * inv);
             v.y = pack_bf16x2(ot[t][4 * q4 + 2] * inv, ot[t][4 * q4 + 3] * inv);
+            if (l == 0.f) v = u32x2{0u, 0u};              // a row that sees nothing
             *reinterpret_cast<u32x2*>(own + r32 * G::kPitch + (32 * t + 8 * q4 + 4 * hf) * 2) = v;
         }
     lds_wave_sync();
@@ -283,18 +307,22 @@ hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream
          : p.D > 64 ? launch<128, true, ROPE>(p, lp, wide, s) : launch<64, true, ROPE>(p, lp, wide, s);
 }
 
-// Eight query tiles per workgroup from 1,024 positions on (half the K and V rows fetched per query row), else four (two workgroups per
-// CU, and fewer waves without a tile).
+// Eight query tiles per workgroup from 1,024 positions on (half the K and V rows fetched per query row) where that leaves a workgroup for
+// every CU, else four, in twice the workgroups (one head of width 64, 1,024 keys: 23 against 30 us; 4 / 1 heads of width 128, 2,000 keys: 69
+// against 82).
 bool long_params(const HopParams& p, LongParams* lp, bool* wide) {
     if (p.n < 1 || p.D < 8 || p.D > 128 || p.D % 4 != 0 || !mfma_forward_layout_ok(p)) return false;
-    *wide = p.n >= 1024;
     // Heads that share K and the value input, four of them per workgroup on the same query tile(s): the waves' work is equal under
-    // the causal mask and no wave is without a tile (32 / 8 heads of width 128, 200 x 64: 82 against 96 us for tiles of one head; 400 x 50: 147
-    // against 182).
+    // the causal mask and no wave is without a tile.
     lp->heads = p.G % 4 == 0 && p.vin_heads != p.Hq && p.n > 2 * kKeys ? 4u : 1u;
-    const int rows = (*wide ? 8 : 4) / (int)lp->heads * kTile;
-    lp->qblocks = (uint32_t)((p.n + rows - 1) / rows);
-    const int64_t units = (int64_t)p.B * p.fibres * lp->qblocks * p.Hkv;
+    int64_t units = 0;
+    for (const int waves : {8, 4}) {
+        const int rows = waves / (int)lp->heads * kTile;
+        lp->qblocks = (uint32_t)((p.n + rows - 1) / rows);
+        units = (int64_t)p.B * p.fibres * lp->qblocks * p.Hkv;
+        *wide = waves == 8;
+        if (p.n >= 1024 && units * (p.G / (int)lp->heads) >= 256) break;
+    }
     if (units <= 0 || units > 0x7ffffff0LL || p.G > (1 << 19)) return false;
     lp->units = (uint32_t)units;
     lp->q_row = (uint32_t)(p.q.st * 2); lp->k_row = (uint32_t)(p.k.st * 2);
