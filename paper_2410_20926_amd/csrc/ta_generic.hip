@@ -51,6 +51,14 @@ __device__ inline T* row_ptr_w(const Tensor& t, int64_t b, int64_t tok, int64_t 
     return reinterpret_cast<T*>(t.p) + b * t.sb + tok * t.st + h * t.sh;
 }
 
+// Workgroups are numbered over a grid of two dimensions: HIP refuses one of 2^32 lanes or more in a dimension (2^24
+// workgroups of 256).
+__device__ inline int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+inline dim3 grid_of(int64_t blocks) {                     // at most 2^31 workgroups
+    const int64_t x = blocks < ((int64_t)1 << 20) ? blocks : (int64_t)1 << 20;
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+
 // Rotary encoding inside a hop (Sec. 3.2, per-axis positions): sine and cosine of the angle by
 // which feature pair (2 pr, 2 pr + 1) of a row at position a on the hop's axis is turned,
 // a * base^(-2 pr / D), formed in double precision.
@@ -122,7 +130,8 @@ __global__ __launch_bounds__(kThreads) void generic_forward_kernel(HopParams p, 
     float* Ks = Qs + kQB * D;               // [TK][D+1]
     float* Vs = Ks + TK * (D + 1);          // [TK][D]
 
-    int64_t bid = blockIdx.x;
+    int64_t bid = flat_block();
+    if (bid >= (int64_t)p.B * p.Hq * p.fibres * qblocks) return;   // whole workgroup leaves together
     const int qb = (int)(bid % qblocks); bid /= qblocks;
     const int64_t f = bid % p.fibres; bid /= p.fibres;
     const int h = (int)(bid % p.Hq);
@@ -223,7 +232,8 @@ __global__ __launch_bounds__(kThreads) void generic_backward_kernel(BwdParams bp
     float* tB = tA + TK * pitch;            // [TK][D+1]
     float* rowbuf = tB + TK * pitch;        // [kWaves][2][D]
 
-    int64_t bid = blockIdx.x;
+    int64_t bid = flat_block();
+    if (bid >= (int64_t)p.B * p.Hkv * p.fibres) return;   // whole workgroup leaves together
     const int64_t f = bid % p.fibres; bid /= p.fibres;
     const int g = (int)(bid % p.Hkv);
     const int b = (int)(bid / p.Hkv);
@@ -443,9 +453,9 @@ hipError_t launch_generic_forward(const HopParams& p, int dtype, hipStream_t s) 
     const size_t smem = sizeof(float) * ((size_t)kQB * p.D + (size_t)TK * (p.D + 1) + (size_t)TK * p.D);
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     if (dtype == TA_F32)
-        hipLaunchKernelGGL(generic_forward_kernel<float>, dim3((unsigned)blocks), dim3(kThreads), smem, s, p, TK, qblocks);
+        hipLaunchKernelGGL(generic_forward_kernel<float>, grid_of(blocks), dim3(kThreads), smem, s, p, TK, qblocks);
     else
-        hipLaunchKernelGGL(generic_forward_kernel<uint16_t>, dim3((unsigned)blocks), dim3(kThreads), smem, s, p, TK, qblocks);
+        hipLaunchKernelGGL(generic_forward_kernel<uint16_t>, grid_of(blocks), dim3(kThreads), smem, s, p, TK, qblocks);
     return hipGetLastError();
 }
 
@@ -467,9 +477,9 @@ hipError_t launch_generic_backward(const BwdParams& bp, int dtype, hipStream_t s
     const size_t smem = backward_smem(p.n, p.G, p.D);
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     if (dtype == TA_F32)
-        hipLaunchKernelGGL(generic_backward_kernel<float>, dim3((unsigned)blocks), dim3(kThreads), smem, s, bp, TK);
+        hipLaunchKernelGGL(generic_backward_kernel<float>, grid_of(blocks), dim3(kThreads), smem, s, bp, TK);
     else
-        hipLaunchKernelGGL(generic_backward_kernel<uint16_t>, dim3((unsigned)blocks), dim3(kThreads), smem, s, bp, TK);
+        hipLaunchKernelGGL(generic_backward_kernel<uint16_t>, grid_of(blocks), dim3(kThreads), smem, s, bp, TK);
     return hipGetLastError();
 }
 

@@ -236,3 +236,22 @@ def test_scores_at_the_ends_of_the_range():
         ref = (w / w.sum(-1, keepdim=True)) @ v[0, :, 0].double().cpu()
         keep = [r for r in range(rows) if r not in (1, 2, 3)]
         assert (o[0, keep, 0] - ref[keep]).abs().max() <= TOL["f32"] * rows      # values up to `rows`
+
+
+def test_more_workgroups_than_one_grid_dimension_holds():
+    """16,777,280 fibres of an odd-width head, one workgroup each: a one-dimensional grid of 256 lanes per workgroup ends at 2^24."""
+    H, D, dims = 8, 2, (2097160, 2)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, g = (torch.randn((1, dims[0] * 2, H, D), generator=gen, device="cuda") for _ in range(4))
+    plan = ta.ta_plan_create(1, H, H, D, dims, ta.TA_F32, False)
+    o, dx, dq, dk = (torch.full_like(q, 7.0) for _ in range(4))
+    ta.ta_axis_attn_forward(plan, 1, q, k, v, ta.TA_VIN_O, o)
+    ta.ta_axis_attn_backward(plan, 1, q, k, v, ta.TA_VIN_O, g, dx, dq, dk, False)
+    f = [x.view(dims[0], 2, H, D).transpose(1, 2).double() for x in (q, k, v, g)]         # [fibre, head, position, feature]
+    p = torch.softmax((f[0][:, :, :, None] * f[1][:, :, None]).sum(-1) / D ** 0.5, -1)    # [fibre, head, row, key]
+    dp = (f[3][:, :, :, None] * f[2][:, :, None]).sum(-1)
+    ds = p * (dp - (p * dp).sum(-1, keepdim=True)) / D ** 0.5
+    for got, w, x in ((o, p, f[2]), (dx, p.transpose(2, 3), f[3]), (dq, ds, f[1]), (dk, ds.transpose(2, 3), f[0])):
+        ref = (w[..., None] * x[:, :, None]).sum(-2)
+        err = (got.view(dims[0], 2, H, D).transpose(1, 2) - ref).abs().max().item()
+        assert err <= 8 * TOL["f32"], err                      # sums of a few products up to 40
