@@ -240,7 +240,7 @@ def measure(torch, ta, w, args, steps, warmup):
     groups = {}
     for d, pos, axis, kind, sec in records:
         groups.setdefault((d, pos, axis, kind), []).append(sec)
-    kernel_totals = {}                                   # kernel name -> [bytes, seconds, launches]
+    kernel_totals = {}                                   # kernel name -> [bytes, seconds, launches, device function]
     for (d, pos, axis, kind), ts in groups.items():
         bwd = d == "bwd"
         if d == "fwd2":
@@ -248,30 +248,34 @@ def measure(torch, ta, w, args, steps, warmup):
             if w.backward:                               # plus the write of the O between the two hops
                 nbytes += w.batch * w.seq_len * w.n_q_heads * w.head_dim * 2
             flops = plan.hop_flops(axis, False) + plan.hop_flops(axis + 1, False)
-            name = plan.pair_kernel(axis, kind)
+            name = function = plan.pair_kernel(axis, kind)
         else:
             nbytes = plan.hop_bytes(axis, kind, bwd, bwd and pos != m - 1)
             flops = plan.hop_flops(axis, bwd)
             name = plan.hop_backward_kernel(axis, kind) if bwd else plan.hop_kernel(axis, kind)
+            function = plan.hop_function(axis, kind, bwd)
         avg = sum(ts) / len(ts)
         gbs = nbytes / avg / 1e9
         hops.append({"pass": d, "hop": pos, "axis": axis, "n": w.dims[axis], "kernel": name, "us": round(avg * 1e6, 2),
                      "algorithmic_bytes": nbytes, "GBps": round(gbs, 1), "frac_of_8TBps": round(gbs / HBM_PEAK_GBS, 4),
                      "TFLOPs_executed": round(flops / avg / 1e12, 1)})
-        tot = kernel_totals.setdefault(name, [0.0, 0.0, 0])
+        if d == "fwd" and 0 <= plan.small_pair_position() <= pos:
+            hops[-1]["in_the_step"] = "one launch for the last two hops (mfma_fwd_pair_small_kernel); timed here hop by hop"
+        tot = kernel_totals.setdefault(name, [0.0, 0.0, 0, function])
         tot[0] += nbytes * len(ts)
         tot[1] += sum(ts)
         tot[2] += len(ts)
     # roofline of the dominant kernel (most time in the timed region), all its launches averaged
     dom = max(kernel_totals, key=lambda k_: kernel_totals[k_][1])
-    nb, sec, launches = kernel_totals[dom]
+    nb, sec, launches, function = kernel_totals[dom]
     achieved = nb / sec / 1e9
     # HBM bytes per launch from the hardware counters of an earlier rocprofv3 --pmc run of this
     # command (FETCH_SIZE and WRITE_SIZE, scaled by the copy kernel; see profiles/), when one is stored
     traffic, traffic_source = None, None
     tpath = os.path.join(ROOT, "profiles", f"traffic_{w.name}.json")
     if os.path.exists(tpath):
-        rec = json.load(open(tpath)).get(dom)
+        stored = json.load(open(tpath))
+        rec = stored.get(dom) or stored.get(function)
         if rec:
             traffic = rec["fetch_bytes_per_launch"] + rec["write_bytes_per_launch"]
             traffic_source = (f"stored: profiles/traffic_{w.name}.json, written by `python -m paper_2410_20926_amd.counters` from the "
@@ -317,7 +321,7 @@ def main():
         step_ms[name] = ms
         others[name] = {"tokens_per_s": tps, "ms_per_step": ms, "workload": describe(ow),
                         "roofline_kernel": rf["kernel"], "roofline_GBps": rf["achieved"], "roofline_frac": rf["frac"],
-                        "per_hop": [{k_: h_[k_] for k_ in ("pass", "hop", "n", "kernel", "us", "GBps", "frac_of_8TBps")}
+                        "per_hop": [{k_: h_[k_] for k_ in ("pass", "hop", "n", "kernel", "us", "GBps", "frac_of_8TBps", "in_the_step") if k_ in h_}
                                     for h_ in rf["per_hop"]]}
 
     # the plain copy kernel on 1 GiB (read once, written once): the copy rate this machine reaches, next to the 8 TB/s peak;

@@ -136,15 +136,21 @@ int64_t ta_plan_seq_len(const ta_plan_t* plan);               /* N; -1 on NULL *
 int64_t ta_plan_axis_stride(const ta_plan_t* plan, int axis); /* tokens between neighbours on `axis`; -1 on error */
 int64_t ta_plan_axis_fibres(const ta_plan_t* plan, int axis); /* N / n_axis per (batch, head); -1 on error */
 int     ta_plan_hop_axis(const ta_plan_t* plan, int hop_position); /* axis run at position 0..m-1; -1 on error */
-/* Name of the kernel variant the plan chose for the forward hop on `axis` with value
+/* Name of the kind of kernel the plan chose for the forward hop on `axis` with value
  * input `vin` ("mfma_bf16_n32", "mfma_bf16_n64", "mfma_bf16_stream", their group-shared forms
- * "..._shared" and, when the value input is per key/value head, "..._shared_kv", "generic"); NULL on
- * error.  Static storage. */
+ * "..._shared" and, when the value input is per key/value head, "..._shared_kv"; "generic": every fp32 hop, and
+ * bf16 hops that no bf16 kernel takes); NULL on error.  Static storage.  Several device functions share a name:
+ * ta_plan_hop_function tells them apart. */
 const char* ta_plan_hop_kernel(const ta_plan_t* plan, int axis, int vin);
-/* Same for the backward of that hop ("mfma_bf16_bwd_n32", "mfma_bf16_bwd_blocked" for axes of 33 to
- * 1024 positions, "generic", or "unsupported" when
+/* Same for the backward of that hop ("mfma_bf16_bwd_n32"; "mfma_bf16_bwd_n64" for axes of 33 to 64 positions whose heads
+ * of width 64 or 128 come in groups of 1, 2 or a multiple of 4; "mfma_bf16_bwd_blocked" for other axes of 33 to
+ * 1024 positions; "generic", or "unsupported" when
  * ta_axis_attn_backward would return TA_ERR_UNSUPPORTED); NULL on error. */
 const char* ta_plan_hop_backward_kernel(const ta_plan_t* plan, int axis, int vin);
+/* Name of the device function that ta_axis_attn_forward (backward = 0) or ta_axis_attn_backward (backward != 0) launches
+ * for that hop, as a profiler shows it without its template arguments ("mfma_fwd_long_kernel", "f32_bwd_kernel" ...);
+ * "unsupported", or NULL on error.  Static storage. */
+const char* ta_plan_hop_function(const ta_plan_t* plan, int axis, int vin, int backward);
 
 /* Cost model of one hop (App. C.2, Table 5, with the fibre count N/n_i that Eq. 4
  * implies).  Bytes are ALGORITHMIC HBM bytes: each of Q, K, value-input read once,
@@ -196,8 +202,11 @@ double      ta_plan_pair_bytes(const ta_plan_t* plan, int axis, int vin);
  * hops, or -1 when it runs every hop on its own (no fused kernel for the plan, a hop order other than the
  * default, or a head width that is not a multiple of 32, for which the pair is slower than the two hops).
  * (Where the two innermost axes hold at most 256 tokens the multi-hop forward may run their hops in one launch of its own; that
- * changes neither this answer nor the workspace.) */
+ * changes neither this answer nor the workspace: ta_plan_small_pair_position.) */
 int         ta_plan_fused_position(const ta_plan_t* plan);
+/* Hop position at which ta_multihop_forward runs the last two hops, on small slabs, in one launch (device function
+ * mfma_fwd_pair_small_kernel), or -1. */
+int         ta_plan_small_pair_position(const ta_plan_t* plan);
 
 /* ---- per-axis attention, backward (the paper gives none: Sec. 3.2 only states that a
  *      backward exists; this is the derivative of the hop above) -----------------------

@@ -8,7 +8,7 @@ reads   RAW_DIR/prof_W/W_kernel_stats.csv               kernel trace with --stat
         RAW_DIR/pmc_W_FETCH_SIZE/W_counter_collection.csv, RAW_DIR/pmc_W_WRITE_SIZE/...
         RAW_DIR/sq_W_1/..., RAW_DIR/sq_W_2/...          (optional) compute-unit counters
 writes  OUT/tensattn_W.txt   the summary text
-        OUT/traffic_W.json   {plan kernel name: {fetch_bytes_per_launch, write_bytes_per_launch}}
+        OUT/traffic_W.json   {plan kernel name or device function (traffic_key): {fetch_bytes_per_launch, write_bytes_per_launch}}
 
 HBM traffic arithmetic.  rocprofv3 --pmc reports FETCH_SIZE and WRITE_SIZE per dispatch in KiB:
     bytes(dispatch) = Counter_Value * 1024 * scale,
@@ -48,20 +48,29 @@ def short(name: str):
     return m.group(1) if m else None
 
 
-def plan_name(k: str) -> str:
-    """The plan's name (ta_plan_hop_kernel and friends) of a kernel instantiation."""
+def traffic_key(k: str) -> str:
+    """What bench.py looks a kernel instantiation up by: the plan's name (ta_plan_hop_kernel and friends) where that and the
+    instantiation determine each other, else the device function (ta_plan_hop_function)."""
     base = k.split("<")[0]
     args = [x.strip() for x in k[k.index("<") + 1:k.rindex(">")].split(",")] if "<" in k else []
     if base == "mfma_fwd_pair_kernel": return "mfma_bf16_pair_n32"
     if base == "mfma_bwd_kernel": return "mfma_bf16_bwd_n32"
-    if base == "mfma_bwd2_kernel": return "mfma_bf16_bwd_n64"
-    if base == "mfma_bwd_resident_kernel": return "mfma_bf16_bwd_n64" if args[1] == "2" and args[3] == "false" else "mfma_bf16_bwd_blocked"
-    if base in ("mfma_bwd_stream_kernel", "mfma_bwd_long_kernel"): return "mfma_bf16_bwd_blocked"
     if base == "mfma_fwd_kernel": return "mfma_bf16_n32" if args[1] == "1" else "mfma_bf16_n64"
     if base == "mfma_fwd_shared_kernel": return ("mfma_bf16_n32" if args[1] == "1" else "mfma_bf16_n64") + "_shared" + ("_kv" if args[2] == "true" else "")
-    if base == "mfma_fwd_long_kernel": return "mfma_bf16_stream"          # (the plan's name also says which heads share K: not in the symbol)
-    if base == "mfma_fwd_stream_chunked_kernel": return "mfma_bf16_stream_shared_kv"
-    return k
+    return base
+
+
+def traffic_record(traffic):
+    """{instantiation: {FETCH_SIZE, WRITE_SIZE (bytes per launch), launches}} -> {key: bytes per launch}, the launches of all
+    instantiations with one key taken together."""
+    sums = {}
+    for k, t in traffic.items():
+        f = sums.setdefault(traffic_key(k), {"FETCH_SIZE": 0.0, "WRITE_SIZE": 0.0, "launches": 0})
+        for c in ("FETCH_SIZE", "WRITE_SIZE"):
+            f[c] += t[c] * t["launches"]
+        f["launches"] += t["launches"]
+    return {k: {"fetch_bytes_per_launch": f["FETCH_SIZE"] / f["launches"], "write_bytes_per_launch": f["WRITE_SIZE"] / f["launches"]}
+            for k, f in sums.items()}
 
 
 def counter_rows(path: str):
@@ -110,7 +119,8 @@ def summarise(wl: str, raw: str, out_dir: str) -> str:
                 if not any(abs(x - u) < 0.002 * u for u in uniq):
                     uniq.append(x)
             out.append(f"  {k}: {len(v)} launches, scaled MB per launch (distinct values): " + ", ".join(f"{u / 1e6:.1f}" for u in uniq))
-            traffic.setdefault(k, {})[c] = sum(v) / len(v)
+            t = traffic.setdefault(k, {})
+            t[c], t["launches"] = sum(v) / len(v), len(v)
 
     if os.path.exists(f"{raw}/sq_{wl}_1/{wl}_counter_collection.csv"):
         out.append("\n== compute-unit counters (per launch, averaged over the launches of each kernel) ==")
@@ -137,8 +147,7 @@ def summarise(wl: str, raw: str, out_dir: str) -> str:
     text = "\n".join(out) + "\n"
     os.makedirs(out_dir, exist_ok=True)
     open(os.path.join(out_dir, f"tensattn_{wl}.txt"), "w").write(text)
-    json.dump({plan_name(k): {"fetch_bytes_per_launch": t["FETCH_SIZE"], "write_bytes_per_launch": t["WRITE_SIZE"]} for k, t in traffic.items()},
-              open(os.path.join(out_dir, f"traffic_{wl}.json"), "w"), indent=1)
+    json.dump(traffic_record(traffic), open(os.path.join(out_dir, f"traffic_{wl}.json"), "w"), indent=1)
     return text
 
 

@@ -391,6 +391,22 @@ const char* ta_plan_hop_backward_kernel(const ta_plan_t* pl, int axis, int vin) 
     return "unsupported";
 }
 
+const char* ta_plan_hop_function(const ta_plan_t* pl, int axis, int vin, int backward) {
+    if (!pl || axis < 0 || axis >= pl->order || (vin != 0 && vin != 1)) return nullptr;
+    if (!backward) {
+        const ta::HopParams hp = hop_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr);
+        const int kid = pl->kernel_id[axis][vin];
+        return kid == ta::K_NONE ? "unsupported" : kid == ta::K_GENERIC ? ta::generic_forward_function(hp, pl->desc.dtype) : ta::mfma_forward_function(hp, kid);
+    }
+    const ta::BwdParams bp = bwd_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr, nullptr, nullptr, nullptr, 0);
+    const int id = pl->bwd_id[axis][vin];
+    return id == BWD_NONE ? "unsupported" : id == BWD_GENERIC ? ta::generic_backward_function(bp, pl->desc.dtype) : ta::mfma_backward_function(bp);
+}
+
+int ta_plan_small_pair_position(const ta_plan_t* pl) {
+    return pl && pl->small_pair && ta_plan_fused_position(pl) < 0 ? pl->order - 2 : -1;
+}
+
 static bool pair_ok(const ta_plan* pl, int axis, int vin) {
     return axis >= 0 && axis + 1 < pl->order && pl->pair[axis][vin];
 }

@@ -444,6 +444,11 @@ bool generic_forward_supports(const HopParams& p) {
     return per_seq > 0 && per_seq <= 0x7fffffffLL / ((int64_t)p.B * p.Hq);
 }
 
+const char* generic_forward_function(const HopParams& p, int dtype) {
+    if (dtype != TA_F32 || !f32_forward_supports(p)) return "generic_forward_kernel";
+    return p.n <= 32 ? "f32_fwd_kernel" : "f32_fwd_long_kernel";
+}
+
 hipError_t launch_generic_forward(const HopParams& p, int dtype, hipStream_t s) {
     if (!generic_forward_supports(p)) return hipErrorInvalidValue;
     if (dtype == TA_F32 && f32_forward_supports(p)) return launch_f32_forward(p, s);
@@ -466,6 +471,11 @@ static size_t backward_smem(int32_t n, int32_t G, int32_t D) {
 
 bool generic_backward_supports(const HopParams& p) {
     return backward_smem(p.n, p.G, p.D) <= 64 * 1024 && p.fibres > 0 && p.fibres <= 0x7fffffffLL / ((int64_t)p.B * p.Hkv);
+}
+
+const char* generic_backward_function(const BwdParams& bp, int dtype) {
+    if (dtype != TA_F32 || !f32_backward_supports(bp)) return "generic_backward_kernel";
+    return bp.hop.n <= 32 ? "f32_bwd_kernel" : "f32_bwd_long_kernel";
 }
 
 hipError_t launch_generic_backward(const BwdParams& bp, int dtype, hipStream_t s) {

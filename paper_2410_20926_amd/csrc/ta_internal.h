@@ -105,6 +105,11 @@ hipError_t launch_f32_backward(const BwdParams& bp, hipStream_t s);
 bool       f32_forward_supports(const HopParams& p);
 bool       f32_backward_supports(const BwdParams& bp);
 bool       generic_backward_supports(const HopParams& p);   // the row statistics fit LDS and the grid fits
+// Names of the device functions that the launchers run for a hop they accept.
+const char* generic_forward_function(const HopParams& p, int dtype);
+const char* generic_backward_function(const BwdParams& bp, int dtype);
+const char* mfma_forward_function(const HopParams& p, int kernel_id);
+const char* mfma_backward_function(const BwdParams& bp);
 hipError_t launch_mfma_forward(const HopParams& p, int kernel_id, hipStream_t s);
 hipError_t launch_mfma_forward_stream(const HopParams& p, hipStream_t s);
 hipError_t launch_mfma_forward_long(const HopParams& p, hipStream_t s);
@@ -113,6 +118,7 @@ bool       mfma_forward_supports(int32_t n, int32_t D, int dtype, int* kernel_id
 bool       mfma_forward_layout_ok(const HopParams& p);   // strides and sizes fit the kernel's 32-bit row offsets
 bool       mfma_forward_feasible(const HopParams& p, int kernel_id);   // layout_ok and the launch grid fits
 bool       mfma_forward_stream_feasible(const HopParams& p);
+bool       mfma_forward_stream_chunked(const HopParams& p);   // all query tiles of a fibre in one workgroup
 bool       mfma_backward_supports(const BwdParams& bp, int dtype);
 bool       mfma_backward_is_blocked(const BwdParams& bp, int dtype);   // the variants for axes longer than one tile
 bool       mfma_backward_is_two_tile(const BwdParams& bp, int dtype);  // the variant for axes of two tiles

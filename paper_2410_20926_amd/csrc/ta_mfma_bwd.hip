@@ -1125,6 +1125,21 @@ bool mfma_backward_is_two_tile(const BwdParams& bp, int dtype) {
     return backward_variant(bp, dtype) >= 3 && p.n <= 2 * kTile && (p.D == 64 || p.D == 128) && (p.G <= 2 || p.G % 4 == 0);
 }
 
+// Long axes: the blocked kernel runs a group's heads side by side, a wave each; the long kernel one head after the other, eight
+// tiles at a time.  The former is ahead where it fills the chip and the latter's eight waves have five or six tiles (100 fibres of 129 / 160
+// positions, 16 / 4 heads of width 128: 212 / 245 against 241 / 256 us; from seven tiles on, 200 x 64, 32 / 8 heads: 513 against 440 us).
+static bool runs_blocked(const HopParams& p) { return p.G >= 4 && p.n <= 6 * kTile && (int64_t)p.B * p.Hkv * p.fibres >= 256; }
+
+const char* mfma_backward_function(const BwdParams& bp) {
+    switch (backward_variant(bp, TA_BF16)) {
+        case 1: return "mfma_bwd_kernel";
+        case 2: return runs_blocked(bp.hop) ? "mfma_bwd_stream_kernel" : "mfma_bwd_long_kernel";
+        case 3: return "mfma_bwd2_kernel";
+        case 4: return "mfma_bwd_resident_kernel";
+    }
+    return nullptr;
+}
+
 hipError_t launch_mfma_backward(const BwdParams& user, hipStream_t s) {
     const int variant = backward_variant(user, TA_BF16);
     if (variant == 0) return hipErrorInvalidValue;
@@ -1156,10 +1171,7 @@ hipError_t launch_mfma_backward(const BwdParams& user, hipStream_t s) {
         bp.acc_k = base == 0 ? user.accumulate : 1;
         bp.acc_x = base == 0 ? 0 : 1;
         hipError_t e;
-        // Long axes: the blocked kernel below runs a group's heads side by side, a wave each; the long kernel one head after the other, eight
-        // tiles at a time.  The former is ahead where it fills the chip and the latter's eight waves have five or six tiles (100 fibres of 129 / 160
-        // positions, 16 / 4 heads of width 128: 212 / 245 against 241 / 256 us; from seven tiles on, 200 x 64, 32 / 8 heads: 513 against 440 us).
-        if (variant == 2 && !(G >= 4 && bp.hop.n <= 6 * kTile && (int64_t)bp.hop.B * bp.hop.Hkv * bp.hop.fibres >= 256)) e = launch_mfma_backward_long(bp, s);
+        if (variant == 2 && !runs_blocked(bp.hop)) e = launch_mfma_backward_long(bp, s);
         else if (variant == 2) e = bp.hop.D == 128 ? launch_stream<128, false>(bp, s) : bp.hop.D == 64 ? launch_stream<64, false>(bp, s)
                                  : bp.hop.D > 64 ? launch_stream<128, true>(bp, s) : launch_stream<64, true>(bp, s);
         else if (bp.hop.D == 128) e = launch<128, false>(bp, tp, s);

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         f32x16 dk[R::kHT], dx[R::kHT];
 #pragma unroll
         for (int t = 0; t < R::kHT; ++t) { dk[t] = f32x16{}; dx[t] = f32x16{}; }
-        if (s == 0 && lane < kTile) {                     // (read between barriers (4) and (6) of a head; visible from barrier (1) on)
+        if (s == 0 && lane < kTile) {                     // (read from barrier (4) to barrier (7) of a head; visible from barrier (1) on)
             const uint32_t tok = at.tok0 + (uint32_t)min(kTile * w + lane, n - 1) * stride;
             rowoff[lane] = u32x4{tok * sp.q_row, tok * sp.k_row, tok * sp.v_row, tok * sp.o_row};
         }

@@ -681,6 +681,12 @@ bool mfma_forward_feasible(const HopParams& p, int kernel_id) {
     return make_tile_params(p, KT, &tp);
 }
 
+const char* mfma_forward_function(const HopParams& p, int kernel_id) {
+    if (kernel_id == K_MFMA_BF16_STREAM)
+        return !mfma_forward_stream_feasible(p) ? "mfma_fwd_long_kernel" : mfma_forward_stream_chunked(p) ? "mfma_fwd_stream_chunked_kernel" : "mfma_fwd_stream_shared_kernel";
+    return p.G % kWavesPerBlock == 0 ? "mfma_fwd_shared_kernel" : "mfma_fwd_kernel";
+}
+
 hipError_t launch_mfma_forward(const HopParams& p, int kernel_id, hipStream_t s) {
     if (kernel_id == K_MFMA_BF16_STREAM) return mfma_forward_stream_feasible(p) ? launch_mfma_forward_stream(p, s) : launch_mfma_forward_long(p, s);
     if (!mfma_forward_feasible(p, kernel_id)) return hipErrorInvalidValue;

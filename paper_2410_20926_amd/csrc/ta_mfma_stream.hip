@@ -513,6 +513,11 @@ bool mfma_forward_stream_feasible(const HopParams& p) {
     return stream_params(p, &sp);
 }
 
+bool mfma_forward_stream_chunked(const HopParams& p) {
+    StreamParams sp;
+    return stream_params(p, &sp) && sp.qchunk > 1;
+}
+
 hipError_t launch_mfma_forward_stream(const HopParams& p, hipStream_t s) {
     StreamParams sp;
     if (!stream_params(p, &sp)) return hipErrorInvalidValue;

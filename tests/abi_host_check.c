@@ -56,13 +56,13 @@ int main(void) {
                 for (int a = -1; a <= order; ++a) {
                     (void)ta_plan_axis_stride(p, a); (void)ta_plan_axis_fibres(p, a); (void)ta_plan_hop_axis(p, a);
                     for (int vin = -1; vin <= 2; ++vin) {
-                        (void)ta_plan_hop_kernel(p, a, vin); (void)ta_plan_hop_backward_kernel(p, a, vin);
+                        (void)ta_plan_hop_kernel(p, a, vin); (void)ta_plan_hop_backward_kernel(p, a, vin); (void)ta_plan_hop_function(p, a, vin, 0); (void)ta_plan_hop_function(p, a, vin, 1);
                         (void)ta_plan_pair_kernel(p, a, vin); (void)ta_plan_pair_bytes(p, a, vin);
                         (void)ta_plan_hop_bytes(p, a, vin, 1, 1); (void)ta_plan_hop_flops(p, a, 0);
                     }
                 }
                 (void)ta_plan_workspace_bytes(p, 0); (void)ta_plan_workspace_bytes(p, 1);
-                (void)ta_plan_backward_scratch_bytes(p); (void)ta_plan_fused_position(p);
+                (void)ta_plan_backward_scratch_bytes(p); (void)ta_plan_fused_position(p); (void)ta_plan_small_pair_position(p);
                 ta_plan_destroy(p);
                 calls += 8;
             }

@@ -326,9 +326,42 @@ def test_kernels_for_other_head_widths():
     assert p.hop_backward_kernel(1, ta.TA_VIN_O) == "mfma_bf16_bwd_n32"
     two_tiles = ta.ta_plan_create(1, 32, 32, 100, (64, 16), ta.TA_BF16, True)
     assert two_tiles.hop_kernel(0, ta.TA_VIN_KV) == "mfma_bf16_n64"
-    assert two_tiles.hop_backward_kernel(0, ta.TA_VIN_KV) == "mfma_bf16_bwd_blocked"      # narrow heads stay on the blocked kernel
+    assert two_tiles.hop_backward_kernel(0, ta.TA_VIN_KV) == "mfma_bf16_bwd_blocked"      # narrow heads: no two-tile form
     assert ta.ta_plan_create(1, 32, 8, 128, (64, 16), ta.TA_BF16, True).hop_backward_kernel(0, ta.TA_VIN_KV) == "mfma_bf16_bwd_n64"
     long_axis = ta.ta_plan_create(1, 8, 2, 96, (128, 4), ta.TA_BF16, True)
     assert long_axis.hop_kernel(0, ta.TA_VIN_KV) == "mfma_bf16_stream_shared_kv"
     odd = ta.ta_plan_create(1, 4, 4, 90, (16, 16), ta.TA_BF16, True)       # even, not a multiple of 4
     assert odd.hop_kernel(0, ta.TA_VIN_KV) == "generic"
+
+
+def test_device_functions_of_a_plan():
+    """ta_plan_hop_function tells apart what shares one plan name, and ta_plan_small_pair_position says where two hops are one launch."""
+    def fn(Hq, Hkv, D, dims, axis, vin, backward, dtype=ta.TA_BF16):
+        return ta.ta_plan_create(1, Hq, Hkv, D, dims, dtype, True).hop_function(axis, vin, backward)
+    KV, O = ta.TA_VIN_KV, ta.TA_VIN_O
+    assert fn(4, 4, 64, (16, 4), 0, KV, False, ta.TA_F32) == "f32_fwd_kernel" and fn(4, 4, 64, (33, 4), 0, KV, False, ta.TA_F32) == "f32_fwd_long_kernel"
+    assert fn(4, 4, 64, (32, 4), 0, KV, True, ta.TA_F32) == "f32_bwd_kernel" and fn(4, 4, 64, (33, 4), 0, KV, True, ta.TA_F32) == "f32_bwd_long_kernel"
+    assert fn(4, 4, 90, (16, 4), 0, KV, False, ta.TA_F32) == "generic_forward_kernel" and fn(4, 4, 130, (16, 4), 0, KV, True) == "generic_backward_kernel"
+    assert fn(8, 2, 128, (32, 4), 0, KV, False) == "mfma_fwd_shared_kernel" and fn(8, 8, 128, (64, 4), 0, KV, False) == "mfma_fwd_kernel"
+    assert fn(8, 2, 128, (128, 4), 0, KV, False) == "mfma_fwd_stream_chunked_kernel" and fn(8, 2, 128, (129, 4), 0, KV, False) == "mfma_fwd_stream_shared_kernel"
+    assert fn(8, 2, 128, (96, 4), 0, O, False) == "mfma_fwd_stream_chunked_kernel" and fn(8, 2, 128, (97, 4), 0, O, False) == "mfma_fwd_long_kernel"
+    assert fn(8, 2, 100, (96, 4), 0, O, False) == "mfma_fwd_long_kernel" and fn(8, 2, 128, (1024, 4), 0, KV, False) == "mfma_fwd_long_kernel"
+    assert fn(8, 8, 128, (200, 4), 0, KV, False) == "mfma_fwd_long_kernel"
+    assert fn(8, 2, 128, (32, 4), 0, KV, True) == "mfma_bwd_kernel" and fn(8, 2, 128, (40, 4), 0, KV, True) == "mfma_bwd2_kernel"
+    assert fn(8, 2, 128, (40, 256), 0, KV, True) == "mfma_bwd_resident_kernel" and fn(24, 4, 128, (64, 4), 0, KV, True) == "mfma_bwd_resident_kernel"
+    assert fn(8, 2, 128, (130, 4), 0, KV, True) == "mfma_bwd_long_kernel" and fn(8, 2, 128, (130, 128), 0, KV, True) == "mfma_bwd_stream_kernel"
+    assert fn(8, 1, 64, (4096, 2), 0, KV, True, ta.TA_F32) == "unsupported" and fn(8, 2, 128, (16, 4), 2, KV, False) is None
+    small = lambda *a, **k: ta.ta_plan_create(1, *a, ta.TA_BF16, True, **k).small_pair_position()
+    assert small(8, 2, 128, (5, 10, 9)) == 1 and small(8, 2, 128, (10, 9)) == 0
+    assert small(8, 2, 128, (32, 16, 16)) == 1 and small(4, 4, 128, (3, 16, 16)) == -1       # two tiles per wave: from 256 slabs of a head on
+    assert small(8, 2, 100, (5, 10, 9)) == -1 and small(8, 2, 128, (32, 32)) == -1 and small(8, 2, 128, (10, 9), hop_order=(1, 0)) == -1
+
+
+def test_traffic_of_several_instantiations_is_averaged():
+    from paper_2410_20926_amd import counters
+    rec = counters.traffic_record({
+        "mfma_bwd_resident_kernel<128, 2, 1, false, false>": {"FETCH_SIZE": 4.0, "WRITE_SIZE": 2.0, "launches": 1},
+        "mfma_bwd_resident_kernel<128, 2, 2, false, false>": {"FETCH_SIZE": 1.0, "WRITE_SIZE": 1.0, "launches": 3},
+        "mfma_fwd_shared_kernel<128, 1, true, false, false>": {"FETCH_SIZE": 5.0, "WRITE_SIZE": 3.0, "launches": 7}})
+    assert rec == {"mfma_bwd_resident_kernel": {"fetch_bytes_per_launch": 1.75, "write_bytes_per_launch": 1.25},
+                   "mfma_bf16_n32_shared_kv": {"fetch_bytes_per_launch": 5.0, "write_bytes_per_launch": 3.0}}
