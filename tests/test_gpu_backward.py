@@ -43,7 +43,7 @@ CASES = [
     ((100, 2), 1, 8, 1, 128, False, "bf16"),         # four tiles, 8 heads per group
     ((2, 200), 1, 4, 2, 64, True, "bf16"),           # seven tiles
     ((333,), 1, 2, 2, 128, True, "bf16"),            # one long axis: plain causal attention, 11 tiles
-    ((1024, 2), 1, 4, 1, 128, True, "bf16"),         # the longest axis the blocked kernel takes (more than 64 KB of LDS)
+    ((1024, 2), 1, 4, 1, 128, True, "bf16"),         # the longest axis that has a matrix-core backward (more than 64 KB of LDS)
     ((3, 16, 8), 1, 2, 1, 128, True, "bf16"),        # packed fibres (2 and 4 per tile), 2 heads per group
     ((5, 7, 3), 2, 4, 4, 64, True, "bf16"),          # odd lengths: ragged tiles with padding rows
     ((32, 3), 1, 8, 2, 128, False, "bf16"),
@@ -51,14 +51,14 @@ CASES = [
     ((4, 16), 1, 16, 1, 128, True, "bf16"),          # 16 heads per group: two launches of 8 heads, the second adds to dK, dV
     ((8, 32), 2, 32, 1, 64, True, "bf16"),           # multi-query: 32 heads on one key/value head, four launches
     ((64, 4), 1, 16, 1, 128, False, "bf16"),         # 16 heads per group on a two-tile axis: four launches of 4 heads
-    ((66, 2), 1, 16, 1, 128, False, "bf16"),         # the blocked kernel with 16 heads per group
+    ((66, 2), 1, 16, 1, 128, False, "bf16"),         # the resident kernel with 16 heads per group
     ((6, 5), 1, 12, 1, 64, True, "bf16"),            # 12 heads per group: a launch of 8 and one of 4
     ((8, 16), 1, 7, 1, 128, True, "bf16"),           # 7 heads per group (28 query / 4 key-value heads is a real geometry)
-    ((5, 40), 2, 6, 2, 128, False, "bf16"),          # 3 heads per group, blocked kernel on the second axis
+    ((5, 40), 2, 6, 2, 128, False, "bf16"),          # 3 heads per group, the resident kernel on the second axis
     ((6, 9), 1, 4, 4, 100, True, "bf16"),            # head width 100: 8-byte-granular rows in 128-wide tiles
     ((32, 4, 8), 2, 8, 2, 96, True, "bf16"),         # width 96, groups of 4 heads, three hops (dQ, dK accumulate)
     ((16, 32), 1, 2, 2, 40, False, "bf16"),          # width 40 in 64-wide tiles
-    ((40, 3), 1, 2, 2, 100, True, "bf16"),           # width 100 on an axis of two tiles: the blocked kernel
+    ((40, 3), 1, 2, 2, 100, True, "bf16"),           # width 100 on an axis of two tiles: the resident kernel
     ((3, 90), 1, 4, 1, 96, False, "bf16"),           # width 96, three tiles, a group of 4 heads
     ((32, 8), 2, 16, 2, 128, False, "bf16"),         # 8 heads per group, full-width heads
 ]

@@ -38,7 +38,8 @@ def test_resident_backward_matches_oracle(dims, B, Hq, Hkv, D, causal, window, l
     got, plan, dev = multihop_forward(q, k, v, dims, "bf16", causal, save=True, **pkw)
     ref = orc.tensorized_attention_forward(q, k, v, dims, causal, valid_len=list(lens) if lens else None, **kw)
     assert np.abs(got - ref).max() <= TOL["bf16"]
-    assert plan.hop_backward_kernel(plan.hop_axis(int(np.argmax([33 <= n <= 128 for n in dims]))), ta.TA_VIN_O) in ("mfma_bf16_bwd_blocked", "mfma_bf16_bwd_n64")
+    axis = int(np.argmax([33 <= n <= 128 for n in dims]))
+    assert plan.hop_function(axis, ta.TA_VIN_KV if axis == 0 else ta.TA_VIN_O, True) == "mfma_bwd_resident_kernel"
     grads = multihop_backward(plan, dev, d_o, "bf16")
     check_backward(grads, q, k, v, d_o, dims, causal, "bf16", valid_len=list(lens) if lens else None, **kw)
     again = multihop_backward(plan, dev, d_o, "bf16")

@@ -2,7 +2,7 @@
 4 KB canary regions inside one larger allocation; after the call the canaries must be intact.
 Covers the per-axis forward, the fused pair, the multi-hop forward and the multi-hop backward on
 a ragged shape (tiles with padding rows, a ragged last tile), a strided head-major layout and a
-shape with long axes (streaming forward, blocked backward)."""
+shape with long axes (streaming forward, long-axis backward)."""
 import numpy as np
 import pytest
 import torch
@@ -48,7 +48,7 @@ CASES = [
     ((3, 50), 1, 4, 1, 128, "bf16", True, False),        # two-tile axis with a ragged second tile
     ((2, 32, 32), 1, 8, 2, 128, "bf16", True, False),    # fused last pair
     ((6, 32), 2, 4, 2, 64, "bf16", True, True),          # head-major strides
-    ((130, 3), 1, 4, 1, 128, "bf16", False, False),      # streaming forward, blocked backward, ragged last tile
+    ((130, 3), 1, 4, 1, 128, "bf16", False, False),      # streaming forward, long-axis backward, ragged last tile
     ((6, 9), 1, 4, 4, 100, "bf16", True, False),         # narrow head: 8-byte-granular rows
     ((4, 2, 3), 1, 2, 1, 8, "f32", True, False),         # generic kernels
     ((5, 37), 1, 4, 1, 40, "f32", False, True),          # generic kernels, head-major

@@ -35,6 +35,8 @@ def test_fp32_hops_match_oracle(dims, B, Hq, Hkv, D, causal, window, valid_len, 
     ref = orc.tensorized_attention_forward(q, k, v, dims, causal, valid_len=valid_len, **kw)
     err = np.abs(got - ref).max()
     assert np.isfinite(got).all() and err <= TOL["f32"], f"forward: {err:.3e}"
+    for axis, n in enumerate(dims):
+        assert [plan.hop_function(axis, ta.TA_VIN_O, b) for b in (False, True)] == (["f32_fwd_kernel", "f32_bwd_kernel"] if n <= 32 else ["f32_fwd_long_kernel", "f32_bwd_long_kernel"])
     grads = multihop_backward(plan, dev, d_o, "f32")
     check_backward(grads, q, k, v, d_o, dims, causal, "f32", valid_len=valid_len, **kw)
 

@@ -25,9 +25,21 @@ CASES = [
     ((513,), 2, 2, 2, 96, False, None, (513, 0), None),
     ((769, 2), 1, 4, 1, 128, True, (300, 0), None, None),
     ((1100,), 1, 2, 1, 64, True, None, None, 10000.0),
-    ((200, 2), 1, 8, 2, 100, True, None, (390,), 10000.0),      # four heads per workgroup, narrow rows
-    ((1030,), 2, 8, 2, 64, True, None, (1030, 500), None),      # four heads per workgroup, two tiles of each
+    ((200, 2), 1, 8, 2, 100, True, None, (390,), 10000.0),
+    ((1030,), 2, 8, 2, 64, True, None, (1030, 500), None),      # four heads per workgroup
+    ((1060,), 1, 4, 1, 100, False, (600,), None, 10000.0),      # the same, narrow rows
+    ((1056, 8), 1, 64, 8, 40, True, None, (8000,), None),       # the same, more workgroups than CUs: two tiles of each head
+    ((3, 90), 1, 8, 2, 128, True, None, (200,), 10000.0),       # later hop, heads that share K
+    ((2, 70), 2, 4, 1, 64, False, (0, 40), None, None),
 ]
+
+
+def forward_function(dims, axis, Hq, Hkv, D):
+    """Four heads that share K side by side on up to four tiles, or below 1,024 positions (512 in 64-wide tiles) where they share the values too."""
+    n = dims[axis]
+    if Hq // Hkv % 4 == 0 and (n < (1024 if D > 64 else 512) if axis == 0 else n <= 96 and D in (64, 128)):
+        return "mfma_fwd_stream_chunked_kernel" if n <= 128 else "mfma_fwd_stream_shared_kernel"
+    return "mfma_fwd_long_kernel"
 
 
 @pytest.mark.parametrize("dims,B,Hq,Hkv,D,causal,window,lens,rope", CASES)
@@ -39,7 +51,8 @@ def test_long_axis_forward_matches_oracle(dims, B, Hq, Hkv, D, causal, window, l
     if lens is not None:
         pkw["valid_lens"] = torch.tensor(lens, dtype=torch.int64, device="cuda")
     got, plan, _ = multihop_forward(q, k, v, dims, "bf16", causal, **pkw)
-    assert "mfma_bf16_stream" in plan.hop_kernel(int(np.argmax(dims)), ta.TA_VIN_O)
+    axis = int(np.argmax(dims))
+    assert plan.hop_function(axis, ta.TA_VIN_KV if axis == 0 else ta.TA_VIN_O) == forward_function(dims, axis, Hq, Hkv, D)
     ref = orc.tensorized_attention_forward(q, k, v, dims, causal, valid_len=list(lens) if lens else None, **kw)
     err = np.abs(got - ref).max()
     assert np.isfinite(got).all() and err <= TOL["bf16"], f"{err:.3e}"

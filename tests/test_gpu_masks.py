@@ -155,7 +155,7 @@ LENS_CASES = [
     ((5, 7, 3), 4, 2, 64, False, "bf16", [105, 37, 0, 1]),
     ((2, 32, 32), 8, 2, 128, False, "bf16", [2048, 1500, 1024, 31]),      # fused pair: whole slabs of padding, ragged slabs
     ((3, 50), 2, 2, 128, True, "bf16", [150, 149, 51]),                   # two key tiles
-    ((130, 3), 4, 1, 128, False, "bf16", [390, 200, 3]),                  # streaming forward, blocked backward
+    ((130, 3), 4, 1, 128, False, "bf16", [390, 200, 3]),                  # streaming forward, long-axis backward
     ((64, 4), 4, 1, 64, False, "bf16", [256, 100]),
     ((4, 2, 3), 2, 1, 8, False, "f32", [24, 5, 0]),                       # generic kernels
     ((5, 37), 4, 1, 40, True, "f32", [185, 90]),

@@ -15,15 +15,16 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # dims, B, Hq, Hkv, D, causal, window, valid_lens, rope base, axes with a table per fibre
-    ((3, 16, 16), 1, 4, 4, 128, True, None, None, None, ()),
-    ((2, 8, 32), 2, 8, 2, 128, False, None, (500, 77), None, ()),
-    ((32, 8), 1, 2, 1, 64, True, None, None, 10000.0, ()),
-    ((5, 10, 9), 1, 3, 3, 128, True, (0, 4, 3), None, None, (2,)),
-    ((15, 17), 1, 2, 2, 64, False, None, (200,), None, (0,)),
-    ((2, 12, 20), 1, 4, 2, 40, True, None, None, 200.0, ()),
-    ((16, 16, 16), 2, 8, 2, 128, True, None, (4096, 1500), None, ()),     # 256 slabs: two tiles per wave
+    ((5, 10, 9), 1, 3, 3, 128, True, (0, 4, 3), None, None, (2,)),         # 3 and 4 tiles
+    ((10, 9), 1, 4, 1, 64, True, None, None, 10000.0, ()),                 # two axes: the value input is per key/value head
+    ((12, 8), 2, 4, 2, 128, False, None, (96, 41), None, (0,)),
+    ((2, 8, 12), 1, 4, 2, 40, True, None, None, 200.0, ()),                # narrow rows
+    ((3, 11, 8), 1, 2, 2, 128, False, (0, 9, 0), None, 10000.0, (1, 2)),   # the encoding at full width, a table per column
+    ((4, 16, 8), 2, 8, 2, 64, False, None, (500, 77), None, (1,)),         # whole tiles; one element nearly all padding
+    ((16, 16, 16), 2, 8, 2, 128, True, None, (4096, 1500), None, ()),      # 256 slabs: two tiles per wave
     ((18, 15, 16), 2, 8, 8, 40, False, None, None, 10000.0, ()),
-    ((4, 31, 8), 1, 2, 2, 128, False, (0, 9, 0), None, 10000.0, (1, 2)),
+    ((32, 20, 8), 1, 8, 2, 128, True, None, (5000,), 10000.0, ()),         # 8 column tiles, 5 row tiles
+    ((32, 7, 20), 1, 8, 4, 64, False, None, None, None, (2,)),             # 5 column tiles, 7 row tiles
 ]
 
 
@@ -40,6 +41,7 @@ def test_small_slabs_match_oracle_and_single_hops(dims, B, Hq, Hkv, D, causal, w
     okw = dict(kw, valid_len=list(lens) if lens else None, axis_masks=masks)
     got, plan, _ = multihop_forward(q, k, v, dims, "bf16", causal, **pkw)
     saved, plan, dev = multihop_forward(q, k, v, dims, "bf16", causal, save=True, **pkw)
+    assert plan.small_pair_position() == m - 2
     ref = orc.tensorized_attention_forward(q, k, v, dims, causal, **okw)
     err = np.abs(got - ref).max()
     assert np.isfinite(got).all() and err <= TOL["bf16"], f"{err:.3e}"
