@@ -1127,8 +1127,12 @@ bool mfma_backward_is_two_tile(const BwdParams& bp, int dtype) {
 
 // Long axes: the blocked kernel runs a group's heads side by side, a wave each; the long kernel one head after the other, eight
 // tiles at a time.  The former is ahead where it fills the chip and the latter's eight waves have five or six tiles (100 fibres of 129 / 160
-// positions, 16 / 4 heads of width 128: 212 / 245 against 241 / 256 us; from seven tiles on, 200 x 64, 32 / 8 heads: 513 against 440 us).
-static bool runs_blocked(const HopParams& p) { return p.G >= 4 && p.n <= 6 * kTile && (int64_t)p.B * p.Hkv * p.fibres >= 256; }
+// positions, 16 / 4 heads of width 128: 212 / 245 against 241 / 256 us; from seven tiles on, 200 x 64, 32 / 8 heads: 513 against 440 us), and,
+// for five tiles, where a whole launch of eight heads is at hand (a training step of 130 x 16, 32 / 1 heads of width 128: 869 against 948 us,
+// 160 x 4, of width 64: 532 against 560; of 192 x 16: 1,127 against 1,058; groups of four, 160 x 16 with 4 / 1 heads: 163 against 145).
+static bool runs_blocked(const HopParams& p) {
+    return (p.G >= 4 && p.n <= 6 * kTile && (int64_t)p.B * p.Hkv * p.fibres >= 256) || (p.G >= 8 && p.n <= 5 * kTile);
+}
 
 const char* mfma_backward_function(const BwdParams& bp) {
     switch (backward_variant(bp, TA_BF16)) {
