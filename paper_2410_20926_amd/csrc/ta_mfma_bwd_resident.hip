@@ -12,9 +12,10 @@
 // rounding.  While a head is worked on, the next head's rows (or the next fibre's: a workgroup takes every
 // gridDim.x-th one) are on their way into registers, half a tile per wave and tensor.
 //
-// What bounds it: memory, and seven barriers per head of which one workgroup per CU (width 128, n > 64) hides little.  The
+// What bounds it: memory, and seven barriers per head of which one workgroup per CU (width 128, n > 64) hides little (LDS active 30 % of
+// the time, 41 % of that in bank conflicts, matrix units busy 9 %).  The
 // blocked kernel, which it replaces up to 128, gathers every tile again at each visit, waits for each, and forms S and dP up to
-// four times.  128 x 128 tokens, 32 / 8 heads of width 128, causal: hops of 437 / 395 us -> 215 / 214 us (4.2 and 3.3 TB/s);
+// four times.  128 x 128 tokens, 32 / 8 heads of width 128, causal: hops of 437 / 395 us -> 196 / 186 us;
 // 100 x 100, batch 2, 12 heads of width 96: 407 -> 218 us; 64 x 64 x 32, 32 / 8 heads: the two-tile kernel's 1522 / 1544 us -> 1365 / 1185 us
 // (5.3 and 4.8 TB/s).  A first form with one wave per tile and 512 registers took 450 us at 128 x 128: it spilled, and a
 // reload waits for every row requested before it.

@@ -9,8 +9,8 @@
 //   The weights of each 32-key tile are rounded relative to the row's maximum up to that tile (see below), and the accumulators are
 // rescaled only when some row's maximum has grown; the sum of the ROUNDED weights is one dot product per pair of weights.  A tile that
 // no row of the query tile sees (half of a diagonal block, padding) is left out.
-//   What bounds it: for long axes the matrix pipe (per 64-key block a wave needs 32 matrix instructions of 32 cycles) and the vector
-// pipe (32 exponentials of 16 cycles, as much again for the rest, 256 cycles for each rescaling), on short ones memory and the wait for the
+//   What bounds it: for long axes the vector and matrix pipes (32,768 keys of width 128: 8 vector instructions per matrix instruction,
+// matrix units busy 37 % of the time, LDS active 51 %, half of that in bank conflicts), on short ones memory and the wait for the
 // first rows.  The kernel it replaces took 32 keys per barrier, rescaled the accumulators for every tile and, without groups of four heads,
 // fetched every K and V row once per query tile.  32 / 8 heads of width 128: 32,768 keys, causal, 10.9 -> 9.9 ms (0.9 PFLOP/s; a
 // large bf16 matrix product reaches 1.15 on this card), 4,096 keys, not causal, 405 -> 375 us; with the second hop, 128 x 128, 200 -> 184 us;
