@@ -1104,6 +1104,8 @@ static int backward_variant(const BwdParams& bp, int dtype) {
     // (8 x 50 tokens, 16 / 4 heads of width 128: 23.5 against 27.1 us), and with 64-wide heads in groups of one or two, whose few bytes
     // per head do not cover the resident kernel's barriers (32,768 tokens as 64 x 512, 32 heads: 286 against 356 us; groups of four: 237
     // against 195 us).
+    // Large groups on few fibres and narrow heads gain as well (training steps against the blocked kernel, 128 x 4, 32 / 1 heads of width 128: 373
+    // against 651 us; 60 x 4, 32 / 1 heads of width 100: 354 against 466; 48 x 16, 16 / 2 heads of width 40: 68 against 133).
     const int64_t units = (int64_t)p.B * p.Hkv * p.fibres;
     if (p.n <= 2 * kTile && full && ((p.D == 64 && p.G <= 2) || (p.G % 4 == 0 && units < 512))) return 3;
     if (p.n <= 4 * kTile && units <= 0x7fffffffLL) return 4;
