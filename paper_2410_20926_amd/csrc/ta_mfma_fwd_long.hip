@@ -3,19 +3,22 @@
 //
 // A workgroup is NW consecutive 32-row query tiles of ONE query head, a wave each (or NW / 4 tiles of four heads that share K and the
 // value input).  They walk the same key blocks: every
-// wave fetches its share of a block's K and value rows, which enter LDS once for all of them (two buffers, one barrier
-// per block; the block after next is requested when a block is written, so its rows have a whole block's work to
+// wave fetches its share of a block's K and value rows, which enter LDS once for all of them (two buffers and one barrier
+// per block, or three and two; the block after next is requested when a block is written, so its rows have a whole block's work to
 // arrive).  Per block a wave forms S^T = K Q^T for two 32-key tiles, the softmax of 64 keys at once, O^T += V^T P^T.
 //   The weights of each 32-key tile are rounded relative to the row's maximum up to that tile (see below), and the accumulators are
 // rescaled only when some row's maximum has grown; the sum of the ROUNDED weights is one dot product per pair of weights.  A tile that
 // no row of the query tile sees (half of a diagonal block, padding) is left out.
-//   What bounds it: for long axes the vector and matrix pipes (32,768 keys of width 128: 8 vector instructions per matrix instruction,
-// matrix units busy 37 % of the time, LDS active 51 %, half of that in bank conflicts), on short ones memory and the wait for the
-// first rows.  The kernel it replaces took 32 keys per barrier, rescaled the accumulators for every tile and, without groups of four heads,
-// fetched every K and V row once per query tile.  32 / 8 heads of width 128: 32,768 keys, causal, 10.9 -> 9.9 ms (0.9 PFLOP/s; a
-// large bf16 matrix product reaches 1.15 on this card), 4,096 keys, not causal, 405 -> 375 us; with the second hop, 128 x 128, 200 -> 184 us;
-// 8 heads of 1,024 x 16: 140 -> 116 us, of width 64, 512 x 64: 101 -> 86 us.  (A reference that moved only when the maximum had passed
-// it by 2^6 took 8.7 ms, with 3 per cent more error.)
+//   In step, eight waves reach their products, then their softmax, then their products together, and either pipe of a SIMD is idle while
+// the other works (32,768 keys of width 128: matrix units busy 37 % of 22.7 M cycles).  On long axes the two halves of the workgroup
+// therefore work half a block apart (kPhases): busy 50 % of 16.9 M cycles; the operands of a product are read from LDS a stage ahead, and blocks
+// that every row sees whole run without the code for masks.  Value rows lie 16 or 48 banks apart, so that the transposed reads have no bank
+// conflicts (half of the LDS cycles before).  The time falls less than the cycles, because the clock falls from 2.33 to about 1.95 GHz.
+//   What bounds it: for long axes the power the card may draw (1.03 PFLOP/s; a large bf16 matrix product reaches 1.18), on short ones
+// memory and the wait for the first rows.  32 / 8 heads of width 128: 32,768 keys, causal, 9.8 -> 8.6 ms, 16,384 keys, not causal, 4.84 -> 4.08 ms;
+// 32 heads of width 64, 8,192 x 2, not causal, 1,567 -> 1,331 us; four tiles: 4,096 keys, not causal, 405 -> 375 us; with the second hop, 128 x 128,
+// 200 -> 184 us; 8 heads of 1,024 x 16: 140 -> 116 us, of width 64, 512 x 64: 101 -> 86 us (against a kernel that took 32 keys per barrier and
+// rescaled for every tile).  (A reference that moved only when the maximum had passed it by 2^6 took 12 % less in step, with 3 per cent more error.)
 #include "ta_mfma_common.h"
 #include <type_traits>
 
@@ -39,12 +42,18 @@ struct LongParams {
     uint32_t q_row, k_row, v_row, o_row;                  // token pitch in bytes
 };
 
-// SHORT: at most two blocks (n <= 128): both are requested at once and stay, no barrier between them.
+// kShort: at most two blocks (n <= 128): both are requested at once and stay, no barrier between them.  kPhases: the two halves of the
+// workgroup work half a block apart (see the loop).
+enum Form { kShort, kBlocks, kPhases };
 // NARROW: the head is narrower than the D-wide tile; see load_chunk.
-template <int D, int NW, bool SHORT, bool NARROW, bool ROPE>
+template <int D, int NW, Form FORM, bool NARROW, bool ROPE>
 __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, LongParams lp) {
     using G = Geo<D>;
-    constexpr int kBlock = kKeys * G::kPitch;             // one K or value block
+    constexpr bool SHORT = FORM == kShort, kPhased = FORM == kPhases;
+    static_assert(!kPhased || NW == 8, "two sets of four waves");
+    constexpr int kVPitch = 2 * D + 64;                   // value rows 16 or 48 banks apart: the four rows of a transposed read on banks of their own
+    constexpr int kBlock = kKeys * G::kPitch, kVBlock = kKeys * kVPitch;   // one K, one value block
+    constexpr int kBuffers = kPhased ? 3 : 2;
     constexpr int kRows = NW * G::kRowsPerPass;           // rows the workgroup fetches per pass
     constexpr int kMine = kKeys / kRows;                  // passes
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -100,31 +109,52 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
     keys(qt * kTile, qt * kTile + kTile - 1, kTile, wb, we);
     if (qt * kTile >= nreal) we = wb;
 
-    // this wave's share of block j: rows w * kRowsPerPass + lrow + i * kRows
+    // this wave's share of a block: rows w * kRowsPerPass + lrow + i * kRows; rows past the fibre's end: its last one, never visible
     struct Raw { u32x4 v[kMine]; uint32_t mis; };
     const int myrow = w * G::kRowsPerPass + lrow;
     auto request = [&](const char* base, uint32_t pitch, int j, Raw& raw) {
         raw.mis = 0u;
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
-            const uint32_t r = (uint32_t)min(j * kKeys + i * kRows + myrow, n - 1);   // rows past the end: the last one, never visible
+            const uint32_t r = (uint32_t)min(j * kKeys + i * kRows + myrow, n - 1);
             uint32_t mis;
             raw.v[i] = gather_request<NARROW, false>(base, (tok0 + r * stride) * pitch, lbyte, dbytes, mis);
             raw.mis |= mis ? 1u << i : 0u;
         }
     };
-    auto write = [&](char* block, int j, Raw& raw, bool turn) {
+    // the same for one block after the other (kPhased: two additions and two minima instead of products): `off` = this lane's first row of
+    // the block to be requested next
+    auto request_next = [&](const char* base, uint32_t pitch, uint32_t& off, Raw& raw) {
+        const uint32_t hop = stride * pitch, last = (tok0 + (uint32_t)(n - 1) * stride) * pitch;
+        raw.mis = 0u;
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            uint32_t mis;
+            raw.v[i] = gather_request<NARROW, false>(base, min(__builtin_elementwise_add_sat(off, (uint32_t)(i * kRows) * hop), last), lbyte, dbytes, mis);
+            raw.mis |= mis ? 1u << i : 0u;
+        }
+        off = min(__builtin_elementwise_add_sat(off, (uint32_t)kKeys * hop), last);
+    };
+    auto write = [&](char* block, uint32_t pitch, int j, Raw& raw, bool turn) {
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
             u32x4 x = gather_ready<NARROW>(raw.v[i], (raw.mis >> i) & 1u, lbyte, dbytes);
             if (ROPE && turn) x = rope_chunk(x, (float)min(j * kKeys + i * kRows + myrow, n - 1), rev);
-            *reinterpret_cast<u32x4*>(block + (i * kRows + myrow) * G::kPitch + lbyte) = x;
+            *reinterpret_cast<u32x4*>(block + (uint32_t)(i * kRows + myrow) * pitch + lbyte) = x;
         }
     };
-    Raw kr, vr, k2, v2;                                   // (k2, v2: SHORT only)
+    Raw kr, vr, k2, v2;                                   // (k2: kPhased and SHORT, v2: SHORT only)
     if constexpr (SHORT) { jb = 0; je = (n + kKeys - 1) / kKeys; }
-    request(kbase, lp.k_row, jb, kr);
-    request(vbase, lp.v_row, jb, vr);
+    const uint32_t row0 = tok0 + (uint32_t)min(jb * kKeys + myrow, n - 1) * stride;
+    uint32_t koff = row0 * lp.k_row, voff = row0 * lp.v_row;
+    if constexpr (kPhased) {
+        request_next(kbase, lp.k_row, koff, kr);
+        request_next(kbase, lp.k_row, koff, k2);
+        request_next(vbase, lp.v_row, voff, vr);
+    } else {
+        request(kbase, lp.k_row, jb, kr);
+        request(vbase, lp.v_row, jb, vr);
+    }
     if constexpr (SHORT) {
         request(kbase, lp.k_row, 1, k2);
         request(vbase, lp.v_row, 1, v2);
@@ -146,13 +176,16 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
         read_natural<D>(own + r32 * G::kPitch + hf * 16, qop);
     }
     __syncthreads();                                      // the query rows have left LDS
-    char* sK = smem;                                      // two blocks
-    char* sV = smem + 2 * kBlock;
-    write(sK, jb, kr, true);
-    write(sV, jb, vr, false);
+    char* sK = smem;                                      // kBuffers blocks
+    char* sV = smem + kBuffers * kBlock;
+    write(sK, G::kPitch, jb, kr, true);
+    write(sV, kVPitch, jb, vr, false);
+    if constexpr (SHORT || kPhased) write(sK + kBlock, G::kPitch, jb + 1, k2, true);
     if constexpr (SHORT) {
-        write(sK + kBlock, 1, k2, true);
-        write(sV + kBlock, 1, v2, false);
+        write(sV + kVBlock, kVPitch, 1, v2, false);
+    } else if constexpr (kPhased) {
+        request_next(kbase, lp.k_row, koff, kr);
+        request_next(vbase, lp.v_row, voff, vr);
     } else {
         request(kbase, lp.k_row, jb + 1, kr);
         request(vbase, lp.v_row, jb + 1, vr);
@@ -160,7 +193,7 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
     __syncthreads();
 
     const uint32_t nat = (uint32_t)(r32 * G::kPitch + hf * 16);
-    const uint32_t trn = (uint32_t)((4 * hf + ((lane & 15) >> 2)) * G::kPitch + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2);
+    const uint32_t trn = (uint32_t)((4 * hf + ((lane & 15) >> 2)) * kVPitch + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2);
     const float sl2 = p.scale * kLog2e;
     const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
     float m = -INFINITY, l = 0.f;                         // reference value (log2 domain); sum of this lane's weights
@@ -168,99 +201,212 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
 #pragma unroll
     for (int t = 0; t < G::kDTiles; ++t) ot[t] = f32x16{};
 
-#pragma unroll 1
-    for (int j = jb; j < je; ++j) {
-        const int slot = (j - jb) & 1;
-        if constexpr (!SHORT) {
-            if (j + 1 < je) {                             // the other buffer was last read before the last barrier
-                write(sK + (slot ^ 1) * kBlock, j + 1, kr, true);
-                write(sV + (slot ^ 1) * kBlock, j + 1, vr, false);
-            }
-            request(kbase, lp.k_row, j + 2, kr);
-            request(vbase, lp.v_row, j + 2, vr);
+    auto rescale = [&](float c) {
+#pragma unroll
+        for (int d = 0; d < G::kDTiles; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ot[d][r] *= c;
+    };
+    // masked keys of one or two tiles from number c on; tiles that every row sees whole skip this
+    auto mask = [&](auto& st, int c) {
+        constexpr int TILES = sizeof(st) / sizeof(st[0]);
+        uint32_t vis[TILES], all = 0xffffffffu;
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            vis[t] = range_mask(min(max(klo - kTile * (c + t), 0), kTile), min(max(khi - kTile * (c + t), 0), kTile));
+            if (p.mask && qrow < nreal && c + t < p.mask_words) vis[t] &= table_word(p, (uint32_t)f, qrow, c + t);
+            all &= vis[t];
         }
-        // key tiles of the block that some row of the query tile sees: the other half of a diagonal block and padding are left out
-        const int first = max(2 * j, wb) - 2 * j, end = min(2 * j + 2, we) - 2 * j;
-        if (first < end) {
-            // weights of TILES tiles from `first` on, sums and maxima moved on; the first tile's value operands are on their way meanwhile
-            u32x4 vop[G::kDTiles][2], pop[2][2];
-            float corr[2] = {1.f, 1.f};
-            bool grows[2] = {false, false};
-            auto values = [&](int t) { read_transposed<D>(sV + slot * kBlock + t * (kTile * G::kPitch) + trn, vop); };
-            auto weights = [&](auto tag) {
-                constexpr int TILES = decltype(tag)::value;
-                const char* kt = sK + slot * kBlock + first * (kTile * G::kPitch) + nat;
-                f32x16 st[TILES] = {};
+        if (!__all(all == 0xffffffffu)) {
 #pragma unroll
-                for (int s = 0; s < G::kKSteps; ++s)
+            for (int t = 0; t < TILES; ++t)
 #pragma unroll
-                    for (int t = 0; t < TILES; ++t) st[t] = mma(*reinterpret_cast<const u32x4*>(kt + t * (kTile * G::kPitch) + 32 * s), qop[s], st[t]);
-                values(first);
-                // masked keys; tiles that every row sees whole skip this
-                uint32_t vis[TILES], all = 0xffffffffu;
+                for (int r = 0; r < 16; ++r) st[t][r] = ((vis[t] >> (4 * hf + 8 * (r / 4) + (r % 4))) & 1u) ? st[t][r] : -INFINITY;
+        }
+    };
+    // One tile's weights, relative to the row's maximum up to and including that tile, so that the largest is exactly 1:
+    // relative to the maximum of both tiles of a block, or to one that lags behind, more of them are rounded (3 per cent more error at
+    // 4,096 keys).
+    auto weights = [&](const f32x16& st, u32x4 (&pop)[2], float& corr, bool& grows) {
+        float mx = st[0];
 #pragma unroll
-                for (int t = 0; t < TILES; ++t) {
-                    const int c = 2 * j + first + t;
-                    vis[t] = range_mask(min(max(klo - kTile * c, 0), kTile), min(max(khi - kTile * c, 0), kTile));
-                    if (p.mask && qrow < nreal) vis[t] &= table_word(p, (uint32_t)f, qrow, c);
-                    all &= vis[t];
-                }
-                if (!__all(all == 0xffffffffu)) {
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[r]);
+        mx = both_halves_max(mx);
+        mx = mx == -INFINITY ? mx : mx * sl2;
+        grows = __any(mx > m);                            // (m = -inf: any finite maximum passes it)
+        const float top = mx > m ? mx : m;
+        corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top);
+        m = top;
+        l *= corr;
+        const float ref = m == -INFINITY ? 0.f : m;
 #pragma unroll
-                    for (int t = 0; t < TILES; ++t)
+        for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) st[t][r] = ((vis[t] >> (4 * hf + 8 * (r / 4) + (r % 4))) & 1u) ? st[t][r] : -INFINITY;
-                }
-                // Each tile's weights are relative to the row's maximum up to and including that tile, so that the largest is exactly 1:
-                // relative to the maximum of both tiles, or to one that lags behind, more of them are rounded (3 per cent more error at
-                // 4,096 keys).
+            for (int e = 0; e < 4; ++e) {
+                const int r = 8 * s2 + 2 * e;
+                const uint32_t pk = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(st[r], sl2, -ref)), __builtin_amdgcn_exp2f(fmaf(st[r + 1], sl2, -ref)));
+                l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, l, false);
+                pop[s2][e] = pk;
+            }
+    };
+    // value operand: features 32 d + r32, 16-row step s2 of a tile (see read_transposed)
+    auto operand = [&](const char* tile, int d, int s2) {
+        const char* a0 = tile + 16 * s2 * kVPitch + 64 * d;
+        const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a0)));
+        const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a0 + 8 * kVPitch)));
+        return u32x4{lo.x, lo.y, hi.x, hi.y};
+    };
+    if constexpr (kPhased) {
+        // Waves 0-3 and 4-7 work half a block apart, a barrier after each half: while one set forms products (O^T += V^T P^T of block
+        // j - 1, then S^T of block j) the other is in the softmax and the staging of its next block, so that the matrix and the
+        // vector pipe of a SIMD have one of its two waves each.  In block j's softmax K of block j + 2 and the value input of block j + 1 are
+        // written, over blocks j - 1 and j - 2, which the later set has read a phase before; the earlier set reads them two phases later.
+        constexpr int kHalf = G::kKSteps / 2;
+        using Rows = u32x4[2][kHalf];                     // half the features of a block's two key tiles
+        using Values = u32x4[G::kDTiles][2];
+        auto key_rows = [&](int slot, int half, Rows& k) {
 #pragma unroll
-                for (int t = 0; t < TILES; ++t) {
-                    float mx = st[t][0];
+            for (int s = 0; s < kHalf; ++s)
 #pragma unroll
-                    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[t][r]);
-                    mx = both_halves_max(mx);
-                    mx = mx == -INFINITY ? mx : mx * sl2;
-                    grows[t] = __any(mx > m);             // (m = -inf: any finite maximum passes it)
-                    const float top = mx > m ? mx : m;
-                    corr[t] = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top);
-                    m = top;
-                    l *= corr[t];
-                    const float ref = m == -INFINITY ? 0.f : m;
+                for (int t = 0; t < 2; ++t) k[t][s] = *reinterpret_cast<const u32x4*>(sK + slot * kBlock + t * (kTile * G::kPitch) + nat + 32 * (half * kHalf + s));
+        };
+        auto score = [&](const Rows& k, int half, f32x16 (&st)[2]) {
 #pragma unroll
-                    for (int s2 = 0; s2 < 2; ++s2)
+            for (int s = 0; s < kHalf; ++s)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int r = 8 * s2 + 2 * e;
-                            const uint32_t pk = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(st[t][r], sl2, -ref)), __builtin_amdgcn_exp2f(fmaf(st[t][r + 1], sl2, -ref)));
-                            l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, l, false);
-                            pop[t][s2][e] = pk;
-                        }
-                }
-            };
-            if (end - first == 2) weights(std::integral_constant<int, 2>{});
-            else weights(std::integral_constant<int, 1>{});
+                for (int t = 0; t < 2; ++t) st[t] = mma(k[t][s], qop[half * kHalf + s], st[t]);
+        };
+        auto value_rows = [&](int slot, int t, Values& v) {
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                for (int d = 0; d < G::kDTiles; ++d) v[d][s2] = operand(sV + slot * kVBlock + t * (kTile * kVPitch) + trn, d, s2);
+        };
+        auto value = [&](const Values& v, const u32x4 (&w2)[2]) {
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                for (int d = 0; d < G::kDTiles; ++d) ot[d] = mma(v[d][s2], w2[s2], ot[d]);
+        };
+        // blocks [ia, iz): every row of this wave's tile sees all of their keys
+        int ia = je, iz = je;
+        if (!p.mask && qt * kTile + kTile <= nreal) {
+            int lo, hi, lo2, hi2;
+            visible_range(qt * kTile, 0, n, p.causal, p.window, lo, hi);
+            visible_range(qt * kTile + kTile - 1, 0, n, p.causal, p.window, lo2, hi2);
+            ia = min(max((max(lo2, 0) + kKeys - 1) / kKeys, jb), je);
+            iz = max(min(min(hi, nreal) / kKeys, je), ia);
+        }
+        Rows ka;
+        key_rows(0, 0, ka);
+        int slot = 0;                                     // block j's buffer
+        auto step = [&](int j, auto tag) {
+            constexpr bool kAll = decltype(tag)::value;
+            const int next = slot == 2 ? 0 : slot + 1, after = slot == 0 ? 2 : slot - 1;
+            // (both tiles of every block, so that no accumulator is copied where branches meet: one that no row sees gets weights of zero
+            // and is left out of the value product)
+            Rows kb;
+            key_rows(slot, 1, kb);
+            f32x16 st[2] = {};
+            score(ka, 0, st);
+            score(kb, 1, st);
+            __builtin_amdgcn_s_setprio(0);
+            __syncthreads();
+            Values va, vb;
+            value_rows(slot, 0, va);
+            u32x4 pop[2][2];
+            float corr[2];
+            bool grows[2];
+            if constexpr (!kAll) mask(st, 2 * j);
+            weights(st[0], pop[0], corr[0], grows[0]);
+            if (grows[0]) rescale(corr[0]);
+            weights(st[1], pop[1], corr[1], grows[1]);
+            write(sK + after * kBlock, G::kPitch, j + 2, kr, true);   // (past the last block: the fibre's last row, not used)
+            write(sV + next * kVBlock, kVPitch, j + 1, vr, false);
+            request_next(kbase, lp.k_row, koff, kr);
+            request_next(vbase, lp.v_row, voff, vr);
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2)                // formed here: they would be moved down to where they are used
+                asm volatile("" : "+v"(pop[0][s2]), "+v"(pop[1][s2]));
+            __syncthreads();
+            __builtin_amdgcn_s_setprio(1);
+            value_rows(slot, 1, vb);
+            if (kAll || (2 * j >= wb && 2 * j < we)) value(va, pop[0]);
+            if (grows[1]) rescale(corr[1]);
+            key_rows(next, 0, ka);                        // (past the last block: what is there, not used)
+            if (kAll || (2 * j + 1 >= wb && 2 * j + 1 < we)) value(vb, pop[1]);
+            slot = next;
+        };
+        if (w >= 4) __syncthreads();
+        __builtin_amdgcn_s_setprio(1);
+        int j = jb;
+        for (int stop = ia;; stop = je) {
 #pragma unroll 1
-            for (int t = first; t < end; ++t) {           // one body: two would copy the accumulators from one to the other
-                if (grows[0]) {
+            for (; j < stop; ++j) step(j, std::false_type{});
+            if (j >= je) break;
+#pragma unroll 1
+            for (; j < iz; ++j) step(j, std::true_type{});
+        }
+        __builtin_amdgcn_s_setprio(0);
+        if (w < 4) __syncthreads();
+        __syncthreads();                                  // every block has been read
+    } else {
+#pragma unroll 1
+        for (int j = jb; j < je; ++j) {
+            const int slot = (j - jb) & 1;
+            if constexpr (!SHORT) {
+                if (j + 1 < je) {                             // the other buffer was last read before the last barrier
+                    write(sK + (slot ^ 1) * kBlock, G::kPitch, j + 1, kr, true);
+                    write(sV + (slot ^ 1) * kVBlock, kVPitch, j + 1, vr, false);
+                }
+                request(kbase, lp.k_row, j + 2, kr);
+                request(vbase, lp.v_row, j + 2, vr);
+            }
+            // key tiles of the block that some row of the query tile sees: the other half of a diagonal block and padding are left out
+            const int first = max(2 * j, wb) - 2 * j, end = min(2 * j + 2, we) - 2 * j;
+            if (first < end) {
+                // weights of TILES tiles from `first` on, sums and maxima moved on; the first tile's value operands are on their way meanwhile
+                u32x4 vop[G::kDTiles][2], pop[2][2];
+                float corr[2] = {1.f, 1.f};
+                bool grows[2] = {false, false};
+                auto values = [&](int t) {
 #pragma unroll
                     for (int d = 0; d < G::kDTiles; ++d)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) ot[d][r] *= corr[0];
-                }
+                        for (int s2 = 0; s2 < 2; ++s2) vop[d][s2] = operand(sV + slot * kVBlock + t * (kTile * kVPitch) + trn, d, s2);
+                };
+                auto score = [&](auto tag) {
+                    constexpr int TILES = decltype(tag)::value;
+                    const char* kt = sK + slot * kBlock + first * (kTile * G::kPitch) + nat;
+                    f32x16 st[TILES] = {};
 #pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2)
+                    for (int s = 0; s < G::kKSteps; ++s)
 #pragma unroll
-                    for (int d = 0; d < G::kDTiles; ++d) ot[d] = mma(vop[d][s2], pop[0][s2], ot[d]);
-                if (t + 1 < end) {
-                    values(t + 1);
-                    pop[0][0] = pop[1][0]; pop[0][1] = pop[1][1]; corr[0] = corr[1]; grows[0] = grows[1];
+                        for (int t = 0; t < TILES; ++t) st[t] = mma(*reinterpret_cast<const u32x4*>(kt + t * (kTile * G::kPitch) + 32 * s), qop[s], st[t]);
+                    values(first);
+                    mask(st, 2 * j + first);
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) weights(st[t], pop[t], corr[t], grows[t]);
+                };
+                if (end - first == 2) score(std::integral_constant<int, 2>{});
+                else score(std::integral_constant<int, 1>{});
+#pragma unroll 1
+                for (int t = first; t < end; ++t) {           // one body: two would copy the accumulators from one to the other
+                    if (grows[0]) rescale(corr[0]);
+#pragma unroll
+                    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+                        for (int d = 0; d < G::kDTiles; ++d) ot[d] = mma(vop[d][s2], pop[0][s2], ot[d]);
+                    if (t + 1 < end) {
+                        values(t + 1);
+                        pop[0][0] = pop[1][0]; pop[0][1] = pop[1][1]; corr[0] = corr[1]; grows[0] = grows[1];
+                    }
                 }
             }
+            if (!SHORT) __syncthreads();                      // block j has been read, block j + 1 is complete
         }
-        if (!SHORT) __syncthreads();                      // block j has been read, block j + 1 is complete
+        if (SHORT) __syncthreads();                       // every block has been read
     }
-    if (SHORT) __syncthreads();                           // every block has been read
 
     // ---- normalise, round, transpose through LDS, store ----------------------------------------------------
     l += __shfl_xor(l, 32);
@@ -285,21 +431,27 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
     }
 }
 
-template <int D, int NW, bool SHORT, bool NARROW, bool ROPE>
+template <int D, int NW, Form FORM, bool NARROW, bool ROPE>
 hipError_t launch(const HopParams& p, const LongParams& lp, hipStream_t s) {
-    constexpr int smem = 4 * kKeys * Geo<D>::kPitch;      // also holds NW query or output tiles
+    constexpr int smem = (FORM == kPhases ? 3 : 2) * kKeys * (Geo<D>::kPitch + 2 * D + 64);   // also holds NW query or output tiles
     static_assert(smem >= NW * kTile * Geo<D>::kPitch, "the transit tiles fit");
     if (smem > 64 * 1024) {
-        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_fwd_long_kernel<D, NW, SHORT, NARROW, ROPE>), smem);
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_fwd_long_kernel<D, NW, FORM, NARROW, ROPE>), smem);
         if (e != hipSuccess) return e;
     }
     const uint32_t rows = (lp.units + 7u) / 8u, y = rows < 32768u ? rows : 32768u;
-    hipLaunchKernelGGL((mfma_fwd_long_kernel<D, NW, SHORT, NARROW, ROPE>), dim3(8u * (uint32_t)p.G / lp.heads, y, (rows + y - 1) / y), dim3(64 * NW), smem, s, p, lp);
+    hipLaunchKernelGGL((mfma_fwd_long_kernel<D, NW, FORM, NARROW, ROPE>), dim3(8u * (uint32_t)p.G / lp.heads, y, (rows + y - 1) / y), dim3(64 * NW), smem, s, p, lp);
     return hipGetLastError();
 }
 template <int D, bool NARROW, bool ROPE>
 hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream_t s) {
-    return p.n <= 2 * kKeys ? launch<D, 4, true, NARROW, ROPE>(p, lp, s) : wide ? launch<D, 8, false, NARROW, ROPE>(p, lp, s) : launch<D, 4, false, NARROW, ROPE>(p, lp, s);
+    if (p.n <= 2 * kKeys) return launch<D, 4, kShort, NARROW, ROPE>(p, lp, s);
+    if (!wide) return launch<D, 4, kBlocks, NARROW, ROPE>(p, lp, s);
+    if constexpr (!ROPE) {
+        if (!NARROW || p.n >= 4096) return launch<D, 8, kPhases, NARROW, ROPE>(p, lp, s);
+    }
+    if constexpr (NARROW || ROPE) return launch<D, 8, kBlocks, NARROW, ROPE>(p, lp, s);
+    return hipErrorInvalidValue;                          // (not reached)
 }
 template <bool ROPE>
 hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream_t s) {
@@ -307,21 +459,28 @@ hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream
          : p.D > 64 ? launch<128, true, ROPE>(p, lp, wide, s) : launch<64, true, ROPE>(p, lp, wide, s);
 }
 
-// Eight query tiles per workgroup from 1,024 positions on (half the K and V rows fetched per query row) where that leaves a workgroup for
-// every CU, else four, in twice the workgroups (one head of width 64, 1,024 keys: 23 against 30 us; 4 / 1 heads of width 128, 2,000 keys: 69
-// against 82).
+// Eight query tiles per workgroup (half the K and V rows fetched per query row) on long axes, where that leaves a workgroup for every CU;
+// else four, in twice the workgroups (one head of width 64, 1,024 keys: 23 against 30 us; 4 / 1 heads of width 128, 2,000 keys: 69 against
+// 82).  Long means, each side measured on its own (us):
+//   rows as wide as the tile: 2,048 positions, and the two halves of the workgroup work in phases.  Causal, 32 / 8 heads of 128: 1,300 x 32
+//     708 with four tiles, 763 with eight; 2,048 x 16 811 and 783; 3,000 x 8 809 and 750; 16,384 2,534 and 2,138.
+//   narrower rows: 1,024 positions, in phases from 4,096 on.  12 heads of 100, causal: 3,000 x 8 427 in step, 443 in phases;
+//     8,192 x 2 638 and 599; 16,384 1,190 and 1,078.
+//   encoded rows: 1,024 positions, never in phases: turning K makes the softmax half of a block the longer one (32 / 8 heads of 128,
+//     2,048 x 16: 902 in step, 969 in phases).
 bool long_params(const HopParams& p, LongParams* lp, bool* wide) {
     if (p.n < 1 || p.D < 8 || p.D > 128 || p.D % 4 != 0 || !mfma_forward_layout_ok(p)) return false;
     // Heads that share K and the value input, four of them per workgroup on the same query tile(s): the waves' work is equal under
     // the causal mask and no wave is without a tile.
     lp->heads = p.G % 4 == 0 && p.vin_heads != p.Hq && p.n > 2 * kKeys ? 4u : 1u;
+    const int longer = !p.rope && (p.D == 64 || p.D == 128) ? 2048 : 1024;
     int64_t units = 0;
     for (const int waves : {8, 4}) {
         const int rows = waves / (int)lp->heads * kTile;
         lp->qblocks = (uint32_t)((p.n + rows - 1) / rows);
         units = (int64_t)p.B * p.fibres * lp->qblocks * p.Hkv;
         *wide = waves == 8;
-        if (p.n >= 1024 && units * (p.G / (int)lp->heads) >= 256) break;
+        if (p.n >= longer && units * (p.G / (int)lp->heads) >= 256) break;
     }
     if (units <= 0 || units > 0x7ffffff0LL || p.G > (1 << 19)) return false;
     lp->units = (uint32_t)units;

@@ -1,0 +1,81 @@
+"""The long-axis forward whose workgroup works in two phases (eight query tiles, enough of them for every CU), at its edges: axes that end
+one row after and before a tile, a block and a workgroup, single heads and groups of four, bands, padding, bit tables, narrow rows.  A part of
+the same call on its own has too few workgroups for it and runs four tiles in step, with the same arithmetic in the same order: same bits.
+One part is compared with 64 bits."""
+import math
+
+import pytest
+import torch
+
+import paper_2410_20926_amd as ta
+from gpu_util import TOL
+from paper_2410_20926_amd.workloads import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def call(q, k, v, n, causal, window, valid, table=None):
+    B, _, H, D = q.shape
+    plan = ta.ta_plan_create(B, H, k.shape[2], D, (n,), ta.TA_BF16, causal, window=(window,), valid_len=valid, axis_masks=[table])
+    o = torch.full_like(q, 7.0)
+    ta.ta_axis_attn_forward(plan, 0, q, k, v, ta.TA_VIN_KV, o)
+    return o
+
+
+def band_table(n, window):
+    a, c = torch.arange(n)[:, None], torch.arange(n)[None, :]
+    return torch.from_numpy(ta.pack_axis_mask(((a - c).abs() < window).numpy())).cuda()
+
+
+@pytest.mark.parametrize("n,B,H,Hkv,D,causal,window,valid,tabled", [
+    (2048, 4, 8, 8, 64, True, 0, 0, False),
+    (2049, 4, 8, 8, 128, True, 0, 0, False),
+    (2111, 30, 1, 1, 128, False, 700, 0, False),
+    (2111, 30, 1, 1, 64, False, 700, 0, True),
+    (2080, 2, 16, 4, 128, True, 0, 1500, False),            # four heads that share K and the values side by side
+    (2303, 2, 16, 4, 64, False, 90, 2301, False),
+    (4097, 4, 4, 4, 100, True, 0, 0, False),
+    (4128, 4, 4, 4, 40, False, 1000, 4000, False),
+])
+def test_phases_give_the_bits_of_four_tiles_in_step(n, B, H, Hkv, D, causal, window, valid, tabled):
+    q, k, v = (torch.from_numpy(x).cuda().to(torch.bfloat16) for x in make_inputs(B, n, H, Hkv, D, seed=890 + n + D, dtype="bf16"))
+    G, rows = H // Hkv, 256 // (4 if H // Hkv == 4 else 1)
+    blocks = (n + rows - 1) // rows
+    assert B * Hkv * blocks >= 256 > blocks                # the whole call in phases, a part of it not
+    table = band_table(n, window) if tabled else None
+    whole = call(q, k, v, n, causal, 0 if tabled else window, valid, table)
+    for b in range(0, B, 3):
+        for g in range(Hkv):
+            at = slice(b, b + 1), slice(None), slice(g * G, (g + 1) * G)
+            kv = slice(b, b + 1), slice(None), slice(g, g + 1)
+            part = call(q[at].contiguous(), k[kv].contiguous(), v[kv].contiguous(), n, causal, window, valid)
+            assert torch.equal(part, whole[at]), (b, g)
+    a, c = torch.arange(n, device="cuda")[:, None], torch.arange(n, device="cuda")[None, :]
+    live = valid or n
+    see = (a < live) & (c < live) & ((c <= a) if causal else (c == c)) & (((a - c).abs() < window) if window else (c == c))
+    Q, K, V = (x[0, :, 0].double() for x in (q, k, v))
+    p = torch.softmax((Q @ K.t() / math.sqrt(D)).masked_fill(~see, -math.inf), -1).nan_to_num(0.0)
+    err = (whole[0, :, 0].double() - p @ V).abs().max().item()
+    assert err <= TOL["bf16"], f"{err:.3e}"
+
+
+@pytest.mark.parametrize("n,D,causal,window,valid", [(2080, 128, True, 0, 2080), (2100, 64, False, 300, 1700)])
+def test_values_out_of_reach_stay_out(n, D, causal, window, valid):
+    """An infinity in a value row reaches only the query tiles some row of which sees a key of its tile of 32, padding reaches no row."""
+    B, H = 4, 8
+    q, k, v = (torch.from_numpy(x).cuda().to(torch.bfloat16) for x in make_inputs(B, n, H, H, D, seed=893, dtype="bf16"))
+    clean = call(q, k, v, n, causal, window, valid)
+    assert (clean[:, valid:] == 0).all()
+    bad_k, bad_v = k.clone(), v.clone()
+    bad_k[:, valid:], bad_v[:, (valid + 31) // 32 * 32:] = float("nan"), float("inf")
+    assert torch.equal(call(q, bad_k, bad_v, n, causal, window, valid), clean)
+    for c in (45, valid // 2, valid - 1):
+        bad_v = v.clone()
+        bad_v[:, c] = float("inf")
+        got = call(q, k, bad_v, n, causal, window, valid)
+        c0 = c // 32 * 32
+        for a0 in range(0, valid, 32):
+            a1 = a0 + 31
+            if (causal and c0 > a1) or (window and (c0 - a1 >= window or a0 - (c0 + 31) >= window)):
+                assert torch.equal(got[:, a0:a1 + 1], clean[:, a0:a1 + 1]), (c, a0)
+        assert not torch.isfinite(got[0, c]).any()
