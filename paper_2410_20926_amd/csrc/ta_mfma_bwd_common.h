@@ -37,7 +37,7 @@ __device__ inline void prefetch_tile(u32x4 (&old)[Geo<D>::kDTiles * 2], const u3
         for (int i = 0; i < 4; ++i) {
             if constexpr (NARROW) {
                 const uint32_t fbyte = (uint32_t)(half * 64 + (lane & 7) * 8) * 2;
-                old[half * 4 + i] = load_chunk<true, true>(gbase, tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, fbyte, dbytes);
+                old[half * 4 + i] = load_chunk<true, false>(gbase, tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, fbyte, dbytes);
             } else {
                 old[half * 4 + i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gbase + tile_out_offset<D>(rowoff, which, half, i, lane)));
             }

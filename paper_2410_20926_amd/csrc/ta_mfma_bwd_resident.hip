@@ -123,7 +123,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         for (int i = 0; i < kMine; ++i) {
             const uint32_t rr = (uint32_t)min(kTile * w + (s * kMine + i) * G::kRowsPerPass + row, n - 1);
             uint32_t mis;
-            raw.v[i] = gather_request<NARROW, decltype(once)::value>(base, (x.tok0 + rr * stride) * pitch, lbyte, dbytes, mis);
+            raw.v[i] = gather_request<NARROW, decltype(once)::value && !NARROW>(base, (x.tok0 + rr * stride) * pitch, lbyte, dbytes, mis);
             if constexpr (NARROW) raw.mis |= mis ? 1u << i : 0u;
         }
     };
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         uint32_t obyte;
         out_lane(orow, obyte);
 #pragma unroll
-        for (int i = 0; i < R::kOut; ++i) old[i] = load_chunk<NARROW, true>(base, row_offset(which, i * R::kOutRows + orow), obyte, dbytes);
+        for (int i = 0; i < R::kOut; ++i) old[i] = load_chunk<NARROW, !NARROW>(base, row_offset(which, i * R::kOutRows + orow), obyte, dbytes);
     };
     auto finish = [&](const f32x16 (&acc)[R::kHT], float mult, int which, char* base, const u32x4 (&old)[R::kOut], bool add, bool turn) {
         int orow;

@@ -31,6 +31,13 @@ namespace {
 
 using namespace mfma;
 
+// Whether rows that one wave alone reads are streamed past the caches.  A narrow row shares its first and last cache line with the neighbouring
+// heads' rows, so that a streamed line crosses HBM once per row in it.  That decides it for rows of a few lines' parts in 64-wide tiles (8 sequences
+// of 20 x 28 x 23, 8 / 2 heads of width 40: 159 -> 134 us through the cache; 2 sequences, 32 heads: 220 -> 195); wider rows are mostly whole lines,
+// and their forward is faster streamed (32 x 32 x 32, 32 heads of width 100: 510 us against 530; 24 x 25 x 26, 12 heads of width 96: 290 / 314).
+template <int D, bool NARROW>
+constexpr bool streamed_rows() { return !NARROW || D > 64; }
+
 constexpr int kWavesPerBlock = 4;
 
 // KT = number of 32-key tiles a unit may walk (1: n <= 32, 2: n <= 64).
@@ -134,11 +141,11 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) {
                     const u32x4 off = rowoff[j * kTile + i * G::kRowsPerPass + lrow];
-                    kreg[j][i] = gather_chunk<NARROW, decltype(k_nt)::value>(kb, off.y, lbyte, dbytes);
+                    kreg[j][i] = gather_chunk<NARROW, decltype(k_nt)::value && streamed_rows<D, NARROW>()>(kb, off.y, lbyte, dbytes);
                     voff[j][i] = off.z;
-                    if (j == 0) vreg[j][i] = gather_chunk<NARROW, decltype(v_nt)::value>(vb, voff[j][i], lbyte, dbytes);
+                    if (j == 0) vreg[j][i] = gather_chunk<NARROW, decltype(v_nt)::value && streamed_rows<D, NARROW>()>(vb, voff[j][i], lbyte, dbytes);
                     if (KT == 1) {
-                        qreg[i] = gather_chunk<NARROW, true>(qb, off.x, lbyte, dbytes);
+                        qreg[i] = gather_chunk<NARROW, streamed_rows<D, NARROW>()>(qb, off.x, lbyte, dbytes);
                         ooff[i] = off.w;
                     }
                 }
@@ -152,7 +159,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
             const u32x4 off = rowoff[qt * kTile + i * G::kRowsPerPass + lrow];
-            qreg[i] = gather_chunk<NARROW, true>(qb, off.x, lbyte, dbytes);
+            qreg[i] = gather_chunk<NARROW, streamed_rows<D, NARROW>()>(qb, off.x, lbyte, dbytes);
             ooff[i] = off.w;
         }
     }
@@ -434,7 +441,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const u32x4 off = rowoff[qt * kTile + i * G::kRowsPerPass + lrow];
-        qreg[i] = gather_chunk<NARROW, true>(qb, off.x, lbyte, dbytes);
+        qreg[i] = gather_chunk<NARROW, streamed_rows<D, NARROW>()>(qb, off.x, lbyte, dbytes);
         ooff[i] = off.w;
     }
 #pragma unroll
@@ -450,7 +457,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) {
                     const u32x4 off = rowoff[j * kTile + i * G::kRowsPerPass + lrow];
-                    vreg[j][i] = (KT == 1) ? gather_chunk<NARROW, true>(vb, off.z, lbyte, dbytes)
+                    vreg[j][i] = (KT == 1) ? gather_chunk<NARROW, streamed_rows<D, NARROW>()>(vb, off.z, lbyte, dbytes)
                                            : gather_chunk<NARROW, false>(vb, off.z, lbyte, dbytes);   // with two query tiles a value tile is read twice: keep it cached
                 }
             }
