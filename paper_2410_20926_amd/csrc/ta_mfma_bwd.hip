@@ -24,7 +24,8 @@ namespace {
 
 using namespace mfma;
 
-// blockDim.x = 64 * G (G = query heads per key/value head: 1, 2, 4 or 8); grid = (Hkv, tiles_lo, B * tiles_hi).
+// blockDim.x = 64 * G (G = query heads per key/value head), grid = (Hkv, tiles_lo, B * tiles_hi); for G = 1 a workgroup is 1, 2 or 4 heads side by
+// side and grid.x = Hkv / heads.
 // TABLE: the axis has a caller's bit table; MULTI: the group has more than 8 heads and this launch
 // covers 8 of them (separate instantiations keep the common case free of both).
 // ROPE: the hop scores with rotary-encoded Q and K (separate instantiations, so that the plain kernel carries none of it).
@@ -34,12 +35,13 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     const HopParams& p = bp.hop;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = MULTI ? bp.wg_heads : p.G;
+    const int w = nw == 1 ? 0 : wave;                     // heads without a group stand side by side in a workgroup, each on its own
 
     uint32_t bx, ty;
     workgroup_xy<NARROW>(bx, ty);
-    const int g = (int)bx;
+    const int g = nw == 1 ? (int)(bx * (blockDim.x >> 6)) + wave : (int)bx;
     const int h = g * p.G + (MULTI ? bp.head_base : 0) + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + ty;
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     const int n = p.n;
 
     float* red = reinterpret_cast<float*>(smem);          // workgroup-shared reduction area
-    char* buf = smem + (nw > 1 ? G::kRedBytes : 0) + w * G::kWaveBytes;
+    char* buf = smem + (nw > 1 ? G::kRedBytes : 0) + wave * G::kWaveBytes;
     float* stats = reinterpret_cast<float*>(buf + G::kBufBytes);
     u32x4* rowoff = reinterpret_cast<u32x4*>(buf + G::kBufBytes + G::kStats);   // per row: byte offsets in (q, k, v_in, o) layouts
 
@@ -1059,9 +1061,16 @@ template <int D, bool NARROW>
 hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     const HopParams& p = bp.hop;
     const bool multi = p.G > bp.wg_heads, table = p.mask != nullptr;
-    const size_t smem = (size_t)(bp.wg_heads > 1 ? BGeo<D>::kRedBytes : 0) + (size_t)bp.wg_heads * BGeo<D>::kWaveBytes;
-    const dim3 grid((unsigned)p.Hkv, tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
-    const dim3 block(64 * bp.wg_heads);
+    // Heads without a group: neighbouring heads of a tile in one workgroup, so that a token's rows of all of them are asked for, and written,
+    // from one CU at about the same time (training steps of 32 x 32 x 32, 32 heads of width 128: one head per workgroup 1,734 us, two 1,654, four 1,617;
+    // 8 sequences of 16 x 16 x 16, 8 heads of width 64: 235, 224, 219).  Narrow rows, which an XCD takes in order anyway, want two (width 100: 1,743,
+    // 1,723, 1,750 us).
+    int side = 1;
+    if (p.G == 1)
+        for (side = NARROW ? 2 : 4; p.Hkv % side != 0;) side /= 2;
+    const size_t smem = (size_t)(bp.wg_heads > 1 ? BGeo<D>::kRedBytes : 0) + (size_t)bp.wg_heads * side * BGeo<D>::kWaveBytes;
+    const dim3 grid((unsigned)(p.Hkv / side), tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
+    const dim3 block(64 * bp.wg_heads * side);
     const void* kf;
     if (p.rope) kf = multi ? (table ? (const void*)mfma_bwd_kernel<D, true, true, NARROW, true> : (const void*)mfma_bwd_kernel<D, false, true, NARROW, true>)
                            : (table ? (const void*)mfma_bwd_kernel<D, true, false, NARROW, true> : (const void*)mfma_bwd_kernel<D, false, false, NARROW, true>);

@@ -177,7 +177,7 @@ __device__ inline void chain_sum(f32x16 (&acc)[Geo<D>::kDTiles], float* red, int
                 for (int e = 0; e < 4; ++e) acc[t][4 * q4 + e] += v[e];
             }
     }
-    __syncthreads();                                      // red may be reused
+    if (nw > 1) __syncthreads();                          // red may be reused
 }
 
 constexpr int kStreamMaxLds = 160 * 1024;              // LDS of one compute unit

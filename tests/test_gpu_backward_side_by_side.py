@@ -1,0 +1,46 @@
+"""GPU parity of the one-tile backward where heads have no group and one, two or four of them share a workgroup: head counts that leave one, two or
+four, whole and narrow rows (neighbours share cache lines), packed and ragged tiles, masks, the encoding, a partial last tile."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2410_20926_amd as ta
+from gpu_util import TOL, multihop_backward, multihop_forward
+from oracle import tensattn_oracle as orc
+from paper_2410_20926_amd.workloads import make_inputs
+from grad_bounds import check_backward
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dims, B, heads, D, causal, window, valid_lens, rope base, axes with a table
+    ((7, 32), 1, 1, 128, True, None, None, None, ()),
+    ((9, 11), 2, 2, 64, False, None, (99, 40), None, ()),
+    ((31, 5), 1, 3, 128, True, (4, 0), None, None, (1,)),
+    ((3, 6, 17), 1, 4, 64, True, None, None, 10000.0, ()),
+    ((16, 13), 1, 6, 100, False, None, None, None, (0,)),
+    ((5, 32), 2, 8, 100, True, None, (160, 33), None, ()),
+    ((20, 9), 1, 12, 128, False, None, None, 500.0, ()),
+    ((4, 4, 10), 1, 5, 40, True, None, None, None, ()),
+    ((32, 2), 1, 16, 20, True, None, None, None, ()),
+]
+
+
+@pytest.mark.parametrize("dims,B,H,D,causal,window,lens,rope,axes", CASES)
+def test_ungrouped_heads_match_oracle(dims, B, H, D, causal, window, lens, rope, axes):
+    N = int(np.prod(dims))
+    rng = np.random.default_rng(N + H)
+    q, k, v, d_o = make_inputs(B, N, H, H, D, seed=9100 + N + H, dtype="bf16", with_grad=True)
+    masks = [(rng.random((n, n)) < 0.7) | np.eye(n, dtype=bool) if i in axes else None for i, n in enumerate(dims)]
+    kw = dict(window=window, rope_base=rope)
+    pkw = dict(kw, axis_masks=[None if x is None else torch.from_numpy(ta.pack_axis_mask(x)).cuda() for x in masks])
+    if lens is not None:
+        pkw["valid_lens"] = torch.tensor(lens, dtype=torch.int64, device="cuda")
+    okw = dict(kw, valid_len=list(lens) if lens else None, axis_masks=masks)
+    got, plan, dev = multihop_forward(q, k, v, dims, "bf16", causal, save=True, **pkw)
+    assert np.abs(got - orc.tensorized_attention_forward(q, k, v, dims, causal, **okw)).max() <= TOL["bf16"]
+    assert plan.hop_function(0, ta.TA_VIN_KV, True) == "mfma_bwd_kernel"
+    grads = multihop_backward(plan, dev, d_o, "bf16")
+    check_backward(grads, q, k, v, d_o, dims, causal, "bf16", **okw)
+    again = multihop_backward(plan, dev, d_o, "bf16")
+    assert all(np.array_equal(a, b) for a, b in zip(grads, again))
