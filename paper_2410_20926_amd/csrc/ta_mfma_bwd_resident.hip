@@ -123,7 +123,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         for (int i = 0; i < kMine; ++i) {
             const uint32_t rr = (uint32_t)min(kTile * w + (s * kMine + i) * G::kRowsPerPass + row, n - 1);
             uint32_t mis;
-            raw.v[i] = gather_request<NARROW, decltype(once)::value && !NARROW>(base, (x.tok0 + rr * stride) * pitch, lbyte, dbytes, mis);
+            raw.v[i] = gather_request<NARROW, decltype(once)::value>(base, (x.tok0 + rr * stride) * pitch, lbyte, dbytes, mis);
             if constexpr (NARROW) raw.mis |= mis ? 1u << i : 0u;
         }
     };
