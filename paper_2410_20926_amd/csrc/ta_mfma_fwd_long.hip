@@ -46,12 +46,17 @@ struct LongParams {
 // workgroup work half a block apart (see the loop).
 enum Form { kShort, kBlocks, kPhases };
 // NARROW: the head is narrower than the D-wide tile; see load_chunk.
+// 64-wide heads in step: three waves per SIMD, i.e. at most 168 registers (with the 170 that the compiler takes by itself and two waves, 32 / 8 heads
+// of 512 x 64: 254 us, here 223).
 template <int D, int NW, Form FORM, bool NARROW, bool ROPE>
-__global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, LongParams lp) {
+__global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void mfma_fwd_long_kernel(HopParams p, LongParams lp) {
     using G = Geo<D>;
     constexpr bool SHORT = FORM == kShort, kPhased = FORM == kPhases;
     static_assert(!kPhased || NW == 8, "two sets of four waves");
-    constexpr int kVPitch = 2 * D + 64;                   // value rows 16 or 48 banks apart: the four rows of a transposed read on banks of their own
+    // Value rows 16 or 48 banks apart (the four rows of a transposed read on banks of their own), except where blocks of a few hundred keys are
+    // worked on in step: there the LDS is not what bounds the kernel, and the smaller buffers are worth 1 to 2 per cent (32 / 8 heads, 512 x 16 of
+    // width 128 120.8 us against 122.2; 200 x 64 of width 64 85.0 / 87.1; 16 / 4 heads of width 100, 400 x 30, the other way: 141.4 / 137.5).
+    constexpr int kVPitch = FORM == kBlocks ? 2 * D + 16 : 2 * D + 64;
     constexpr int kBlock = kKeys * G::kPitch, kVBlock = kKeys * kVPitch;   // one K, one value block
     constexpr int kBuffers = kPhased ? 3 : 2;
     constexpr int kRows = NW * G::kRowsPerPass;           // rows the workgroup fetches per pass
@@ -433,7 +438,7 @@ __global__ __launch_bounds__(64 * NW, 2) void mfma_fwd_long_kernel(HopParams p, 
 
 template <int D, int NW, Form FORM, bool NARROW, bool ROPE>
 hipError_t launch(const HopParams& p, const LongParams& lp, hipStream_t s) {
-    constexpr int smem = (FORM == kPhases ? 3 : 2) * kKeys * (Geo<D>::kPitch + 2 * D + 64);   // also holds NW query or output tiles
+    constexpr int smem = (FORM == kPhases ? 3 : 2) * kKeys * (Geo<D>::kPitch + 2 * D + (FORM == kBlocks ? 16 : 64));   // also holds NW query or output tiles
     static_assert(smem >= NW * kTile * Geo<D>::kPitch, "the transit tiles fit");
     if (smem > 64 * 1024) {
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_fwd_long_kernel<D, NW, FORM, NARROW, ROPE>), smem);
