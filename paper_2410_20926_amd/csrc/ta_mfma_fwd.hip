@@ -177,8 +177,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
         rope_rates(p, lcol, rev);
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
-            // (passes whose rows are all padding stay as they are)
-            if (((real_rows >> (qt * kTile + i * G::kRowsPerPass)) & ((1u << G::kRowsPerPass) - 1u)) == 0) continue;
+            if (qt * kTile + i * G::kRowsPerPass >= rows_valid) break;      // (passes past the last row stay as they are)
             float c[4], sn[4];
             rope_sincos(row_pos(qt * kTile + i * G::kRowsPerPass + lrow), rev, c, sn);
             qreg[i] = rope_apply(qreg[i], c, sn);
