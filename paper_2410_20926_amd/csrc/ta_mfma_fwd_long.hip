@@ -113,6 +113,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
     keys(qb * tiles * kTile, (qb + 1) * tiles * kTile - 1, kKeys, jb, je);
     keys(qt * kTile, qt * kTile + kTile - 1, kTile, wb, we);
     if (qt * kTile >= nreal) we = wb;
+    // A workgroup of nothing but padding writes zeros and takes no block; in phases, where no wave leaves a tile's scores out, it would cost as much as
+    // any other (8 sequences of up to 16,713 keys, 8 / 2 heads of width 64, causal: 3,061 us, so 1,868; in step 2,325).
+    if (qb * tiles * kTile >= nreal) je = jb;
 
     // this wave's share of a block: rows w * kRowsPerPass + lrow + i * kRows; rows past the fibre's end: its last one, never visible
     struct Raw { u32x4 v[kMine]; uint32_t mis; };
@@ -470,7 +473,8 @@ hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream
 //   rows as wide as the tile: 2,048 positions, and the two halves of the workgroup work in phases.  Causal, 32 / 8 heads of 128: 1,300 x 32
 //     708 with four tiles, 763 with eight; 2,048 x 16 811 and 783; 3,000 x 8 809 and 750; 16,384 2,534 and 2,138.
 //   narrower rows: 1,024 positions, in phases from 4,096 on.  12 heads of 100, causal: 3,000 x 8 427 in step, 443 in phases;
-//     8,192 x 2 638 and 599; 16,384 1,190 and 1,078.
+//     8,192 x 2 638 and 599; 16,384 1,190 and 1,078.  (Where the last round of workgroups comes out badly the order can turn: 8 sequences of 9,000, 4
+//     heads of 100, 1,100 and 1,165.)
 //   encoded rows: 1,024 positions, never in phases: turning K makes the softmax half of a block the longer one (32 / 8 heads of 128,
 //     2,048 x 16: 902 in step, 969 in phases).
 bool long_params(const HopParams& p, LongParams* lp, bool* wide) {
