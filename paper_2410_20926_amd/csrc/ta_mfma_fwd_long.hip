@@ -296,12 +296,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
 #pragma unroll
                 for (int d = 0; d < G::kDTiles; ++d) ot[d] = mma(v[d][s2], w2[s2], ot[d]);
         };
-        // blocks [ia, iz): every row of this wave's tile sees all of their keys
+        // blocks [ia, iz): every row of this wave's tile sees all of their keys (rows past the fibre's end may: they are not stored)
         int ia = je, iz = je;
-        if (!p.mask && qt * kTile + kTile <= nreal) {
+        if (!p.mask && (nreal == n || qt * kTile + kTile <= nreal)) {
             int lo, hi, lo2, hi2;
             visible_range(qt * kTile, 0, n, p.causal, p.window, lo, hi);
-            visible_range(qt * kTile + kTile - 1, 0, n, p.causal, p.window, lo2, hi2);
+            visible_range(min(qt * kTile + kTile, n) - 1, 0, n, p.causal, p.window, lo2, hi2);
             ia = min(max((max(lo2, 0) + kKeys - 1) / kKeys, jb), je);
             iz = max(min(min(hi, nreal) / kKeys, je), ia);
         }
@@ -346,8 +346,24 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
             slot = next;
         };
         if (w >= 4) __syncthreads();
-        __builtin_amdgcn_s_setprio(1);
         int j = jb;
+        if (wb >= we) {
+            // A wave whose tile lies past the fibre's end or in padding only fetches, with the barriers of the others.  It formed scores and weights of
+            // nothing in the longest workgroup of a causal axis, and a tile that is cut off there took every block for a masked one: 8 sequences of
+            // 9,000, causal, 4 heads of width 40, 763 us (8,960: 595), so 614; in step 703.  6,600, 4 heads of width 100: 657, so 593; in step 645.
+#pragma unroll 1
+            for (; j < je; ++j) {
+                const int next = slot == 2 ? 0 : slot + 1, after = slot == 0 ? 2 : slot - 1;
+                __syncthreads();
+                write(sK + after * kBlock, G::kPitch, j + 2, kr, true);
+                write(sV + next * kVBlock, kVPitch, j + 1, vr, false);
+                request_next(kbase, lp.k_row, koff, kr);
+                request_next(vbase, lp.v_row, voff, vr);
+                __syncthreads();
+                slot = next;
+            }
+        }
+        __builtin_amdgcn_s_setprio(1);
         for (int stop = ia;; stop = je) {
 #pragma unroll 1
             for (; j < stop; ++j) step(j, std::false_type{});
@@ -473,8 +489,7 @@ hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream
 //   rows as wide as the tile: 2,048 positions, and the two halves of the workgroup work in phases.  Causal, 32 / 8 heads of 128: 1,300 x 32
 //     708 with four tiles, 763 with eight; 2,048 x 16 811 and 783; 3,000 x 8 809 and 750; 16,384 2,534 and 2,138.
 //   narrower rows: 1,024 positions, in phases from 4,096 on.  12 heads of 100, causal: 3,000 x 8 427 in step, 443 in phases;
-//     8,192 x 2 638 and 599; 16,384 1,190 and 1,078.  (Where the last round of workgroups comes out badly the order can turn: 8 sequences of 9,000, 4
-//     heads of 100, 1,100 and 1,165.)
+//     8,192 x 2 638 and 599; 16,384 1,190 and 1,078.
 //   encoded rows: 1,024 positions, never in phases: turning K makes the softmax half of a block the longer one (32 / 8 heads of 128,
 //     2,048 x 16: 902 in step, 969 in phases).
 bool long_params(const HopParams& p, LongParams* lp, bool* wide) {

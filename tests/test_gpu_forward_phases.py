@@ -79,3 +79,42 @@ def test_values_out_of_reach_stay_out(n, D, causal, window, valid):
             if (causal and c0 > a1) or (window and (c0 - a1 >= window or a0 - (c0 + 31) >= window)):
                 assert torch.equal(got[:, a0:a1 + 1], clean[:, a0:a1 + 1]), (c, a0)
         assert not torch.isfinite(got[0, c]).any()
+
+
+@pytest.mark.parametrize("vin", [ta.TA_VIN_KV, ta.TA_VIN_O])
+@pytest.mark.parametrize("dims,axis,B,H,Hkv,D,causal,window,valid", [
+    ((2056, 3), 0, 2, 8, 8, 128, True, 0, 0),               # 8 rows past a workgroup: one wave works, on a quarter of a tile, seven fetch
+    ((3, 2200), 1, 2, 8, 8, 64, True, 0, 0),                # five tiles, the last of 24 rows
+    ((2200, 3), 0, 2, 16, 4, 64, False, 2100, 0),           # groups of four: two tiles per workgroup
+    ((2, 4100, 2), 1, 1, 4, 4, 100, True, 0, 0),            # several fibres, rows apart and narrow
+    ((4100, 3), 0, 2, 4, 4, 40, False, 0, 9000),            # padding begins inside the axis
+])
+def test_last_workgroup_and_rows_apart(dims, axis, B, H, Hkv, D, causal, window, valid, vin):
+    """Axes that end a few rows into a workgroup, with rows that are not neighbours in memory and several fibres: same bits as four tiles in step."""
+    N, n = math.prod(dims), dims[axis]
+    q, k, v = (torch.from_numpy(x).cuda().to(torch.bfloat16) for x in make_inputs(B, N, H, Hkv, D, seed=896 + N + D, dtype="bf16"))
+    x = q.flip(0, 1).contiguous() if vin == ta.TA_VIN_O else v
+    G = H // Hkv
+
+    def hop(q, k, x):
+        plan = ta.ta_plan_create(q.shape[0], q.shape[2], k.shape[2], D, dims, ta.TA_BF16, causal, valid_len=valid,
+                                 window=tuple(window if a == axis else 0 for a in range(len(dims))))
+        o = torch.full_like(q, 7.0)
+        ta.ta_axis_attn_forward(plan, axis, q, k, x, vin, o)
+        return o
+    whole = hop(q, k, x)
+    for b in range(B):
+        for g in range(0, Hkv, 3):
+            at = slice(b, b + 1), slice(None), slice(g * G, (g + 1) * G)
+            kv = slice(b, b + 1), slice(None), slice(g, g + 1)
+            assert torch.equal(hop(q[at].contiguous(), k[kv].contiguous(), x[at if vin == ta.TA_VIN_O else kv].contiguous()), whole[at]), (b, g)
+    if valid:
+        assert not whole[:, valid:].any()
+    fibre = torch.arange(N, device="cuda").view(dims).movedim(axis, -1).reshape(-1, n)[1]    # the second fibre of the last sequence's first head
+    a, c = torch.arange(n, device="cuda")[:, None], torch.arange(n, device="cuda")[None, :]
+    live = fibre < (valid or N)
+    see = live[:, None] & live[None, :] & ((c <= a) if causal else (c == c)) & (((a - c).abs() < window) if window else (c == c))
+    Q, K, X = (t[-1, fibre, 0].double() for t in (q, k, x))
+    p = torch.softmax((Q @ K.t() / math.sqrt(D)).masked_fill(~see, -math.inf), -1).nan_to_num(0.0)
+    err = (whole[-1, fibre, 0].double() - p @ X).abs().max().item()
+    assert err <= TOL["bf16"], f"{err:.3e}"
