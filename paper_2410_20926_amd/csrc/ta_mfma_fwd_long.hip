@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
             vis[t] = range_mask(min(max(klo - kTile * (c + t), 0), kTile), min(max(khi - kTile * (c + t), 0), kTile));
-            if (p.mask && qrow < nreal && c + t < p.mask_words) vis[t] &= table_word(p, (uint32_t)f, qrow, c + t);
+            if (p.mask && qrow < nreal && (!kPhased || c + t < p.mask_words)) vis[t] &= table_word(p, (uint32_t)f, qrow, c + t);
             all &= vis[t];
         }
         if (!__all(all == 0xffffffffu)) {
@@ -416,7 +416,14 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
                 else score(std::integral_constant<int, 1>{});
 #pragma unroll 1
                 for (int t = first; t < end; ++t) {           // one body: two would copy the accumulators from one to the other
-                    if (grows[0]) rescale(corr[0]);
+                    if constexpr (SHORT) {
+                        if (grows[0]) rescale(corr[0]);
+                    } else if (grows[0]) {                    // (the same: as a call it cost eight waves of 64-wide heads 2 per cent)
+#pragma unroll
+                        for (int d = 0; d < G::kDTiles; ++d)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) ot[d][r] *= corr[0];
+                    }
 #pragma unroll
                     for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
