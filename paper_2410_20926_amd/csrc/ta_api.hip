@@ -403,6 +403,12 @@ const char* ta_plan_hop_function(const ta_plan_t* pl, int axis, int vin, int bac
     return id == BWD_NONE ? "unsupported" : id == BWD_GENERIC ? ta::generic_backward_function(bp, pl->desc.dtype) : ta::mfma_backward_function(bp);
 }
 
+const char* ta_plan_hop_form(const ta_plan_t* pl, int axis, int vin) {
+    const char* function = ta_plan_hop_function(pl, axis, vin, 0);
+    if (!function || strcmp(function, "mfma_fwd_long_kernel") != 0) return function ? "" : nullptr;
+    return ta::mfma_forward_long_form(hop_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr));
+}
+
 int ta_plan_small_pair_position(const ta_plan_t* pl) {
     return pl && pl->small_pair && ta_plan_fused_position(pl) < 0 ? pl->order - 2 : -1;
 }

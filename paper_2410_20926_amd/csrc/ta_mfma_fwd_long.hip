@@ -20,6 +20,7 @@
 // 200 -> 184 us; 8 heads of 1,024 x 16: 140 -> 116 us, of width 64, 512 x 64: 101 -> 86 us (against a kernel that took 32 keys per barrier and
 // rescaled for every tile).  (A reference that moved only when the maximum had passed it by 2^6 took 12 % less in step, with 3 per cent more error.)
 #include "ta_mfma_common.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace ta {
@@ -43,8 +44,9 @@ struct LongParams {
 };
 
 // kShort: at most two blocks (n <= 128): both are requested at once and stay, no barrier between them.  kPhases: the two halves of the
-// workgroup work half a block apart (see the loop).
+// workgroup work half a block apart (see the loop); never with a bit table.
 enum Form { kShort, kBlocks, kPhases };
+struct Choice { Form form; int waves; };                  // waves per workgroup: 4, or 8 (kPhases: always)
 // NARROW: the head is narrower than the D-wide tile; see load_chunk.
 // 64-wide heads in step: three waves per SIMD, i.e. at most 168 registers (with the 170 that the compiler takes by itself and two waves, 32 / 8 heads
 // of 512 x 64: 254 us, here 223).
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
             vis[t] = range_mask(min(max(klo - kTile * (c + t), 0), kTile), min(max(khi - kTile * (c + t), 0), kTile));
-            if (p.mask && qrow < nreal && (!kPhased || c + t < p.mask_words)) vis[t] &= table_word(p, (uint32_t)f, qrow, c + t);
+            if (!kPhased && p.mask && qrow < nreal) vis[t] &= table_word(p, (uint32_t)f, qrow, c + t);
             all &= vis[t];
         }
         if (!__all(all == 0xffffffffu)) {
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
         };
         // blocks [ia, iz): every row of this wave's tile sees all of their keys (rows past the fibre's end may: they are not stored)
         int ia = je, iz = je;
-        if (!p.mask && (nreal == n || qt * kTile + kTile <= nreal)) {
+        if (nreal == n || qt * kTile + kTile <= nreal) {
             int lo, hi, lo2, hi2;
             visible_range(qt * kTile, 0, n, p.causal, p.window, lo, hi);
             visible_range(min(qt * kTile + kTile, n) - 1, 0, n, p.causal, p.window, lo2, hi2);
@@ -475,46 +477,56 @@ hipError_t launch(const HopParams& p, const LongParams& lp, hipStream_t s) {
     return hipGetLastError();
 }
 template <int D, bool NARROW, bool ROPE>
-hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream_t s) {
-    if (p.n <= 2 * kKeys) return launch<D, 4, kShort, NARROW, ROPE>(p, lp, s);
-    if (!wide) return launch<D, 4, kBlocks, NARROW, ROPE>(p, lp, s);
+hipError_t launch(const HopParams& p, const LongParams& lp, const Choice& how, hipStream_t s) {
+    if (how.form == kShort) return launch<D, 4, kShort, NARROW, ROPE>(p, lp, s);
+    if (how.waves == 4) return launch<D, 4, kBlocks, NARROW, ROPE>(p, lp, s);
     if constexpr (!ROPE) {
-        if (!NARROW || p.n >= 4096) return launch<D, 8, kPhases, NARROW, ROPE>(p, lp, s);
+        if (how.form == kPhases) return launch<D, 8, kPhases, NARROW, ROPE>(p, lp, s);
     }
     if constexpr (NARROW || ROPE) return launch<D, 8, kBlocks, NARROW, ROPE>(p, lp, s);
     return hipErrorInvalidValue;                          // (not reached)
 }
 template <bool ROPE>
-hipError_t launch(const HopParams& p, const LongParams& lp, bool wide, hipStream_t s) {
-    return p.D == 128 ? launch<128, false, ROPE>(p, lp, wide, s) : p.D == 64 ? launch<64, false, ROPE>(p, lp, wide, s)
-         : p.D > 64 ? launch<128, true, ROPE>(p, lp, wide, s) : launch<64, true, ROPE>(p, lp, wide, s);
+hipError_t launch(const HopParams& p, const LongParams& lp, const Choice& how, hipStream_t s) {
+    return p.D == 128 ? launch<128, false, ROPE>(p, lp, how, s) : p.D == 64 ? launch<64, false, ROPE>(p, lp, how, s)
+         : p.D > 64 ? launch<128, true, ROPE>(p, lp, how, s) : launch<64, true, ROPE>(p, lp, how, s);
 }
 
-// Eight query tiles per workgroup (half the K and V rows fetched per query row) on long axes, where that leaves a workgroup for every CU;
-// else four, in twice the workgroups (one head of width 64, 1,024 keys: 23 against 30 us; 4 / 1 heads of width 128, 2,000 keys: 69 against
-// 82).  Long means, each side measured on its own (us):
-//   rows as wide as the tile: 2,048 positions, and the two halves of the workgroup work in phases.  Causal, 32 / 8 heads of 128: 1,300 x 32
-//     708 with four tiles, 763 with eight; 2,048 x 16 811 and 783; 3,000 x 8 809 and 750; 16,384 2,534 and 2,138.
-//   narrower rows: 1,024 positions, in phases from 4,096 on.  12 heads of 100, causal: 3,000 x 8 427 in step, 443 in phases;
-//     8,192 x 2 638 and 599; 16,384 1,190 and 1,078.
-//   encoded rows: 1,024 positions, never in phases: turning K makes the softmax half of a block the longer one (32 / 8 heads of 128,
-//     2,048 x 16: 902 in step, 969 in phases).
-bool long_params(const HopParams& p, LongParams* lp, bool* wide) {
+// Eight query tiles per workgroup (half the K and V rows fetched per query row), in phases or in step, where the axis is long and that leaves a workgroup
+// for every CU; else four, in twice the workgroups (one head of width 64, 1,024 keys: 23 against 30 us; 4 / 1 heads of width 128, 2,000 keys: 69 against
+// 82).  In phases a wave takes every block that any row of its workgroup sees, and a block with masked keys costs it more; so the keys that a row sees
+// (`reach`: the axis, or a window) decide as well, and calls with a bit table stay in step.  Measured on either side (us; 4: four tiles, 8: eight in step,
+// p: phases):
+//   rows as wide as the tile, from 2,048 positions on: phases, unless a window leaves fewer than 1,280 keys (heads without a group of four 1,536, 64-wide
+//     2,048).  Causal, 32 / 8 heads of 128: 2,048 x 16 4 811, p 783; 16,384 2,534, 2,138; two sequences of 16,384, window 64 4 149, p 282; 1,024 740, 755;
+//     2,048 1,305, 1,221; 16 heads of 64, window 64 57, 117; 1,024 223, 262; 3,000 521, 530.  Tables of random bits, four sequences of 4,096, not causal:
+//     32 / 8 heads of 128 4 1,455, p 1,579; of 64 857, 1,216.  (A table that hides nothing, 16,384, 32 / 8 heads of 128: 5,237, 4,810.)
+//   narrower rows: eight from 1,024 positions on, in phases from 4,096 positions and 3,000 keys (width up to 64: 1,024) on.  12 heads of 100, causal:
+//     3,000 x 8 8 427, p 443; 8,192 x 2 638, 599; 16,384 1,190, 1,078; two sequences of 16,384, window 64 130, 226; 1,024 382, 446; 3,000 865, 870; 8
+//     heads of 40, window 512 111, 118; 1,280 196, 187.  Tables of random bits, four of 4,096, 12 heads of 100: 665, 771.
+//   encoded rows: eight from 1,024 positions on, never in phases: turning K makes the softmax half of a block the longer one (32 / 8 heads of 128,
+//     2,048 x 16: 8 902, p 969).
+bool long_params(const HopParams& p, LongParams* lp, Choice* how) {
     if (p.n < 1 || p.D < 8 || p.D > 128 || p.D % 4 != 0 || !mfma_forward_layout_ok(p)) return false;
     // Heads that share K and the value input, four of them per workgroup on the same query tile(s): the waves' work is equal under
     // the causal mask and no wave is without a tile.
     lp->heads = p.G % 4 == 0 && p.vin_heads != p.Hq && p.n > 2 * kKeys ? 4u : 1u;
-    const int longer = !p.rope && (p.D == 64 || p.D == 128) ? 2048 : 1024;
-    int64_t units = 0;
-    for (const int waves : {8, 4}) {
-        const int rows = waves / (int)lp->heads * kTile;
-        lp->qblocks = (uint32_t)((p.n + rows - 1) / rows);
-        units = (int64_t)p.B * p.fibres * lp->qblocks * p.Hkv;
-        *wide = waves == 8;
-        if (p.n >= longer && units * (p.G / (int)lp->heads) >= 256) break;
-    }
-    if (units <= 0 || units > 0x7ffffff0LL || p.G > (1 << 19)) return false;
-    lp->units = (uint32_t)units;
+    const int groups = p.G / (int)lp->heads;
+    auto blocks = [&](int waves) { const int rows = waves / (int)lp->heads * kTile; return (p.n + rows - 1) / rows; };
+    auto units = [&](int waves) { return (int64_t)p.B * p.fibres * blocks(waves) * p.Hkv; };
+    const bool whole = p.D == 64 || p.D == 128;
+    const int64_t reach = p.window > 0 ? std::min<int64_t>(p.n, p.causal ? p.window : 2 * (int64_t)p.window - 1) : p.n;
+    const int64_t wgs = units(8) * groups;
+    const bool eight = p.n >= 1024 && wgs >= 256;
+    bool phases = eight && !p.rope && !p.mask;
+    if (!whole) phases = phases && p.n >= 4096 && reach >= (p.D > 64 ? 3000 : 1024);
+    else phases = phases && p.n >= 2048 && reach >= (p.D == 64 ? 2048 : lp->heads == 4 ? 1280 : 1536);
+    how->form = p.n <= 2 * kKeys ? kShort : phases ? kPhases : kBlocks;
+    how->waves = phases || (eight && (!whole || p.rope)) ? 8 : 4;
+    lp->qblocks = (uint32_t)blocks(how->waves);
+    const int64_t n_units = units(how->waves);
+    if (n_units <= 0 || n_units > 0x7ffffff0LL || p.G > (1 << 19)) return false;
+    lp->units = (uint32_t)n_units;
     lp->q_row = (uint32_t)(p.q.st * 2); lp->k_row = (uint32_t)(p.k.st * 2);
     lp->v_row = (uint32_t)(p.vin.st * 2); lp->o_row = (uint32_t)(p.o.st * 2);
     return true;
@@ -524,15 +536,22 @@ bool long_params(const HopParams& p, LongParams* lp, bool* wide) {
 
 bool mfma_forward_long_feasible(const HopParams& p) {
     LongParams lp;
-    bool wide;
-    return long_params(p, &lp, &wide);
+    Choice how;
+    return long_params(p, &lp, &how);
+}
+
+const char* mfma_forward_long_form(const HopParams& p) {
+    LongParams lp;
+    Choice how;
+    if (!long_params(p, &lp, &how)) return "unsupported";
+    return how.form == kShort ? "two_blocks" : how.form == kPhases ? "eight_tiles_in_phases" : how.waves == 8 ? "eight_tiles_in_step" : "four_tiles_in_step";
 }
 
 hipError_t launch_mfma_forward_long(const HopParams& p, hipStream_t s) {
     LongParams lp;
-    bool wide;
-    if (!long_params(p, &lp, &wide)) return hipErrorInvalidValue;
-    return p.rope ? launch<true>(p, lp, wide, s) : launch<false>(p, lp, wide, s);
+    Choice how;
+    if (!long_params(p, &lp, &how)) return hipErrorInvalidValue;
+    return p.rope ? launch<true>(p, lp, how, s) : launch<false>(p, lp, how, s);
 }
 
 }  // namespace ta

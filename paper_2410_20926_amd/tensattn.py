@@ -22,7 +22,7 @@ EXPORTS = [
     "ta_axis_attn_backward", "ta_multihop_forward", "ta_multihop_backward", "ta_rope_apply", "ta_copy_bytes", "ta_stream_mix", "ta_stream_slabs",
     "ta_status_string", "ta_last_error_detail", "ta_version",
     "ta_axis_pair_attn_forward", "ta_plan_pair_kernel", "ta_plan_pair_bytes", "ta_plan_fused_position", "ta_plan_hop_function", "ta_plan_small_pair_position",
-    "ta_multihop_forward_static",
+    "ta_multihop_forward_static", "ta_plan_hop_form",
 ]
 TA_STATIC_WORKSPACE_BYTES = 64 << 20
 
@@ -79,6 +79,8 @@ def load_library():
     lib.ta_plan_hop_backward_kernel.restype = C.c_char_p
     lib.ta_plan_hop_function.argtypes = [vp, i, i, i]
     lib.ta_plan_hop_function.restype = C.c_char_p
+    lib.ta_plan_hop_form.argtypes = [vp, i, i]
+    lib.ta_plan_hop_form.restype = C.c_char_p
     lib.ta_plan_small_pair_position.argtypes = [vp]
     lib.ta_plan_small_pair_position.restype = i
     lib.ta_plan_hop_bytes.argtypes = [vp, i, i, i, i]
@@ -250,6 +252,10 @@ class Plan:
 
     def hop_function(self, axis: int, vin: int, backward: bool = False) -> Optional[str]:
         s = load_library().ta_plan_hop_function(self._h, axis, vin, int(backward))
+        return s.decode() if s is not None else None
+
+    def hop_form(self, axis: int, vin: int) -> Optional[str]:
+        s = load_library().ta_plan_hop_form(self._h, axis, vin)
         return s.decode() if s is not None else None
 
     def small_pair_position(self) -> int:

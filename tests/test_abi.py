@@ -365,3 +365,28 @@ def test_traffic_of_several_instantiations_is_averaged():
         "mfma_fwd_shared_kernel<128, 1, true, false, false>": {"FETCH_SIZE": 5.0, "WRITE_SIZE": 3.0, "launches": 7}})
     assert rec == {"mfma_bwd_resident_kernel": {"fetch_bytes_per_launch": 1.75, "write_bytes_per_launch": 1.25},
                    "mfma_bf16_n32_shared_kv": {"fetch_bytes_per_launch": 5.0, "write_bytes_per_launch": 3.0}}
+
+
+def test_forms_of_the_long_axis_forward():
+    """Windows that are short against a workgroup and bit tables are not run in phases."""
+    FOUR, EIGHT, PHASES = "four_tiles_in_step", "eight_tiles_in_step", "eight_tiles_in_phases"
+
+    def form(n, B, Hq, Hkv, D, causal=True, window=0, table=False, rope=None, vin=ta.TA_VIN_KV):
+        # (a table's address is only kept here)
+        return ta.ta_plan_create(B, Hq, Hkv, D, (n,), ta.TA_BF16, causal, window=(window,), axis_masks=[0x1000 if table else None], rope_base=rope).hop_form(0, vin)
+    assert form(128, 8, 8, 8, 128) == "two_blocks" and form(200, 8, 8, 8, 128) == FOUR
+    for Hq, Hkv, D, least in ((32, 8, 128, 1280), (8, 8, 128, 1536), (32, 8, 64, 2048), (16, 16, 64, 2048)):
+        assert form(4096, 4, Hq, Hkv, D) == PHASES and form(2048, 8, Hq, Hkv, D) == PHASES
+        for w in (64, 256, least - 1):
+            assert form(4096, 4, Hq, Hkv, D, window=w) == FOUR
+        assert form(4096, 4, Hq, Hkv, D, window=least) == PHASES
+        assert form(4096, 4, Hq, Hkv, D, False, window=least // 2) == FOUR and form(4096, 4, Hq, Hkv, D, False, window=least // 2 + 1) == PHASES
+        assert form(4096, 4, Hq, Hkv, D, table=True) == FOUR and form(1500, 8, Hq, Hkv, D, table=True) == FOUR
+        assert form(4096, 4, Hq, Hkv, D, rope=0.0) == EIGHT
+    for Hq, Hkv, D, least in ((12, 12, 100, 3000), (16, 4, 100, 3000), (8, 8, 40, 1024)):
+        assert form(4096, 8, Hq, Hkv, D) == PHASES and form(4095, 8, Hq, Hkv, D) == EIGHT
+        assert form(4096, 8, Hq, Hkv, D, window=least - 1) == EIGHT and form(4096, 8, Hq, Hkv, D, window=least) == PHASES
+        assert form(4096, 8, Hq, Hkv, D, table=True) == EIGHT
+    assert form(1023, 8, 12, 12, 100) == FOUR
+    assert form(4096, 1, 1, 1, 128) == FOUR                # 16 workgroups of eight tiles for 256 CUs
+    assert ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(0, ta.TA_VIN_KV) == "" and ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(2, 0) is None
