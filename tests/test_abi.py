@@ -368,7 +368,7 @@ def test_traffic_of_several_instantiations_is_averaged():
 
 
 def test_forms_of_the_long_axis_forward():
-    """Windows that are short against a workgroup and bit tables are not run in phases."""
+    """Windows that are short against a workgroup and bit tables are not run in phases; axes of 1,024 to 2,047 positions are where the workgroups come out even."""
     FOUR, EIGHT, PHASES = "four_tiles_in_step", "eight_tiles_in_step", "eight_tiles_in_phases"
 
     def form(n, B, Hq, Hkv, D, causal=True, window=0, table=False, rope=None, vin=ta.TA_VIN_KV):
@@ -389,4 +389,9 @@ def test_forms_of_the_long_axis_forward():
         assert form(4096, 8, Hq, Hkv, D, table=True) == EIGHT
     assert form(1023, 8, 12, 12, 100) == FOUR
     assert form(4096, 1, 1, 1, 128) == FOUR                # 16 workgroups of eight tiles for 256 CUs
+    # 1,024 to 2,047 positions
+    assert form(2047, 4, 8, 8, 128, False) == PHASES and form(2047, 4, 8, 8, 128) == PHASES and form(2047, 4, 8, 8, 64) == PHASES     # 256 workgroups
+    assert form(1500, 8, 8, 8, 128, False) == FOUR         # 384: the second round half empty
+    assert form(1024, 8, 32, 8, 128) == FOUR and form(1024, 8, 32, 8, 128, False) == PHASES      # equal waves under the mask as it is
+    assert form(2047, 4, 8, 8, 128, False, window=2046) == PHASES and form(2047, 4, 8, 8, 128, False, window=300) == FOUR
     assert ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(0, ta.TA_VIN_KV) == "" and ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(2, 0) is None

@@ -33,6 +33,9 @@ def band_table(n, window):
 
 @pytest.mark.parametrize("n,B,H,Hkv,D,causal,window,valid,tabled", [
     (2048, 4, 8, 8, 64, True, 0, 0, False),
+    (2047, 4, 8, 8, 128, True, 0, 0, False),                # 256 workgroups: one full round of them
+    (1029, 12, 8, 8, 64, False, 0, 1025, False),            # 480, and 1,020: the last round is nearly full
+    (1025, 15, 16, 4, 128, False, 0, 0, False),
     (2049, 4, 8, 8, 128, True, 0, 0, False),
     (2111, 30, 1, 1, 128, False, 700, 0, False),            # (short windows and tables: four tiles in the whole call too)
     (2111, 30, 1, 1, 64, False, 700, 0, True),
