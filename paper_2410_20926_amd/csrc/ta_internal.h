@@ -61,6 +61,7 @@ struct BwdParams {
     // set by the MFMA launcher: groups of more than 8 query heads are run 8 heads per launch
     int32_t wg_heads;        // heads (= waves) per workgroup
     int32_t head_base;       // first head of the group this launch covers
+    int32_t side;            // heads without a group side by side in a workgroup of the one-tile kernel
     int32_t acc_k, acc_x;    // add to dk / to the group-summed d_vin (every launch after a group's first)
 };
 

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
 
     uint32_t bx, ty;
     workgroup_xy<NARROW>(bx, ty);
-    const int g = nw == 1 ? (int)(bx * (blockDim.x >> 6)) + wave : (int)bx;
+    const int g = nw == 1 ? (int)bx * bp.side + wave : (int)bx;
     const int h = g * p.G + (MULTI ? bp.head_base : 0) + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + ty;
@@ -1057,17 +1057,28 @@ hipError_t launch_stream(const BwdParams& bp, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Heads without a group: neighbouring heads of a tile in one workgroup, so that a token's rows of all of them are asked for, and written, from one CU at
+// about the same time - where there are waves for the whole chip (256 CUs, 8 waves of width 128 or 12 of width 64 each); with fewer, four waves
+// to a CU leave the others idle.  Training steps, one head per workgroup and four (us): 32 x 32 x 32, 32 heads of width 128 1,734 and 1,617 (two: 1,654);
+// 2,808 waves a hop of width 64 (27 x 25 x 26, 4 heads) 75.6 and 72.0; 2,048 of width 128 115.5 and 111.1, of width 64 61.2 and 62.8; 1,088 of width 128
+// 66.7 and 78.7; 256 of width 64 34.2 and 38.3.
+//   Narrow rows, which an XCD takes in order anyway, want two (32 x 32 x 32, 32 heads of width 100: 1,743, two 1,723, four 1,750 us), but not on tiles of
+// several fibres (16 x 16 x 16, 32 heads of width 100: 231 and 241) nor where rows end with a 64-byte sector (32 x 32 x 16, 12 heads of width 96: 322
+// and 339).
+template <int D, bool NARROW>
+int heads_side_by_side(const HopParams& p, const TileParams& tp) {
+    const int64_t waves = (int64_t)p.Hkv * tp.tiles * p.B;
+    if (p.G != 1 || waves < (NARROW ? 2048 : D == 128 ? 1792 : 2560) || (NARROW && (p.n <= 16 || p.D * 2 % 64 == 0))) return 1;
+    int side = NARROW ? 2 : 4;
+    while (p.Hkv % side != 0) side /= 2;
+    return side;
+}
+
 template <int D, bool NARROW>
 hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     const HopParams& p = bp.hop;
     const bool multi = p.G > bp.wg_heads, table = p.mask != nullptr;
-    // Heads without a group: neighbouring heads of a tile in one workgroup, so that a token's rows of all of them are asked for, and written,
-    // from one CU at about the same time (training steps of 32 x 32 x 32, 32 heads of width 128: one head per workgroup 1,734 us, two 1,654, four 1,617;
-    // 8 sequences of 16 x 16 x 16, 8 heads of width 64: 235, 224, 219).  Narrow rows, which an XCD takes in order anyway, want two (width 100: 1,743,
-    // 1,723, 1,750 us).
-    int side = 1;
-    if (p.G == 1)
-        for (side = NARROW ? 2 : 4; p.Hkv % side != 0;) side /= 2;
+    const int side = heads_side_by_side<D, NARROW>(p, tp);
     const size_t smem = (size_t)(bp.wg_heads > 1 ? BGeo<D>::kRedBytes : 0) + (size_t)bp.wg_heads * side * BGeo<D>::kWaveBytes;
     const dim3 grid((unsigned)(p.Hkv / side), tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
     const dim3 block(64 * bp.wg_heads * side);
@@ -1077,6 +1088,7 @@ hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     else        kf = multi ? (table ? (const void*)mfma_bwd_kernel<D, true, true, NARROW, false> : (const void*)mfma_bwd_kernel<D, false, true, NARROW, false>)
                            : (table ? (const void*)mfma_bwd_kernel<D, true, false, NARROW, false> : (const void*)mfma_bwd_kernel<D, false, false, NARROW, false>);
     BwdParams bpc = bp;
+    bpc.side = side;
     TileParams tpc = tp;
     void* args[2] = {&bpc, &tpc};
     if (smem > 64 * 1024) {

@@ -1,5 +1,6 @@
-"""GPU parity of the one-tile backward where heads have no group and one, two or four of them share a workgroup: head counts that leave one, two or
-four, whole and narrow rows (neighbours share cache lines), packed and ragged tiles, masks, the encoding, a partial last tile."""
+"""GPU parity of the one-tile backward where heads have no group and one, two or four of them share a workgroup: one in small calls, compared with
+the oracle (whole and narrow rows, packed and ragged tiles, masks, the encoding, a partial last tile); two or four in calls that fill the chip, compared
+bit for bit with each head in a call of its own, where it has a workgroup to itself."""
 import numpy as np
 import pytest
 import torch
@@ -44,3 +45,28 @@ def test_ungrouped_heads_match_oracle(dims, B, H, D, causal, window, lens, rope,
     check_backward(grads, q, k, v, d_o, dims, causal, "bf16", **okw)
     again = multihop_backward(plan, dev, d_o, "bf16")
     assert all(np.array_equal(a, b) for a, b in zip(grads, again))
+
+
+@pytest.mark.parametrize("dims,B,H,D,causal,window,lens,rope,axes", [
+    ((31, 16), 2, 60, 128, True, None, None, None, ()),     # 1,860 waves on the second axis: four heads side by side
+    ((32, 25), 4, 26, 64, False, None, (800, 431, 32, 1), None, ()),   # two: 26 heads do not divide by four
+    ((20, 30), 4, 36, 64, True, (0, 5), None, 500.0, (0,)),
+    ((27, 30), 2, 40, 100, True, None, None, None, (1,)),   # narrow rows: two
+    ((17, 31), 3, 45, 20, False, None, None, None, ()),     # 45 heads: one
+])
+def test_heads_side_by_side_give_the_bits_of_heads_alone(dims, B, H, D, causal, window, lens, rope, axes):
+    N = int(np.prod(dims))
+    rng = np.random.default_rng(N + H)
+    q, k, v, d_o = make_inputs(B, N, H, H, D, seed=9200 + N + H, dtype="bf16", with_grad=True)
+    kw = dict(window=window, rope_base=rope, axis_masks=[torch.from_numpy(ta.pack_axis_mask((rng.random((n, n)) < 0.7) | np.eye(n, dtype=bool))).cuda()
+                                                         if i in axes else None for i, n in enumerate(dims)])
+    if lens is not None:
+        kw["valid_lens"] = torch.tensor(lens, dtype=torch.int64, device="cuda")
+
+    def step(h):
+        _, plan, dev = multihop_forward(*(np.ascontiguousarray(t[:, :, h]) for t in (q, k, v)), dims, "bf16", causal, save=True, **kw)
+        return multihop_backward(plan, dev, np.ascontiguousarray(d_o[:, :, h]), "bf16")
+    whole = step(slice(None))
+    assert all(np.isfinite(x).all() for x in whole)
+    for h in (0, 1, 2, 3, H // 2, H - 2, H - 1):
+        assert all(np.array_equal(x[:, :, h:h + 1], y) for x, y in zip(whole, step(slice(h, h + 1)))), h
