@@ -177,7 +177,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
         rope_rates(p, lcol, rev);
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
-            if (qt * kTile + i * G::kRowsPerPass >= rows_valid) break;      // (passes past the last row stay as they are)
+            // Passes past the last row stay as they are; with two tiles the choice costs more than it saves (12 heads of width 100, 64 x 40 x 9, first hop
+            // 77 us without it, 91 with; one tile, 2 x 20 x 28 x 23 80 and 75).
+            if (KT == 1 && i * G::kRowsPerPass >= rows_valid) break;
             float c[4], sn[4];
             rope_sincos(row_pos(qt * kTile + i * G::kRowsPerPass + lrow), rev, c, sn);
             qreg[i] = rope_apply(qreg[i], c, sn);

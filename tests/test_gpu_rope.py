@@ -86,6 +86,8 @@ ROPE_CASES = [
     ((128, 4), 1, 4, 1, 128, True, "bf16"),          # streaming, group-shared, a workgroup walks all query tiles
     ((200, 2), 1, 8, 2, 64, False, "bf16"),          # streaming, group-shared, a workgroup per query tile
     ((6, 9), 1, 4, 4, 100, True, "bf16"),            # narrow head width
+    ((3, 50), 1, 3, 3, 100, True, "bf16"),           # the same on two key tiles, a ragged second one
+    ((41, 3), 2, 2, 2, 40, False, "bf16"),
     ((32, 4, 8), 1, 8, 2, 96, True, "bf16"),
     ((16, 16), 1, 1, 1, 64, False, "f32"),           # generic kernels (double-precision angles)
     ((4, 2, 3), 2, 4, 2, 8, True, "f32"),
