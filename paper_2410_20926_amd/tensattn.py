@@ -145,8 +145,11 @@ def _stream(stream) -> Optional[int]:
     """A raw hipStream_t.  None = torch's current stream when torch is in use."""
     if stream is None:
         import torch
-        if torch.cuda.is_initialized():                    # (a torch.cuda.Stream object made for its handle costs 2 us of a 10 us call)
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+        # a torch.cuda.Stream object made for its handle costs 2 us of a 10 us call; the handle alone has no public name, so a torch that
+        # has dropped the private ones gets the object
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw and device and torch.cuda.is_initialized():
+            return raw(device()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None

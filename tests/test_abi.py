@@ -395,3 +395,18 @@ def test_forms_of_the_long_axis_forward():
     assert form(1024, 8, 32, 8, 128) == FOUR and form(1024, 8, 32, 8, 128, False) == PHASES      # equal waves under the mask as it is
     assert form(2047, 4, 8, 8, 128, False, window=2046) == PHASES and form(2047, 4, 8, 8, 128, False, window=300) == FOUR
     assert ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(0, ta.TA_VIN_KV) == "" and ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(2, 0) is None
+
+
+def test_stream_lookup_without_torch_private_names(monkeypatch):
+    """A torch that has dropped the private way to the current stream's handle is asked for a stream object."""
+    import torch
+    asked = []
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: asked.append(1) or type("S", (), {"cuda_stream": 77}))
+    for gone in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        with monkeypatch.context() as m:
+            m.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 55 + device, raising=False)
+            m.setattr(torch._C, "_cuda_getDevice", lambda: 1, raising=False)
+            assert binding._stream(None) == 56 and not asked
+            m.delattr(torch._C, gone)
+            assert binding._stream(None) == 77 and asked.pop()
