@@ -151,9 +151,10 @@ const char* ta_plan_hop_backward_kernel(const ta_plan_t* plan, int axis, int vin
  * for that hop, as a profiler shows it without its template arguments ("mfma_fwd_long_kernel", "f32_bwd_kernel" ...);
  * "unsupported", or NULL on error.  Static storage. */
 const char* ta_plan_hop_function(const ta_plan_t* plan, int axis, int vin, int backward);
-/* Which form of that device function the forward hop runs, where it has several: mfma_fwd_long_kernel is launched as
- * "two_blocks", "four_tiles_in_step", "eight_tiles_in_step" or "eight_tiles_in_phases"; "" for the others, NULL on error.  Static storage. */
-const char* ta_plan_hop_form(const ta_plan_t* plan, int axis, int vin);
+/* Which form of that device function the hop runs, where it has several: mfma_fwd_long_kernel is launched as
+ * "two_blocks", "four_tiles_in_step", "eight_tiles_in_step" or "eight_tiles_in_phases", mfma_bwd_kernel on rows narrower than its tile as
+ * "rows_cached", "rows_streamed" or "heads_in_pairs"; "" for the others, NULL on error.  Static storage. */
+const char* ta_plan_hop_form(const ta_plan_t* plan, int axis, int vin, int backward);
 
 /* Cost model of one hop (App. C.2, Table 5, with the fibre count N/n_i that Eq. 4
  * implies).  Bytes are ALGORITHMIC HBM bytes: each of Q, K, value-input read once,

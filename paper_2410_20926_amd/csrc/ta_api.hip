@@ -403,8 +403,10 @@ const char* ta_plan_hop_function(const ta_plan_t* pl, int axis, int vin, int bac
     return id == BWD_NONE ? "unsupported" : id == BWD_GENERIC ? ta::generic_backward_function(bp, pl->desc.dtype) : ta::mfma_backward_function(bp);
 }
 
-const char* ta_plan_hop_form(const ta_plan_t* pl, int axis, int vin) {
-    const char* function = ta_plan_hop_function(pl, axis, vin, 0);
+const char* ta_plan_hop_form(const ta_plan_t* pl, int axis, int vin, int backward) {
+    const char* function = ta_plan_hop_function(pl, axis, vin, backward);
+    if (function && strcmp(function, "mfma_bwd_kernel") == 0)
+        return ta::mfma_backward_form(bwd_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr, nullptr, nullptr, nullptr, 0));
     if (!function || strcmp(function, "mfma_fwd_long_kernel") != 0) return function ? "" : nullptr;
     return ta::mfma_forward_long_form(hop_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr));
 }

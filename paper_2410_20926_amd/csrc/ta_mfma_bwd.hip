@@ -24,24 +24,29 @@ namespace {
 
 using namespace mfma;
 
+// How rows that one wave alone reads come in, and whether heads without a group may stand side by side in a workgroup.
+enum BwdRows { kWhole, kNarrow, kNarrowStreamed, kNarrowPairs };   // streamed, one to four; through the caches, one; streamed, one; through the caches, two
+
 // blockDim.x = 64 * G (G = query heads per key/value head), grid = (Hkv, tiles_lo, B * tiles_hi); for G = 1 a workgroup is 1, 2 or 4 heads side by
 // side and grid.x = Hkv / heads.
 // TABLE: the axis has a caller's bit table; MULTI: the group has more than 8 heads and this launch
 // covers 8 of them (separate instantiations keep the common case free of both).
 // ROPE: the hop scores with rotary-encoded Q and K (separate instantiations, so that the plain kernel carries none of it).
-template <int D, bool TABLE, bool MULTI, bool NARROW, bool ROPE>
+template <int D, bool TABLE, bool MULTI, BwdRows ROWS, bool ROPE>
 __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TileParams tp) {
     using G = BGeo<D>;
+    constexpr bool NARROW = ROWS != kWhole, STREAMED = ROWS == kWhole || ROWS == kNarrowStreamed;
+    constexpr bool SIDE = ROWS == kWhole || ROWS == kNarrowPairs;
     const HopParams& p = bp.hop;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = MULTI ? bp.wg_heads : p.G;
-    const int w = nw == 1 ? 0 : wave;                     // heads without a group stand side by side in a workgroup, each on its own
+    const int w = SIDE && nw == 1 ? 0 : wave;             // heads without a group stand side by side in a workgroup, each on its own
 
     uint32_t bx, ty;
     workgroup_xy<NARROW>(bx, ty);
-    const int g = nw == 1 ? (int)bx * bp.side + wave : (int)bx;
+    const int g = SIDE && nw == 1 ? (int)bx * bp.side + wave : (int)bx;
     const int h = g * p.G + (MULTI ? bp.head_base : 0) + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + ty;
@@ -92,22 +97,20 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     // ---- gather Q, K, X, G rows: every load is issued before the first wait, in the order of first use
     //      (loads complete in order: Q and K can be staged while X and G are still on their way) ------------
     u32x4 qraw[G::kPasses], kraw[G::kPasses], xraw[G::kPasses], graw[G::kPasses];
-    // Rows read by this wave alone are streamed; rows every wave of the group reads stay cached, and so do narrow rows, whose
-    // first and last lines the neighbouring heads read as well: streamed, those lines crossed HBM once per head, previous dQ and dK worst (two
-    // requests per row: +24 % on a hop's reads at width 100; its training step of 32 x 32 x 32, 32 heads: 1,872 -> 1,741 us).
+    // Rows every wave of the group reads stay cached; rows that this wave alone reads are streamed, narrow ones by choice (narrow_rows).
 #pragma unroll
-    for (int i = 0; i < G::kPasses; ++i) qraw[i] = gather_chunk<NARROW, !NARROW>(qb, rowoff[i * G::kRowsPerPass + lrow].x, lbyte, dbytes);
+    for (int i = 0; i < G::kPasses; ++i) qraw[i] = gather_chunk<NARROW, STREAMED>(qb, rowoff[i * G::kRowsPerPass + lrow].x, lbyte, dbytes);
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) kraw[i] = gather_chunk<NARROW, false>(kb, rowoff[i * G::kRowsPerPass + lrow].y, lbyte, dbytes);
     if (vin_is_o) {                                        // one choice for all eight requests, not one per request
 #pragma unroll
-        for (int i = 0; i < G::kPasses; ++i) xraw[i] = gather_chunk<NARROW, !NARROW>(xb, rowoff[i * G::kRowsPerPass + lrow].z, lbyte, dbytes);
+        for (int i = 0; i < G::kPasses; ++i) xraw[i] = gather_chunk<NARROW, STREAMED>(xb, rowoff[i * G::kRowsPerPass + lrow].z, lbyte, dbytes);
     } else {
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) xraw[i] = gather_chunk<NARROW, false>(xb, rowoff[i * G::kRowsPerPass + lrow].z, lbyte, dbytes);
     }
 #pragma unroll
-    for (int i = 0; i < G::kPasses; ++i) graw[i] = gather_chunk<NARROW, !NARROW>(gb, rowoff[i * G::kRowsPerPass + lrow].w, lbyte, dbytes);
+    for (int i = 0; i < G::kPasses; ++i) graw[i] = gather_chunk<NARROW, STREAMED>(gb, rowoff[i * G::kRowsPerPass + lrow].w, lbyte, dbytes);
     __builtin_amdgcn_sched_barrier(0);
 
     // rotary encoding: Q and K rows are turned by their position on the axis before anything uses them;
@@ -270,10 +273,10 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
         if constexpr (MULTI) {
             u32x4 oldx[G::kDTiles * 2] = {};              // the sum of the group's earlier heads
             if (bp.acc_x && w == nw - 1) prefetch_tile<D, NARROW>(oldx, rowoff, 2, dxb, lane, dbytes);
-            chain_sum<D>(acc, red, w, nw, lane);
+            chain_sum<D, SIDE>(acc, red, w, nw, lane);
             if (w == nw - 1) store_tile<D, NARROW>(acc, 1.f, buf, rowoff, 2, dxb, oldx, bp.acc_x != 0, rows_valid, lane, dbytes);
         } else {
-            chain_sum<D>(acc, red, w, nw, lane);
+            chain_sum<D, SIDE>(acc, red, w, nw, lane);
             if (w == nw - 1) store_tile<D, NARROW>(acc, 1.f, buf, rowoff, 2, dxb, oldq, false, rows_valid, lane, dbytes);
         }
     }
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) acc[t] = mma(qT[t][s2], dsNop[s2], acc[t]);
     }
-    chain_sum<D>(acc, red, w, nw, lane);
+    chain_sum<D, SIDE>(acc, red, w, nw, lane);
     if (w == nw - 1) store_tile<D, NARROW>(acc, p.scale, buf, rowoff, 1, dkb, oldk, acc_k, rows_valid, lane, dbytes, enc);
 }
 
@@ -1062,31 +1065,49 @@ hipError_t launch_stream(const BwdParams& bp, hipStream_t s) {
 // to a CU leave the others idle.  Training steps, one head per workgroup and four (us): 32 x 32 x 32, 32 heads of width 128 1,734 and 1,617 (two: 1,654);
 // 2,808 waves a hop of width 64 (27 x 25 x 26, 4 heads) 75.6 and 72.0; 2,048 of width 128 115.5 and 111.1, of width 64 61.2 and 62.8; 1,088 of width 128
 // 66.7 and 78.7; 256 of width 64 34.2 and 38.3.
-//   Narrow rows, which an XCD takes in order anyway, want two (32 x 32 x 32, 32 heads of width 100: 1,743, two 1,723, four 1,750 us), but not on tiles of
-// several fibres (16 x 16 x 16, 32 heads of width 100: 231 and 241) nor where rows end with a 64-byte sector (32 x 32 x 16, 12 heads of width 96: 322
-// and 339).
-template <int D, bool NARROW>
-int heads_side_by_side(const HopParams& p, const TileParams& tp) {
-    const int64_t waves = (int64_t)p.Hkv * tp.tiles * p.B;
-    if (p.G != 1 || waves < (NARROW ? 2048 : D == 128 ? 1792 : 2560) || (NARROW && (p.n <= 16 || p.D * 2 % 64 == 0))) return 1;
-    int side = NARROW ? 2 : 4;
+int heads_side_by_side(const HopParams& p, const TileParams& tp, BwdRows rows) {
+    if (p.G != 1 || rows == kNarrow || rows == kNarrowStreamed) return 1;
+    if (rows == kNarrowPairs) return 2;
+    int side = (int64_t)p.Hkv * tp.tiles * p.B < (p.D == 128 ? 1792 : 2560) ? 1 : 4;
     while (p.Hkv % side != 0) side /= 2;
     return side;
 }
 
-template <int D, bool NARROW>
+// Narrow rows share their first and last line with the neighbouring heads' rows.  Taken in order by an XCD (workgroup_xy) one head per workgroup
+// and the caches serve that best.  (Heads, width, tokens by axis length; one hop, first or accumulating, us.)
+//   Where the workgroups of a batch are not a multiple of eight they are dealt out to the XCDs as they come, and neighbours want to be in one
+// workgroup: 12 heads of 40, 1,846 x 16 x 2 131 -> 109; 12 heads of 100, 369 x 27 54.6 -> 51.3; in order it is the other way round: 12 of 40, 3,163 x 27
+// 102 and 116, 12 of 100, 204 x 21 x 2 46.8 and 48.3.  As above, with waves for the chip (1,024 to 1,536 waves of width 80 to 112: 3 per cent ahead; fewer,
+// 2 behind).
+//   A call whose tensors are a little more than the 256 MB of the last-level cache evicts by a hop's end what the next pass, or hop, begins with; streamed
+// rows leave it part of that.  Cached and streamed: 32 heads of 100, 70 x 32 x 4 (401 MB) 109 and 96; 85 x 32 (122 MB) 32.2 and 35.4; 12 heads,
+// 2,736 x 32 (1.5 GB) 351 and 364; 32 / 8 heads of 96, 162 x 32 x 4 (510 MB) 228 and 207; 46 x 32 x 4 (145 MB) 57.9 and 59.6; 1,806 x 32 (2 GB) 558 and 566;
+// 8 heads of 40, 3,163 x 27 (383 MB) 102 and 96.  Means over 3,000 calls: streamed ahead from 280 MB to 560 (groups 1,400; widths up to 64 450) by 5 per
+// cent, behind by 4 to 13 outside.  The previous dQ and dK come through the caches everywhere: streamed, their two requests per row crossed HBM twice (2
+// to 10 per cent).
+BwdRows narrow_rows(const HopParams& p, const TileParams& tp) {
+    const uint32_t batch = (uint32_t)p.Hkv * tp.tiles_lo;    // workgroups that are put in order together, one head in each
+    if (p.G == 1 && p.Hkv % 2 == 0 && batch % 8 != 0 && (int64_t)p.Hkv * tp.tiles * p.B >= 1280) return kNarrowPairs;
+    const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (3.0 * p.Hq + 2.0 * p.Hkv + 2.0 * p.vin_heads);
+    return bytes >= 280e6 && bytes < (p.D <= 64 ? 450e6 : p.G == 1 ? 560e6 : 1400e6) ? kNarrowStreamed : kNarrow;
+}
+
+template <int D, BwdRows ROWS, bool ROPE>
+const void* kernel_of(bool multi, bool table) {
+    if constexpr (ROWS == kNarrowPairs) return table ? (const void*)mfma_bwd_kernel<D, true, false, ROWS, ROPE> : (const void*)mfma_bwd_kernel<D, false, false, ROWS, ROPE>;
+    else return multi ? (table ? (const void*)mfma_bwd_kernel<D, true, true, ROWS, ROPE> : (const void*)mfma_bwd_kernel<D, false, true, ROWS, ROPE>)
+                      : (table ? (const void*)mfma_bwd_kernel<D, true, false, ROWS, ROPE> : (const void*)mfma_bwd_kernel<D, false, false, ROWS, ROPE>);
+}
+
+template <int D, BwdRows ROWS>
 hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     const HopParams& p = bp.hop;
     const bool multi = p.G > bp.wg_heads, table = p.mask != nullptr;
-    const int side = heads_side_by_side<D, NARROW>(p, tp);
+    const int side = heads_side_by_side(p, tp, ROWS);
     const size_t smem = (size_t)(bp.wg_heads > 1 ? BGeo<D>::kRedBytes : 0) + (size_t)bp.wg_heads * side * BGeo<D>::kWaveBytes;
     const dim3 grid((unsigned)(p.Hkv / side), tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
     const dim3 block(64 * bp.wg_heads * side);
-    const void* kf;
-    if (p.rope) kf = multi ? (table ? (const void*)mfma_bwd_kernel<D, true, true, NARROW, true> : (const void*)mfma_bwd_kernel<D, false, true, NARROW, true>)
-                           : (table ? (const void*)mfma_bwd_kernel<D, true, false, NARROW, true> : (const void*)mfma_bwd_kernel<D, false, false, NARROW, true>);
-    else        kf = multi ? (table ? (const void*)mfma_bwd_kernel<D, true, true, NARROW, false> : (const void*)mfma_bwd_kernel<D, false, true, NARROW, false>)
-                           : (table ? (const void*)mfma_bwd_kernel<D, true, false, NARROW, false> : (const void*)mfma_bwd_kernel<D, false, false, NARROW, false>);
+    const void* kf = p.rope ? kernel_of<D, ROWS, true>(multi, table) : kernel_of<D, ROWS, false>(multi, table);
     BwdParams bpc = bp;
     bpc.side = side;
     TileParams tpc = tp;
@@ -1096,6 +1117,14 @@ hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
         if (e != hipSuccess) return e;
     }
     return hipLaunchKernel(kf, grid, block, args, smem, s);
+}
+template <int D>
+hipError_t launch_narrow(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
+    switch (narrow_rows(bp.hop, tp)) {
+        case kNarrowPairs: return launch<D, kNarrowPairs>(bp, tp, s);
+        case kNarrowStreamed: return launch<D, kNarrowStreamed>(bp, tp, s);
+        default: return launch<D, kNarrow>(bp, tp, s);
+    }
 }
 
 }  // namespace
@@ -1169,6 +1198,15 @@ const char* mfma_backward_function(const BwdParams& bp) {
     return nullptr;
 }
 
+const char* mfma_backward_form(const BwdParams& bp) {
+    HopParams hp = bp.hop;
+    hp.o = bp.d_o;
+    TileParams tp;
+    if (hp.D == 64 || hp.D == 128 || !make_tile_params(hp, 1, &tp)) return "";
+    const BwdRows rows = narrow_rows(hp, tp);
+    return rows == kNarrowPairs ? "heads_in_pairs" : rows == kNarrowStreamed ? "rows_streamed" : "rows_cached";
+}
+
 hipError_t launch_mfma_backward(const BwdParams& user, hipStream_t s) {
     const int variant = backward_variant(user, TA_BF16);
     if (variant == 0) return hipErrorInvalidValue;
@@ -1203,9 +1241,9 @@ hipError_t launch_mfma_backward(const BwdParams& user, hipStream_t s) {
         if (variant == 2 && !runs_blocked(bp.hop)) e = launch_mfma_backward_long(bp, s);
         else if (variant == 2) e = bp.hop.D == 128 ? launch_stream<128, false>(bp, s) : bp.hop.D == 64 ? launch_stream<64, false>(bp, s)
                                  : bp.hop.D > 64 ? launch_stream<128, true>(bp, s) : launch_stream<64, true>(bp, s);
-        else if (bp.hop.D == 128) e = launch<128, false>(bp, tp, s);
-        else if (bp.hop.D == 64)  e = launch<64, false>(bp, tp, s);
-        else                      e = bp.hop.D > 64 ? launch<128, true>(bp, tp, s) : launch<64, true>(bp, tp, s);
+        else if (bp.hop.D == 128) e = launch<128, kWhole>(bp, tp, s);
+        else if (bp.hop.D == 64)  e = launch<64, kWhole>(bp, tp, s);
+        else                      e = bp.hop.D > 64 ? launch_narrow<128>(bp, tp, s) : launch_narrow<64>(bp, tp, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

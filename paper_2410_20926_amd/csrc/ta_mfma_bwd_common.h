@@ -150,7 +150,8 @@ __device__ inline void store_tile_plain(const f32x16 (&acc)[Geo<D>::kDTiles], fl
 
 // Sum of acc over the workgroup's waves in wave order; the total ends in the LAST wave's
 // registers.  `red` is a workgroup-shared fp32 area in lane-major layout.
-template <int D>
+// LONE: with nw = 1 the workgroup's waves have nothing to do with each other.
+template <int D, bool LONE = false>
 __device__ inline void chain_sum(f32x16 (&acc)[Geo<D>::kDTiles], float* red, int w, int nw, int lane) {
     constexpr int kT = Geo<D>::kDTiles;
     for (int s = 0; s + 1 < nw; ++s) {
@@ -177,7 +178,7 @@ __device__ inline void chain_sum(f32x16 (&acc)[Geo<D>::kDTiles], float* red, int
                 for (int e = 0; e < 4; ++e) acc[t][4 * q4 + e] += v[e];
             }
     }
-    if (nw > 1) __syncthreads();                          // red may be reused
+    if (!LONE || nw > 1) __syncthreads();                 // red may be reused
 }
 
 constexpr int kStreamMaxLds = 160 * 1024;              // LDS of one compute unit

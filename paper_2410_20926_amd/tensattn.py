@@ -79,7 +79,7 @@ def load_library():
     lib.ta_plan_hop_backward_kernel.restype = C.c_char_p
     lib.ta_plan_hop_function.argtypes = [vp, i, i, i]
     lib.ta_plan_hop_function.restype = C.c_char_p
-    lib.ta_plan_hop_form.argtypes = [vp, i, i]
+    lib.ta_plan_hop_form.argtypes = [vp, i, i, i]
     lib.ta_plan_hop_form.restype = C.c_char_p
     lib.ta_plan_small_pair_position.argtypes = [vp]
     lib.ta_plan_small_pair_position.restype = i
@@ -257,8 +257,8 @@ class Plan:
         s = load_library().ta_plan_hop_function(self._h, axis, vin, int(backward))
         return s.decode() if s is not None else None
 
-    def hop_form(self, axis: int, vin: int) -> Optional[str]:
-        s = load_library().ta_plan_hop_form(self._h, axis, vin)
+    def hop_form(self, axis: int, vin: int, backward: bool = False) -> Optional[str]:
+        s = load_library().ta_plan_hop_form(self._h, axis, vin, int(backward))
         return s.decode() if s is not None else None
 
     def small_pair_position(self) -> int:

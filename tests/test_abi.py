@@ -397,6 +397,30 @@ def test_forms_of_the_long_axis_forward():
     assert ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(0, ta.TA_VIN_KV) == "" and ta.ta_plan_create(1, 8, 2, 128, (16, 16), ta.TA_BF16, True).hop_form(2, 0) is None
 
 
+def test_forms_of_the_one_tile_backward():
+    """Narrow rows: pairs of heads where workgroups of one are not dealt out in order and there are waves for the chip, streamed where the call is a little
+    larger than the last-level cache; whole rows have one form."""
+    CACHED, STREAMED, PAIRS = "rows_cached", "rows_streamed", "heads_in_pairs"
+
+    def form(n, fibres, B, Hq, Hkv, D, vin=ta.TA_VIN_KV):
+        return ta.ta_plan_create(B, Hq, Hkv, D, (n, fibres), ta.TA_BF16, True).hop_form(0, vin, True)
+
+    def streamed(Hq, Hkv, D, vin):                         # fibres of 32 rows from and up to which a call streams
+        rows = [form(32, 8 * i, 1, Hq, Hkv, D, vin) for i in range(1, 700)]
+        first = rows.index(STREAMED)
+        assert set(rows[:first]) == {CACHED} and set(rows[first:]) == {CACHED, STREAMED}
+        mb = 32 * 8 * D * 2 * (3 * Hq + 2 * Hkv + 2 * (Hq if vin else Hkv)) / 1e6
+        return (first + 1) * mb, (first + 1 + rows[first:].index(CACHED)) * mb, mb
+    for Hq, Hkv, D, vin, end in ((8, 8, 100, 1, 560), (8, 8, 40, 0, 450), (16, 4, 96, 0, 1400), (16, 4, 112, 1, 1400), (32, 2, 40, 1, 450)):
+        low, high, step = streamed(Hq, Hkv, D, vin)
+        assert 280 <= low < 280 + step and end <= high < end + step
+    assert form(32, 123, 4, 12, 12, 100) == PAIRS and form(32, 124, 4, 12, 12, 100) == CACHED      # 1,476 and 1,488 workgroups of one head
+    assert form(16, 246, 4, 12, 12, 40) == PAIRS and form(32, 60, 4, 11, 11, 100) == CACHED and form(32, 61, 4, 24, 12, 100) == CACHED
+    assert form(32, 53, 2, 12, 12, 100) == CACHED and form(32, 55, 2, 12, 12, 100) == PAIRS         # 1,272 and 1,320 waves
+    assert form(32, 303, 4, 12, 12, 100) == PAIRS          # (651 MB and out of order)
+    assert form(32, 123, 4, 12, 12, 128) == "" and form(33, 123, 4, 12, 12, 100) == ""
+
+
 def test_stream_lookup_without_torch_private_names(monkeypatch):
     """A torch that has dropped the private way to the current stream's handle is asked for a stream object."""
     import torch
