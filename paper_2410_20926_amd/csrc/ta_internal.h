@@ -111,6 +111,7 @@ const char* generic_forward_function(const HopParams& p, int dtype);
 const char* generic_backward_function(const BwdParams& bp, int dtype);
 const char* mfma_forward_function(const HopParams& p, int kernel_id);
 const char* mfma_backward_function(const BwdParams& bp);
+const char* mfma_forward_form(const HopParams& p, int kernel_id);   // which form of mfma_fwd_kernel and mfma_fwd_shared_kernel
 const char* mfma_forward_long_form(const HopParams& p);   // which form of mfma_fwd_long_kernel
 const char* mfma_backward_form(const BwdParams& bp);      // which form of mfma_bwd_kernel
 hipError_t launch_mfma_forward(const HopParams& p, int kernel_id, hipStream_t s);

@@ -31,21 +31,22 @@ namespace {
 
 using namespace mfma;
 
-// Whether rows that one wave alone reads are streamed past the caches.  A narrow row shares its first and last cache line with the neighbouring
-// heads' rows, so that a streamed line crosses HBM once per row in it.  That decides it for rows of a few lines' parts in 64-wide tiles (8 sequences
-// of 20 x 28 x 23, 8 / 2 heads of width 40: 159 -> 134 us through the cache; 2 sequences, 32 heads: 220 -> 195); wider rows are mostly whole lines,
-// and their forward is faster streamed (32 x 32 x 32, 32 heads of width 100: 510 us against 530; 24 x 25 x 26, 12 heads of width 96: 290 / 314).
-template <int D, bool NARROW>
-constexpr bool streamed_rows() { return !NARROW || D > 64; }
+// How rows that one wave alone reads come in: whole rows are streamed past the caches, rows narrower than their tile by choice.  A narrow row shares its
+// first and last cache line with the neighbouring heads' rows, so that a streamed line crosses HBM once per row in it.  That decides it for rows of a
+// few lines' parts in 64-wide tiles (8 sequences of 20 x 28 x 23, 8 / 2 heads of width 40: 159 -> 134 us through the cache; 2 sequences, 32 heads: 220 ->
+// 195); wider rows are mostly whole lines, and their forward is faster streamed (32 x 32 x 32, 32 heads of width 100: 510 us against 530; 24 x 25 x 26, 12
+// heads of width 96: 290 / 314).
+enum FwdRows { kWhole, kNarrow, kNarrowStreamed };        // streamed; through the caches; streamed
 
 constexpr int kWavesPerBlock = 4;
 
 // KT = number of 32-key tiles a unit may walk (1: n <= 32, 2: n <= 64).
-// NARROW: the head is narrower than the D-wide tile (p.D features of 2 bytes per row); see load_chunk.
+// ROWS: narrow: the head is narrower than the D-wide tile (p.D features of 2 bytes per row); see load_chunk.
 // ROPE: the hop scores with rotary-encoded Q and K (instantiated separately: the plain kernels carry none of it).
-template <int D, int KT, bool NARROW, bool ROPE>
+template <int D, int KT, FwdRows ROWS, bool ROPE>
 __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopParams p, TileParams tp) {
     using G = Geo<D>;
+    constexpr bool NARROW = ROWS != kWhole, STREAMED = ROWS != kNarrow;
     constexpr int kRows = kTile * KT;                     // rows of the unit's fibre set that have a table entry
     constexpr int kWaveBytes = G::kBufBytes + kRows * 16;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -143,11 +144,11 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) {
                     const u32x4 off = rowoff[j * kTile + i * G::kRowsPerPass + lrow];
-                    kreg[j][i] = gather_chunk<NARROW, decltype(k_nt)::value && streamed_rows<D, NARROW>()>(kb, off.y, lbyte, dbytes);
+                    kreg[j][i] = gather_chunk<NARROW, decltype(k_nt)::value && STREAMED>(kb, off.y, lbyte, dbytes);
                     voff[j][i] = off.z;
-                    if (j == 0) vreg[j][i] = gather_chunk<NARROW, decltype(v_nt)::value && streamed_rows<D, NARROW>()>(vb, voff[j][i], lbyte, dbytes);
+                    if (j == 0) vreg[j][i] = gather_chunk<NARROW, decltype(v_nt)::value && STREAMED>(vb, voff[j][i], lbyte, dbytes);
                     if (KT == 1) {
-                        qreg[i] = gather_chunk<NARROW, streamed_rows<D, NARROW>()>(qb, off.x, lbyte, dbytes);
+                        qreg[i] = gather_chunk<NARROW, STREAMED>(qb, off.x, lbyte, dbytes);
                         ooff[i] = off.w;
                     }
                 }
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
             const u32x4 off = rowoff[qt * kTile + i * G::kRowsPerPass + lrow];
-            qreg[i] = gather_chunk<NARROW, streamed_rows<D, NARROW>()>(qb, off.x, lbyte, dbytes);
+            qreg[i] = gather_chunk<NARROW, STREAMED>(qb, off.x, lbyte, dbytes);
             ooff[i] = off.w;
         }
     }
@@ -357,9 +358,10 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 // (a previous O) still goes through the wave's private transit tile.
 // VS: the value input is shared too (first hop).  Then the private tile only carries Q in and O
 // out, one lane per row, and is used in two halves of 16 rows to halve its LDS footprint.
-template <int D, int KT, bool VS, bool NARROW, bool ROPE>
+template <int D, int KT, bool VS, FwdRows ROWS, bool ROPE>
 __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel(HopParams p, TileParams tp) {
     using G = Geo<D>;
+    constexpr bool NARROW = ROWS != kWhole, STREAMED = ROWS != kNarrow;
     constexpr int kRows = kTile * KT;
     constexpr int kTileBytes = kTile * G::kPitch;                           // one row-major 32-row tile
     constexpr int kShare = G::kPasses / kWavesPerBlock;                     // load passes per wave per shared tile
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const u32x4 off = rowoff[qt * kTile + i * G::kRowsPerPass + lrow];
-        qreg[i] = gather_chunk<NARROW, streamed_rows<D, NARROW>()>(qb, off.x, lbyte, dbytes);
+        qreg[i] = gather_chunk<NARROW, STREAMED>(qb, off.x, lbyte, dbytes);
         ooff[i] = off.w;
     }
 #pragma unroll
@@ -463,7 +465,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) {
                     const u32x4 off = rowoff[j * kTile + i * G::kRowsPerPass + lrow];
-                    vreg[j][i] = (KT == 1) ? gather_chunk<NARROW, streamed_rows<D, NARROW>()>(vb, off.z, lbyte, dbytes)
+                    vreg[j][i] = (KT == 1) ? gather_chunk<NARROW, STREAMED>(vb, off.z, lbyte, dbytes)
                                            : gather_chunk<NARROW, false>(vb, off.z, lbyte, dbytes);   // with two query tiles a value tile is read twice: keep it cached
                 }
             }
@@ -636,25 +638,25 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
     }
 }
 
-template <int D, int KT, bool NARROW>
+template <int D, int KT, FwdRows ROWS>
 hipError_t launch_shared(const HopParams& p, const TileParams& tp, hipStream_t s) {
     const size_t tile = (size_t)kTile * Geo<D>::kPitch;
     const bool vs = p.vin_heads != p.Hq;
     const size_t smem = (vs ? 2 : 1) * KT * tile + (size_t)kTile * KT * 16 + kWavesPerBlock * (vs ? tile / 2 : tile);
     const dim3 grid((unsigned)(p.Hq / kWavesPerBlock), tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
-    const void* kf = p.rope ? (vs ? (const void*)mfma_fwd_shared_kernel<D, KT, true, NARROW, true> : (const void*)mfma_fwd_shared_kernel<D, KT, false, NARROW, true>)
-                            : (vs ? (const void*)mfma_fwd_shared_kernel<D, KT, true, NARROW, false> : (const void*)mfma_fwd_shared_kernel<D, KT, false, NARROW, false>);
+    const void* kf = p.rope ? (vs ? (const void*)mfma_fwd_shared_kernel<D, KT, true, ROWS, true> : (const void*)mfma_fwd_shared_kernel<D, KT, false, ROWS, true>)
+                            : (vs ? (const void*)mfma_fwd_shared_kernel<D, KT, true, ROWS, false> : (const void*)mfma_fwd_shared_kernel<D, KT, false, ROWS, false>);
     HopParams pc = p;
     TileParams tc = tp;
     void* args[2] = {&pc, &tc};
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }
 
-template <int D, int KT, bool NARROW>
+template <int D, int KT, FwdRows ROWS>
 hipError_t launch(const HopParams& p, const TileParams& tp, hipStream_t s) {
     const size_t smem = (size_t)kWavesPerBlock * (Geo<D>::kBufBytes + kTile * KT * 16);
     const dim3 grid((unsigned)((p.Hq + kWavesPerBlock - 1) / kWavesPerBlock), tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
-    const void* kf = p.rope ? (const void*)mfma_fwd_kernel<D, KT, NARROW, true> : (const void*)mfma_fwd_kernel<D, KT, NARROW, false>;
+    const void* kf = p.rope ? (const void*)mfma_fwd_kernel<D, KT, ROWS, true> : (const void*)mfma_fwd_kernel<D, KT, ROWS, false>;
     HopParams pc = p;
     TileParams tc = tp;
     void* args[2] = {&pc, &tc};
@@ -685,11 +687,29 @@ bool mfma_forward_supports(int32_t n, int32_t D, int dtype, int* kernel_id) {
 }
 
 namespace {
-template <int D, bool NARROW>
-hipError_t launch_width(const HopParams& p, const TileParams& tp, int KT, hipStream_t s) {
-    if (p.G % kWavesPerBlock == 0)                     // 4 query heads of a workgroup share their key/value head
-        return KT == 1 ? launch_shared<D, 1, NARROW>(p, tp, s) : launch_shared<D, 2, NARROW>(p, tp, s);
-    return KT == 1 ? launch<D, 1, NARROW>(p, tp, s) : launch<D, 2, NARROW>(p, tp, s);
+// Two tiles of narrow rows in 64-wide tiles, by the bytes of the call: one that is a little larger than the 256 MB of the last-level cache evicts by its end
+// what the next pass, or hop, begins with, and streamed rows leave it part of that (cached and streamed, means over 1,500 calls: 282 to 390 MB 3 to 4 per
+// cent behind, at most 12; 200 to 270 MB 7 to 14 ahead, from 400 MB on 1 to 2.  8 heads of 40, 260 x 56 x 8, 299 MB, 101 and 93 us).  One tile is ahead
+// cached at every size.
+FwdRows narrow_rows(const HopParams& p, int KT) {
+    const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (2.0 * p.Hq + p.Hkv + p.vin_heads);
+    return p.D > 64 || (KT == 2 && bytes >= 282e6 && bytes < 390e6) ? kNarrowStreamed : kNarrow;
+}
+
+template <int D, int KT, FwdRows ROWS>
+hipError_t launch_heads(const HopParams& p, const TileParams& tp, hipStream_t s) {
+    if (p.G % kWavesPerBlock == 0) return launch_shared<D, KT, ROWS>(p, tp, s);   // 4 query heads of a workgroup share their key/value head
+    return launch<D, KT, ROWS>(p, tp, s);
+}
+template <int KT>
+hipError_t launch_width(const HopParams& p, const TileParams& tp, hipStream_t s) {
+    if (p.D == 128) return launch_heads<128, KT, kWhole>(p, tp, s);
+    if (p.D == 64) return launch_heads<64, KT, kWhole>(p, tp, s);
+    if (p.D > 64) return launch_heads<128, KT, kNarrowStreamed>(p, tp, s);
+    if constexpr (KT == 2) {
+        if (narrow_rows(p, KT) == kNarrowStreamed) return launch_heads<64, KT, kNarrowStreamed>(p, tp, s);
+    }
+    return launch_heads<64, KT, kNarrow>(p, tp, s);
 }
 }  // namespace
 
@@ -707,15 +727,18 @@ const char* mfma_forward_function(const HopParams& p, int kernel_id) {
     return p.G % kWavesPerBlock == 0 ? "mfma_fwd_shared_kernel" : "mfma_fwd_kernel";
 }
 
+const char* mfma_forward_form(const HopParams& p, int kernel_id) {
+    if (p.D == 64 || p.D == 128) return "";
+    return narrow_rows(p, kernel_id == K_MFMA_BF16_N32 ? 1 : 2) == kNarrow ? "rows_cached" : "rows_streamed";
+}
+
 hipError_t launch_mfma_forward(const HopParams& p, int kernel_id, hipStream_t s) {
     if (kernel_id == K_MFMA_BF16_STREAM) return mfma_forward_stream_feasible(p) ? launch_mfma_forward_stream(p, s) : launch_mfma_forward_long(p, s);
     if (!mfma_forward_feasible(p, kernel_id)) return hipErrorInvalidValue;
     const int KT = kernel_id == K_MFMA_BF16_N32 ? 1 : 2;
     TileParams tp;
     if (!make_tile_params(p, KT, &tp)) return hipErrorInvalidValue;
-    if (p.D == 128) return launch_width<128, false>(p, tp, KT, s);
-    if (p.D == 64) return launch_width<64, false>(p, tp, KT, s);
-    return p.D > 64 ? launch_width<128, true>(p, tp, KT, s) : launch_width<64, true>(p, tp, KT, s);
+    return KT == 1 ? launch_width<1>(p, tp, s) : launch_width<2>(p, tp, s);
 }
 
 }  // namespace ta

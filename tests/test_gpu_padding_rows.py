@@ -40,3 +40,24 @@ def test_padding_is_not_read(dims, Hq, Hkv, D, causal, lens, rope, vin):
             out.append(to_host(o))
         assert np.isfinite(out[1]).all() and np.array_equal(*out)
         assert all(not out[0][b, n:].any() for b, n in enumerate(lens))
+
+
+@pytest.mark.parametrize("H,Hkv,rope", [(8, 8, None), (8, 2, 500.0), (6, 2, None)])
+@pytest.mark.parametrize("vin", [ta.TA_VIN_KV, ta.TA_VIN_O])
+def test_streamed_narrow_rows_give_the_bits_of_cached_ones(H, Hkv, rope, vin):
+    """Two tiles, heads of 40 features: a call a little larger than the last-level cache, and each end of it alone."""
+    B, n, D, heads = 4, 56, 40, 2 * H + Hkv + (H if vin else Hkv)
+    dims = (round(330e6 / (2 * B * n * D * heads)), n)
+    gen = torch.Generator(device="cuda").manual_seed(9500 + H)
+    q, k, x = (torch.randn((B, dims[0] * n, h, D), generator=gen, device="cuda").bfloat16() for h in (H, Hkv, H if vin else Hkv))
+
+    def hop(form, q, k, x):
+        plan = ta.ta_plan_create(q.shape[0], H, Hkv, D, dims, ta.TA_BF16, False, rope_base=rope)
+        assert plan.hop_form(1, vin) == form
+        o = torch.full_like(q, float("nan"))
+        ta.ta_axis_attn_forward(plan, 1, q, k, x, vin, o)
+        return o
+    whole = hop("rows_streamed", q, k, x)
+    assert torch.isfinite(whole).all()
+    for b in (0, B - 1):
+        assert torch.equal(whole[b:b + 1], hop("rows_cached", *(t[b:b + 1].contiguous() for t in (q, k, x))))
