@@ -44,6 +44,7 @@ def short(name: str):
     """`mfma_fwd_pair_kernel<128, false, false>` from a demangled kernel symbol of the library; None for other kernels."""
     if not name.startswith("void ta::") and not name.startswith("ta::"):
         return None
+    name = re.sub(r"\((?:\w+::|\(anonymous namespace\)::)+\w+\)(?=\d)", "", name)     # (ta::(anonymous namespace)::Form)2 -> 2
     m = re.search(r"(\w+_kernel(<[^>(]*>)?)\(", name)
     return m.group(1) if m else None
 

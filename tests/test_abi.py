@@ -367,6 +367,15 @@ def test_traffic_of_several_instantiations_is_averaged():
                    "mfma_bf16_n32_shared_kv": {"fetch_bytes_per_launch": 5.0, "write_bytes_per_launch": 3.0}}
 
 
+def test_kernel_names_with_enumerators():
+    """A profiler writes an enumerator among a kernel's template arguments with its type."""
+    from paper_2410_20926_amd.counters import short
+    ns, end = "void ta::(anonymous namespace)::", "(ta::BwdParams, ta::mfma::TileParams)"
+    assert short(ns + "mfma_bwd_kernel<128, false, false, (ta::(anonymous namespace)::BwdRows)1, false>" + end) == "mfma_bwd_kernel<128, false, false, 1, false>"
+    assert short(ns + "mfma_fwd_long_kernel<64, 8, (ta::(anonymous namespace)::Form)2, true, false>(ta::HopParams)") == "mfma_fwd_long_kernel<64, 8, 2, true, false>"
+    assert short(ns + "copy_kernel(void*)") == "copy_kernel" and short("void at::native::sum_kernel<1>(int)") is None
+
+
 def test_forms_of_the_long_axis_forward():
     """Windows that are short against a workgroup and bit tables are not run in phases; axes of 1,024 to 2,047 positions are where the workgroups come out even."""
     FOUR, EIGHT, PHASES = "four_tiles_in_step", "eight_tiles_in_step", "eight_tiles_in_phases"
