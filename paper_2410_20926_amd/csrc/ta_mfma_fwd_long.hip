@@ -8,14 +8,15 @@
 // arrive).  Per block a wave forms S^T = K Q^T for two 32-key tiles, the softmax of 64 keys at once, O^T += V^T P^T.
 //   The weights of each 32-key tile are rounded relative to the row's maximum up to that tile (see below), and the accumulators are
 // rescaled only when some row's maximum has grown; the sum of the ROUNDED weights is one dot product per pair of weights.  A tile that
-// no row of the query tile sees (half of a diagonal block, padding) is left out.
+// no row of the query tile sees (half of a diagonal block, padding) is left out; in phases (below) only its value product is.
 //   In step, eight waves reach their products, then their softmax, then their products together, and either pipe of a SIMD is idle while
 // the other works (32,768 keys of width 128: matrix units busy 37 % of 22.7 M cycles).  On long axes the two halves of the workgroup
 // therefore work half a block apart (kPhases): busy 50 % of 16.9 M cycles; the operands of a product are read from LDS a stage ahead, and blocks
-// that every row sees whole run without the code for masks.  Value rows lie 16 or 48 banks apart, so that the transposed reads have no bank
+// that every row sees whole run without the code for masks.  At width 128 that form takes 256 registers and spills 42 (narrow rows 58); the body
+// with masks reloads 8 to 15 of them a block, the one without none.  Value rows lie 16 or 48 banks apart, so that the transposed reads have no bank
 // conflicts (half of the LDS cycles before).  The time falls less than the cycles, because the clock falls from 2.33 to about 1.95 GHz.
-//   What bounds it: for long axes the power the card may draw (1.03 PFLOP/s; a large bf16 matrix product reaches 1.18), on short ones
-// memory and the wait for the first rows.  32 / 8 heads of width 128: 32,768 keys, causal, 9.8 -> 8.6 ms, 16,384 keys, not causal, 4.84 -> 4.08 ms;
+//   What bounds it: for long axes the power the card may draw (1.04 PFLOP/s; a large bf16 matrix product reaches 1.15), on short ones
+// memory and the wait for the first rows.  32 / 8 heads of width 128: 32,768 keys, causal, 9.86 -> 8.46 ms, 16,384 keys, not causal, 4.84 -> 4.08 ms;
 // 32 heads of width 64, 8,192 x 2, not causal, 1,567 -> 1,331 us; four tiles: 4,096 keys, not causal, 405 -> 375 us; with the second hop, 128 x 128,
 // 200 -> 184 us; 8 heads of 1,024 x 16: 140 -> 116 us, of width 64, 512 x 64: 101 -> 86 us (against a kernel that took 32 keys per barrier and
 // rescaled for every tile).  (A reference that moved only when the maximum had passed it by 2^6 took 12 % less in step, with 3 per cent more error.)
