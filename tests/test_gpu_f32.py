@@ -257,3 +257,25 @@ def test_more_workgroups_than_one_grid_dimension_holds():
         ref = (w[..., None] * x[:, :, None]).sum(-2)
         err = (got.view(dims[0], 2, H, D).transpose(1, 2) - ref).abs().max().item()
         assert err <= 8 * TOL["f32"], err                      # sums of a few products up to 40
+
+
+@pytest.mark.parametrize("n,D,tabled,window,valid", [(16, 64, False, 0, 0), (3, 36, True, 0, 100), (11, 64, False, 4, 0), (7, 100, True, 0, 0), (16, 128, False, 0, 333), (5, 128, False, 2, 0)])
+def test_large_and_small_calls_give_the_same_bits(n, D, tabled, window, valid):
+    """On 16-row tiles calls of more than 4,096 waves work visibility out at another place than smaller ones."""
+    B, H, tiles = 16, 8, 40
+    dims = (tiles * (16 // n) - (1 if n < 16 else 0), n)   # (the last tile is not full)
+    assert B * H * tiles > 4096 > H * tiles
+    gen = torch.Generator(device="cuda").manual_seed(8300 + n + D)
+    q, k, v = (torch.randn((B, dims[0] * n, H, D), generator=gen, device="cuda") for _ in range(3))
+    seen = torch.rand((n, n), generator=gen, device="cuda") < 0.7
+    table = torch.from_numpy(ta.pack_axis_mask(seen.cpu().numpy())).cuda() if tabled else None
+
+    def hop(q, k, v):
+        plan = ta.ta_plan_create(q.shape[0], H, H, D, dims, ta.TA_F32, not tabled, window=(0, window), valid_len=valid, axis_masks=[None, table])
+        o = torch.full_like(q, float("nan"))
+        ta.ta_axis_attn_forward(plan, 1, q, k, v, ta.TA_VIN_O, o)
+        return o
+    whole = hop(q, k, v)
+    assert torch.isfinite(whole).all()
+    for b in (0, B - 1):
+        assert torch.equal(whole[b:b + 1], hop(*(t[b:b + 1].contiguous() for t in (q, k, v))))
