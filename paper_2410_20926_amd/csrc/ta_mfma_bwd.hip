@@ -1080,7 +1080,7 @@ int heads_side_by_side(const HopParams& p, const TileParams& tp, BwdRows rows) {
 // workgroup: 12 heads of 40, 1,846 x 16 x 2 131 -> 109; 12 heads of 100, 369 x 27 54.6 -> 51.3; in order it is the other way round: 12 of 40, 3,163 x 27
 // 102 and 116, 12 of 100, 204 x 21 x 2 46.8 and 48.3.  As above, with waves for the chip (1,024 to 1,536 waves of width 80 to 112: 3 per cent ahead; fewer,
 // 2 behind).  Large calls of wide rows whose pairs are in order as well are ahead in pairs (training step of 32 x 32 x 32, 32 heads of 100 1,751 and 1,731;
-// one hop of width 112 from 560 MB on 3 to 14 per cent; smaller ones 1 to 5 behind).
+// one hop of width 112 from 560 MB on 3 to 14 per cent; smaller ones 1 to 5 behind, and encoded ones of width 100 2).
 //   A call whose tensors are a little more than the 256 MB of the last-level cache evicts by a hop's end what the next pass, or hop, begins with; streamed
 // rows leave it part of that.  Cached and streamed: 32 heads of 100, 70 x 32 x 4 (401 MB) 109 and 96; 85 x 32 (122 MB) 32.2 and 35.4; 12 heads,
 // 2,736 x 32 (1.5 GB) 351 and 364; 32 / 8 heads of 96, 162 x 32 x 4 (510 MB) 228 and 207; 46 x 32 x 4 (145 MB) 57.9 and 59.6; 1,806 x 32 (2 GB) 558 and 566;
@@ -1091,7 +1091,8 @@ BwdRows narrow_rows(const HopParams& p, const TileParams& tp) {
     const uint32_t batch = (uint32_t)p.Hkv * tp.tiles_lo;    // workgroups that are put in order together, one head in each
     const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (3.0 * p.Hq + 2.0 * p.Hkv + 2.0 * p.vin_heads);
     if (p.G == 1 && p.Hkv % 2 == 0 && batch % 8 != 0 && (int64_t)p.Hkv * tp.tiles * p.B >= 1280) return kNarrowPairs;
-    if (p.G == 1 && batch % 16 == 0 && p.n > 16 && p.D >= 100 && p.D * 2 % 64 != 0 && bytes >= (p.D >= 112 ? 560e6 : 1e9)) return kNarrowPairs;
+    if (p.G == 1 && batch % 16 == 0 && p.n > 16 && p.D >= 100 && p.D * 2 % 64 != 0 && (p.D >= 112 ? bytes >= 560e6 : bytes >= 1e9 && !p.rope))
+        return kNarrowPairs;
     return bytes >= 280e6 && bytes < (p.D <= 64 ? 450e6 : p.G == 1 ? 560e6 : 1400e6) ? kNarrowStreamed : kNarrow;
 }
 

@@ -411,8 +411,8 @@ def test_forms_of_the_one_tile_backward():
     larger than the last-level cache; whole rows have one form."""
     CACHED, STREAMED, PAIRS = "rows_cached", "rows_streamed", "heads_in_pairs"
 
-    def form(n, fibres, B, Hq, Hkv, D, vin=ta.TA_VIN_KV):
-        return ta.ta_plan_create(B, Hq, Hkv, D, (n, fibres), ta.TA_BF16, True).hop_form(0, vin, True)
+    def form(n, fibres, B, Hq, Hkv, D, vin=ta.TA_VIN_KV, rope=None):
+        return ta.ta_plan_create(B, Hq, Hkv, D, (n, fibres), ta.TA_BF16, True, rope_base=rope).hop_form(0, vin, True)
 
     def streamed(Hq, Hkv, D, vin):                         # fibres of 32 rows from and up to which a call streams
         rows = [form(32, 8 * i, 1, Hq, Hkv, D, vin) for i in range(1, 700)]
@@ -430,6 +430,7 @@ def test_forms_of_the_one_tile_backward():
     # large calls whose pairs are in order too: 32 heads of 32 x 32 x 32, 1.47 GB; 0.73 GB of width 100, 112, 96 (whole sectors) and 112 on packed tiles
     assert form(32, 1024, 1, 32, 32, 100) == PAIRS and form(32, 512, 1, 32, 32, 100) == CACHED and form(32, 512, 1, 32, 32, 112) == PAIRS
     assert form(32, 1024, 1, 32, 32, 96) == CACHED and form(16, 1024, 1, 32, 32, 112) == CACHED and form(32, 3001, 1, 8, 8, 100) == CACHED
+    assert form(32, 1024, 1, 32, 32, 100, rope=0.0) == CACHED and form(32, 1024, 1, 32, 32, 112, rope=0.0) == form(32, 123, 4, 12, 12, 100, rope=0.0) == PAIRS
     assert form(32, 123, 4, 12, 12, 128) == "" and form(33, 123, 4, 12, 12, 100) == ""
 
 
