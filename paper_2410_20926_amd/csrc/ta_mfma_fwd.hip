@@ -688,12 +688,13 @@ bool mfma_forward_supports(int32_t n, int32_t D, int dtype, int* kernel_id) {
 
 namespace {
 // Two tiles of narrow rows in 64-wide tiles, by the bytes of the call: one that is a little larger than the 256 MB of the last-level cache evicts by its end
-// what the next pass, or hop, begins with, and streamed rows leave it part of that (cached and streamed, means over 1,500 calls: 282 to 390 MB 3 to 4 per
-// cent behind, at most 12; 200 to 270 MB 7 to 14 ahead, from 400 MB on 1 to 2.  8 heads of 40, 260 x 56 x 8, 299 MB, 101 and 93 us).  One tile is ahead
-// cached at every size.
+// what the next pass, or hop, begins with, and streamed rows leave it part of that (cached against streamed, means over 1,500 calls: 282 to 390 MB 4 per
+// cent behind, 8 where four heads share K, at most 12; 200 to 270 MB 7 to 14 ahead, from 420 MB on 1 to 2.  8 heads of 40, 260 x 56 x 8, 299 MB, 101 and 93
+// us).  Where a group shares the value input too, cached rows are level or ahead (282 to 390 MB 1 per cent; 8 / 2 heads of 40, 1,765 x 37 x 3 135 and 145
+// us), and on one tile ahead at every size.
 FwdRows narrow_rows(const HopParams& p, int KT) {
     const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (2.0 * p.Hq + p.Hkv + p.vin_heads);
-    return p.D > 64 || (KT == 2 && bytes >= 282e6 && bytes < 390e6) ? kNarrowStreamed : kNarrow;
+    return p.D > 64 || (KT == 2 && p.vin_heads == p.Hq && bytes >= 282e6 && bytes < 390e6) ? kNarrowStreamed : kNarrow;
 }
 
 template <int D, int KT, FwdRows ROWS>

@@ -438,11 +438,12 @@ def test_forms_of_the_one_and_two_tile_forward():
     """Rows of up to 60 features: through the caches, but streamed on two tiles in calls a little larger than the last-level cache; wider narrow rows: streamed."""
     def form(n, fibres, Hq, Hkv, D, vin=ta.TA_VIN_KV):
         return ta.ta_plan_create(1, Hq, Hkv, D, (n, fibres), ta.TA_BF16, True).hop_form(0, vin)
-    for Hq, Hkv, D, vin in ((8, 8, 40, 0), (8, 2, 40, 1), (16, 4, 20, 0)):
+    for Hq, Hkv, D, vin in ((8, 8, 40, 0), (8, 2, 40, 1), (6, 2, 20, 1)):
         mb = 50 * D * 2 * (2 * Hq + Hkv + (Hq if vin else Hkv)) / 1e6
         for at, streamed in ((270, False), (281, False), (283, True), (389, True), (391, False), (1000, False)):
             assert form(50, round(at / mb), Hq, Hkv, D, vin) == ("rows_streamed" if streamed else "rows_cached")
             assert form(25, round(2 * at / mb), Hq, Hkv, D, vin) == "rows_cached"
+    assert {form(50, i, 8, 2, 40, 0) for i in range(200, 8000, 200)} == {"rows_cached"}      # a group's heads share the values
     assert form(50, 10, 8, 2, 100) == form(20, 10, 8, 8, 72) == "rows_streamed" and form(50, 10, 8, 2, 128) == form(20, 10, 8, 8, 64) == ""
 
 
