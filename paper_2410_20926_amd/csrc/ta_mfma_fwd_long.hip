@@ -505,6 +505,7 @@ hipError_t launch(const HopParams& p, const LongParams& lp, const Choice& how, h
 //   the same, 1,024 to 2,047 positions: phases where the workgroups of eight come out even over the CUs, but not where a causal mask works the four tiles
 //     of a group's heads alike, or there are many rounds of unequal workgroups anyway.  8 heads of 128, four sequences of 2,047 4 93, p 80, causal 90, 73;
 //     eight of 1,500 109, 115, causal 92, 95; 1,100 x 32, causal, 200, 239; 32 / 8 heads, eight of 1,024 186, 178, causal 121, 134.
+//     Lengths of the sequences upset what comes out even (64 drawn calls: causal 13 per cent behind, 64-wide 8, others level): four tiles.
 //   narrower rows: eight from 1,024 positions on, in phases from 4,096 positions and 3,000 keys (width up to 64: 1,024) on.  12 heads of 100, causal:
 //     3,000 x 8 8 427, p 443; 8,192 x 2 638, 599; 16,384 1,190, 1,078; two sequences of 16,384, window 64 130, 226; 1,024 382, 446; 3,000 865, 870; 8
 //     heads of 40, window 512 111, 118; 1,280 196, 187.  Tables of random bits, four of 4,096, 12 heads of 100: 665, 771.
@@ -525,7 +526,7 @@ bool long_params(const HopParams& p, LongParams* lp, Choice* how) {
     bool phases = eight && !p.rope && !p.mask;
     if (!whole) phases = phases && p.n >= 4096 && reach >= (p.D > 64 ? 3000 : 1024);
     else if (p.n >= 2048) phases = phases && reach >= (p.D == 64 ? 2048 : lp->heads == 4 ? 1280 : 1536);
-    else phases = phases && reach == p.n && (wgs % 256 == 0 || wgs % 256 >= 192) && (!p.causal || (lp->heads == 1 && wgs <= (p.D == 128 ? 768 : 256)));
+    else phases = phases && reach == p.n && !p.valid_lens && (wgs % 256 == 0 || wgs % 256 >= 192) && (!p.causal || (lp->heads == 1 && wgs <= (p.D == 128 ? 768 : 256)));
     how->form = p.n <= 2 * kKeys ? kShort : phases ? kPhases : kBlocks;
     how->waves = phases || (eight && (!whole || p.rope)) ? 8 : 4;
     lp->qblocks = (uint32_t)blocks(how->waves);

@@ -380,9 +380,9 @@ def test_forms_of_the_long_axis_forward():
     """Windows that are short against a workgroup and bit tables are not run in phases; axes of 1,024 to 2,047 positions are where the workgroups come out even."""
     FOUR, EIGHT, PHASES = "four_tiles_in_step", "eight_tiles_in_step", "eight_tiles_in_phases"
 
-    def form(n, B, Hq, Hkv, D, causal=True, window=0, table=False, rope=None, vin=ta.TA_VIN_KV):
-        # (a table's address is only kept here)
-        return ta.ta_plan_create(B, Hq, Hkv, D, (n,), ta.TA_BF16, causal, window=(window,), axis_masks=[0x1000 if table else None], rope_base=rope).hop_form(0, vin)
+    def form(n, B, Hq, Hkv, D, causal=True, window=0, table=False, rope=None, vin=ta.TA_VIN_KV, lens=None):
+        # (a table's address, and that of lengths, is only kept here)
+        return ta.ta_plan_create(B, Hq, Hkv, D, (n,), ta.TA_BF16, causal, window=(window,), axis_masks=[0x1000 if table else None], rope_base=rope, valid_lens=lens).hop_form(0, vin)
     assert form(128, 8, 8, 8, 128) == "two_blocks" and form(200, 8, 8, 8, 128) == FOUR
     for Hq, Hkv, D, least in ((32, 8, 128, 1280), (8, 8, 128, 1536), (32, 8, 64, 2048), (16, 16, 64, 2048)):
         assert form(4096, 4, Hq, Hkv, D) == PHASES and form(2048, 8, Hq, Hkv, D) == PHASES
@@ -400,6 +400,7 @@ def test_forms_of_the_long_axis_forward():
     assert form(4096, 1, 1, 1, 128) == FOUR                # 16 workgroups of eight tiles for 256 CUs
     # 1,024 to 2,047 positions
     assert form(2047, 4, 8, 8, 128, False) == PHASES and form(2047, 4, 8, 8, 128) == PHASES and form(2047, 4, 8, 8, 64) == PHASES     # 256 workgroups
+    assert form(2047, 4, 8, 8, 128, lens=0x1000) == FOUR and form(2048, 4, 8, 8, 128, lens=0x1000) == PHASES
     assert form(1500, 8, 8, 8, 128, False) == FOUR         # 384: the second round half empty
     assert form(1024, 8, 32, 8, 128) == FOUR and form(1024, 8, 32, 8, 128, False) == PHASES      # equal waves under the mask as it is
     assert form(2047, 4, 8, 8, 128, False, window=2046) == PHASES and form(2047, 4, 8, 8, 128, False, window=300) == FOUR
