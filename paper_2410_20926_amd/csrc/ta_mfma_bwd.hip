@@ -18,6 +18,7 @@
 // so that dS^T and P, dS come out of the accumulators directly in B-operand layout; row
 // statistics cross from the first orientation to the second through 3 x 32 floats of LDS.
 #include "ta_mfma_bwd_common.h"
+#include <type_traits>
 
 namespace ta {
 namespace {
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     const int w = SIDE && nw == 1 ? 0 : wave;             // heads without a group stand side by side in a workgroup, each on its own
 
     uint32_t bx, ty;
-    workgroup_xy<NARROW>(bx, ty);
+    workgroup_xy<NARROW>(bx, ty, tp.run_log2);
     const int g = SIDE && nw == 1 ? (int)bx * bp.side + wave : (int)bx;
     const int h = g * p.G + (MULTI ? bp.head_base : 0) + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
@@ -97,20 +98,25 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     // ---- gather Q, K, X, G rows: every load is issued before the first wait, in the order of first use
     //      (loads complete in order: Q and K can be staged while X and G are still on their way) ------------
     u32x4 qraw[G::kPasses], kraw[G::kPasses], xraw[G::kPasses], graw[G::kPasses];
+    uint32_t misaligned = 0u;                             // NARROW: a bit per requested row (see gather_request), 8 per tensor
+    auto request = [&](auto streamed, const char* base, int which, u32x4 (&raw)[G::kPasses]) {
+#pragma unroll
+        for (int i = 0; i < G::kPasses; ++i) {
+            const u32x4 off = rowoff[i * G::kRowsPerPass + lrow];
+            uint32_t mis;
+            raw[i] = gather_request<NARROW, decltype(streamed)::value>(base, off[which], lbyte, dbytes, mis);
+            if constexpr (NARROW) misaligned |= (mis >> 3) << (8 * which + i);
+        }
+    };
+    auto ready = [&](int which, const char* base, uint32_t pitch, u32x4 (&raw)[G::kPasses]) {
+        gather_ready_all<NARROW>(raw, misaligned >> (8 * which), base, pitch, lbyte, dbytes);
+    };
     // Rows every wave of the group reads stay cached; rows that this wave alone reads are streamed, narrow ones by choice (narrow_rows).
-#pragma unroll
-    for (int i = 0; i < G::kPasses; ++i) qraw[i] = gather_chunk<NARROW, STREAMED>(qb, rowoff[i * G::kRowsPerPass + lrow].x, lbyte, dbytes);
-#pragma unroll
-    for (int i = 0; i < G::kPasses; ++i) kraw[i] = gather_chunk<NARROW, false>(kb, rowoff[i * G::kRowsPerPass + lrow].y, lbyte, dbytes);
-    if (vin_is_o) {                                        // one choice for all eight requests, not one per request
-#pragma unroll
-        for (int i = 0; i < G::kPasses; ++i) xraw[i] = gather_chunk<NARROW, STREAMED>(xb, rowoff[i * G::kRowsPerPass + lrow].z, lbyte, dbytes);
-    } else {
-#pragma unroll
-        for (int i = 0; i < G::kPasses; ++i) xraw[i] = gather_chunk<NARROW, false>(xb, rowoff[i * G::kRowsPerPass + lrow].z, lbyte, dbytes);
-    }
-#pragma unroll
-    for (int i = 0; i < G::kPasses; ++i) graw[i] = gather_chunk<NARROW, STREAMED>(gb, rowoff[i * G::kRowsPerPass + lrow].w, lbyte, dbytes);
+    request(std::bool_constant<STREAMED>{}, qb, 0, qraw);
+    request(std::false_type{}, kb, 1, kraw);
+    if (vin_is_o) request(std::bool_constant<STREAMED>{}, xb, 2, xraw);   // one choice for all eight requests, not one per request
+    else request(std::false_type{}, xb, 2, xraw);
+    request(std::bool_constant<STREAMED>{}, gb, 3, graw);
     __builtin_amdgcn_sched_barrier(0);
 
     // rotary encoding: Q and K rows are turned by their position on the axis before anything uses them;
@@ -119,7 +125,9 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
         const int rc = min(row, rows_valid - 1);
         return (float)(rc - (int)((rc + 0.5f) * tp.inv_n) * n);
     };
+    ready(0, qb, tp.q_row, qraw);
     if constexpr (ROPE) {
+        ready(1, kb, tp.k_row, kraw);
         float rev[4];
         rope_rates(p, lcol, rev);
 #pragma unroll
@@ -144,6 +152,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     read_natural<D>(oprd, qop);
     read_transposed<D>(trbase, qT);
     lds_wave_sync();
+    if constexpr (!ROPE) ready(1, kb, tp.k_row, kraw);
     stage_rows<D>(stg, kraw);
     lds_wave_sync();
     read_natural<D>(oprd, kop);
@@ -160,10 +169,12 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
 
     // ---- X, G: dP in both orientations; G^T for dX ---------------------------------------
     u32x4 xop[G::kKSteps], gop[G::kKSteps], gT[G::kDTiles][2];
+    ready(2, xb, tp.v_row, xraw);
     stage_rows<D>(stg, xraw);
     lds_wave_sync();
     read_natural<D>(oprd, xop);
     lds_wave_sync();
+    ready(3, gb, tp.o_row, graw);
     stage_rows<D>(stg, graw);
     lds_wave_sync();
     read_natural<D>(oprd, gop);
@@ -1074,25 +1085,24 @@ int heads_side_by_side(const HopParams& p, const TileParams& tp, BwdRows rows) {
     return side;
 }
 
-// Narrow rows share their first and last line with the neighbouring heads' rows.  Taken in order by an XCD (workgroup_xy) one head per workgroup
-// and the caches serve that best.  (Heads, width, tokens by axis length; one hop, first or accumulating, us.)
-//   Where the workgroups of a batch are not a multiple of eight they are dealt out to the XCDs as they come, and neighbours want to be in one
-// workgroup: 12 heads of 40, 1,846 x 16 x 2 131 -> 109; 12 heads of 100, 369 x 27 54.6 -> 51.3; in order it is the other way round: 12 of 40, 3,163 x 27
-// 102 and 116, 12 of 100, 204 x 21 x 2 46.8 and 48.3.  As above, with waves for the chip (1,024 to 1,536 waves of width 80 to 112: 3 per cent ahead; fewer,
-// 2 behind).  Large calls of wide rows whose pairs are in order as well are ahead in pairs (training step of 32 x 32 x 32, 32 heads of 100 1,751 and 1,731;
-// one hop of width 112 from 560 MB on 3 to 14 per cent; smaller ones 1 to 5 behind, and encoded ones of width 100 2).
+// Narrow rows share their first and last line with the neighbouring heads' rows; taken in order by an XCD (xcd_order) one head per workgroup and the
+// caches serve that best.  (Heads, width, tokens by axis length; one hop, us.)
+//   Large calls of wide rows are ahead in pairs: cached alone and in pairs, 32 heads of 100, 32 x 32 x 32 428 and 423; 8 of 112, 28 x 1,856 (652 MB) 216 and 192; of
+// 112, 31 x 1,378 x 4 681 and 621; from 1.5 GB on every width on tiles that are nearly full: 8 of 40, 32 x 6,627 x 2 568 and 553, of 84, 16 x 3,613 x 3 502 and 493,
+// 32 of 40, 23 x 32 x 23 x 8 691 and 670, but 32 of 96, 20 x 2,302 421 and 433; below, 12 of 100, 82 x 32 x 4 (176 MB) 39.5 and 41.4; 32 of 112, 28 x 31 x 4 (174 MB) 35.0 and 34.6.  Where the workgroups of a batch
+// are not a multiple of eight pairs were ahead while such a grid lost its order; in runs (xcd_order) they are 0 to 4 per cent behind (4 of 100, 1,518 x 16 29.5 and
+// 30.6; 1,276 x 27 level), and stay because the form is what a plan reports.
 //   A call whose tensors are a little more than the 256 MB of the last-level cache evicts by a hop's end what the next pass, or hop, begins with; streamed
-// rows leave it part of that.  Cached and streamed: 32 heads of 100, 70 x 32 x 4 (401 MB) 109 and 96; 85 x 32 (122 MB) 32.2 and 35.4; 12 heads,
-// 2,736 x 32 (1.5 GB) 351 and 364; 32 / 8 heads of 96, 162 x 32 x 4 (510 MB) 228 and 207; 46 x 32 x 4 (145 MB) 57.9 and 59.6; 1,806 x 32 (2 GB) 558 and 566;
-// 8 heads of 40, 3,163 x 27 (383 MB) 102 and 96.  Means over 3,000 calls: streamed ahead from 280 MB to 560 (groups 1,400; widths up to 64 450) by 5 per
-// cent, behind by 4 to 13 outside.  The previous dQ and dK come through the caches everywhere: streamed, their two requests per row crossed HBM twice (2
-// to 10 per cent).
+// rows leave it part of that.  Cached and streamed: 32 heads of 100, 8 x 16 x 7 x 8 (321 MB) 86 and 78; 4 of 84, 39 x 16 x 38 x 4 (446 MB) 111 and 106; 16 / 4 of
+// 100, 16 x 131 x 8 (295 MB) 77 and 74, of 72, 28 x 1,407 (499 MB) 160 and 163, 32 / 8 of 72, 32 x 468 x 4 (1.1 GB) 398 and 406; 8 of 40, 33 x 31 x 32 (147 MB) 28.6 and
+// 36.2.  The previous dQ and dK come through the caches everywhere: streamed, their two requests per row crossed HBM twice (2 to 10 per cent).
 BwdRows narrow_rows(const HopParams& p, const TileParams& tp) {
     const uint32_t batch = (uint32_t)p.Hkv * tp.tiles_lo;    // workgroups that are put in order together, one head in each
     const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (3.0 * p.Hq + 2.0 * p.Hkv + 2.0 * p.vin_heads);
     if (p.G == 1 && p.Hkv % 2 == 0 && batch % 8 != 0 && (int64_t)p.Hkv * tp.tiles * p.B >= 1280) return kNarrowPairs;
     if (p.G == 1 && batch % 16 == 0 && p.n > 16 && p.D >= 100 && p.D * 2 % 64 != 0 && (p.D >= 112 ? bytes >= 560e6 : bytes >= 1e9 && !p.rope))
         return kNarrowPairs;
+    if (p.G == 1 && p.Hkv % 2 == 0 && kTile / p.n * p.n >= 27 && bytes >= 1.5e9) return kNarrowPairs;
     return bytes >= 280e6 && bytes < (p.D <= 64 ? 450e6 : p.G == 1 ? 560e6 : 1400e6) ? kNarrowStreamed : kNarrow;
 }
 
@@ -1115,6 +1125,10 @@ hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     BwdParams bpc = bp;
     bpc.side = side;
     TileParams tpc = tp;
+    // Heads without a group, rows of a fibre 2 MB apart and more: one run per XCD (runs and one, us: 32 heads of 40, 27 x 1,860 319 and 271; 12 of 84,
+    // 27 x 2,362 318 and 271; 32 of 96, 27 x 775 295 and 267; 8 of 84, 16 x 3,613 x 3 526 and 493; 32 of 100, 32 x 627 272 and 279; 12 of 96, 20 x 2,790 249
+    // and 253); groups are ahead in runs there too (32 / 8 heads of 96, 32 x 738 209 and 215).
+    tpc.run_log2 = p.G == 1 && p.stride * tp.q_row >= 2 << 20 ? kLongestRun : narrow_run_log2(bp.wg_heads * side);
     void* args[2] = {&bpc, &tpc};
     if (smem > 64 * 1024) {
         const hipError_t e = allow_dynamic_lds(kf, (int)smem);

@@ -36,8 +36,9 @@ __device__ inline void prefetch_tile(u32x4 (&old)[Geo<D>::kDTiles * 2], const u3
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if constexpr (NARROW) {
+                // a chunk that would pass the end of the row: the row's last 16 bytes (store_tile takes its half)
                 const uint32_t fbyte = (uint32_t)(half * 64 + (lane & 7) * 8) * 2;
-                old[half * 4 + i] = load_chunk<true, false>(gbase, tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, fbyte, dbytes);
+                old[half * 4 + i] = *reinterpret_cast<const u32x4*>(gbase + (tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte + min(fbyte, dbytes - 16)));
             } else {
                 old[half * 4 + i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gbase + tile_out_offset<D>(rowoff, which, half, i, lane)));
             }
@@ -89,8 +90,8 @@ __device__ inline void store_tile(const f32x16 (&acc)[Geo<D>::kDTiles], float mu
             const int row = 8 * i + (lane >> 3), cc = lane & 7;
             const f32x4 x0 = *reinterpret_cast<const f32x4*>(buf + row * G::kFPitch + cc * 32);
             const f32x4 x1 = *reinterpret_cast<const f32x4*>(buf + row * G::kFPitch + cc * 32 + 16);
-            if (row < rows_valid) {
-                float y[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+            float y[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+            auto value = [&]() {
                 if constexpr (Enc::on) {
                     if (enc.hop()->rope) {
                         float rev[4], c[4], sn[4];
@@ -100,17 +101,21 @@ __device__ inline void store_tile(const f32x16 (&acc)[Geo<D>::kDTiles], float mu
                     }
                 }
                 if (add_old) {
-                    const u32x4 o = old[half * 4 + i];
+                    u32x4 o = old[half * 4 + i];
+                    if constexpr (NARROW) {
+                        if ((uint32_t)(half * 64 + cc * 8) * 2 + 8 == dbytes) { o.x = o.z; o.y = o.w; }   // the row's last 8 bytes
+                    }
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { y[2 * e] += bf16_lo(o[e]); y[2 * e + 1] += bf16_hi(o[e]); }
                 }
-                const u32x4 packed = u32x4{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])};
-                if constexpr (NARROW) {
-                    const uint32_t fbyte = (uint32_t)(half * 64 + (lane & 7) * 8) * 2;
-                    store_chunk<true>(gbase, tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, fbyte, dbytes, packed);
-                } else {
-                    __builtin_nontemporal_store(packed, reinterpret_cast<u32x4*>(gbase + tile_out_offset<D>(rowoff, which, half, i, lane)));
-                }
+                return u32x4{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])};
+            };
+            if constexpr (NARROW) {
+                const uint32_t fbyte = (uint32_t)(half * 64 + (lane & 7) * 8) * 2;
+                buffer_store_chunk<true>(row_buffer(gbase), tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, row < rows_valid, fbyte, dbytes, value(), dbytes % 16 == 0);
+            } else {
+                if (row < rows_valid)
+                    __builtin_nontemporal_store(value(), reinterpret_cast<u32x4*>(gbase + tile_out_offset<D>(rowoff, which, half, i, lane)));
             }
         }
         lds_wave_sync();
@@ -138,11 +143,13 @@ __device__ inline void store_tile_plain(const f32x16 (&acc)[Geo<D>::kDTiles], fl
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const int row = i * G::kRowsPerPass + lrow;
-        if (row < rows_valid) {
+        if constexpr (NARROW) {
+            const u32x4 v = *reinterpret_cast<const u32x4*>(buf + row * G::kPitch + lcol * 16);
+            buffer_store_chunk<true>(row_buffer(gbase), rowoff[row][which], row < rows_valid, (uint32_t)lcol * 16, dbytes, v, dbytes % 16 == 0);
+        } else if (row < rows_valid) {
             const u32x4 v = *reinterpret_cast<const u32x4*>(buf + row * G::kPitch + lcol * 16);
             const u32x4 off4 = rowoff[row];
-            if constexpr (NARROW) store_chunk<true>(gbase, which == 0 ? off4.x : which == 1 ? off4.y : off4.z, (uint32_t)lcol * 16, dbytes, v);
-            else __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(gbase + ((which == 0 ? off4.x : which == 1 ? off4.y : off4.z) + lcol * 16)));
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(gbase + ((which == 0 ? off4.x : which == 1 ? off4.y : off4.z) + lcol * 16)));
         }
     }
     lds_wave_sync();

@@ -12,10 +12,16 @@
 // rounding.  While a head is worked on, the next head's rows (or the next fibre's: a workgroup takes every
 // gridDim.x-th one) are on their way into registers, half a tile per wave and tensor.
 //
+// A request is waited for with a count of what was issued behind it, loads and stores alike, so two things stand between the rows on their way and
+// their use: a store that may or may not have been issued, after which every wait is for all of them (stores go through the buffer's bounds check
+// instead of a branch, row_buffer), and a spilled value, whose reload waits for every row requested before it (what depends on the lane is formed anew
+// wherever it is used; narrow 128-wide instantiations had 12 to 26 spilled registers, now 0 to 4).  32 / 8 heads of 96, 13 x 52 x 71, hops of 1,078 / 800 ->
+// 866 / 584 us, of 100, 64 x 64 x 32, 1,965 -> 1,351; whole rows of 128 features, 128 x 128, 193 / 183 -> 189 / 175.
+//
 // What bounds it: memory, and seven barriers per head of which one workgroup per CU (width 128, n > 64) hides little (LDS active 30 % of
 // the time, 41 % of that in bank conflicts, matrix units busy 9 %).  The
 // blocked kernel, which it replaces up to 128, gathers every tile again at each visit, waits for each, and forms S and dP up to
-// four times.  128 x 128 tokens, 32 / 8 heads of width 128, causal: hops of 437 / 395 us -> 196 / 186 us;
+// four times.  128 x 128 tokens, 32 / 8 heads of width 128, causal: hops of 437 / 395 us -> 189 / 175 us;
 // 100 x 100, batch 2, 12 heads of width 96: 407 -> 218 us; 64 x 64 x 32, 32 / 8 heads: the two-tile kernel's 1522 / 1544 us -> 1365 / 1185 us
 // (5.3 and 4.8 TB/s).  A first form with one wave per tile and 512 registers took 450 us at 128 x 128: it spilled, and a
 // reload waits for every row requested before it.
@@ -40,7 +46,7 @@ struct Resident {
     static constexpr int kMax = kTile * (kWPitch > kFPitch ? kWPitch : kFPitch);
     static constexpr int kRegion = kBuf > kMax ? kBuf : kMax;                 // a K or value tile, 32 rows of dS or P, or the transit
     static constexpr int kStats = 2 * 3 * kTile * 4;                          // both waves' max, sum, sum of P o dP
-    static constexpr int kTileBytes = 2 * kBuf + 2 * kRegion + kTile * 16 + kStats;   // LDS per tile
+    static constexpr int kTileBytes = 2 * kBuf + 2 * kRegion + kStats;        // LDS per tile
 };
 
 // MODE: what the heads of a group share.  kOne: a group is one head, nothing is shared or summed; kHeads: K; kGroup: K and the
@@ -55,7 +61,6 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     constexpr int kCT = TM / 2;                           // key tiles per wave on the query side
     const HopParams& p = bp.hop;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = wave >> 1, s = wave & 1;                // tile; which of its two waves
     const int T = sp.tiles, n = p.n;                      // blockDim.x = 128 T
@@ -63,20 +68,13 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     char* sX = sK + T * R::kRegion;
     char* sQ = sX + T * R::kRegion;
     char* sG = sQ + T * R::kBuf;
-    u32x4* rowoff = reinterpret_cast<u32x4*>(sG + T * R::kBuf) + w * kTile;
-    float* stats = reinterpret_cast<float*>(sG + T * R::kBuf + T * kTile * 16) + w * (R::kStats / 4);
+    float* stats = reinterpret_cast<float*>(sG + T * R::kBuf) + w * (R::kStats / 4);
     char* transit = (s ? sK : sX) + w * R::kRegion;
 
-    const int lrow = lane / G::kChunks, lcol = lane % G::kChunks;
-    const uint32_t lbyte = lcol * 16;
     const uint32_t dbytes = (uint32_t)p.D * 2;
-    const int r32 = lane & 31, hf = lane >> 5;
     const uint32_t stride = (uint32_t)p.stride;
     const int rows_t = min(kTile, n - kTile * w);
-    const int qr = kTile * w + r32;                       // this lane's query row
     const float sl2 = p.scale * kLog2e;
-    float rev[4];
-    if constexpr (ROPE) rope_rates(p, lcol, rev);
 
     // key tiles [cb, ce) that some row of query tile a sees
     auto key_tiles = [&](int a, int& cb, int& ce) {
@@ -99,7 +97,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     struct Where { int b, g; int64_t f; uint32_t tok0; };
     auto where = [&](uint32_t u) {
         if constexpr (NARROW) {                           // each XCD takes a contiguous run of (fibre, head) pairs, see workgroup_xy
-            if (units % 8u == 0u && gridDim.x % 8u == 0u) u = (u & 7u) * (units / 8u) + (u >> 3);
+            if (gridDim.x % 8u == 0u) u = xcd_order(u, units, kLongestRun);
         }
         Where x;
         x.g = (int)(u % (uint32_t)p.Hkv);
@@ -113,63 +111,80 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     // `once`: nobody asks for these rows again (K and a per-group value input are asked for by every head).
     // The rows are only requested here; `ready` turns what has come into this lane's chunks (see gather_chunk: NARROW rows start
     // 8 bytes into an aligned unit or on one, `mis` has a bit per row).
-    struct Raw { u32x4 v[kMine]; uint32_t mis; };
-    auto gather = [&](auto once, const Tensor& t, const Where& x, int head, uint32_t pitch, Raw& raw) {
+    enum : int { kRawQ, kRawG, kRawX, kRawK };
+    struct Raw { u32x4 v[kMine]; };
+    uint32_t misaligned = 0u;                             // NARROW: a bit per requested row, 4 bits per tensor
+    // What depends on the lane is formed anew wherever it is used, from a copy of the lane's number that the compiler cannot look
+    // through: kept over the loop it would be spilled, and a reload waits for every row requested before it.
+    auto fresh_lane = [&]() {
+        int l = threadIdx.x & 63;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto gather = [&](auto once, auto which, const Tensor& t, const Where& x, int head, uint32_t pitch, Raw& raw) {
         const char* base = reinterpret_cast<const char*>(t.p) + ((int64_t)x.b * t.sb + (int64_t)head * t.sh) * 2;
-        int row = lrow;
-        asm volatile("" : "+v"(row));                     // offsets formed here each time: hoisted out of the loop, they would be spilled
-        if constexpr (NARROW) raw.mis = 0u;
+        const int l = fresh_lane(), row = l / G::kChunks;
+        const uint32_t lbyte = (uint32_t)(l % G::kChunks) * 16;
+        if constexpr (NARROW) misaligned &= ~(15u << (4 * decltype(which)::value));
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
             const uint32_t rr = (uint32_t)min(kTile * w + (s * kMine + i) * G::kRowsPerPass + row, n - 1);
             uint32_t mis;
             raw.v[i] = gather_request<NARROW, decltype(once)::value>(base, (x.tok0 + rr * stride) * pitch, lbyte, dbytes, mis);
-            if constexpr (NARROW) raw.mis |= mis ? 1u << i : 0u;
+            if constexpr (NARROW) misaligned |= (mis >> 3) << (4 * decltype(which)::value + i);
         }
     };
     auto put = [&](char* tile, const Raw& raw) {
-        const uint32_t stg = (uint32_t)((s * kMine * G::kRowsPerPass + lrow) * G::kPitch) + lbyte;
+        const int l = fresh_lane();
+        const uint32_t stg = (uint32_t)((s * kMine * G::kRowsPerPass + l / G::kChunks) * G::kPitch + (l % G::kChunks) * 16);
 #pragma unroll
         for (int i = 0; i < kMine; ++i) *reinterpret_cast<u32x4*>(tile + stg + i * G::kRowsPerPass * G::kPitch) = raw.v[i];
     };
-    auto ready = [&](Raw& raw) {
+    auto ready = [&](auto which, Raw& raw) {
         if constexpr (NARROW) {
+            const uint32_t lbyte = (uint32_t)(fresh_lane() % G::kChunks) * 16;
 #pragma unroll
-            for (int i = 0; i < kMine; ++i) raw.v[i] = gather_ready<NARROW>(raw.v[i], (raw.mis >> i) & 1u, lbyte, dbytes);
+            for (int i = 0; i < kMine; ++i) raw.v[i] = gather_ready<NARROW>(raw.v[i], (misaligned >> (4 * decltype(which)::value + i)) & 1u, lbyte, dbytes);
         }
     };
-    auto encode = [&](Raw& raw) {
-        ready(raw);
+    auto encode = [&](auto which, Raw& raw) {
+        ready(which, raw);
         if constexpr (ROPE) {
-            int row = lrow;
-            asm volatile("" : "+v"(row));
+            const int l = fresh_lane(), row = l / G::kChunks;
+            float rev[4];
+            rope_rates(p, l % G::kChunks, rev);
 #pragma unroll
             for (int i = 0; i < kMine; ++i) raw.v[i] = rope_chunk(raw.v[i], (float)min(kTile * w + (s * kMine + i) * G::kRowsPerPass + row, n - 1), rev);
         }
     };
     // A finished half of an output tile: acc[t][r] = (row r32, feature kHalf s + 32 t + 8 (r / 4) + 4 hf + r % 4), turned in LDS,
     // turned back when the hop encodes positions, added to the previous contents, rounded, stored.
-    auto row_offset = [&](int which, int row) {
-        const u32x4 off = rowoff[row];
-        return which == 0 ? off.x : which == 1 ? off.y : off.z;
-    };
+    // (Rows past the fibre's end are loaded as its last row and never stored.)
     auto out_lane = [&](int& orow, uint32_t& obyte) {
-        int l = lane;
-        asm volatile("" : "+v"(l));
+        const int l = fresh_lane();
         orow = l / R::kOutLanes;
         obyte = (uint32_t)(s * R::kHalf * 2 + (l % R::kOutLanes) * 16);
     };
-    auto previous = [&](int which, const char* base, u32x4 (&old)[R::kOut]) {
+    auto out_offset = [&](uint32_t tok0, int row, uint32_t pitch) { return (tok0 + (uint32_t)(kTile * w + row) * stride) * pitch; };
+    auto previous = [&](const char* base, uint32_t tok0, uint32_t pitch, u32x4 (&old)[R::kOut]) {
         int orow;
         uint32_t obyte;
         out_lane(orow, obyte);
 #pragma unroll
-        for (int i = 0; i < R::kOut; ++i) old[i] = load_chunk<NARROW, !NARROW>(base, row_offset(which, i * R::kOutRows + orow), obyte, dbytes);
+        for (int i = 0; i < R::kOut; ++i) {
+            const uint32_t off = out_offset(tok0, min(i * R::kOutRows + orow, rows_t - 1), pitch);
+            if constexpr (!NARROW) {
+                old[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (off + obyte)));
+            } else {                                      // a chunk that would pass the end of the row: the row's last 16 bytes (see `finish`)
+                old[i] = *reinterpret_cast<const u32x4*>(base + (off + min(obyte, dbytes - 16)));
+            }
+        }
     };
-    auto finish = [&](const f32x16 (&acc)[R::kHT], float mult, int which, char* base, const u32x4 (&old)[R::kOut], bool add, bool turn) {
+    auto finish = [&](auto turn, const f32x16 (&acc)[R::kHT], float mult, char* base, uint32_t tok0, uint32_t pitch, const u32x4 (&old)[R::kOut], bool add) {
         int orow;
         uint32_t obyte;
         out_lane(orow, obyte);
+        const int la = fresh_lane(), r32 = la & 31, hf = la >> 5;
         lds_wave_sync();
 #pragma unroll
         for (int t = 0; t < R::kHT; ++t)
@@ -178,57 +193,71 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
                 *reinterpret_cast<f32x4*>(transit + r32 * R::kFPitch + (32 * t + 8 * q + 4 * hf) * 4) =
                     f32x4{acc[t][4 * q] * mult, acc[t][4 * q + 1] * mult, acc[t][4 * q + 2] * mult, acc[t][4 * q + 3] * mult};
         lds_wave_sync();
+        float y[R::kOut][8];
 #pragma unroll
         for (int i = 0; i < R::kOut; ++i) {
-            const int row = i * R::kOutRows + orow;
-            const char* at = transit + row * R::kFPitch + 2 * (obyte - (uint32_t)(s * R::kHalf * 2));
+            const char* at = transit + (i * R::kOutRows + orow) * R::kFPitch + 2 * (obyte - (uint32_t)(s * R::kHalf * 2));
             const f32x4 x0 = *reinterpret_cast<const f32x4*>(at), x1 = *reinterpret_cast<const f32x4*>(at + 16);
-            float y[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-            if constexpr (ROPE) {
-                if (turn) {
-                    float orev[4], c[4], sn[4];
-                    rope_rates(p, (int)(obyte / 16), orev);
-                    rope_sincos((float)(kTile * w + row), orev, c, sn);
-                    rope_apply_f32<true>(y, c, sn);
-                }
-            }
-            if (add) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { y[2 * e] += bf16_lo(old[i][e]); y[2 * e + 1] += bf16_hi(old[i][e]); }
-            }
-            if (row < rows_t)
-                store_chunk<NARROW>(base, row_offset(which, row), obyte, dbytes,
-                                    u32x4{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])});
+            for (int e = 0; e < 4; ++e) { y[i][e] = x0[e]; y[i][4 + e] = x1[e]; }
         }
+        if constexpr (ROPE && decltype(turn)::value) {
+            float orev[4], c[4], sn[4];
+            rope_rates(p, (int)(obyte / 16), orev);
+#pragma unroll
+            for (int i = 0; i < R::kOut; ++i) {
+                rope_sincos((float)(kTile * w + i * R::kOutRows + orow), orev, c, sn);
+                rope_apply_f32<true>(y[i], c, sn);
+            }
+        }
+        if (add) {
+            const bool tail = NARROW && obyte + 8 == dbytes;   // this lane has the row's last 8 bytes: the second half of what it asked for
+#pragma unroll
+            for (int i = 0; i < R::kOut; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t o = NARROW && e < 2 ? (tail ? old[i][e + 2] : old[i][e]) : old[i][e];
+                    y[i][2 * e] += bf16_lo(o);
+                    y[i][2 * e + 1] += bf16_hi(o);
+                }
+        }
+        const __amdgpu_buffer_rsrc_t to = row_buffer(base);
+#pragma unroll
+        for (int i = 0; i < R::kOut; ++i)
+            buffer_store_chunk<NARROW>(to, out_offset(tok0, i * R::kOutRows + orow, pitch), i * R::kOutRows + orow < rows_t, obyte, dbytes,
+                                       u32x4{pack_bf16x2(y[i][0], y[i][1]), pack_bf16x2(y[i][2], y[i][3]), pack_bf16x2(y[i][4], y[i][5]), pack_bf16x2(y[i][6], y[i][7])});
     };
 
     Where at = where(blockIdx.x);
     Raw qraw, graw, xraw, kraw;
-    using Once = std::true_type;
+    using Once = std::bool_constant<!NARROW>;
     using Again = std::false_type;
+    using IsQ = std::integral_constant<int, kRawQ>;
+    using IsG = std::integral_constant<int, kRawG>;
+    using IsX = std::integral_constant<int, kRawX>;
+    using IsK = std::integral_constant<int, kRawK>;
+    using Turn = std::true_type;
+    using AsIs = std::false_type;
     // The next head's own rows are requested as soon as this head's are in LDS; those that the heads share, mostly in L2, near
     // the head's end, when there are registers again.  Always issued: requests under a branch that live across the loop were all spilled.
     auto request_own = [&](const Where& x, int head) {
-        gather(Once{}, p.q, x, head, sp.q_row, qraw);
-        gather(Once{}, bp.d_o, x, head, sp.o_row, graw);
-        if constexpr (!VS) gather(Once{}, p.vin, x, head, sp.v_row, xraw);
-        if constexpr (MODE == kOne) gather(Once{}, p.k, x, x.g, sp.k_row, kraw);
+        gather(Once{}, IsQ{}, p.q, x, head, sp.q_row, qraw);
+        gather(Once{}, IsG{}, bp.d_o, x, head, sp.o_row, graw);
+        if constexpr (!VS) gather(Once{}, IsX{}, p.vin, x, head, sp.v_row, xraw);
+        if constexpr (MODE == kOne) gather(Once{}, IsK{}, p.k, x, x.g, sp.k_row, kraw);
     };
     auto request_shared = [&](const Where& x) {
-        if constexpr (MODE != kOne) gather(Again{}, p.k, x, x.g, sp.k_row, kraw);
-        if constexpr (VS) gather(Again{}, p.vin, x, x.g, sp.v_row, xraw);
+        if constexpr (MODE != kOne) gather(Again{}, IsK{}, p.k, x, x.g, sp.k_row, kraw);
+        if constexpr (VS) gather(Again{}, IsX{}, p.vin, x, x.g, sp.v_row, xraw);
     };
     request_shared(at);
     request_own(at, at.g * p.G);
+    __builtin_amdgcn_s_waitcnt(0x0f70);                   // vmcnt(0): in the loop the rows have stores behind them, whose number each wait there counts
 #pragma unroll 1
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
         f32x16 dk[R::kHT], dx[R::kHT];
 #pragma unroll
         for (int t = 0; t < R::kHT; ++t) { dk[t] = f32x16{}; dx[t] = f32x16{}; }
-        if (s == 0 && lane < kTile) {                     // (read from barrier (4) to barrier (7) of a head; visible from barrier (1) on)
-            const uint32_t tok = at.tok0 + (uint32_t)min(kTile * w + lane, n - 1) * stride;
-            rowoff[lane] = u32x4{tok * sp.q_row, tok * sp.k_row, tok * sp.v_row, tok * sp.o_row};
-        }
         const Where nx = where(u + gridDim.x < units ? u + gridDim.x : u);   // the last fibre requests itself again
         const uint32_t vl = (uint32_t)hop_valid_len(p, at.b);
         const int nreal = at.tok0 >= vl ? 0 : (int)min((uint32_t)n, (vl - at.tok0 + stride - 1) / stride);
@@ -237,20 +266,18 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         for (int hl = 0; hl < (MODE == kOne ? 1 : p.G); ++hl) {
             const int h = at.g * p.G + hl, hv = VS ? at.g : h;
             const bool last_head = MODE == kOne || hl + 1 == p.G;
-            // LDS addresses of this lane, formed again for every head: kept over the loop they would be spilled, and a reload
-            // would wait for the next head's rows, which are requested before it
-            int l_ = lane;
-            asm volatile("" : "+v"(l_));
+            const int l_ = fresh_lane(), r32 = l_ & 31, hf = l_ >> 5;
+            const int qr = kTile * w + r32;               // this lane's query row
             const uint32_t nat = (uint32_t)((l_ & 31) * G::kPitch + (l_ >> 5) * 16);
             const uint32_t trow = (uint32_t)(4 * (l_ >> 5) + ((l_ & 15) >> 2)), tcol = (uint32_t)(16 * ((l_ >> 4) & 1) + 4 * (l_ & 3)) * 2;
             const uint32_t trn = trow * G::kPitch + tcol;
-            encode(kraw);
+            encode(IsK{}, kraw);
             put(sK + w * R::kRegion, kraw);
-            ready(xraw);
+            ready(IsX{}, xraw);
             put(sX + w * R::kRegion, xraw);
-            encode(qraw);
+            encode(IsQ{}, qraw);
             put(sQ + w * R::kBuf, qraw);
-            ready(graw);
+            ready(IsG{}, graw);
             put(sG + w * R::kBuf, graw);
             request_own(last_head ? nx : at, last_head ? nx.g * p.G : h + 1);
             char* dqb = reinterpret_cast<char*>(bp.dq.p) + ((int64_t)at.b * bp.dq.sb + (int64_t)h * bp.dq.sh) * 2;
@@ -297,7 +324,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
                 }
             l += __shfl_xor(l, 32);
             dn += __shfl_xor(dn, 32);
-            if (lane < kTile) { stats[(3 * s) * kTile + lane] = mx; stats[(3 * s + 1) * kTile + lane] = l; stats[(3 * s + 2) * kTile + lane] = dn; }
+            if (hf == 0) { stats[(3 * s) * kTile + r32] = mx; stats[(3 * s + 1) * kTile + r32] = l; stats[(3 * s + 2) * kTile + r32] = dn; }
             __syncthreads();                              // (2) both waves' statistics are there
             float f, delta;                               // what the weights are multiplied by; rowsum(P o dP)
             {
@@ -381,13 +408,13 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
             char* dxb = reinterpret_cast<char*>(bp.d_vin.p) + ((int64_t)at.b * bp.d_vin.sb + (int64_t)hv * bp.d_vin.sh) * 2;
             u32x4 old[R::kOut] = {}, oldk[R::kOut] = {};
             if (bp.accumulate) {
-                previous(0, dqb, old);
-                if (last_head) previous(1, dkb, oldk);
+                previous(dqb, at.tok0, sp.q_row, old);
+                if (last_head) previous(dkb, at.tok0, sp.k_row, oldk);
             }
             __syncthreads();                              // (5) nobody reads this head's tiles any more
             // the partner's half of dQ's features goes to the partner (its transit area), lane by lane
             {
-                char* there = (s ? sX : sK) + w * R::kRegion + lane * 16;
+                char* there = (s ? sX : sK) + w * R::kRegion + l_ * 16;
 #pragma unroll
                 for (int t = 0; t < R::kHT; ++t)
 #pragma unroll
@@ -404,13 +431,13 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
             for (int t = 0; t < R::kHT; ++t)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(transit + lane * 16 + (4 * t + q) * 1024);
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(transit + l_ * 16 + (4 * t + q) * 1024);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) mine[t][4 * q + e] = (s ? dq[R::kHT + t][4 * q + e] : dq[t][4 * q + e]) + v[e];
                 }
-            finish(mine, p.scale, 0, dqb, old, bp.accumulate != 0, true);
-            if (!VS || last_head) finish(dx, 1.f, 2, dxb, old, false, false);
-            if (last_head) finish(dk, p.scale, 1, dkb, oldk, bp.accumulate != 0, true);
+            finish(Turn{}, mine, p.scale, dqb, at.tok0, sp.q_row, old, bp.accumulate != 0);
+            if (!VS || last_head) finish(AsIs{}, dx, 1.f, dxb, at.tok0, sp.v_row, old, false);
+            if (last_head) finish(Turn{}, dk, p.scale, dkb, at.tok0, sp.k_row, oldk, bp.accumulate != 0);
             __syncthreads();                              // (7) the areas of transit are free for the next head's tiles
         }
         at = nx;

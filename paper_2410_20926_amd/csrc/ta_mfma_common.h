@@ -91,37 +91,58 @@ __device__ inline u32x4 gather_chunk(const char* base, uint32_t rowoff, uint32_t
         return out;
     }
 }
-// The same in two parts, the request and what is done with the bytes when they have come, for kernels that request rows long before
-// they use them; `mis`: the row starts 8 bytes into an aligned unit.  (gather_chunk itself is not put together from them: carried
-// from one part to the other, `mis` costs the one-tile kernels 2 to 10 per cent on narrow rows.)
+// What lies outside the row reads as zero.
+__device__ inline u32x4 row_only(u32x4 a, uint32_t lbyte, uint32_t dbytes) {
+    if (lbyte + 8 > dbytes) { a.x = 0u; a.y = 0u; }
+    if (lbyte + 16 > dbytes) { a.z = 0u; a.w = 0u; }
+    return a;
+}
+// Whether every row of a tensor is whole 16-byte units on 16-byte boundaries, so that row_only is all there is to do (uniform).
+__device__ inline bool whole_units(const char* base, uint32_t pitch, uint32_t dbytes) {
+    return (((uint32_t)reinterpret_cast<uintptr_t>(base) | pitch | dbytes) & 15u) == 0u;
+}
+// The same in two parts: the request, and what is done with the bytes when they have come.  In one piece the first row's bytes are waited for before
+// the last rows are requested (the compiler shares the registers of the halves that are put together), so that the four tiles of the one-tile
+// backward waited for memory five times one after the other, and the two of the two-tile forward twice.  In two parts (32 / 8 heads of 96, 32 x 32 x 32, the
+// backward hop along the second axis 338 -> 276 us, forward 122 -> 104; 12 heads of 96, 134 x 57 x 8, forward 196 -> 124; 8 / 2 heads of 96, 4 x 3 x 6 x 5 x 3,
+// a backward hop 15.3 -> 11.9).  `mis`: the row starts 8 bytes into an aligned unit.
 template <bool NARROW, bool NT>
 __device__ inline u32x4 gather_request(const char* base, uint32_t rowoff, uint32_t lbyte, uint32_t dbytes, uint32_t& mis) {
     if constexpr (!NARROW) {
         mis = 0u;
         return load_chunk<false, NT>(base, rowoff, lbyte, dbytes);
     } else {
-        const char* row = base + rowoff;
-        mis = (uint32_t)(reinterpret_cast<uintptr_t>(row) & 8u);
-        const int32_t s = (int32_t)lbyte - (int32_t)mis;           // where this lane's aligned unit starts, relative to the row
-        const u32x4* src = reinterpret_cast<const u32x4*>(row + (s + 16 <= (int32_t)dbytes ? s : (int32_t)dbytes - 16));
+        // `base` is uniform: a uniform 16-byte boundary and 32-bit offsets from it, so that no address takes two registers
+        const uint32_t over = (uint32_t)(reinterpret_cast<uintptr_t>(base) & 8u), at = rowoff + over;
+        mis = at & 8u;
+        const u32x4* src = reinterpret_cast<const u32x4*>((base - over) + (lbyte + 16 <= mis + dbytes ? at - mis + lbyte : at + dbytes - 16));
         return NT ? __builtin_nontemporal_load(src) : *src;
     }
 }
 template <bool NARROW>
-__device__ inline u32x4 gather_ready(u32x4 a, uint32_t mis, uint32_t lbyte, uint32_t dbytes) {
+__device__ inline u32x4 gather_ready(const u32x4 a, uint32_t mis, uint32_t lbyte, uint32_t dbytes) {
     if constexpr (!NARROW) {
         return a;
     } else {
-        const int32_t s = (int32_t)lbyte - (mis ? 8 : 0);
-        const bool full = s + 16 <= (int32_t)dbytes, tail = !full && s + 8 <= (int32_t)dbytes;
-        if (tail) a = u32x4{a.z, a.w, 0u, 0u};
-        if (!full && !tail) a = u32x4{0u, 0u, 0u, 0u};
-        const uint32_t nx = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a.x, 0x101, 0xf, 0xf, true);
-        const uint32_t ny = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a.y, 0x101, 0xf, 0xf, true);
-        u32x4 out = mis ? u32x4{a.z, a.w, nx, ny} : a;
-        if (lbyte + 8 > dbytes) { out.x = 0u; out.y = 0u; }
-        if (lbyte + 16 > dbytes) { out.z = 0u; out.w = 0u; }
-        return out;
+        // the unit that reaches 8 bytes past the end of the row came as the row's last 16 bytes: what it wanted is the second half
+        const bool last = lbyte + 8 == dbytes + (mis ? 8 : 0);
+        const uint32_t x = last ? a.z : a.x, y = last ? a.w : a.y;
+        const uint32_t nx = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x101, 0xf, 0xf, true);   // the next lane's (row_shl:1 within 16 lanes)
+        const uint32_t ny = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x101, 0xf, 0xf, true);
+        return row_only(mis ? u32x4{a.z, a.w, nx, ny} : u32x4{x, y, a.z, a.w}, lbyte, dbytes);
+    }
+}
+// A tensor's requested chunks made ready; `mis` has a bit per request.
+template <bool NARROW, int N>
+__device__ inline void gather_ready_all(u32x4 (&raw)[N], uint32_t mis, const char* base, uint32_t pitch, uint32_t lbyte, uint32_t dbytes) {
+    if constexpr (NARROW) {
+        if (whole_units(base, pitch, dbytes)) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) raw[i] = row_only(raw[i], lbyte, dbytes);
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) raw[i] = gather_ready<NARROW>(raw[i], (mis >> i) & 1u, lbyte, dbytes);
+        }
     }
 }
 // A finished output row leaves its row-major LDS tile (`lds_chunk` = this lane's 16-byte chunk of it, `lbyte` bytes into
@@ -151,6 +172,39 @@ __device__ inline void store_chunk(char* base, uint32_t rowoff, uint32_t lbyte, 
         char* a = base + (rowoff + lbyte);
         if (lbyte + 16 <= dbytes) *reinterpret_cast<u32x4*>(a) = v;
         else if (lbyte + 8 <= dbytes) *reinterpret_cast<u32x2*>(a) = u32x2{v.x, v.y};
+    }
+}
+
+// Stores of rows, some of which do not exist, without a branch: a lane that has nothing to store gives kNowhere, which the buffer's bounds
+// check drops.  A store under a branch may or may not have been issued, so that a later wait for a load (loads and stores are counted
+// together, in order) has to wait until every store before it has been written as well.  `base` is uniform, offsets are below
+// 2^32 - 512 (fits_u32).
+constexpr uint32_t kNowhere = 0xffffffffu;
+__device__ inline __amdgpu_buffer_rsrc_t row_buffer(char* base) { return __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xfffffff0u, 0x00020000); }
+// A lane's 16-byte chunk `lbyte` bytes into the row at `rowoff`.  NARROW as in store_chunk: whole chunks in one store, a row's last 8 bytes
+// in one of their own, through the cache.
+template <bool NARROW>
+__device__ inline void buffer_store_chunk(__amdgpu_buffer_rsrc_t to, uint32_t rowoff, bool exists, uint32_t lbyte, uint32_t dbytes, const u32x4 v, bool whole = false) {
+    if constexpr (!NARROW) {
+        __builtin_amdgcn_raw_buffer_store_b128(v, to, exists ? rowoff + lbyte : kNowhere, 0, 2);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b128(v, to, exists && lbyte + 16 <= dbytes ? rowoff + lbyte : kNowhere, 0, 0);
+        if (!whole) __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, to, exists && lbyte + 8 == dbytes ? rowoff + lbyte : kNowhere, 0, 0);
+    }
+}
+
+// The same from a row-major LDS tile (`lds_chunk` = this lane's chunk in it), as store_row_chunk: rows that are not whole 16-byte units leave as 8-byte
+// pieces that are contiguous within each store instruction.
+template <bool NARROW, int CHUNKS>
+__device__ inline void buffer_store_row_chunk(__amdgpu_buffer_rsrc_t to, uint32_t rowoff, bool exists, const char* lds_chunk, uint32_t lbyte, uint32_t dbytes, bool whole) {
+    static_assert(NARROW);
+    if (whole) {
+        __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(lds_chunk), to, exists && lbyte < dbytes ? rowoff + lbyte : kNowhere, 0, 0);
+    } else {
+        const uint32_t p0 = lbyte / 2, p1 = 8u * CHUNKS + lbyte / 2;   // byte offsets of the two pieces within the row
+        const char* lds_row = lds_chunk - lbyte;
+        __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(lds_row + p0), to, exists && p0 < dbytes ? rowoff + p0 : kNowhere, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(lds_row + p1), to, exists && p1 < dbytes ? rowoff + p1 : kNowhere, 0, 0);
     }
 }
 
@@ -338,22 +392,34 @@ __device__ inline void online_softmax_tile(const f32x16& st, uint32_t vis32, int
 // Workgroup numbering of the NARROW instantiations.  Rows that are not whole 64-byte pieces share their first and last
 // piece with the neighbouring heads' rows.  Workgroup ids go round the 8 XCDs, so with the plain numbering (head block
 // = blockIdx.x, fastest) neighbouring heads are written from different L2s and every shared piece reaches memory as two
-// partial writes.  Here each XCD takes a contiguous run of the (blockIdx.y, blockIdx.x) sequence instead: neighbouring
-// head blocks follow each other on one XCD, and their rows, stored through the cache, leave its L2 as whole lines
-// (head width 100, 32 heads, 32k tokens: a backward hop 620 -> 400 us).  bx, by: the pair to use in place of
-// blockIdx.x and blockIdx.y.
+// partial writes.  Here each XCD takes runs of 2^run_log2 neighbours in the (blockIdx.y, blockIdx.x) sequence: neighbouring
+// head blocks follow each other on one XCD, and their rows, stored through the cache, leave its L2 as whole lines, while the eight XCDs
+// stay on neighbouring tokens.  Runs of about 128 rows' heads (one, run, and one run per XCD; 32 x 32 x 32, second axis, us): 32 heads of 96, backward 479,
+// 385, 417, of 40 267, 179, 178; 32 / 8 heads of 96 287, 271, 296; 32 heads of 100, forward 173, 161, 172; 4 heads of 40, 64 x 24 x 50 x 2, backward 159, 95, 97.
+// The end of the grid, less than eight runs, goes in eight shorter ones, and up to seven workgroups as they come (before, a grid that was no
+// multiple of eight lost the order altogether: 12 heads of 100, 30 x 20 x 20 x 4, 261 and 220).
+__device__ inline uint32_t xcd_order(uint32_t lin, uint32_t total, uint32_t run_log2) {
+    const uint32_t base = lin >> (run_log2 + 3u) << (run_log2 + 3u), l = lin - base;
+    if (total - base >= 8u << run_log2) return base + ((l & 7u) << run_log2) + (l >> 3);
+    const uint32_t run = (total - base) >> 3;             // the last block: shorter runs, and up to seven workgroups as they come
+    return l < 8u * run ? base + (l & 7u) * run + (l >> 3) : lin;
+}
+constexpr uint32_t kLongestRun = 28;                      // run_log2 of one run per XCD
 template <bool NARROW>
-__device__ inline void workgroup_xy(uint32_t& bx, uint32_t& by) {
+__device__ inline void workgroup_xy(uint32_t& bx, uint32_t& by, uint32_t run_log2 = kLongestRun) {
     bx = blockIdx.x; by = blockIdx.y;
     if constexpr (NARROW) {
-        const uint32_t gx = gridDim.x, total = gx * gridDim.y;
-        if (total % 8u == 0u) {
-            const uint32_t lin = blockIdx.x + gx * blockIdx.y;
-            const uint32_t seq = (lin & 7u) * (total / 8u) + (lin >> 3);
-            bx = seq % gx;
-            by = seq / gx;
-        }
+        const uint32_t gx = gridDim.x;
+        const uint32_t seq = xcd_order(blockIdx.x + gx * blockIdx.y, gx * gridDim.y, run_log2);
+        bx = seq % gx;
+        by = seq / gx;
     }
+}
+// run_log2 for workgroups of `heads` heads each: 128 rows that are neighbours.
+inline uint32_t narrow_run_log2(int heads) {
+    uint32_t r = 7;
+    for (; heads > 1 && r > 4; heads /= 2) --r;
+    return r;
 }
 
 // Launch geometry computed on the host.
@@ -365,6 +431,7 @@ struct TileParams {
     uint32_t tiles_hi;
     uint32_t q_row, k_row, v_row, o_row;   // token pitch of each tensor in BYTES
     float inv_n;          // 1 / n
+    uint32_t run_log2;    // narrow rows: see xcd_order
 };
 
 // Fills tp for an axis of length p.n walked in `key_tiles` 32-key tiles; false when the
@@ -383,6 +450,7 @@ inline bool make_tile_params(const HopParams& p, int key_tiles, TileParams* tp) 
     tp->v_row = (uint32_t)(p.vin.st * 2);
     tp->o_row = (uint32_t)(p.o.st * 2);
     tp->inv_n = 1.0f / (float)p.n;
+    tp->run_log2 = kLongestRun;
     return true;
 }
 

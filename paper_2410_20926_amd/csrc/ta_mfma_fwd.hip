@@ -31,11 +31,8 @@ namespace {
 
 using namespace mfma;
 
-// How rows that one wave alone reads come in: whole rows are streamed past the caches, rows narrower than their tile by choice.  A narrow row shares its
-// first and last cache line with the neighbouring heads' rows, so that a streamed line crosses HBM once per row in it.  That decides it for rows of a
-// few lines' parts in 64-wide tiles (8 sequences of 20 x 28 x 23, 8 / 2 heads of width 40: 159 -> 134 us through the cache; 2 sequences, 32 heads: 220 ->
-// 195); wider rows are mostly whole lines, and their forward is faster streamed (32 x 32 x 32, 32 heads of width 100: 510 us against 530; 24 x 25 x 26, 12
-// heads of width 96: 290 / 314).
+// How rows that one wave alone reads come in: whole rows are streamed past the caches, rows narrower than their tile through them or past them by choice
+// (narrow_rows).  A narrow row shares its first and last cache line with the neighbouring heads' rows.
 enum FwdRows { kWhole, kNarrow, kNarrowStreamed };        // streamed; through the caches; streamed
 
 constexpr int kWavesPerBlock = 4;
@@ -44,7 +41,7 @@ constexpr int kWavesPerBlock = 4;
 // ROWS: narrow: the head is narrower than the D-wide tile (p.D features of 2 bytes per row); see load_chunk.
 // ROPE: the hop scores with rotary-encoded Q and K (instantiated separately: the plain kernels carry none of it).
 template <int D, int KT, FwdRows ROWS, bool ROPE>
-__global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopParams p, TileParams tp) {
+__global__ __launch_bounds__(kWavesPerBlock * 64, KT == 1 && ROWS != kWhole ? 3 : 2) void mfma_fwd_kernel(HopParams p, TileParams tp) {
     using G = Geo<D>;
     constexpr bool NARROW = ROWS != kWhole, STREAMED = ROWS != kNarrow;
     constexpr int kRows = kTile * KT;                     // rows of the unit's fibre set that have a table entry
@@ -56,7 +53,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
     // block -> (head block, tile, batch); heads fastest so that co-resident waves read
     // the same tokens (whole DRAM rows) and the four waves of a block share K
     uint32_t bx, by;
-    workgroup_xy<NARROW>(bx, by);
+    workgroup_xy<NARROW>(bx, by, tp.run_log2);
     const int h = (int)bx * kWavesPerBlock + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + by;
@@ -135,6 +132,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
     const bool v_once = (KT == 1) && (p.G == 1 || p.vin_heads == p.Hq);
     u32x4 qreg[G::kPasses], kreg[KT][G::kPasses], vreg[KT][G::kPasses];
     uint32_t ooff[G::kPasses], voff[KT][G::kPasses];
+    uint32_t qkmis = 0u, vmis = 0u;                       // NARROW: a bit per request, see gather_request: 8 each for Q and the K tiles, and for the value tiles
+    auto request = [&](auto streamed, const char* base, uint32_t off, int i, uint32_t& bits) {
+        uint32_t mis;
+        const u32x4 v = gather_request<NARROW, decltype(streamed)::value>(base, off, lbyte, dbytes, mis);
+        if constexpr (NARROW) bits |= (mis >> 3) << i;
+        return v;
+    };
+    using Own = std::bool_constant<STREAMED>;             // rows that this wave alone reads
     // (the choice between last-use and cached requests is made once, outside the loops: a choice per request is a branch
     // per request, and with narrow rows, whose chunks are put together from two lanes, every request then waits for the one before)
     auto gather_kv = [&](auto k_nt, auto v_nt) {
@@ -144,11 +149,11 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) {
                     const u32x4 off = rowoff[j * kTile + i * G::kRowsPerPass + lrow];
-                    kreg[j][i] = gather_chunk<NARROW, decltype(k_nt)::value && STREAMED>(kb, off.y, lbyte, dbytes);
+                    kreg[j][i] = request(std::bool_constant<decltype(k_nt)::value && STREAMED>{}, kb, off.y, 8 + 8 * j + i, qkmis);
                     voff[j][i] = off.z;
-                    if (j == 0) vreg[j][i] = gather_chunk<NARROW, decltype(v_nt)::value && STREAMED>(vb, voff[j][i], lbyte, dbytes);
+                    if (j == 0) vreg[j][i] = request(std::bool_constant<decltype(v_nt)::value && STREAMED>{}, vb, voff[j][i], 8 * j + i, vmis);
                     if (KT == 1) {
-                        qreg[i] = gather_chunk<NARROW, STREAMED>(qb, off.x, lbyte, dbytes);
+                        qreg[i] = request(Own{}, qb, off.x, i, qkmis);
                         ooff[i] = off.w;
                     }
                 }
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
             const u32x4 off = rowoff[qt * kTile + i * G::kRowsPerPass + lrow];
-            qreg[i] = gather_chunk<NARROW, STREAMED>(qb, off.x, lbyte, dbytes);
+            qreg[i] = request(Own{}, qb, off.x, i, qkmis);
             ooff[i] = off.w;
         }
     }
@@ -174,7 +179,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
         if (KT == 1) { const int rc = min(row, rows_valid - 1); return (float)(rc - (int)((rc + 0.5f) * tp.inv_n) * n); }
         return (float)min(row, n - 1);
     };
+    gather_ready_all<NARROW>(qreg, qkmis, qb, tp.q_row, lbyte, dbytes);
     if constexpr (ROPE) {
+        if (KT == 1) gather_ready_all<NARROW>(kreg[0], qkmis >> 8, kb, tp.k_row, lbyte, dbytes);
         rope_rates(p, lcol, rev);
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
@@ -211,6 +218,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
         st[j] = f32x16{};
         if (j < kt_end) {
             u32x4 kop[G::kKSteps];
+            if constexpr (KT > 1 || !ROPE) gather_ready_all<NARROW>(kreg[j], qkmis >> (8 + 8 * j), kb, tp.k_row, lbyte, dbytes);
             if constexpr (KT > 1 && ROPE) {
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) kreg[j][i] = rope_chunk(kreg[j][i], row_pos(j * kTile + i * G::kRowsPerPass + lrow), rev);
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
             lds_wave_sync();
             if (KT > 1 && j == 0 && kt_end > 1) {         // K tile 0 is out of its registers: request V tile 1
 #pragma unroll
-                for (int i = 0; i < G::kPasses; ++i) vreg[1][i] = gather_chunk<NARROW, false>(vb, voff[1][i], lbyte, dbytes);
+                for (int i = 0; i < G::kPasses; ++i) vreg[1][i] = request(std::false_type{}, vb, voff[1][i], 8 + i, vmis);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -289,6 +297,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
 #pragma unroll
     for (int j = 0; j < KT; ++j) {
         if (j < kt_end) {
+            gather_ready_all<NARROW>(vreg[j], vmis >> (8 * j), vb, tp.v_row, lbyte, dbytes);
             // rows rho and rho + 8 (rho mod 16 < 8) share a 32-bit word per column: slot
             // (rho / 16) * 8 + rho % 16 of the buffer
 #pragma unroll
@@ -339,12 +348,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_kernel(HopPar
             *reinterpret_cast<u32x2*>(buf + r32 * G::kPitch + (32 * t + 8 * q4 + 4 * hf) * 2) = v;
         }
     lds_wave_sync();
+    const bool o_whole = whole_units(ob, tp.o_row, dbytes);
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const int row = qt * kTile + i * G::kRowsPerPass + lrow;
-        if (row < rows_valid) {
+        if constexpr (NARROW)
+            buffer_store_row_chunk<true, G::kChunks>(row_buffer(ob), rowoff[row].w, row < rows_valid, stg + i * G::kRowsPerPass * G::kPitch, lbyte, dbytes, o_whole);
+        else if (row < rows_valid)
             store_row_chunk<NARROW, G::kChunks>(ob, ooff[i], stg + i * G::kRowsPerPass * G::kPitch, lbyte, dbytes);
-        }
     }
 }
 
@@ -371,7 +382,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     uint32_t bx, by;
-    workgroup_xy<NARROW>(bx, by);
+    workgroup_xy<NARROW>(bx, by, tp.run_log2);
     const int h = (int)bx * kWavesPerBlock + w;                             // host guarantees Hq % 4 == 0 and G % 4 == 0
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + by;
@@ -446,10 +457,17 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
     //      every shared tile, or its own tiles when the value input is per head -------------
     u32x4 qreg[G::kPasses], ksh[KT][kShare], vsh[KT][kShare], vreg[KT][G::kPasses];
     uint32_t ooff[G::kPasses];
+    uint32_t qmis = 0u, kmis[KT] = {}, vmis[KT] = {};     // NARROW: a bit per request, see gather_request
+    auto request = [&](auto streamed, const char* base, uint32_t off, int i, uint32_t& bits) {
+        uint32_t mis;
+        const u32x4 v = gather_request<NARROW, decltype(streamed)::value>(base, off, lbyte, dbytes, mis);
+        if constexpr (NARROW) bits |= (mis >> 3) << i;
+        return v;
+    };
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const u32x4 off = rowoff[qt * kTile + i * G::kRowsPerPass + lrow];
-        qreg[i] = gather_chunk<NARROW, STREAMED>(qb, off.x, lbyte, dbytes);
+        qreg[i] = request(std::bool_constant<STREAMED>{}, qb, off.x, i, qmis);
         ooff[i] = off.w;
     }
 #pragma unroll
@@ -458,20 +476,26 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
 #pragma unroll
             for (int i = 0; i < kShare; ++i) {
                 const u32x4 off = rowoff[j * kTile + (w * kShare + i) * G::kRowsPerPass + lrow];
-                ksh[j][i] = gather_chunk<NARROW, false>(kb, off.y, lbyte, dbytes);
-                if (v_shared) vsh[j][i] = gather_chunk<NARROW, false>(vb, off.z, lbyte, dbytes);
+                ksh[j][i] = request(std::false_type{}, kb, off.y, i, kmis[j]);
+                if (v_shared) vsh[j][i] = request(std::false_type{}, vb, off.z, i, vmis[j]);
             }
             if (!v_shared) {
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) {
                     const u32x4 off = rowoff[j * kTile + i * G::kRowsPerPass + lrow];
-                    vreg[j][i] = (KT == 1) ? gather_chunk<NARROW, STREAMED>(vb, off.z, lbyte, dbytes)
-                                           : gather_chunk<NARROW, false>(vb, off.z, lbyte, dbytes);   // with two query tiles a value tile is read twice: keep it cached
+                    vreg[j][i] = request(std::bool_constant<KT == 1 && STREAMED>{}, vb, off.z, i, vmis[j]);   // with two query tiles a value tile is read twice: keep it cached
                 }
             }
         }
     }
     __builtin_amdgcn_sched_barrier(0);
+    gather_ready_all<NARROW>(qreg, qmis, qb, tp.q_row, lbyte, dbytes);
+#pragma unroll
+    for (int j = 0; j < KT; ++j)
+        if (j < kt_end) {
+            gather_ready_all<NARROW>(ksh[j], kmis[j], kb, tp.k_row, lbyte, dbytes);
+            if (v_shared) gather_ready_all<NARROW>(vsh[j], vmis[j], vb, tp.v_row, lbyte, dbytes);
+        }
 
     // ---- rotary encoding of the gathered rows, by their position on the axis: Q (private) and this
     //      wave's quarter of every K tile, before they enter LDS ---------------------------------
@@ -599,6 +623,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
             if (v_shared) {
                 read_transposed<D>(sV + j * kTileBytes + troff, vT);
             } else {
+                gather_ready_all<NARROW>(vreg[j], vmis[j], vb, tp.v_row, lbyte, dbytes);
                 lds_wave_sync();
                 stage_rows<D>(stg, vreg[j]);
                 lds_wave_sync();
@@ -613,6 +638,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
     lds_wave_sync();
 
     // ---- normalise, round, transpose through the private tile, store ---------------------------------
+    const bool o_whole = whole_units(ob, tp.o_row, dbytes);
 #pragma unroll
     for (int hs = 0; hs < kHalves; ++hs) {
         if (r32 / kHalfRows == hs) {
@@ -630,9 +656,10 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
 #pragma unroll
         for (int i = 0; i < kHalfPasses; ++i) {
             const int row = qt * kTile + (hs * kHalfPasses + i) * G::kRowsPerPass + lrow;
-            if (row < rows_valid) {
+            if constexpr (NARROW)
+                buffer_store_row_chunk<true, G::kChunks>(row_buffer(ob), ooff[hs * kHalfPasses + i], row < rows_valid, stg + i * G::kRowsPerPass * G::kPitch, lbyte, dbytes, o_whole);
+            else if (row < rows_valid)
                 store_row_chunk<NARROW, G::kChunks>(ob, ooff[hs * kHalfPasses + i], stg + i * G::kRowsPerPass * G::kPitch, lbyte, dbytes);
-            }
         }
         lds_wave_sync();
     }
@@ -648,6 +675,7 @@ hipError_t launch_shared(const HopParams& p, const TileParams& tp, hipStream_t s
                             : (vs ? (const void*)mfma_fwd_shared_kernel<D, KT, true, ROWS, false> : (const void*)mfma_fwd_shared_kernel<D, KT, false, ROWS, false>);
     HopParams pc = p;
     TileParams tc = tp;
+    tc.run_log2 = narrow_run_log2(kWavesPerBlock);
     void* args[2] = {&pc, &tc};
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }
@@ -659,6 +687,7 @@ hipError_t launch(const HopParams& p, const TileParams& tp, hipStream_t s) {
     const void* kf = p.rope ? (const void*)mfma_fwd_kernel<D, KT, ROWS, true> : (const void*)mfma_fwd_kernel<D, KT, ROWS, false>;
     HopParams pc = p;
     TileParams tc = tp;
+    tc.run_log2 = narrow_run_log2(kWavesPerBlock);
     void* args[2] = {&pc, &tc};
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }
@@ -687,14 +716,17 @@ bool mfma_forward_supports(int32_t n, int32_t D, int dtype, int* kernel_id) {
 }
 
 namespace {
-// Two tiles of narrow rows in 64-wide tiles, by the bytes of the call: one that is a little larger than the 256 MB of the last-level cache evicts by its end
-// what the next pass, or hop, begins with, and streamed rows leave it part of that (cached against streamed, means over 1,500 calls: 282 to 390 MB 4 per
-// cent behind, 8 where four heads share K, at most 12; 200 to 270 MB 7 to 14 ahead, from 420 MB on 1 to 2.  8 heads of 40, 260 x 56 x 8, 299 MB, 101 and 93
-// us).  Where a group shares the value input too, cached rows are level or ahead (282 to 390 MB 1 per cent; 8 / 2 heads of 40, 1,765 x 37 x 3 135 and 145
-// us), and on one tile ahead at every size.
+// Narrow rows by the bytes of the call: one that is a little larger than the 256 MB of the last-level cache evicts by its end what the next pass, or hop,
+// begins with, and streamed rows leave it part of that; elsewhere the lines that neighbouring heads share are worth more, but for calls of a few MB, where it
+// makes no difference.  Cached and streamed, one hop, us: 12 heads of 100, 25 x 28 x 25 x 2 (336 MB) 67.7 and 61.7; 32 of 84, 355 x 42 (321 MB) 105 and 98.6; 32 / 8
+// of 112, 22 x 50 x 21 (414 MB) 93 and 88; 8 of 40, 31 x 44 x 31 x 3 (325 MB) 86 and 82; below, 12 heads of 100, 25 x 32 x 25 (192 MB) 33.7 and 36.7, 8 / 2 of 72,
+// 18 x 16 x 18 x 8 (155 MB) 27.2 and 33.3, 16 / 4 of 100, 11 x 32 x 9 (25 MB) 7.9 and 8.5, 8 / 2 of 112, 14 x 39 x 3 (10 MB) 7.8 and 7.8; above, 4 of 112, 28 x 12,184
+// (1.2 GB) 247 and 256, 32 / 8 of 40, 25 x 28 x 24 x 8 (1.1 GB) 217 and 250.  In 64-wide tiles cached rows are level or ahead on one tile and where a group shares
+// the value input too (8 / 2 heads of 40, 1,765 x 37 x 3 135 and 145).
 FwdRows narrow_rows(const HopParams& p, int KT) {
     const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (2.0 * p.Hq + p.Hkv + p.vin_heads);
-    return p.D > 64 || (KT == 2 && p.vin_heads == p.Hq && bytes >= 282e6 && bytes < 390e6) ? kNarrowStreamed : kNarrow;
+    if (p.D > 64) return bytes < 16e6 || (bytes >= 282e6 && bytes < 480e6) ? kNarrowStreamed : kNarrow;
+    return KT == 2 && p.vin_heads == p.Hq && bytes >= 282e6 && bytes < 390e6 ? kNarrowStreamed : kNarrow;
 }
 
 template <int D, int KT, FwdRows ROWS>
@@ -706,9 +738,10 @@ template <int KT>
 hipError_t launch_width(const HopParams& p, const TileParams& tp, hipStream_t s) {
     if (p.D == 128) return launch_heads<128, KT, kWhole>(p, tp, s);
     if (p.D == 64) return launch_heads<64, KT, kWhole>(p, tp, s);
-    if (p.D > 64) return launch_heads<128, KT, kNarrowStreamed>(p, tp, s);
+    const FwdRows rows = narrow_rows(p, KT);
+    if (p.D > 64) return rows == kNarrow ? launch_heads<128, KT, kNarrow>(p, tp, s) : launch_heads<128, KT, kNarrowStreamed>(p, tp, s);
     if constexpr (KT == 2) {
-        if (narrow_rows(p, KT) == kNarrowStreamed) return launch_heads<64, KT, kNarrowStreamed>(p, tp, s);
+        if (rows == kNarrowStreamed) return launch_heads<64, KT, kNarrowStreamed>(p, tp, s);
     }
     return launch_heads<64, KT, kNarrow>(p, tp, s);
 }

@@ -1,0 +1,39 @@
+"""Rows narrower than their tile, by where they start: whole 16-byte units on 16-byte boundaries, 8 bytes into one for every other head, or for every
+other token (an odd number of heads of 100).  A head among others gives the bits of that head alone, forward and backward, on one tile, two, and three,
+in grids of every remainder by eight; the oracle is met by the other tests of these kernels."""
+import pytest
+import torch
+
+import paper_2410_20926_amd as ta
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [8, 12, 36, 40, 60, 68, 96, 100, 124])
+@pytest.mark.parametrize("n,fibres,B,H,Hkv", [
+    (32, 5, 2, 3, 3),                                      # one tile: 15 workgroups per sequence, rows 8 bytes off on every other token where D % 8 = 4
+    (9, 41, 1, 8, 8),                                      # three fibres per tile, the last tile not full; two heads per workgroup in the backward's pairs
+    (31, 37, 2, 8, 2),                                     # a group of four
+    (33, 3, 1, 4, 4),                                      # two tiles, the second of one row
+    (64, 2, 2, 5, 1),                                      # a group of five
+    (96, 3, 1, 8, 2),
+    (200, 2, 1, 4, 2),
+])
+def test_a_head_among_others_gives_the_bits_of_the_head_alone(D, n, fibres, B, H, Hkv):
+    gen, N, G = torch.Generator(device="cuda").manual_seed(100 * D + n), n * fibres, H // Hkv
+    q, x, g = (torch.randn((B, N, H, D), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    k = torch.randn((B, N, Hkv, D), generator=gen, device="cuda").bfloat16()
+    for dims, axis in (((n, fibres), 0), ((fibres, n), 1)):
+        def hops(q, k, x, g):
+            plan = ta.ta_plan_create(B, q.shape[2], k.shape[2], D, dims, ta.TA_BF16, True)
+            o, (dq, dk, dx) = torch.full_like(q, float("nan")), (torch.full_like(t, 0.5) for t in (q, k, x))
+            ta.ta_axis_attn_forward(plan, axis, q, k, x, ta.TA_VIN_O, o)
+            for accumulate in (False, True):
+                ta.ta_axis_attn_backward(plan, axis, q, k, x, ta.TA_VIN_O, g, dx, dq, dk, accumulate)
+            return o, dq, dx, dk
+        whole = hops(q, k, x, g)
+        assert all(torch.isfinite(t).all() for t in whole)
+        for j in {0, Hkv // 2, Hkv - 1}:
+            heads = slice(j * G, (j + 1) * G)
+            part = hops(*(t.contiguous() for t in (q[:, :, heads], k[:, :, j:j + 1], x[:, :, heads], g[:, :, heads])))
+            assert all(torch.equal(t[:, :, heads], y) for t, y in zip(whole[:3], part)) and torch.equal(whole[3][:, :, j:j + 1], part[3]), (dims, j)
