@@ -371,11 +371,13 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_stream_kernel(BwdParams bp, S
     // rows 32 t + .. of the fibre (clamped to the last one: padding rows of the last tile are
     // masked in the softmax and never stored)
     auto gather = [&](const char* base, uint32_t pitch, int t, u32x4 (&raw)[G::kPasses]) {
+        uint32_t mis = 0u;
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
             const uint32_t rr = (uint32_t)min(kTile * t + i * G::kRowsPerPass + lrow, n - 1);
-            raw[i] = gather_chunk<NARROW, false>(base, (tok0 + rr * stride) * pitch, lbyte, dbytes);
+            raw[i] = gather_noted<NARROW, false>(base, (tok0 + rr * stride) * pitch, lbyte, dbytes, i, mis);
         }
+        gather_ready_all<NARROW>(raw, mis, base, pitch, lbyte, dbytes);
     };
     // rotary encoding: every gathered Q or K tile is turned, row by row, by its position on the axis
     float rev[4];

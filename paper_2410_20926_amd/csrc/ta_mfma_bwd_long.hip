@@ -79,11 +79,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     // rows of tile t as operands contracted over the features, through this wave's transit tile
     auto own = [&](const char* base, uint32_t pitch, int t, bool turn, u32x4 (&op)[G::kKSteps]) {
         u32x4 raw[G::kPasses];
+        uint32_t mis = 0u;
 #pragma unroll
-        for (int i = 0; i < G::kPasses; ++i) {
-            const int r = min(kTile * t + i * G::kRowsPerPass + lrow, n - 1);
-            raw[i] = gather_chunk<NARROW, false>(base, (tok0 + (uint32_t)r * stride) * pitch, lbyte, dbytes);
-            if (ROPE && turn) raw[i] = rope_chunk(raw[i], (float)r, rev);
+        for (int i = 0; i < G::kPasses; ++i)
+            raw[i] = gather_noted<NARROW, false>(base, (tok0 + (uint32_t)min(kTile * t + i * G::kRowsPerPass + lrow, n - 1) * stride) * pitch, lbyte, dbytes, i, mis);
+        gather_ready_all<NARROW>(raw, mis, base, pitch, lbyte, dbytes);
+        if (ROPE && turn) {
+#pragma unroll
+            for (int i = 0; i < G::kPasses; ++i) raw[i] = rope_chunk(raw[i], (float)min(kTile * t + i * G::kRowsPerPass + lrow, n - 1), rev);
         }
         lds_wave_sync();
         stage_rows<D>(transit + lrow * G::kPitch + lbyte, raw);

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     };
     // This wave's half of tile w (rows past the fibre's end: its last row, masked in the softmax and never stored).
     // `once`: nobody asks for these rows again (K and a per-group value input are asked for by every head).
-    // The rows are only requested here; `ready` turns what has come into this lane's chunks (see gather_chunk: NARROW rows start
+    // The rows are only requested here; `ready` turns what has come into this lane's chunks (see gather_request: NARROW rows start
     // 8 bytes into an aligned unit or on one, `mis` has a bit per row).
     enum : int { kRawQ, kRawG, kRawX, kRawK };
     struct Raw { u32x4 v[kMine]; };

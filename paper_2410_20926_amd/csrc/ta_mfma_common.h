@@ -59,38 +59,6 @@ __device__ inline u32x4 load_chunk(const char* base, uint32_t rowoff, uint32_t l
         return v;
     }
 }
-// The same chunk for the row gathers, where the lanes of a row are consecutive lanes that hold consecutive chunks of
-// the whole tile row (chunk = lane % 8 or lane % 16) and every lane of the wave takes part.  NARROW rows start on a
-// multiple of 8 bytes; strided 8-byte halves (load_chunk) ask for every cache line twice and reach 3.5 TB/s in a plain
-// streaming kernel on 200-byte rows, 16-byte requests on 16-byte boundaries 4.65 TB/s.  So a lane asks for the aligned
-// 16 bytes that start at or 8 bytes before its chunk (those 8 bytes lie inside the tensor's span: the tensor itself
-// starts on a 16-byte boundary), never for bytes past the end of the row, and a row that starts 8 bytes into an
-// aligned unit takes the second half of each chunk from the next lane.  Rows are at least 16 bytes long.
-template <bool NARROW, bool NT>
-__device__ inline u32x4 gather_chunk(const char* base, uint32_t rowoff, uint32_t lbyte, uint32_t dbytes) {
-    if constexpr (!NARROW) {
-        return load_chunk<false, NT>(base, rowoff, lbyte, dbytes);
-    } else {
-        const char* row = base + rowoff;
-        const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(row) & 8u);
-        const int32_t s = (int32_t)lbyte - (int32_t)mis;           // where this lane's aligned unit starts, relative to the row
-        // One 16-byte request per lane and no branch (a branch per chunk would make every request wait for the one
-        // before): a unit that would pass the end of the row is replaced by the row's last 16 bytes, whose second
-        // half is the unit's first (the row's length is a multiple of 8, so exactly 8 bytes of the unit are inside).
-        const bool full = s + 16 <= (int32_t)dbytes, tail = !full && s + 8 <= (int32_t)dbytes;
-        const u32x4* src = reinterpret_cast<const u32x4*>(row + (full ? s : (int32_t)dbytes - 16));
-        u32x4 a = NT ? __builtin_nontemporal_load(src) : *src;
-        if (tail) a = u32x4{a.z, a.w, 0u, 0u};
-        if (!full && !tail) a = u32x4{0u, 0u, 0u, 0u};
-        // lane i takes the first half of lane i + 1's unit (row_shl:1 within 16 lanes; nothing comes in at the end)
-        const uint32_t nx = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a.x, 0x101, 0xf, 0xf, true);
-        const uint32_t ny = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a.y, 0x101, 0xf, 0xf, true);
-        u32x4 out = mis ? u32x4{a.z, a.w, nx, ny} : a;
-        if (lbyte + 8 > dbytes) { out.x = 0u; out.y = 0u; }
-        if (lbyte + 16 > dbytes) { out.z = 0u; out.w = 0u; }
-        return out;
-    }
-}
 // What lies outside the row reads as zero.
 __device__ inline u32x4 row_only(u32x4 a, uint32_t lbyte, uint32_t dbytes) {
     if (lbyte + 8 > dbytes) { a.x = 0u; a.y = 0u; }
@@ -101,7 +69,15 @@ __device__ inline u32x4 row_only(u32x4 a, uint32_t lbyte, uint32_t dbytes) {
 __device__ inline bool whole_units(const char* base, uint32_t pitch, uint32_t dbytes) {
     return (((uint32_t)reinterpret_cast<uintptr_t>(base) | pitch | dbytes) & 15u) == 0u;
 }
-// The same in two parts: the request, and what is done with the bytes when they have come.  In one piece the first row's bytes are waited for before
+// The chunk for the row gathers, where the lanes of a row are consecutive lanes that hold consecutive chunks of
+// the whole tile row (chunk = lane % 8 or lane % 16) and every lane of the wave takes part.  NARROW rows start on a
+// multiple of 8 bytes; strided 8-byte halves (load_chunk) ask for every cache line twice and reach 3.5 TB/s in a plain
+// streaming kernel on 200-byte rows, 16-byte requests on 16-byte boundaries 4.65 TB/s.  So a lane asks for the aligned
+// 16 bytes that start at or 8 bytes before its chunk (those 8 bytes lie inside the tensor's span: the tensor itself
+// starts on a 16-byte boundary), never for bytes past the end of the row (a unit that would pass it is replaced by the row's last 16
+// bytes; rows are at least that long), and a row that starts 8 bytes into an
+// aligned unit takes the second half of each chunk from the next lane.
+// Two parts, the request and what is done with the bytes when they have come.  In one piece the first row's bytes are waited for before
 // the last rows are requested (the compiler shares the registers of the halves that are put together), so that the four tiles of the one-tile
 // backward waited for memory five times one after the other, and the two of the two-tile forward twice.  In two parts (32 / 8 heads of 96, 32 x 32 x 32, the
 // backward hop along the second axis 338 -> 276 us, forward 122 -> 104; 12 heads of 96, 134 x 57 x 8, forward 196 -> 124; 8 / 2 heads of 96, 4 x 3 x 6 x 5 x 3,
@@ -131,6 +107,14 @@ __device__ inline u32x4 gather_ready(const u32x4 a, uint32_t mis, uint32_t lbyte
         const uint32_t ny = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x101, 0xf, 0xf, true);
         return row_only(mis ? u32x4{a.z, a.w, nx, ny} : u32x4{x, y, a.z, a.w}, lbyte, dbytes);
     }
+}
+// gather_request that notes its `mis` as bit `at` of `bits`.
+template <bool NARROW, bool NT>
+__device__ inline u32x4 gather_noted(const char* base, uint32_t rowoff, uint32_t lbyte, uint32_t dbytes, int at, uint32_t& bits) {
+    uint32_t mis;
+    const u32x4 v = gather_request<NARROW, NT>(base, rowoff, lbyte, dbytes, mis);
+    if constexpr (NARROW) bits |= (mis >> 3) << at;
+    return v;
 }
 // A tensor's requested chunks made ready; `mis` has a bit per request.
 template <bool NARROW, int N>

@@ -176,11 +176,14 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
     {
         char* own = smem + w * (kTile * G::kPitch);
         u32x4 q[G::kPasses];
+        uint32_t mis = 0u;
 #pragma unroll
-        for (int i = 0; i < G::kPasses; ++i) {
-            const int r = min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1);
-            q[i] = gather_chunk<NARROW, true>(qbase, (tok0 + (uint32_t)r * stride) * lp.q_row, lbyte, dbytes);
-            if constexpr (ROPE) q[i] = rope_chunk(q[i], (float)r, rev);
+        for (int i = 0; i < G::kPasses; ++i)
+            q[i] = gather_noted<NARROW, true>(qbase, (tok0 + (uint32_t)min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1) * stride) * lp.q_row, lbyte, dbytes, i, mis);
+        gather_ready_all<NARROW>(q, mis, qbase, lp.q_row, lbyte, dbytes);
+        if constexpr (ROPE) {
+#pragma unroll
+            for (int i = 0; i < G::kPasses; ++i) q[i] = rope_chunk(q[i], (float)min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1), rev);
         }
         stage_rows<D>(own + lrow * G::kPitch + lbyte, q);
         lds_wave_sync();

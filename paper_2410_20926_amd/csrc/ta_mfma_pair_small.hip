@@ -99,21 +99,24 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_fwd_pair_small_kernel(Hop
         u32x4 q1[G::kPasses], k1[G::kPasses], x1[G::kPasses], q2[G::kPasses], k2[G::kPasses];
         const int c1 = rows1(min(t, sp.t1 - 1)), c2 = rows2(min(t, sp.t2 - 1));   // a wave with a tile of one kind only works on the other kind's last one too and keeps nothing of it
         const int ta = min(t, sp.t1 - 1), tb = min(t, sp.t2 - 1);
+        uint32_t mq1 = 0u, mk1 = 0u, mx1 = 0u, mq2 = 0u, mk2 = 0u;   // NARROW: a bit per request, see gather_request
 #pragma unroll
         for (int j = 0; j < G::kPasses; ++j) {
             const uint32_t tok = tok0 + (uint32_t)row1(ta, min(j * G::kRowsPerPass + lrow, c1 - 1));
-            q1[j] = gather_chunk<NARROW, false>(qb, tok * sp.q_row, lbyte, dbytes);
-            k1[j] = gather_chunk<NARROW, false>(kb, tok * sp.k_row, lbyte, dbytes);
-            x1[j] = gather_chunk<NARROW, false>(xb, tok * sp.v_row, lbyte, dbytes);
+            q1[j] = gather_noted<NARROW, false>(qb, tok * sp.q_row, lbyte, dbytes, j, mq1);
+            k1[j] = gather_noted<NARROW, false>(kb, tok * sp.k_row, lbyte, dbytes, j, mk1);
+            x1[j] = gather_noted<NARROW, false>(xb, tok * sp.v_row, lbyte, dbytes, j, mx1);
         }
 #pragma unroll
         for (int j = 0; j < G::kPasses; ++j) {
             const uint32_t tok = tok0 + (uint32_t)row2(tb, min(j * G::kRowsPerPass + lrow, c2 - 1));
-            q2[j] = gather_chunk<NARROW, false>(qb, tok * sp.q_row, lbyte, dbytes);
-            k2[j] = gather_chunk<NARROW, false>(kb, tok * sp.k_row, lbyte, dbytes);
+            q2[j] = gather_noted<NARROW, false>(qb, tok * sp.q_row, lbyte, dbytes, j, mq2);
+            k2[j] = gather_noted<NARROW, false>(kb, tok * sp.k_row, lbyte, dbytes, j, mk2);
         }
         __builtin_amdgcn_sched_barrier(0);
-        auto scores = [&](u32x4 (&q)[G::kPasses], u32x4 (&k)[G::kPasses], int n, int count) {
+        auto scores = [&](u32x4 (&q)[G::kPasses], u32x4 (&k)[G::kPasses], uint32_t mq, uint32_t mk, int n, int count) {
+            gather_ready_all<NARROW>(q, mq, qb, sp.q_row, lbyte, dbytes);
+            gather_ready_all<NARROW>(k, mk, kb, sp.k_row, lbyte, dbytes);
             if constexpr (ROPE) {
 #pragma unroll
                 for (int j = 0; j < G::kPasses; ++j) {
@@ -138,8 +141,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_fwd_pair_small_kernel(Hop
         // column tile: scores, weights, P1 X
         u32x4 pop[2];
         const int fa = r32 / n1, aa = r32 - fa * n1;
-        const f32x16 s1 = scores(q1, k1, n1, c1);
+        const f32x16 s1 = scores(q1, k1, mq1, mk1, n1, c1);
         const float inv1 = softmax(s1, visible(h1, fa, aa, c1 / n1, tok0 + (uint32_t)(ta * sp.fpt1 + fa), (int64_t)slab * n2 + ta * sp.fpt1 + fa), pop);
+        gather_ready_all<NARROW>(x1, mx1, xb, sp.v_row, lbyte, dbytes);
         lds_wave_sync();
         stage_rows<D>(stg, x1);
         lds_wave_sync();
@@ -157,7 +161,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_fwd_pair_small_kernel(Hop
         }
         // row tile: scores, weights
         const int fb = r32 / n2, ab = r32 - fb * n2;
-        const f32x16 s2t = scores(q2, k2, n2, c2);
+        const f32x16 s2t = scores(q2, k2, mq2, mk2, n2, c2);
         inv2[i] = softmax(s2t, visible(h2, fb, ab, c2 / n2, tok0 + (uint32_t)((tb * sp.fpt2 + fb) * n2), (int64_t)slab * n1 + tb * sp.fpt2 + fb), p2[i]);
     }
     __syncthreads();                                      // the transit tiles are done with: the slab takes their place

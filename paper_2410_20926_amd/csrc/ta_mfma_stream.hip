@@ -79,6 +79,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_shared
     // memory latency that one step of compute does not.
     u32x4 qreg[G::kPasses];
     u32x4 kp[3][kMine], vp[3][kMine];
+    uint32_t kmis[3] = {}, vmis[3] = {}, qmis = 0u;       // NARROW: a bit per request, see gather_request
     uint32_t ooff[G::kPasses];
     // `set` is the same in every lane; the unrolled comparison turns it into scalar branches
     // around code with fixed register names (no indexed registers)
@@ -86,11 +87,12 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_shared
 #pragma unroll
         for (int sidx = 0; sidx < 3; ++sidx)
             if (set == sidx) {
+                kmis[sidx] = vmis[sidx] = 0u;
 #pragma unroll
                 for (int i = 0; i < kMine; ++i) {
                     const uint32_t rk = (uint32_t)min(j * kTile + (w * kMine + i) * G::kRowsPerPass + lrow, n - 1);
-                    kp[sidx][i] = gather_chunk<NARROW, false>(kb, rk * sp.k_step, lbyte, dbytes);
-                    vp[sidx][i] = gather_chunk<NARROW, false>(vb, rk * sp.v_step, lbyte, dbytes);
+                    kp[sidx][i] = gather_noted<NARROW, false>(kb, rk * sp.k_step, lbyte, dbytes, i, kmis[sidx]);
+                    vp[sidx][i] = gather_noted<NARROW, false>(vb, rk * sp.v_step, lbyte, dbytes, i, vmis[sidx]);
                 }
             }
     };
@@ -100,6 +102,8 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_shared
 #pragma unroll
         for (int sidx = 0; sidx < 3; ++sidx)
             if (set == sidx) {
+                gather_ready_all<NARROW>(kp[sidx], kmis[sidx], kb, sp.k_step, lbyte, dbytes);
+                gather_ready_all<NARROW>(vp[sidx], vmis[sidx], vb, sp.v_step, lbyte, dbytes);
 #pragma unroll
                 for (int i = 0; i < kMine; ++i) {
                     const uint32_t at = (uint32_t)(slot * kBuf + ((w * kMine + i) * G::kRowsPerPass + lrow) * G::kPitch) + lbyte;
@@ -112,7 +116,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_shared
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const uint32_t rq = (uint32_t)min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1);
-        qreg[i] = gather_chunk<NARROW, true>(qb, rq * sp.q_step, lbyte, dbytes);
+        qreg[i] = gather_noted<NARROW, true>(qb, rq * sp.q_step, lbyte, dbytes, i, qmis);
         ooff[i] = rq * sp.o_step + lbyte;
     }
     load_shared(0, jbeg);
@@ -124,6 +128,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_shared
     const uint32_t oprd = (uint32_t)(r32 * G::kPitch + hf * 16);
     const uint32_t troff = (uint32_t)((4 * hf + ((lane & 15) >> 2)) * G::kPitch + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2);
 
+    gather_ready_all<NARROW>(qreg, qmis, qb, sp.q_step, lbyte, dbytes);
     if (p.rope) {
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) qreg[i] = rope_chunk(qreg[i], (float)min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1), rev);
@@ -280,19 +285,24 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_chunke
     // of step t in set t % 3).
     u32x4 qreg[G::kPasses], vreg[VS ? 1 : G::kPasses];
     u32x4 kp[3][kMine], vp[3][VS ? kMine : 1];
+    uint32_t kmis[3] = {}, vmis[3] = {}, qmis = 0u;       // NARROW: a bit per request, see gather_request (a per-head value tile: vmis[0])
     auto load_shared = [&](auto set_tag, int j) {
         constexpr int set = decltype(set_tag)::value;
+        kmis[set] = 0u;
+        if (VS) vmis[set] = 0u;
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
             const uint32_t rk = (uint32_t)min(j * kTile + (w * kMine + i) * G::kRowsPerPass + lrow, n - 1);
-            kp[set][i] = gather_chunk<NARROW, false>(kb, rk * sp.k_step, lbyte, dbytes);
-            if (VS) vp[set][i] = gather_chunk<NARROW, false>(vb, rk * sp.v_step, lbyte, dbytes);
+            kp[set][i] = gather_noted<NARROW, false>(kb, rk * sp.k_step, lbyte, dbytes, i, kmis[set]);
+            if (VS) vp[set][i] = gather_noted<NARROW, false>(vb, rk * sp.v_step, lbyte, dbytes, i, vmis[set]);
         }
     };
     float rev[4];                                         // rotary encoding: turn rates of this lane's four feature pairs
     if (p.rope) rope_rates(p, lcol, rev);
     auto write_shared = [&](auto set_tag, int slot, int j) {   // j: the key tile the registers hold (its rows' positions, for the encoding)
         constexpr int set = decltype(set_tag)::value;
+        gather_ready_all<NARROW>(kp[set], kmis[set], kb, sp.k_step, lbyte, dbytes);
+        if constexpr (VS) gather_ready_all<NARROW>(vp[set], vmis[set], vb, sp.v_step, lbyte, dbytes);
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
             const uint32_t at = (uint32_t)(slot * kBuf + ((w * kMine + i) * G::kRowsPerPass + lrow) * G::kPitch) + lbyte;
@@ -302,17 +312,19 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_chunke
         }
     };
     auto load_own_v = [&](int j) {                        // a per-head value tile is this wave's alone
+        if (!VS) vmis[0] = 0u;
 #pragma unroll
         for (int i = 0; i < (VS ? 0 : G::kPasses); ++i) {
             const uint32_t rk = (uint32_t)min(j * kTile + i * G::kRowsPerPass + lrow, n - 1);
-            vreg[i] = gather_chunk<NARROW, false>(vb, rk * sp.v_step, lbyte, dbytes);
+            vreg[i] = gather_noted<NARROW, false>(vb, rk * sp.v_step, lbyte, dbytes, i, vmis[0]);
         }
     };
     auto load_q = [&](int qt) {
+        qmis = 0u;
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i) {
             const uint32_t rq = (uint32_t)min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1);
-            qreg[i] = gather_chunk<NARROW, true>(qb, rq * sp.q_step, lbyte, dbytes);
+            qreg[i] = gather_noted<NARROW, true>(qb, rq * sp.q_step, lbyte, dbytes, i, qmis);
         }
     };
     using S0 = std::integral_constant<int, 0>;
@@ -358,6 +370,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_chunke
             first_of_tile = false;
             // first step of a query tile: its rows become the B operand, the next query tile's rows are requested
             lds_wave_sync();
+            gather_ready_all<NARROW>(qreg, qmis, qb, sp.q_step, lbyte, dbytes);
             if (p.rope) {
 #pragma unroll
                 for (int i = 0; i < G::kPasses; ++i) qreg[i] = rope_chunk(qreg[i], (float)min(qt * kTile + i * G::kRowsPerPass + lrow, n - 1), rev);
@@ -398,6 +411,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_stream_chunke
         if constexpr (VS) {
             read_transposed<D>(sV + slot * kBuf + troff, vT);
         } else {
+            gather_ready_all<NARROW>(vreg, vmis[0], vb, sp.v_step, lbyte, dbytes);
             stage_rows<D>(stg, vreg);
             lds_wave_sync();
             read_transposed<D>(buf + troff, vT);

@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (64, 2, 2, 5, 1),                                      # a group of five
     (96, 3, 1, 8, 2),
     (200, 2, 1, 4, 2),
+    (70, 5, 1, 8, 2),                                      # the streaming forward of groups of four, all query tiles of a fibre in one workgroup
+    (190, 3, 1, 4, 1),                                     # and one per workgroup, on the first hop
 ])
 def test_a_head_among_others_gives_the_bits_of_the_head_alone(D, n, fibres, B, H, Hkv):
     gen, N, G = torch.Generator(device="cuda").manual_seed(100 * D + n), n * fibres, H // Hkv
@@ -26,14 +28,34 @@ def test_a_head_among_others_gives_the_bits_of_the_head_alone(D, n, fibres, B, H
     for dims, axis in (((n, fibres), 0), ((fibres, n), 1)):
         def hops(q, k, x, g):
             plan = ta.ta_plan_create(B, q.shape[2], k.shape[2], D, dims, ta.TA_BF16, True)
-            o, (dq, dk, dx) = torch.full_like(q, float("nan")), (torch.full_like(t, 0.5) for t in (q, k, x))
+            o, o1, (dq, dk, dx) = torch.full_like(q, float("nan")), torch.full_like(q, float("nan")), (torch.full_like(t, 0.5) for t in (q, k, x))
             ta.ta_axis_attn_forward(plan, axis, q, k, x, ta.TA_VIN_O, o)
+            ta.ta_axis_attn_forward(plan, axis, q, k, k, ta.TA_VIN_KV, o1)
             for accumulate in (False, True):
                 ta.ta_axis_attn_backward(plan, axis, q, k, x, ta.TA_VIN_O, g, dx, dq, dk, accumulate)
-            return o, dq, dx, dk
+            return torch.stack((o, o1)), dq, dx, dk
         whole = hops(q, k, x, g)
         assert all(torch.isfinite(t).all() for t in whole)
         for j in {0, Hkv // 2, Hkv - 1}:
             heads = slice(j * G, (j + 1) * G)
             part = hops(*(t.contiguous() for t in (q[:, :, heads], k[:, :, j:j + 1], x[:, :, heads], g[:, :, heads])))
-            assert all(torch.equal(t[:, :, heads], y) for t, y in zip(whole[:3], part)) and torch.equal(whole[3][:, :, j:j + 1], part[3]), (dims, j)
+            assert all(torch.equal(t[..., heads, :], y) for t, y in zip(whole[:3], part)) and torch.equal(whole[3][:, :, j:j + 1], part[3]), (dims, j)
+
+
+@pytest.mark.parametrize("D", [12, 40, 60])
+@pytest.mark.parametrize("dims,H,Hkv", [((3, 12, 7), 3, 3), ((2, 16, 8), 8, 2), ((2, 28, 4), 5, 5)])
+def test_small_slabs_give_the_bits_of_their_heads_alone(D, dims, H, Hkv):
+    gen, N, G = torch.Generator(device="cuda").manual_seed(D + H), dims[0] * dims[1] * dims[2], H // Hkv
+    q = torch.randn((2, N, H, D), generator=gen, device="cuda").bfloat16()
+    k, v = (torch.randn((2, N, Hkv, D), generator=gen, device="cuda").bfloat16() for _ in range(2))
+
+    def forward(q, k, v):
+        plan = ta.ta_plan_create(2, q.shape[2], k.shape[2], D, dims, ta.TA_BF16, True)
+        assert plan.small_pair_position() == 1
+        o, ws = torch.full_like(q, float("nan")), torch.empty(max(plan.workspace_bytes(False), 256), dtype=torch.uint8, device="cuda")
+        ta.ta_multihop_forward(plan, q, k, v, o, ws, plan.workspace_bytes(False))
+        return o
+    whole = forward(q, k, v)
+    assert torch.isfinite(whole).all()
+    for j in range(Hkv):
+        assert torch.equal(whole[:, :, j * G:(j + 1) * G], forward(*(t.contiguous() for t in (q[:, :, j * G:(j + 1) * G], k[:, :, j:j + 1], v[:, :, j:j + 1]))))
