@@ -194,6 +194,7 @@ struct StreamBwdParams {
     uint32_t q_row, k_row, v_row, o_row;   // token pitch in bytes of Q/dQ, K/dK, the value input and its gradient, dO
     uint32_t fibres_lo, fibres_hi;         // gridDim.y; gridDim.z = B * fibres_hi
     int32_t tiles;                         // ceil(n / 32)
+    int32_t parts;                         // the long kernel: workgroups per fibre and key/value head (see parts_of)
 };
 
 // Keys 32 c .. 32 c + 31 that query row qr of the fibre may attend (bit = key), and query

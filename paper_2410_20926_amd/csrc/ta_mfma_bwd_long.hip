@@ -10,11 +10,16 @@
 //                (running max, sum, sum of P o dP), then again for dS^T and dQ^T = K^T dS^T;
 //   key side, per eight key tiles:   the heads' Q and dO stream once: S and dP with a key per lane, dX^T += dO^T P and
 //                dK^T += Q^T dS, summed over the heads in registers.
+// A call of few fibres, which would leave most of the chip idle, goes in parts: the query side of eight tiles of a head and the key side of eight tiles are
+// workgroups of their own, the latter with the statistics once more (parts_of).
 // What bounds it: the chain of one wave's step (two score products, softmax arithmetic, two contractions, twice per block), with two waves
 // per SIMD; five tiles leave three waves idle.  The blocked kernel gathers a tile per wave and visit and waits for it.  Backward hops,
-// width 128 causal: 8 heads of 1,024 x 16 2,790 -> 427 us, 32 / 8 heads of 256 x 128 1,150 -> 794 us, of 200 x 64 513 -> 440 us; width 64: 8 heads
-// of 512 x 64 622 -> 177 us.
+// width 128 causal: 8 heads of 1,024 x 16 2,790 -> 416 us, 32 / 8 heads of 256 x 128 1,150 -> 776 us, of 200 x 64 513 -> 386 us (along the first axis, a value input per head; 424 while what
+// depends on the lane was kept in registers and the key side spilled 52); width 64: 8 heads
+// of 512 x 64 622 -> 161 us.
 #include "ta_mfma_bwd_common.h"
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace ta {
@@ -32,8 +37,9 @@ struct LongGeo {
     static constexpr int kFixed = kStream + kWaves * kTile * 16;
 };
 
-// NARROW: the head is narrower than the D-wide tile; see load_chunk.  VS: the value input is per key/value head.
-template <int D, bool VS, bool NARROW, bool ROPE>
+// NARROW: the head is narrower than the D-wide tile; see load_chunk.  VS: the value input is per key/value head.  PARTS: a workgroup is a part of that (parts_of;
+// instantiated on its own, since the bounds of a part cost the whole 2 to 4 per cent).
+template <int D, bool VS, bool NARROW, bool ROPE, bool PARTS>
 __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams bp, StreamBwdParams sp) {
     using G = BGeo<D>;
     using L = LongGeo<D>;
@@ -46,8 +52,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     uint32_t bx, by;
     workgroup_xy<NARROW>(bx, by);
     const int g = (int)bx;
-    const uint32_t zb = blockIdx.z / sp.fibres_hi;
-    const int64_t f = (int64_t)(blockIdx.z - zb * sp.fibres_hi) * sp.fibres_lo + by;
+    const uint32_t zp = blockIdx.z / sp.fibres_hi;        // the longest parts of every fibre first
+    const int part = PARTS ? (int)(zp / (uint32_t)p.B) : 0;
+    const uint32_t zb = zp - (uint32_t)part * (uint32_t)p.B;
+    const int64_t f = (int64_t)(blockIdx.z - zp * sp.fibres_hi) * sp.fibres_lo + by;
     if (f >= p.fibres) return;                            // whole workgroup leaves together
     const int b = (int)zb;
     const int n = p.n, T = sp.tiles;
@@ -59,39 +67,37 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     u32x4* rowoff = reinterpret_cast<u32x4*>(smem + L::kStream) + w * kTile;
     float* stats = reinterpret_cast<float*>(smem + L::kFixed);   // [head][tile][max | 1 / sum | delta][32]
 
-    const int lrow = lane / G::kChunks, lcol = lane % G::kChunks;
-    const uint32_t lbyte = lcol * 16;
     const uint32_t dbytes = (uint32_t)p.D * 2;
-    const int r32 = lane & 31, hf = lane >> 5;
-    const uint32_t nat = (uint32_t)(r32 * G::kPitch + hf * 16);
-    const uint32_t trn = (uint32_t)((4 * hf + ((lane & 15) >> 2)) * G::kPitch + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2);
     const float sl2 = p.scale * kLog2e;
-    float rev[4];
-    if constexpr (ROPE) rope_rates(p, lcol, rev);
 
-    // A value that is formed again where it is used: kept over the loops below it would be spilled, and a reload waits for the
+    // What depends on the lane is formed again where it is used: kept over the loops below it would be spilled, and a reload waits for the
     // blocks requested before it.
     auto again = [](int x) {
         if (D == 128) asm volatile("" : "+v"(x));
         return x;
     };
+    auto chunk_byte = [&]() { return (uint32_t)(again(lane) % G::kChunks) * 16u; };
     auto slice = [&](const Tensor& t, int head) { return reinterpret_cast<char*>(t.p) + ((int64_t)b * t.sb + (int64_t)head * t.sh) * 2; };
     // rows of tile t as operands contracted over the features, through this wave's transit tile
     auto own = [&](const char* base, uint32_t pitch, int t, bool turn, u32x4 (&op)[G::kKSteps]) {
         u32x4 raw[G::kPasses];
         uint32_t mis = 0u;
+        const int lane_ = again(lane), lrow = lane_ / G::kChunks, r32 = lane_ & 31, hf = lane_ >> 5;
+        const uint32_t lbyte = (uint32_t)(lane_ % G::kChunks) * 16u;
 #pragma unroll
         for (int i = 0; i < G::kPasses; ++i)
             raw[i] = gather_noted<NARROW, false>(base, (tok0 + (uint32_t)min(kTile * t + i * G::kRowsPerPass + lrow, n - 1) * stride) * pitch, lbyte, dbytes, i, mis);
         gather_ready_all<NARROW>(raw, mis, base, pitch, lbyte, dbytes);
         if (ROPE && turn) {
+            float rev[4];
+            rope_rates(p, lane_ % G::kChunks, rev);
 #pragma unroll
             for (int i = 0; i < G::kPasses; ++i) raw[i] = rope_chunk(raw[i], (float)min(kTile * t + i * G::kRowsPerPass + lrow, n - 1), rev);
         }
         lds_wave_sync();
         stage_rows<D>(transit + lrow * G::kPitch + lbyte, raw);
         lds_wave_sync();
-        read_natural<D>(transit + nat, op);
+        read_natural<D>(transit + r32 * G::kPitch + hf * 16, op);
     };
     auto set_rowoff = [&](int t) {
         lds_wave_sync();
@@ -110,6 +116,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     Raw ra, rc;
     auto request = [&](const char* base, uint32_t pitch, int j, Raw& raw) {
         const int myrow = w * G::kRowsPerPass + again(lane) / G::kChunks;
+        const uint32_t lbyte = chunk_byte();
         raw.mis = 0u;
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
@@ -126,6 +133,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     auto stream = [&](const Two& t, auto work) {
         auto write = [&](char* block, int j, const Raw& raw, bool turn) {
             const int myrow = w * G::kRowsPerPass + again(lane) / G::kChunks;
+            const uint32_t lbyte = chunk_byte();
+            float rev[4];
+            if (ROPE && turn) rope_rates(p, (int)lbyte / 16, rev);
 #pragma unroll
             for (int i = 0; i < kMine; ++i) {
                 u32x4 x = gather_ready<NARROW>(raw.v[i], (raw.mis >> i) & 1u, lbyte, dbytes);
@@ -155,26 +165,28 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     };
     auto scores = [&](const char* tile, const u32x4 (&op)[G::kKSteps]) {
         f32x16 x = {};
+        const int l = again(lane);
+        const char* at = tile + (l & 31) * G::kPitch + (l >> 5) * 16;
 #pragma unroll
-        for (int s = 0; s < G::kKSteps; ++s) {
-            x = mma(*reinterpret_cast<const u32x4*>(tile + nat + 32 * s), op[s], x);
-        }
+        for (int s = 0; s < G::kKSteps; ++s) x = mma(*reinterpret_cast<const u32x4*>(at + 32 * s), op[s], x);
         return x;
     };
     // scores that the lane's row (key) does not see become -inf; blocks that all of them see whole are left alone
     auto hide = [&](f32x16& st, uint32_t vis) {
         if (__all(vis == 0xffffffffu)) return;
-        vis >>= 4 * hf;
+        vis >>= 4 * (again(lane) >> 5);
 #pragma unroll
         for (int r = 0; r < 16; ++r) st[r] = ((vis >> (8 * (r / 4) + (r % 4))) & 1u) ? st[r] : -INFINITY;
     };
     // acc^T += (tile)^T w, contracted over the tile's rows
     auto contract = [&](const char* tile, const u32x4 (&wt)[2], f32x16 (&acc)[G::kDTiles]) {
+        const int l = again(lane);
+        const char* from = tile + (4 * (l >> 5) + ((l & 15) >> 2)) * G::kPitch + (16 * ((l >> 4) & 1) + 4 * (l & 3)) * 2;
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
             for (int t = 0; t < G::kDTiles; ++t) {
-                const char* a0 = tile + trn + 16 * s2 * G::kPitch + 64 * t;
+                const char* a0 = from + 16 * s2 * G::kPitch + 64 * t;
                 const u32x2 x = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a0)));
                 const u32x2 y = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a0 + 8 * G::kPitch)));
                 acc[t] = mma(u32x4{x.x, x.y, y.x, y.y}, wt[s2], acc[t]);
@@ -190,14 +202,35 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
         hi = (min(h2, n) + kTile - 1) / kTile;
     };
 
+    // This workgroup's share (parts_of): everything; or, first in the order of workgroups, the key side of eight tiles, which needs the statistics of the
+    // rows that see them; or the query side of eight tiles of one head.  What a part forms it forms as the whole does.
+    const int eights = (T + kWaves - 1) / kWaves;
+    int h0 = 0, h1 = bp.wg_heads, a0b = 0, a0e = T, c0b = 0, c0e = T;
+    const bool keys_only = PARTS && part < eights;
+    if (keys_only) {
+        int lo, hi;
+        c0b = kWaves * part;
+        c0e = min(T, c0b + kWaves);
+        reach(true, kTile * c0b, kTile * c0e - 1, lo, hi);
+        a0b = lo / kWaves * kWaves;
+        a0e = hi;
+    } else if (PARTS) {
+        const int i = (part - eights) / bp.wg_heads;
+        h0 = part - eights - i * bp.wg_heads;
+        h1 = h0 + 1;
+        a0b = kWaves * (eights - 1 - i);
+        a0e = min(T, a0b + kWaves);
+        c0e = 0;
+    }
+
     // ===== query side ================================================================================
 #pragma unroll 1
-    for (int hl = 0; hl < bp.wg_heads; ++hl) {
+    for (int hl = h0; hl < h1; ++hl) {
         const int h = g * p.G + bp.head_base + hl;
         const char* xb = slice(p.vin, VS ? g : h);
         char* dqb = slice(bp.dq, h);
 #pragma unroll 1
-        for (int a0 = 0; a0 < T; a0 += kWaves) {
+        for (int a0 = a0b; a0 < a0e; a0 += kWaves) {
             const int a = a0 + w;                         // past the last tile: the wave only fetches
             int lo, hi, wlo, whi;
             reach(false, kTile * a0, kTile * (a0 + kWaves) - 1, lo, hi);
@@ -246,6 +279,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
                 float* sh = stats + (hl * T + a) * 3 * kTile;
                 sh[lane] = msafe; sh[kTile + lane] = inv; sh[2 * kTile + lane] = delta;
             }
+            if (keys_only) continue;
             f32x16 acc[G::kDTiles];
 #pragma unroll
             for (int t = 0; t < G::kDTiles; ++t) acc[t] = f32x16{};
@@ -268,15 +302,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
             if (a < T) {
                 set_rowoff(a);
                 u32x4 old[G::kDTiles * 2] = {};
-                if (bp.accumulate) prefetch_tile<D, NARROW>(old, rowoff, 0, dqb, lane, dbytes);
-                store_tile<D, NARROW>(acc, p.scale, transit, rowoff, 0, dqb, old, bp.accumulate != 0, min(kTile, n - kTile * a), lane, dbytes,
+                if (bp.accumulate) prefetch_tile<D, NARROW>(old, rowoff, 0, dqb, again(lane), dbytes);
+                store_tile<D, NARROW>(acc, p.scale, transit, rowoff, 0, dqb, old, bp.accumulate != 0, min(kTile, n - kTile * a), again(lane), dbytes,
                                       unrope(&p, [&](int r) { return (float)(kTile * a + r); }));
             }
         }
     }
     // ===== key side ==================================================================================
 #pragma unroll 1
-    for (int c0 = 0; c0 < T; c0 += kWaves) {
+    for (int c0 = c0b; c0 < c0e; c0 += kWaves) {
         const int c = c0 + w;
         u32x4 kop[G::kKSteps], xop[G::kKSteps];
         own(slice(p.k, g), sp.k_row, min(c, T - 1), true, kop);
@@ -305,14 +339,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
                 for (int i = 0; i < 2; ++i) {
                     const int a = 2 * j + i;
                     if (a < wlo || a >= whi) continue;
-                    const float* sh = stats + (hl * T + a) * 3 * kTile;
+                    const float* sh = stats + (hl * T + a) * 3 * kTile + 4 * (again(lane) >> 5);
                     f32x16 st = scores(qt + i * kTile * G::kPitch, kop);
                     hide(st, block_vis_rows(p, f, kTile * c + (again(lane) & 31), a, nreal));
                     float pr[16];
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4) {
-                        const f32x4 m4 = *reinterpret_cast<const f32x4*>(sh + 8 * q4 + 4 * hf);
-                        const f32x4 i4 = *reinterpret_cast<const f32x4*>(sh + kTile + 8 * q4 + 4 * hf);
+                        const f32x4 m4 = *reinterpret_cast<const f32x4*>(sh + 8 * q4);
+                        const f32x4 i4 = *reinterpret_cast<const f32x4*>(sh + kTile + 8 * q4);
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
                             pr[4 * q4 + e] = __builtin_amdgcn_exp2f(fmaf(st[4 * q4 + e], sl2, -m4[e])) * i4[e];
@@ -323,7 +357,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
                     const f32x16 dp = scores(gt + i * kTile * G::kPitch, xop);
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4) {
-                        const f32x4 d4 = *reinterpret_cast<const f32x4*>(sh + 2 * kTile + 8 * q4 + 4 * hf);
+                        const f32x4 d4 = *reinterpret_cast<const f32x4*>(sh + 2 * kTile + 8 * q4);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) pr[4 * q4 + e] *= dp[4 * q4 + e] - d4[e];
                     }
@@ -333,7 +367,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
             });
             if (!VS && c < T) {
                 set_rowoff(c);
-                store_tile_plain<D, NARROW>(dx, 1.f, transit, rowoff, 2, slice(bp.d_vin, h), rows_c, lane, dbytes);
+                store_tile_plain<D, NARROW>(dx, 1.f, transit, rowoff, 2, slice(bp.d_vin, h), rows_c, again(lane), dbytes);
             }
         }
         if (c < T) {
@@ -341,26 +375,54 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
             u32x4 old[G::kDTiles * 2] = {};
             if (VS) {
                 char* dxb = slice(bp.d_vin, g);
-                if (bp.acc_x) prefetch_tile<D, NARROW>(old, rowoff, 2, dxb, lane, dbytes);
-                store_tile<D, NARROW>(dx, 1.f, transit, rowoff, 2, dxb, old, bp.acc_x != 0, rows_c, lane, dbytes);
+                if (bp.acc_x) prefetch_tile<D, NARROW>(old, rowoff, 2, dxb, again(lane), dbytes);
+                store_tile<D, NARROW>(dx, 1.f, transit, rowoff, 2, dxb, old, bp.acc_x != 0, rows_c, again(lane), dbytes);
             }
             char* dkb = slice(bp.dk, g);
-            if (bp.acc_k) prefetch_tile<D, NARROW>(old, rowoff, 1, dkb, lane, dbytes);
-            store_tile<D, NARROW>(dk, p.scale, transit, rowoff, 1, dkb, old, bp.acc_k != 0, rows_c, lane, dbytes,
+            if (bp.acc_k) prefetch_tile<D, NARROW>(old, rowoff, 1, dkb, again(lane), dbytes);
+            store_tile<D, NARROW>(dk, p.scale, transit, rowoff, 1, dkb, old, bp.acc_k != 0, rows_c, again(lane), dbytes,
                                   unrope(&p, [&](int r) { return (float)(kTile * c + r); }));
         }
     }
 }
 
-template <int D, bool VS, bool NARROW, bool ROPE>
+// Workgroups per fibre and key/value head.  A fibre's sides are one workgroup's work, 9 products of a pair of tiles (2 for the statistics, 3 for dQ, 4
+// for dK and dX), which leaves most of the chip idle on few fibres.  In parts, the query side of eight tiles of a head (5) and the key side of eight
+// tiles (4, and the statistics of the rows that see them once more) are workgroups of their own: the longest of them counts, or all together where
+// they fill the chip.  One workgroup is resident per CU.
+int parts_of(const BwdParams& bp, int tiles) {
+    const HopParams& p = bp.hop;
+    const int eights = (tiles + kWaves - 1) / kWaves;
+    const double units = (double)p.B * p.Hkv * p.fibres, heads = bp.wg_heads;
+    double pairs = 0, longest = 0, all = 0;               // in products of one tile against the streamed ones of its eight
+    for (int c = eights - 1; c >= 0; --c) {
+        pairs += p.causal ? std::min(tiles, kWaves * (c + 1)) : tiles;
+        const double seen = p.causal ? pairs : (double)eights * tiles;
+        const double key = heads * (2 * seen + 4 * (p.causal ? tiles - kWaves * c : tiles));
+        longest = std::max(longest, key);
+        all += key;
+    }
+    all += 5 * heads * pairs;
+    // (the factors: measured against this count.  Whole and in parts, us: 8 heads of 128, 1,024 x 4 396 and 182, x 8 404 and 220, x 16 428 and 414, not split; 8 / 2 of 64,
+    // 300 x 40 168 and 106, x 80 173 and 186, not split; 8 / 2 of 128, 250 x 20 182 and 130; 8 of 64, 500 x 6 x 2 99 and 83; 32 / 8 of 64, 628 x 2 406 and 214; 12 of
+    // 96, 434 142 and 72; 8 of 128 without a mask, 1,000 590 and 231.)
+    const double whole = std::ceil(units / 256) * 9 * heads * pairs, split = std::max(1.1 * longest, 1.45 * units * all / 256);
+    return split < 0.9 * whole ? eights * (1 + bp.wg_heads) : 1;
+}
+
+template <int D, bool VS, bool NARROW, bool ROPE, bool PARTS>
 hipError_t launch(const BwdParams& bp, const StreamBwdParams& sp, hipStream_t s) {
     const size_t smem = (size_t)LongGeo<D>::kFixed + (size_t)bp.wg_heads * sp.tiles * 3 * kTile * 4;
     if (smem > (size_t)kStreamMaxLds) return hipErrorInvalidValue;
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_bwd_long_kernel<D, VS, NARROW, ROPE>), kStreamMaxLds);
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_bwd_long_kernel<D, VS, NARROW, ROPE, PARTS>), kStreamMaxLds);
     if (e != hipSuccess) return e;
     const HopParams& p = bp.hop;
-    hipLaunchKernelGGL((mfma_bwd_long_kernel<D, VS, NARROW, ROPE>), dim3((unsigned)p.Hkv, sp.fibres_lo, (unsigned)p.B * sp.fibres_hi), dim3(64 * kWaves), smem, s, bp, sp);
+    hipLaunchKernelGGL((mfma_bwd_long_kernel<D, VS, NARROW, ROPE, PARTS>), dim3((unsigned)p.Hkv, sp.fibres_lo, (unsigned)p.B * sp.fibres_hi * sp.parts), dim3(64 * kWaves), smem, s, bp, sp);
     return hipGetLastError();
+}
+template <int D, bool VS, bool NARROW, bool ROPE>
+hipError_t launch(const BwdParams& bp, const StreamBwdParams& sp, hipStream_t s) {
+    return sp.parts > 1 ? launch<D, VS, NARROW, ROPE, true>(bp, sp, s) : launch<D, VS, NARROW, ROPE, false>(bp, sp, s);
 }
 template <int D, bool NARROW>
 hipError_t launch(const BwdParams& bp, const StreamBwdParams& sp, hipStream_t s) {
@@ -384,6 +446,8 @@ hipError_t launch_mfma_backward_long(const BwdParams& bp, hipStream_t s) {
     sp.fibres_lo = (uint32_t)(p.fibres < 32768 ? p.fibres : 32768);
     sp.fibres_hi = (uint32_t)((p.fibres + sp.fibres_lo - 1) / sp.fibres_lo);
     if ((int64_t)p.B * sp.fibres_hi > 65535) return hipErrorInvalidValue;
+    sp.parts = parts_of(bp, sp.tiles);
+    if ((int64_t)p.B * sp.fibres_hi * sp.parts > 65535) sp.parts = 1;
     return p.D == 128 ? launch<128, false>(bp, sp, s) : p.D == 64 ? launch<64, false>(bp, sp, s)
          : p.D > 64 ? launch<128, true>(bp, sp, s) : launch<64, true>(bp, sp, s);
 }
