@@ -115,12 +115,15 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     struct Raw { u32x4 v[kMine]; };
     uint32_t misaligned = 0u;                             // NARROW: a bit per requested row, 4 bits per tensor
     // What depends on the lane is formed anew wherever it is used, from a copy of the lane's number that the compiler cannot look
-    // through: kept over the loop it would be spilled, and a reload waits for every row requested before it.
+    // through: kept over the loop it would be spilled, and a reload waits for every row requested before it.  64-wide tiles have more room: narrow or
+    // encoded rows form it once per head (32 / 8 heads of 40, 9 x 38 x 42 x 8, 803 -> 754 us), whole rows keep all but row addresses (100 x 50 x 2, 16 / 4 heads, 54 -> 52).
+    int head_lane = threadIdx.x & 63;
     auto fresh_lane = [&]() {
-        int l = threadIdx.x & 63;
-        asm volatile("" : "+v"(l));
+        int l = head_lane;
+        if (D == 128 || !(NARROW || ROPE)) asm volatile("" : "+v"(l));
         return l;
     };
+    auto kept_lane = [&]() { return D == 128 ? fresh_lane() : head_lane; };
     auto gather = [&](auto once, auto which, const Tensor& t, const Where& x, int head, uint32_t pitch, Raw& raw) {
         const char* base = reinterpret_cast<const char*>(t.p) + ((int64_t)x.b * t.sb + (int64_t)head * t.sh) * 2;
         const int l = fresh_lane(), row = l / G::kChunks;
@@ -135,7 +138,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         }
     };
     auto put = [&](char* tile, const Raw& raw) {
-        const int l = fresh_lane();
+        const int l = kept_lane();
         const uint32_t stg = (uint32_t)((s * kMine * G::kRowsPerPass + l / G::kChunks) * G::kPitch + (l % G::kChunks) * 16);
 #pragma unroll
         for (int i = 0; i < kMine; ++i) *reinterpret_cast<u32x4*>(tile + stg + i * G::kRowsPerPass * G::kPitch) = raw.v[i];
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         int orow;
         uint32_t obyte;
         out_lane(orow, obyte);
-        const int la = fresh_lane(), r32 = la & 31, hf = la >> 5;
+        const int la = kept_lane(), r32 = la & 31, hf = la >> 5;
         lds_wave_sync();
 #pragma unroll
         for (int t = 0; t < R::kHT; ++t)
@@ -225,7 +228,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
 #pragma unroll
         for (int i = 0; i < R::kOut; ++i)
             buffer_store_chunk<NARROW>(to, out_offset(tok0, i * R::kOutRows + orow, pitch), i * R::kOutRows + orow < rows_t, obyte, dbytes,
-                                       u32x4{pack_bf16x2(y[i][0], y[i][1]), pack_bf16x2(y[i][2], y[i][3]), pack_bf16x2(y[i][4], y[i][5]), pack_bf16x2(y[i][6], y[i][7])});
+                                       u32x4{pack_bf16x2(y[i][0], y[i][1]), pack_bf16x2(y[i][2], y[i][3]), pack_bf16x2(y[i][4], y[i][5]), pack_bf16x2(y[i][6], y[i][7])}, dbytes % 16 == 0);
     };
 
     Where at = where(blockIdx.x);
@@ -266,7 +269,8 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         for (int hl = 0; hl < (MODE == kOne ? 1 : p.G); ++hl) {
             const int h = at.g * p.G + hl, hv = VS ? at.g : h;
             const bool last_head = MODE == kOne || hl + 1 == p.G;
-            const int l_ = fresh_lane(), r32 = l_ & 31, hf = l_ >> 5;
+            if (D == 64 && (NARROW || ROPE)) asm volatile("" : "+v"(head_lane));
+            const int l_ = fresh_lane(), r32 = kept_lane() & 31, hf = kept_lane() >> 5;
             const int qr = kTile * w + r32;               // this lane's query row
             const uint32_t nat = (uint32_t)((l_ & 31) * G::kPitch + (l_ >> 5) * 16);
             const uint32_t trow = (uint32_t)(4 * (l_ >> 5) + ((l_ & 15) >> 2)), tcol = (uint32_t)(16 * ((l_ >> 4) & 1) + 4 * (l_ & 3)) * 2;
