@@ -319,7 +319,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
 //                             and again for dK_c = sum_a dS_ac^T Q_a
 // Blocks that the causal triangle or the band hides entirely are skipped.
 constexpr int kStreamMaxN = 1024;
-// NARROW: the head is narrower than the D-wide tile; see load_chunk.
+// NARROW: the head is narrower than the D-wide tile; see gather_request.
 template <int D, bool NARROW>
 __global__ __launch_bounds__(512, 2) void mfma_bwd_stream_kernel(BwdParams bp, StreamBwdParams sp) {
     using G = BGeo<D>;

@@ -27,7 +27,7 @@ __device__ inline uint32_t tile_out_offset(const u32x4* rowoff, int which, int h
 
 // Requests the current contents of an output tile (for accumulate = 1) long before the
 // epilogue needs them, in the epilogue's mapping.
-// NARROW (here and below): rows hold only `dbytes` bytes and are 8-byte aligned; see load_chunk.
+// NARROW (here and below): rows hold only `dbytes` bytes and are 8-byte aligned; see gather_request.
 template <int D, bool NARROW = false>
 __device__ inline void prefetch_tile(u32x4 (&old)[Geo<D>::kDTiles * 2], const u32x4* rowoff, int which, const char* gbase, int lane,
                                      uint32_t dbytes = 0) {

@@ -37,7 +37,7 @@ struct LongGeo {
     static constexpr int kFixed = kStream + kWaves * kTile * 16;
 };
 
-// NARROW: the head is narrower than the D-wide tile; see load_chunk.  VS: the value input is per key/value head.  PARTS: a workgroup is a part of that (parts_of;
+// NARROW: the head is narrower than the D-wide tile; see gather_request.  VS: the value input is per key/value head.  PARTS: a workgroup is a part of that (parts_of;
 // instantiated on its own, since the bounds of a part cost the whole 2 to 4 per cent).
 template <int D, bool VS, bool NARROW, bool ROPE, bool PARTS>
 __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams bp, StreamBwdParams sp) {

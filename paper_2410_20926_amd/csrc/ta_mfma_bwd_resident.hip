@@ -50,7 +50,7 @@ struct Resident {
 };
 
 // MODE: what the heads of a group share.  kOne: a group is one head, nothing is shared or summed; kHeads: K; kGroup: K and the
-// value input (the value input is V).  NARROW: the head is narrower than the D-wide tile; see load_chunk.
+// value input (the value input is V).  NARROW: the head is narrower than the D-wide tile; see gather_request.
 enum : int { kOne, kHeads, kGroup };
 template <int D, int TM, int MODE, bool NARROW, bool ROPE>
 __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParams bp, StreamBwdParams sp, uint32_t units) {

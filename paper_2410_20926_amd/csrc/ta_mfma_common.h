@@ -38,28 +38,9 @@ __device__ inline f32x16 mma(const u32x4 a, const u32x4 b, const f32x16 c) {   /
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// One lane's 16-byte chunk (8 features starting at byte `lbyte` of the row at `base + rowoff`).  NARROW:
-// the row holds only `dbytes` bytes (at least 16; a head width that is a multiple of 4 but not of 8 features,
-// or simply narrower than the tile) and starts on a multiple of 8 bytes: what lies outside the row reads as
-// zero, so that the tile's extra features are zero in every operand.  One 16-byte request per lane (on an
-// 8-byte boundary where the row starts on one) and no branch: a branch per request makes every request wait
-// for the one before.  A chunk that would pass the end of the row is replaced by the row's last 16 bytes,
-// whose second half is the chunk's first (the row's length is a multiple of 8).
-template <bool NARROW, bool NT>
-__device__ inline u32x4 load_chunk(const char* base, uint32_t rowoff, uint32_t lbyte, uint32_t dbytes) {
-    if constexpr (!NARROW) {
-        const u32x4* a = reinterpret_cast<const u32x4*>(base + (rowoff + lbyte));
-        return NT ? __builtin_nontemporal_load(a) : *a;
-    } else {
-        const bool full = lbyte + 16 <= dbytes, tail = !full && lbyte + 8 <= dbytes;
-        const u32x4* a = reinterpret_cast<const u32x4*>(base + (rowoff + (full ? lbyte : dbytes - 16)));
-        u32x4 v = NT ? __builtin_nontemporal_load(a) : *a;
-        if (tail) v = u32x4{v.z, v.w, 0u, 0u};
-        if (!full && !tail) v = u32x4{0u, 0u, 0u, 0u};
-        return v;
-    }
-}
-// What lies outside the row reads as zero.
+// Rows of a head that is narrower than the tile (NARROW here and in the kernels: a head width that is a multiple of 4 but not of 8 features, or simply
+// narrower than the tile): a row holds only `dbytes` bytes (at least 16, a multiple of 8) and starts on a multiple of 8 bytes.
+// What lies outside the row reads as zero, so that the tile's extra features are zero in every operand.
 __device__ inline u32x4 row_only(u32x4 a, uint32_t lbyte, uint32_t dbytes) {
     if (lbyte + 8 > dbytes) { a.x = 0u; a.y = 0u; }
     if (lbyte + 16 > dbytes) { a.z = 0u; a.w = 0u; }
@@ -69,14 +50,15 @@ __device__ inline u32x4 row_only(u32x4 a, uint32_t lbyte, uint32_t dbytes) {
 __device__ inline bool whole_units(const char* base, uint32_t pitch, uint32_t dbytes) {
     return (((uint32_t)reinterpret_cast<uintptr_t>(base) | pitch | dbytes) & 15u) == 0u;
 }
-// The chunk for the row gathers, where the lanes of a row are consecutive lanes that hold consecutive chunks of
-// the whole tile row (chunk = lane % 8 or lane % 16) and every lane of the wave takes part.  NARROW rows start on a
-// multiple of 8 bytes; strided 8-byte halves (load_chunk) ask for every cache line twice and reach 3.5 TB/s in a plain
-// streaming kernel on 200-byte rows, 16-byte requests on 16-byte boundaries 4.65 TB/s.  So a lane asks for the aligned
-// 16 bytes that start at or 8 bytes before its chunk (those 8 bytes lie inside the tensor's span: the tensor itself
-// starts on a 16-byte boundary), never for bytes past the end of the row (a unit that would pass it is replaced by the row's last 16
-// bytes; rows are at least that long), and a row that starts 8 bytes into an
-// aligned unit takes the second half of each chunk from the next lane.
+// One lane's 16-byte chunk (8 features starting at byte `lbyte` of the row at `base + rowoff`) for the row gathers, where
+// the lanes of a row are consecutive lanes that hold consecutive chunks of the whole tile row (chunk = lane % 8 or
+// lane % 16) and every lane of the wave takes part.  NARROW rows start on a multiple of 8 bytes; strided 8-byte halves ask
+// for every cache line twice and reach 3.5 TB/s in a plain streaming kernel on 200-byte rows, 16-byte requests on 16-byte
+// boundaries 4.65 TB/s, and a branch per request makes every request wait for the one before.  So a lane asks for the
+// aligned 16 bytes that start at or 8 bytes before its chunk (those 8 bytes lie inside the tensor's span: the tensor itself
+// starts on a 16-byte boundary), never for bytes past the end of the row (a unit that would pass it is replaced by the
+// row's last 16 bytes; rows are at least that long), and a row that starts 8 bytes into an aligned unit takes the second
+// half of each chunk from the next lane.
 // Two parts, the request and what is done with the bytes when they have come.  In one piece the first row's bytes are waited for before
 // the last rows are requested (the compiler shares the registers of the halves that are put together), so that the four tiles of the one-tile
 // backward waited for memory five times one after the other, and the two of the two-tile forward twice.  In two parts (32 / 8 heads of 96, 32 x 32 x 32, the
@@ -86,7 +68,8 @@ template <bool NARROW, bool NT>
 __device__ inline u32x4 gather_request(const char* base, uint32_t rowoff, uint32_t lbyte, uint32_t dbytes, uint32_t& mis) {
     if constexpr (!NARROW) {
         mis = 0u;
-        return load_chunk<false, NT>(base, rowoff, lbyte, dbytes);
+        const u32x4* src = reinterpret_cast<const u32x4*>(base + (rowoff + lbyte));
+        return NT ? __builtin_nontemporal_load(src) : *src;
     } else {
         // `base` is uniform: a uniform 16-byte boundary and 32-bit offsets from it, so that no address takes two registers
         const uint32_t over = (uint32_t)(reinterpret_cast<uintptr_t>(base) & 8u), at = rowoff + over;

@@ -38,7 +38,7 @@ enum FwdRows { kWhole, kNarrow, kNarrowStreamed };        // streamed; through t
 constexpr int kWavesPerBlock = 4;
 
 // KT = number of 32-key tiles a unit may walk (1: n <= 32, 2: n <= 64).
-// ROWS: narrow: the head is narrower than the D-wide tile (p.D features of 2 bytes per row); see load_chunk.
+// ROWS: narrow: the head is narrower than the D-wide tile (p.D features of 2 bytes per row); see gather_request.
 // ROPE: the hop scores with rotary-encoded Q and K (instantiated separately: the plain kernels carry none of it).
 template <int D, int KT, FwdRows ROWS, bool ROPE>
 __global__ __launch_bounds__(kWavesPerBlock * 64, KT == 1 && ROWS != kWhole ? 3 : 2) void mfma_fwd_kernel(HopParams p, TileParams tp) {

@@ -48,7 +48,7 @@ struct LongParams {
 // workgroup work half a block apart (see the loop); never with a bit table.
 enum Form { kShort, kBlocks, kPhases };
 struct Choice { Form form; int waves; };                  // waves per workgroup: 4, or 8 (kPhases: always)
-// NARROW: the head is narrower than the D-wide tile; see load_chunk.
+// NARROW: the head is narrower than the D-wide tile; see gather_request.
 // 64-wide heads in step: three waves per SIMD, i.e. at most 168 registers (with the 170 that the compiler takes by itself and two waves, 32 / 8 heads
 // of 512 x 64: 254 us, here 223).
 template <int D, int NW, Form FORM, bool NARROW, bool ROPE>

@@ -28,7 +28,7 @@ struct SmallParams {
     void* mid;                                            // nullptr, or an O-shaped tensor for the first hop's output
 };
 
-// NARROW: the head is narrower than the D-wide tile; see load_chunk.
+// NARROW: the head is narrower than the D-wide tile; see gather_request.
 template <int D, int kTiles, bool NARROW, bool ROPE>
 __global__ __launch_bounds__(64 * kWaves, 2) void mfma_fwd_pair_small_kernel(HopParams h1, HopParams h2, SmallParams sp) {
     using G = Geo<D>;

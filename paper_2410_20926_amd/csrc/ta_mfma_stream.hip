@@ -25,7 +25,7 @@ struct StreamParams {
     uint32_t q_step, k_step, v_step, o_step;   // bytes between neighbouring rows of a fibre (stride * token pitch)
 };
 
-// NARROW (both kernels): the head is narrower than the D-wide tile; see load_chunk.
+// NARROW (both kernels): the head is narrower than the D-wide tile; see gather_request.
 // Axes of more than four tiles, the value input per key/value head: a workgroup is one query tile of 4 heads of a group,
 // which walk the same key tiles.  Each wave fetches a quarter of every K and V tile into a workgroup-shared,
 // double-buffered LDS tile: K and V leave L2 once per workgroup instead of once per head, with
