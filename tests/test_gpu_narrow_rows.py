@@ -59,3 +59,28 @@ def test_small_slabs_give_the_bits_of_their_heads_alone(D, dims, H, Hkv):
     assert torch.isfinite(whole).all()
     for j in range(Hkv):
         assert torch.equal(whole[:, :, j * G:(j + 1) * G], forward(*(t.contiguous() for t in (q[:, :, j * G:(j + 1) * G], k[:, :, j:j + 1], v[:, :, j:j + 1]))))
+
+
+@pytest.mark.parametrize("F,H,Hkv,n,D", [
+    (4096, 3, 3, 33, 40),                                  # 12,288 (fibre, head) pairs: the first size whose workgroups take four of them
+    (4095, 3, 3, 33, 100),                                 # one fibre less: as many workgroups as are resident
+    (4099, 3, 3, 64, 100),                                 # a last workgroup of fewer, and some of five
+    (3073, 8, 4, 40, 12),                                  # groups of two heads
+])
+def test_two_tile_backward_in_short_shares_gives_the_bits_of_a_few_fibres(F, H, Hkv, n, D):
+    gen = torch.Generator(device="cuda").manual_seed(F + D)
+    q, x, g = (torch.randn((1, F * n, H, D), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    k = torch.randn((1, F * n, Hkv, D), generator=gen, device="cuda").bfloat16()
+
+    def hop(vin, q, k, x, g):
+        plan = ta.ta_plan_create(1, H, Hkv, D, (q.shape[1] // n, n), ta.TA_BF16, True)
+        dq, dk, dx = (torch.full_like(t, 0.5) for t in (q, k, x))
+        ta.ta_axis_attn_backward(plan, 1, q, k, x, vin, g, dx, dq, dk, True)
+        return dq, dk, dx
+    for vin, value in ((ta.TA_VIN_O, x), (ta.TA_VIN_KV, k)):
+        whole = hop(vin, q, k, value, g)
+        assert all(torch.isfinite(t).all() for t in whole)
+        for f in (0, F // 2, F - 5):
+            part = slice(f * n, (f + 5) * n)
+            for a, b in zip(whole, hop(vin, *(t[:, part].clone() for t in (q, k, value, g)))):
+                assert torch.equal(a[:, part], b)
