@@ -464,13 +464,14 @@ hipError_t launch_resident(const BwdParams& bp, hipStream_t s) {
     const int by_lds = (int)((size_t)kStreamMaxLds / smem), by_regs = (D == 64 && TM == 2 ? 6 : 4) / sp.tiles;
     const int per_cu = by_lds < by_regs ? by_lds : by_regs;
     const int64_t most = 256 * (per_cu < 1 ? 1 : per_cu);
-    // Narrow rows share lines with the neighbouring heads' rows, which find them in L2 only as long as their workgroups keep step.  Workgroups that walk a long
-    // share drift apart by more than L2 holds (32 heads of 100, 64 x 64 x 32: 1.5 times the bytes fetched), so where there is enough for it they
-    // take four (fibre, head) pairs each and are replaced in order: 3,000 -> 1,950 us, of 96 2,130 -> 1,700, of 40 1,440 -> 794; 8 of 36, 60 x 238 x 9 x 2,
-    // 507 -> 379; 12 of 100, 40 x 40 x 40, 430 -> 410.  With less it costs a start that nothing hides more often than it gains (128-wide tiles, 3
-    // heads of 100, 54 x 867 x 4, 20 pairs per resident workgroup: 251 and 261; 64-wide, 6 of 48, 34 x 49 x 32, 12 pairs: 98 and 104), as with one workgroup per CU (n > 64,
-    // 12 of 100, 100 x 128 x 10, 711 and 756).  Whole rows share no lines: no difference.
-    const bool in_step = NARROW && TM == 2 && units >= (D == 128 ? 24 : 16) * most;
+    // Narrow rows share lines with the neighbouring heads' rows, which find them in L2 only as long as their workgroups keep step.  Workgroups that walk a
+    // long share drift apart by more than L2 holds (32 heads of 100, 64 x 64 x 32: 1.5 times the bytes fetched), so where there is enough for it they
+    // take four (fibre, head) pairs each and are replaced in order: 3,000 -> 1,950 us, of 96 2,130 -> 1,700, of 40 1,440 -> 794; 8 of 36,
+    // 60 x 238 x 9 x 2, 507 -> 355; at the lower ends of the rule 32 of 48, 63 x 19 x 9 x 2, 196 -> 139, 12 of 100, 251 x 50 x 4, 325 -> 293.
+    // With less it costs a start that nothing hides more often than it gains (long shares and shares of four; 128-wide tiles, 3 heads of 100,
+    // 54 x 867 x 4, 20 pairs per resident workgroup: 251 and 261, 16 / 4 of 72, 62 x 792 x 2, 12 pairs: 476 and 521; 64-wide, 6 of 48, 34 x 49 x 32,
+    // 12 pairs: 98 and 104), as with one workgroup per CU (n > 64, 12 of 100, 100 x 128 x 10, 711 and 756).  Whole rows share no lines: no difference.
+    const bool in_step = NARROW && TM == 2 && units >= (D == 128 ? 22 : 13) * most;
     const uint32_t grid = (uint32_t)(in_step ? units / 4 & ~(int64_t)7 : units < most ? units : most);
     if (smem > 64 * 1024) {
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_bwd_resident_kernel<D, TM, MODE, NARROW, ROPE>), (int)smem);

@@ -62,8 +62,10 @@ def test_small_slabs_give_the_bits_of_their_heads_alone(D, dims, H, Hkv):
 
 
 @pytest.mark.parametrize("F,H,Hkv,n,D", [
-    (4096, 3, 3, 33, 40),                                  # 12,288 (fibre, head) pairs: the first size whose workgroups take four of them
-    (4095, 3, 3, 33, 100),                                 # one fibre less: as many workgroups as are resident
+    (3328, 3, 3, 33, 40),                                  # 9,984 (fibre, head) pairs: the first size whose workgroups take four of them
+    (3327, 3, 3, 33, 36),                                  # one fibre less: as many workgroups as are resident
+    (2816, 4, 4, 33, 100),                                 # the same in 128-wide tiles, 11,264 pairs
+    (2815, 4, 4, 33, 68),
     (4099, 3, 3, 64, 100),                                 # a last workgroup of fewer, and some of five
     (3073, 8, 4, 40, 12),                                  # groups of two heads
 ])
