@@ -472,7 +472,8 @@ hipError_t launch_resident(const BwdParams& bp, hipStream_t s) {
     // 54 x 867 x 4, 20 pairs per resident workgroup: 251 and 261, 16 / 4 of 72, 62 x 792 x 2, 12 pairs: 476 and 521; 64-wide, 6 of 48, 34 x 49 x 32,
     // 12 pairs: 98 and 104), as with one workgroup per CU (n > 64, 12 of 100, 100 x 128 x 10, 711 and 756).  Whole rows share no lines: no difference.
     const bool in_step = NARROW && TM == 2 && units >= (D == 128 ? 22 : 13) * most;
-    const uint32_t grid = (uint32_t)(in_step ? units / 4 & ~(int64_t)7 : units < most ? units : most);
+    // (a grid dimension holds fewer than 2^32 threads, and a workgroup has up to 256 here; from 67 million pairs on the shares are larger)
+    const uint32_t grid = (uint32_t)(in_step ? (units / 4 < 0xffffff ? units / 4 : 0xffffff) & ~(int64_t)7 : units < most ? units : most);
     if (smem > 64 * 1024) {
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(mfma_bwd_resident_kernel<D, TM, MODE, NARROW, ROPE>), (int)smem);
         if (e != hipSuccess) return e;
