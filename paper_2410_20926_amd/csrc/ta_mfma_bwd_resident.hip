@@ -116,11 +116,12 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     uint32_t misaligned = 0u;                             // NARROW: a bit per requested row, 4 bits per tensor
     // What depends on the lane is formed anew wherever it is used, from a copy of the lane's number that the compiler cannot look
     // through: kept over the loop it would be spilled, and a reload waits for every row requested before it.  64-wide tiles have more room: narrow or
-    // encoded rows form it once per head (32 / 8 heads of 40, 9 x 38 x 42 x 8, 803 -> 754 us), whole rows keep all but row addresses (100 x 50 x 2, 16 / 4 heads, 54 -> 52).
+    // encoded rows form it once per head (32 / 8 heads of 40, 9 x 38 x 42 x 8, 803 -> 754 us), whole rows of three and four tiles keep it (8 / 2 heads, 50 x 70, 23.3 -> 22.2 us
+    // against new row addresses, 32 / 8, 100 x 200, 176 -> 168), of two all but row addresses (kept, they take 27 registers more and a wave per SIMD: 32 / 8 heads, 500 x 40, 113 against 145).
     int head_lane = threadIdx.x & 63;
     auto fresh_lane = [&]() {
         int l = head_lane;
-        if (D == 128 || !(NARROW || ROPE)) asm volatile("" : "+v"(l));
+        if (D == 128 || (TM == 2 && !(NARROW || ROPE))) asm volatile("" : "+v"(l));
         return l;
     };
     auto kept_lane = [&]() { return D == 128 ? fresh_lane() : head_lane; };
