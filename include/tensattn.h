@@ -153,7 +153,8 @@ const char* ta_plan_hop_backward_kernel(const ta_plan_t* plan, int axis, int vin
 const char* ta_plan_hop_function(const ta_plan_t* plan, int axis, int vin, int backward);
 /* Which form of that device function the hop runs, where it has several: mfma_fwd_long_kernel is launched as
  * "two_blocks", "four_tiles_in_step", "eight_tiles_in_step" or "eight_tiles_in_phases", mfma_bwd_kernel on rows narrower than its tile as
- * "rows_cached", "rows_streamed" or "heads_in_pairs", mfma_fwd_kernel and mfma_fwd_shared_kernel as one of the first two; "" for the others, NULL on error.  Static storage. */
+ * "rows_cached", "rows_streamed" or "heads_in_pairs", mfma_fwd_kernel and mfma_fwd_shared_kernel as one of the first two, mfma_bwd_long_kernel as
+ * "whole" or "in_parts" (of a group that takes several launches: its first); "" for the others, NULL on error.  Static storage. */
 const char* ta_plan_hop_form(const ta_plan_t* plan, int axis, int vin, int backward);
 
 /* Cost model of one hop (App. C.2, Table 5, with the fibre count N/n_i that Eq. 4

@@ -407,6 +407,8 @@ const char* ta_plan_hop_form(const ta_plan_t* pl, int axis, int vin, int backwar
     const char* function = ta_plan_hop_function(pl, axis, vin, backward);
     if (function && strcmp(function, "mfma_bwd_kernel") == 0)
         return ta::mfma_backward_form(bwd_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr, nullptr, nullptr, nullptr, 0));
+    if (function && strcmp(function, "mfma_bwd_long_kernel") == 0)
+        return ta::mfma_backward_long_in_parts(bwd_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr, nullptr, nullptr, nullptr, 0)) ? "in_parts" : "whole";
     if (function && (strcmp(function, "mfma_fwd_kernel") == 0 || strcmp(function, "mfma_fwd_shared_kernel") == 0))
         return ta::mfma_forward_form(hop_params(pl, axis, nullptr, nullptr, nullptr, vin, nullptr), pl->kernel_id[axis][vin]);
     if (!function || strcmp(function, "mfma_fwd_long_kernel") != 0) return function ? "" : nullptr;

@@ -130,6 +130,7 @@ hipError_t launch_mfma_backward(const BwdParams& bp, hipStream_t s);
 hipError_t launch_mfma_backward_resident(const BwdParams& bp, hipStream_t s);   // its variant for axes of two to four tiles
 hipError_t launch_mfma_backward_long(const BwdParams& bp, hipStream_t s);       // and for longer ones (bp.wg_heads heads from bp.head_base on)
 size_t     mfma_backward_long_lds(int32_t n, int32_t heads, int32_t D);
+bool       mfma_backward_long_in_parts(const BwdParams& bp);                    // few fibres: several workgroups per fibre and key/value head
 // Fused pair of hops (axes h1 then h2 = the two innermost axes) in one kernel.
 bool       mfma_pair_supports(const HopParams& h1, const HopParams& h2, int dtype);
 hipError_t launch_mfma_forward_pair(const HopParams& h1, const HopParams& h2, void* o_mid, hipStream_t s);   // o_mid: nullptr or O-shaped, gets h1's output

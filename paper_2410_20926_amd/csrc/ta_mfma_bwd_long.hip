@@ -437,6 +437,16 @@ size_t mfma_backward_long_lds(int32_t n, int32_t heads, int32_t D) {
     return (size_t)(D > 64 ? LongGeo<128>::kFixed : LongGeo<64>::kFixed) + (size_t)heads * ((n + kTile - 1) / kTile) * 3 * kTile * 4;
 }
 
+// (wg_heads is not set outside a launch: the first launch of a group takes eight heads at most)
+bool mfma_backward_long_in_parts(const BwdParams& bp) {
+    const HopParams& p = bp.hop;
+    const int64_t lo = p.fibres < 32768 ? p.fibres : 32768, hi = (p.fibres + lo - 1) / lo;
+    BwdParams first = bp;
+    if (first.wg_heads == 0) first.wg_heads = p.G < 8 ? p.G : 8;
+    const int parts = parts_of(first, (p.n + kTile - 1) / kTile);
+    return parts > 1 && (int64_t)p.B * hi * parts <= 65535;
+}
+
 hipError_t launch_mfma_backward_long(const BwdParams& bp, hipStream_t s) {
     const HopParams& p = bp.hop;
     StreamBwdParams sp;
@@ -446,8 +456,7 @@ hipError_t launch_mfma_backward_long(const BwdParams& bp, hipStream_t s) {
     sp.fibres_lo = (uint32_t)(p.fibres < 32768 ? p.fibres : 32768);
     sp.fibres_hi = (uint32_t)((p.fibres + sp.fibres_lo - 1) / sp.fibres_lo);
     if ((int64_t)p.B * sp.fibres_hi > 65535) return hipErrorInvalidValue;
-    sp.parts = parts_of(bp, sp.tiles);
-    if ((int64_t)p.B * sp.fibres_hi * sp.parts > 65535) sp.parts = 1;
+    sp.parts = mfma_backward_long_in_parts(bp) ? parts_of(bp, sp.tiles) : 1;
     return p.D == 128 ? launch<128, false>(bp, sp, s) : p.D == 64 ? launch<64, false>(bp, sp, s)
          : p.D > 64 ? launch<128, true>(bp, sp, s) : launch<64, true>(bp, sp, s);
 }

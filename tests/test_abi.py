@@ -436,6 +436,18 @@ def test_forms_of_the_one_tile_backward():
     assert form(32, 123, 4, 12, 12, 128) == "" and form(33, 123, 4, 12, 12, 100) == ""
 
 
+def test_forms_of_the_long_backward():
+    """Few fibres go in parts, a call that fills the chip does not."""
+    def form(n, fibres, Hq, Hkv, D, B=1, causal=True, vin=ta.TA_VIN_KV):
+        plan = ta.ta_plan_create(B, Hq, Hkv, D, (n, fibres), ta.TA_BF16, causal)
+        assert plan.hop_function(0, vin, True) == "mfma_bwd_long_kernel"
+        return plan.hop_form(0, vin, True)
+    for vin in (ta.TA_VIN_KV, ta.TA_VIN_O):
+        assert form(1024, 8, 8, 8, 128, vin=vin) == "in_parts" and form(1024, 16, 8, 8, 128, vin=vin) == form(256, 256, 8, 8, 128, vin=vin) == "whole"
+        assert form(300, 40, 8, 2, 64, vin=vin) == "in_parts" and form(300, 80, 8, 2, 64, vin=vin) == form(300, 10, 8, 2, 64, B=8, vin=vin) == "whole"
+        assert form(129, 1, 1, 1, 40, causal=False, vin=vin) == "in_parts"
+
+
 def test_forms_of_the_one_and_two_tile_forward():
     """Narrow rows: through the caches, but streamed in calls a little larger than the last-level cache; rows of up to 60 features there only on two tiles whose
     value input is not shared by a group."""
