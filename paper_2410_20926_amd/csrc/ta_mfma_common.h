@@ -372,10 +372,13 @@ __device__ inline uint32_t xcd_order(uint32_t lin, uint32_t total, uint32_t run_
     return l < 8u * run ? base + (l & 7u) * run + (l >> 3) : lin;
 }
 constexpr uint32_t kLongestRun = 28;                      // run_log2 of one run per XCD
-template <bool NARROW>
+constexpr uint32_t kAsTheyCome = 31;                      // no order
+// (FEW: run_log2 may be kAsTheyCome)
+template <bool NARROW, bool FEW = false>
 __device__ inline void workgroup_xy(uint32_t& bx, uint32_t& by, uint32_t run_log2 = kLongestRun) {
     bx = blockIdx.x; by = blockIdx.y;
     if constexpr (NARROW) {
+        if (FEW && run_log2 == kAsTheyCome) return;
         const uint32_t gx = gridDim.x;
         const uint32_t seq = xcd_order(blockIdx.x + gx * blockIdx.y, gx * gridDim.y, run_log2);
         bx = seq % gx;
@@ -387,6 +390,12 @@ inline uint32_t narrow_run_log2(int heads) {
     uint32_t r = 7;
     for (; heads > 1 && r > 4; heads /= 2) --r;
     return r;
+}
+// The same for kernels with a form for fewer workgroups than CUs: such a call is as long as one workgroup, which the order's divisions come first in
+// (38 forward hops without them 0.955 of the time, 19 backward ones 0.96; 8 heads of 36, 16 x 100, 5.5 -> 5.2 us; 18 of 256 to 512 workgroups 1.02).
+// Workgroups that share a group's K are not among them: 21 forward hops 1.006 (9 x 51 x 2, 16 / 4 heads of 40, 4.5 -> 4.6).
+inline uint32_t narrow_run_log2(int heads, const dim3& grid) {
+    return (uint64_t)grid.x * grid.y * grid.z < 256 ? kAsTheyCome : narrow_run_log2(heads);
 }
 
 // Launch geometry computed on the host.

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, KT == 1 && ROWS != kWhole ? 3 
     // block -> (head block, tile, batch); heads fastest so that co-resident waves read
     // the same tokens (whole DRAM rows) and the four waves of a block share K
     uint32_t bx, by;
-    workgroup_xy<NARROW>(bx, by, tp.run_log2);
+    workgroup_xy<NARROW, true>(bx, by, tp.run_log2);
     const int h = (int)bx * kWavesPerBlock + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + by;
@@ -687,7 +687,7 @@ hipError_t launch(const HopParams& p, const TileParams& tp, hipStream_t s) {
     const void* kf = p.rope ? (const void*)mfma_fwd_kernel<D, KT, ROWS, true> : (const void*)mfma_fwd_kernel<D, KT, ROWS, false>;
     HopParams pc = p;
     TileParams tc = tp;
-    tc.run_log2 = narrow_run_log2(kWavesPerBlock);
+    tc.run_log2 = narrow_run_log2(kWavesPerBlock, grid);
     void* args[2] = {&pc, &tc};
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }

@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (200, 2, 1, 4, 2),
     (70, 5, 1, 8, 2),                                      # the streaming forward of groups of four, all query tiles of a fibre in one workgroup
     (190, 3, 1, 4, 1),                                     # and one per workgroup, on the first hop
+    (32, 131, 1, 6, 6),                                    # enough workgroups to be put in order, no multiple of eight: 262 forward, 786 backward
+    (17, 299, 1, 8, 2),                                    # 598
 ])
 def test_a_head_among_others_gives_the_bits_of_the_head_alone(D, n, fibres, B, H, Hkv):
     gen, N, G = torch.Generator(device="cuda").manual_seed(100 * D + n), n * fibres, H // Hkv
