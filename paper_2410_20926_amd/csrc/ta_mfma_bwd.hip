@@ -1203,19 +1203,16 @@ bool mfma_backward_is_two_tile(const BwdParams& bp, int dtype) {
 // Long axes: the blocked kernel runs a group's heads side by side, a wave each; the long kernel one head after the other, eight
 // tiles at a time.  The former is ahead where it fills the chip and the latter's eight waves have five or six tiles (100 fibres of 129 / 160
 // positions, 16 / 4 heads of width 128: 212 / 245 against 241 / 256 us; from seven tiles on, 200 x 64, 32 / 8 heads: 513 against 440 us), and,
-// for five tiles, where a whole launch of eight heads is at hand (a training step of 130 x 16, 32 / 1 heads of width 128: 869 against 948 us; of 192 x 16: 1,127
-// against 1,058; groups of four, 160 x 16 with 4 / 1 heads: 163 against 145) and the long kernel would not go in parts, which is from some 130 fibres and key/value
-// heads on (causal hops, blocked and long: 129 x 46, 32 / 4 heads of 128, 198 and 238; 160 x 198, 8 / 1 of 100, 263 and 278; 160 x 347, 16 / 1 of 100, 1,102 and 1,211;
-// 28 with 131 to 600 of them 1.05 on average; in parts, 39 with fewer 0.83, 140 x 5 x 2, 32 / 4 of 64, 112 and 83; 160 x 19 x 2, 16 / 2 of 100, 250 and 177; 140 x 27, 32 / 1 of 128, 741 and 600; 160 x 11 x 2, 16 / 1 of 128, level).
-static bool runs_blocked(const BwdParams& bp) {
-    const HopParams& p = bp.hop;
-    return (p.G >= 4 && p.n <= 6 * kTile && (int64_t)p.B * p.Hkv * p.fibres >= 256) || (p.G >= 8 && p.n <= 5 * kTile && !mfma_backward_long_in_parts(bp));
+// for five tiles, where a whole launch of eight heads is at hand (a training step of 130 x 16, 32 / 1 heads of width 128: 869 against 948 us,
+// 160 x 4, of width 64: 532 against 560; of 192 x 16: 1,127 against 1,058; groups of four, 160 x 16 with 4 / 1 heads: 163 against 145).
+static bool runs_blocked(const HopParams& p) {
+    return (p.G >= 4 && p.n <= 6 * kTile && (int64_t)p.B * p.Hkv * p.fibres >= 256) || (p.G >= 8 && p.n <= 5 * kTile);
 }
 
 const char* mfma_backward_function(const BwdParams& bp) {
     switch (backward_variant(bp, TA_BF16)) {
         case 1: return "mfma_bwd_kernel";
-        case 2: return runs_blocked(bp) ? "mfma_bwd_stream_kernel" : "mfma_bwd_long_kernel";
+        case 2: return runs_blocked(bp.hop) ? "mfma_bwd_stream_kernel" : "mfma_bwd_long_kernel";
         case 3: return "mfma_bwd2_kernel";
         case 4: return "mfma_bwd_resident_kernel";
     }
@@ -1256,14 +1253,13 @@ hipError_t launch_mfma_backward(const BwdParams& user, hipStream_t s) {
         }
         return hipSuccess;
     }
-    const bool blocked = variant == 2 && runs_blocked(user);   // one kernel for every launch of a group
     for (int base = 0; base < G; base += 8) {
         bp.wg_heads = G - base > 8 ? 8 : G - base;
         bp.head_base = base;
         bp.acc_k = base == 0 ? user.accumulate : 1;
         bp.acc_x = base == 0 ? 0 : 1;
         hipError_t e;
-        if (variant == 2 && !blocked) e = launch_mfma_backward_long(bp, s);
+        if (variant == 2 && !runs_blocked(bp.hop)) e = launch_mfma_backward_long(bp, s);
         else if (variant == 2) e = bp.hop.D == 128 ? launch_stream<128, false>(bp, s) : bp.hop.D == 64 ? launch_stream<64, false>(bp, s)
                                  : bp.hop.D > 64 ? launch_stream<128, true>(bp, s) : launch_stream<64, true>(bp, s);
         else if (bp.hop.D == 128) e = launch<128, kWhole>(bp, tp, s);

@@ -350,8 +350,6 @@ def test_device_functions_of_a_plan():
     assert fn(8, 2, 128, (32, 4), 0, KV, True) == "mfma_bwd_kernel" and fn(8, 2, 128, (40, 4), 0, KV, True) == "mfma_bwd2_kernel"
     assert fn(8, 2, 128, (40, 256), 0, KV, True) == "mfma_bwd_resident_kernel" and fn(24, 4, 128, (64, 4), 0, KV, True) == "mfma_bwd_resident_kernel"
     assert fn(8, 2, 128, (130, 4), 0, KV, True) == "mfma_bwd_long_kernel" and fn(8, 2, 128, (130, 128), 0, KV, True) == "mfma_bwd_stream_kernel"
-    assert fn(8, 1, 64, (160, 120), 0, KV, True) == "mfma_bwd_long_kernel" and fn(8, 1, 64, (160, 140), 0, KV, True) == "mfma_bwd_stream_kernel"
-    assert fn(16, 1, 100, (129, 20), 0, O, True) == "mfma_bwd_long_kernel" and fn(8, 1, 128, (161, 140), 0, KV, True) == "mfma_bwd_long_kernel"
     assert fn(8, 1, 64, (4096, 2), 0, KV, True, ta.TA_F32) == "unsupported" and fn(8, 2, 128, (16, 4), 2, KV, False) is None
     small = lambda *a, **k: ta.ta_plan_create(1, *a, ta.TA_BF16, True, **k).small_pair_position()
     assert small(8, 2, 128, (5, 10, 9)) == 1 and small(8, 2, 128, (10, 9)) == 0
