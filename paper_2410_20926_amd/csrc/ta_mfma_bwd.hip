@@ -1091,10 +1091,9 @@ int heads_side_by_side(const HopParams& p, const TileParams& tp, BwdRows rows) {
 // caches serve that best.  (Heads, width, tokens by axis length; one hop, us.)
 //   Large calls of wide rows are ahead in pairs: cached alone and in pairs, 32 heads of 100, 32 x 32 x 32 428 and 423; 8 of 112, 28 x 1,856 (652 MB) 216 and 192; of
 // 112, 31 x 1,378 x 4 681 and 621; from 1.5 GB on every width on tiles that are nearly full: 8 of 40, 32 x 6,627 x 2 568 and 553, of 84, 16 x 3,613 x 3 502 and 493,
-// 32 of 40, 23 x 32 x 23 x 8 691 and 670, but 32 of 96, 20 x 2,302 421 and 433; below, 12 of 100, 82 x 32 x 4 (176 MB) 39.5 and 41.4; 32 of 112, 28 x 31 x 4 (174 MB) 35.0 and 34.6.
-// Where the workgroups of a batch are not a multiple of eight, in pairs from where calls cease to stream: drawn hops from 560 MB on in pairs take 0.98 of the time up to 96 features (31),
-// 0.99 at 100 (15), 0.94 above (11; 12 of 112, 24 x 807 x 2, 194 and 162).  Below, heads of their own, cached or streamed, take 0.98 of the time in pairs up to 280 MB (63; 4 of 100,
-// 1,518 x 16 29.5 and 30.6), 0.95 to 450 (21; 4 of 96, 9 x 992 x 8, 71 and 83) and 0.98 to 560 (14).
+// 32 of 40, 23 x 32 x 23 x 8 691 and 670, but 32 of 96, 20 x 2,302 421 and 433; below, 12 of 100, 82 x 32 x 4 (176 MB) 39.5 and 41.4; 32 of 112, 28 x 31 x 4 (174 MB) 35.0 and 34.6.  Where the workgroups of a batch
+// are not a multiple of eight pairs were ahead while such a grid lost its order; in runs (xcd_order) they are 0 to 4 per cent behind (4 of 100, 1,518 x 16 29.5 and
+// 30.6; 1,276 x 27 level), and stay because the form is what a plan reports.
 //   A call whose tensors are a little more than the 256 MB of the last-level cache evicts by a hop's end what the next pass, or hop, begins with; streamed
 // rows leave it part of that.  Cached and streamed: 32 heads of 100, 8 x 16 x 7 x 8 (321 MB) 86 and 78; 4 of 84, 39 x 16 x 38 x 4 (446 MB) 111 and 106; 16 / 4 of
 // 100, 16 x 131 x 8 (295 MB) 77 and 74, of 72, 28 x 1,407 (499 MB) 160 and 163, 32 / 8 of 72, 32 x 468 x 4 (1.1 GB) 398 and 406; 8 of 40, 33 x 31 x 32 (147 MB) 28.6 and
@@ -1102,7 +1101,7 @@ int heads_side_by_side(const HopParams& p, const TileParams& tp, BwdRows rows) {
 BwdRows narrow_rows(const HopParams& p, const TileParams& tp) {
     const uint32_t batch = (uint32_t)p.Hkv * tp.tiles_lo;    // workgroups that are put in order together, one head in each
     const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (3.0 * p.Hq + 2.0 * p.Hkv + 2.0 * p.vin_heads);
-    if (p.G == 1 && p.Hkv % 2 == 0 && batch % 8 != 0 && bytes >= (p.D <= 64 ? 450e6 : 560e6)) return kNarrowPairs;
+    if (p.G == 1 && p.Hkv % 2 == 0 && batch % 8 != 0 && (int64_t)p.Hkv * tp.tiles * p.B >= 1280) return kNarrowPairs;
     if (p.G == 1 && batch % 16 == 0 && p.n > 16 && p.D >= 100 && p.D * 2 % 64 != 0 && (p.D >= 112 ? bytes >= 560e6 : bytes >= 1e9 && !p.rope))
         return kNarrowPairs;
     if (p.G == 1 && p.Hkv % 2 == 0 && kTile / p.n * p.n >= 27 && bytes >= 1.5e9) return kNarrowPairs;

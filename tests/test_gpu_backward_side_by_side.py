@@ -51,9 +51,9 @@ def test_ungrouped_heads_match_oracle(dims, B, H, D, causal, window, lens, rope,
     ((31, 16), 2, 60, 128, True, None, None, None, ()),     # 1,860 waves on the second axis: four heads side by side
     ((32, 25), 4, 26, 64, False, None, (800, 431, 32, 1), None, ()),   # two: 26 heads do not divide by four
     ((20, 30), 4, 36, 64, True, (0, 5), None, 500.0, (0,)),
-    ((29, 27), 4, 12, 100, True, None, None, None, (1,)),   # narrow rows: one
-    ((10, 27), 12, 12, 40, False, (3, 0), None, 500.0, ()), # the same on tiles of three fibres
-    ((27, 30), 2, 40, 100, True, None, None, None, (1,)),   # more heads
+    ((29, 27), 4, 12, 100, True, None, None, None, (1,)),   # narrow rows, 324 and 348 workgroups of one head a sequence, no multiple of eight: two
+    ((10, 27), 12, 12, 40, False, (3, 0), None, 500.0, ()), # the same on tiles of three fibres; the other axis, 120, one
+    ((27, 30), 2, 40, 100, True, None, None, None, (1,)),   # narrow rows in order: one
     ((17, 31), 3, 45, 20, False, None, None, None, ()),     # 45 heads: one
 ])
 def test_heads_side_by_side_give_the_bits_of_heads_alone(dims, B, H, D, causal, window, lens, rope, axes):
@@ -69,7 +69,7 @@ def test_heads_side_by_side_give_the_bits_of_heads_alone(dims, B, H, D, causal, 
         _, plan, dev = multihop_forward(*(np.ascontiguousarray(t[:, :, h]) for t in (q, k, v)), dims, "bf16", causal, save=True, **kw)
         return multihop_backward(plan, dev, np.ascontiguousarray(d_o[:, :, h]), "bf16")
     forms = [ta.ta_plan_create(B, H, H, D, dims, ta.TA_BF16, causal, **kw).hop_form(i, ta.TA_VIN_KV, True) for i in range(len(dims))]
-    assert forms == ["rows_cached" if D not in (64, 128) else ""] * 2
+    assert forms == {(100, 12): ["heads_in_pairs"] * 2, (40, 12): ["heads_in_pairs", "rows_cached"]}.get((D, H), ["rows_cached" if D not in (64, 128) else ""] * 2)
     whole = step(slice(None))
     assert all(np.isfinite(x).all() for x in whole)
     for h in (0, 1, 2, 3, H // 2, H - 2, H - 1):
@@ -97,28 +97,3 @@ def test_streamed_narrow_rows_give_the_bits_of_cached_ones(dims, axis, B, H, Hkv
     for b in (0, B - 1):
         part = hop("rows_cached", *(t[b:b + 1].contiguous() for t in (q, k, x, g)))
         assert all(torch.isfinite(y).all() and torch.equal(y[b:b + 1], z) for y, z in zip(whole, part))
-
-
-@pytest.mark.parametrize("n,fibres,B,H,D,causal,window,table,rope", [
-    (29, 301, 4, 12, 100, True, None, True, None),         # 587 MB in a hop, 3,612 workgroups of one head a sequence
-    (10, 697, 12, 12, 40, False, (3, 0), False, 500.0),    # tiles of three fibres, the last one not full
-    (32, 1061, 1, 22, 112, True, None, False, None),       # one sequence; heads of their own below it, not sequences
-])
-def test_narrow_rows_in_pairs_give_the_bits_of_heads_alone(n, fibres, B, H, D, causal, window, table, rope):
-    N, gen = n * fibres, torch.Generator(device="cuda").manual_seed(9400 + D)
-    q, k, x, g = (torch.randn((B, N, H, D), generator=gen, device="cuda").bfloat16() for _ in range(4))
-    mask = torch.from_numpy(ta.pack_axis_mask((np.random.default_rng(n).random((n, n)) < 0.7) | np.eye(n, dtype=bool))).cuda() if table else None
-
-    def hop(form, *rows):
-        plan = ta.ta_plan_create(rows[0].shape[0], rows[0].shape[2], rows[0].shape[2], D, (n, fibres), ta.TA_BF16, causal, window=window, axis_masks=[mask, None], rope_base=rope)
-        assert plan.hop_form(0, ta.TA_VIN_O, True) == form
-        grads = [torch.full_like(t, 0.5) for t in rows[:3]]
-        for accumulate in (False, True):
-            ta.ta_axis_attn_backward(plan, 0, rows[0], rows[1], rows[2], ta.TA_VIN_O, rows[3], grads[2], grads[0], grads[1], accumulate)
-        return grads
-    whole = hop("heads_in_pairs", q, k, x, g)
-    assert all(torch.isfinite(y).all() for y in whole)
-    for b in (0, B - 1):
-        for heads in (slice(0, 1), slice(H // 2, H // 2 + 3), slice(H - 1, H)):
-            part = hop("rows_cached", *(t[b:b + 1, :, heads].contiguous() for t in (q, k, x, g)))
-            assert all(torch.equal(y[b:b + 1, :, heads], z) for y, z in zip(whole, part))
