@@ -448,8 +448,7 @@ def test_forms_of_the_long_backward():
 
 
 def test_forms_of_the_one_and_two_tile_forward():
-    """Narrow rows: through the caches, but streamed in calls a little larger than the last-level cache; rows of up to 60 features there only on two tiles whose
-    value input is not shared by a group."""
+    """Rows of up to 60 features: through the caches, but streamed on two tiles in calls a little larger than the last-level cache; wider narrow rows: streamed."""
     def form(n, fibres, Hq, Hkv, D, vin=ta.TA_VIN_KV):
         return ta.ta_plan_create(1, Hq, Hkv, D, (n, fibres), ta.TA_BF16, True).hop_form(0, vin)
     for Hq, Hkv, D, vin in ((8, 8, 40, 0), (8, 2, 40, 1), (6, 2, 20, 1)):
@@ -458,11 +457,7 @@ def test_forms_of_the_one_and_two_tile_forward():
             assert form(50, round(at / mb), Hq, Hkv, D, vin) == ("rows_streamed" if streamed else "rows_cached")
             assert form(25, round(2 * at / mb), Hq, Hkv, D, vin) == "rows_cached"
     assert {form(50, i, 8, 2, 40, 0) for i in range(200, 8000, 200)} == {"rows_cached"}      # a group's heads share the values
-    for n, Hq, Hkv, D, vin in ((50, 8, 2, 100, 0), (20, 8, 8, 72, 1), (32, 16, 4, 96, 1), (33, 3, 3, 124, 0)):
-        mb = n * D * 2 * (2 * Hq + Hkv + (Hq if vin else Hkv)) / 1e6
-        for at, streamed in ((1, False), (15, False), (17, False), (281, False), (283, True), (479, True), (481, False), (1000, False)):
-            assert form(n, round(at / mb), Hq, Hkv, D, vin) == ("rows_streamed" if streamed else "rows_cached")
-    assert form(50, 10, 8, 2, 128) == form(20, 10, 8, 8, 64) == ""
+    assert form(50, 10, 8, 2, 100) == form(20, 10, 8, 8, 72) == "rows_streamed" and form(50, 10, 8, 2, 128) == form(20, 10, 8, 8, 64) == ""
 
 
 def test_stream_lookup_without_torch_private_names(monkeypatch):
