@@ -437,14 +437,19 @@ def test_forms_of_the_one_tile_backward():
 
 def test_forms_of_the_long_backward():
     """Few fibres go in parts, a call that fills the chip does not."""
-    def form(n, fibres, Hq, Hkv, D, B=1, causal=True, vin=ta.TA_VIN_KV):
-        plan = ta.ta_plan_create(B, Hq, Hkv, D, (n, fibres), ta.TA_BF16, causal)
+    def form(n, fibres, Hq, Hkv, D, B=1, causal=True, vin=ta.TA_VIN_KV, **kw):
+        plan = ta.ta_plan_create(B, Hq, Hkv, D, (n, fibres), ta.TA_BF16, causal, **kw)
         assert plan.hop_function(0, vin, True) == "mfma_bwd_long_kernel"
         return plan.hop_form(0, vin, True)
     for vin in (ta.TA_VIN_KV, ta.TA_VIN_O):
         assert form(1024, 8, 8, 8, 128, vin=vin) == "in_parts" and form(1024, 16, 8, 8, 128, vin=vin) == form(256, 256, 8, 8, 128, vin=vin) == "whole"
         assert form(300, 40, 8, 2, 64, vin=vin) == "in_parts" and form(300, 80, 8, 2, 64, vin=vin) == form(300, 10, 8, 2, 64, B=8, vin=vin) == "whole"
         assert form(129, 1, 1, 1, 40, causal=False, vin=vin) == "in_parts"
+        # the calls whose bits are compared in test_gpu_backward_parts.py: a batch, and one of its elements
+        for n, fibres, B, Hq, Hkv, D, causal, kw in ((129, 9, 32, 4, 2, 64, True, {}), (256, 8, 32, 3, 3, 128, True, {}), (257, 8, 32, 2, 2, 40, False, dict(rope_base=500.0)),
+                                                     (300, 6, 40, 4, 2, 100, True, dict(window=(40, 0))), (520, 2, 130, 4, 2, 64, True, dict(rope_base=1e4)),
+                                                     (330, 3, 96, 6, 2, 128, False, dict(window=(100, 0)))):
+            assert form(n, fibres, Hq, Hkv, D, B, causal, vin, **kw) == "whole" and form(n, fibres, Hq, Hkv, D, 1, causal, vin, **kw) == "in_parts"
 
 
 def test_forms_of_the_one_and_two_tile_forward():

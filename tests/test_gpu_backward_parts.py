@@ -26,16 +26,16 @@ def test_parts_give_the_bits_of_the_whole(n, fibres, B, H, Hkv, D, causal, windo
     mask = (np.random.default_rng(n).random((n, n)) < 0.6) | np.eye(n, dtype=bool)
     packed = torch.from_numpy(ta.pack_axis_mask(mask)).cuda()
 
-    def hop(form, b):
+    def hop(b):
         kw = dict(window=(window, 0), rope_base=rope, valid_lens=ends[b].contiguous() if lens else None, axis_masks=[packed if table else None, None])
         rows = [t[b].contiguous() for t in (q, k, x, g)]
         plan = ta.ta_plan_create(rows[0].shape[0], H, Hkv, D, dims, ta.TA_BF16, causal, **kw)
-        assert plan.hop_function(0, vin, True) == "mfma_bwd_long_kernel" and plan.hop_form(0, vin, True) == form
+        assert plan.hop_function(0, vin, True) == "mfma_bwd_long_kernel"
         dq, dk, dx = (torch.full_like(t, 0.25) for t in rows[:3])
         for accumulate in (False, True):
             ta.ta_axis_attn_backward(plan, 0, rows[0], rows[1], rows[2], vin, rows[3], dx, dq, dk, accumulate)
         return dq, dk, dx
-    whole = hop("whole", slice(None))
+    whole = hop(slice(None))
     assert all(torch.isfinite(t).all() for t in whole)
     for b in (0, B // 2, B - 1):
-        assert all(torch.equal(t[b:b + 1], y) for t, y in zip(whole, hop("in_parts", slice(b, b + 1)))), b
+        assert all(torch.equal(t[b:b + 1], y) for t, y in zip(whole, hop(slice(b, b + 1)))), b
