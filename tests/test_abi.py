@@ -465,6 +465,17 @@ def test_forms_of_the_one_and_two_tile_forward():
     assert form(50, 10, 8, 2, 100) == form(20, 10, 8, 8, 72) == "rows_streamed" and form(50, 10, 8, 2, 128) == form(20, 10, 8, 8, 64) == ""
 
 
+def test_forms_of_the_wide_narrow_forward():
+    """Rows of 65 to 127 features: streamed below 16 MB and from 282 to 480 MB, through the caches elsewhere, on either number of tiles, grouped or not."""
+    def form(n, fibres, Hq, Hkv, D, vin, **kw):
+        return ta.ta_plan_create(1, Hq, Hkv, D, (n, fibres), ta.TA_BF16, True, **kw).hop_form(0, vin)
+    for n, Hq, Hkv, D, vin in ((50, 8, 2, 100, 0), (20, 8, 8, 72, 1), (32, 16, 4, 96, 1), (33, 3, 3, 124, 0)):
+        mb = n * D * 2 * (2 * Hq + Hkv + (Hq if vin else Hkv)) / 1e6
+        for at, streamed in ((1, True), (15, True), (17, False), (281, False), (283, True), (479, True), (481, False), (1000, False)):
+            for kw in ({}, dict(rope_base=1e4)):
+                assert form(n, round(at / mb), Hq, Hkv, D, vin, **kw) == ("rows_streamed" if streamed else "rows_cached")
+
+
 def test_stream_lookup_without_torch_private_names(monkeypatch):
     """A torch that has dropped the private way to the current stream's handle is asked for a stream object."""
     import torch

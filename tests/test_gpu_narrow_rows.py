@@ -88,3 +88,27 @@ def test_two_tile_backward_in_short_shares_gives_the_bits_of_a_few_fibres(F, H, 
             part = slice(f * n, (f + 5) * n)
             for a, b in zip(whole, hop(vin, *(t[:, part].clone() for t in (q, k, value, g)))):
                 assert torch.equal(a[:, part], b)
+
+
+@pytest.mark.parametrize("rope", [None, 10000.0])
+@pytest.mark.parametrize("vin", [ta.TA_VIN_KV, ta.TA_VIN_O])
+@pytest.mark.parametrize("n,H,Hkv,D", [(32, 8, 8, 100), (32, 16, 4, 96), (50, 8, 8, 96), (50, 16, 4, 100)])
+def test_streamed_wide_rows_give_the_bits_of_cached_ones(n, H, Hkv, D, vin, rope):
+    """One and two tiles, 128-wide: a forward call a little larger than the last-level cache is streamed, elements of its batch alone are cached, a few of their
+    fibres, which the other tests compare with the oracle, streamed again."""
+    B, heads = 5, 2 * H + Hkv + (H if vin else Hkv)
+    fibres, gen = round(340e6 / (2 * B * n * D * heads)), torch.Generator(device="cuda").manual_seed(n + D)
+    q, k, x = (torch.randn((B, fibres * n, h, D), generator=gen, device="cuda").bfloat16() for h in (H, Hkv, H if vin else Hkv))
+
+    def hop(form, q, k, x):
+        plan = ta.ta_plan_create(q.shape[0], H, Hkv, D, (q.shape[1] // n, n), ta.TA_BF16, True, rope_base=rope)
+        assert plan.hop_form(1, vin) == form and plan.hop_function(1, vin) == ("mfma_fwd_kernel" if H == Hkv else "mfma_fwd_shared_kernel")
+        o = torch.full_like(q, float("nan"))
+        ta.ta_axis_attn_forward(plan, 1, q, k, x, vin, o)
+        return o
+    whole = hop("rows_streamed", q, k, x)
+    assert torch.isfinite(whole).all()
+    for b in (0, 2, B - 1):
+        cached = hop("rows_cached", *(t[b:b + 1].contiguous() for t in (q, k, x)))
+        few = hop("rows_streamed", *(t[b:b + 1, :7 * n].contiguous() for t in (q, k, x)))
+        assert torch.equal(whole[b:b + 1], cached) and torch.equal(cached[:, :7 * n], few)
