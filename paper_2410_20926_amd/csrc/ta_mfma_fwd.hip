@@ -680,14 +680,27 @@ hipError_t launch_shared(const HopParams& p, const TileParams& tp, hipStream_t s
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }
 
+double call_bytes(const HopParams& p) { return 2.0 * p.B * p.fibres * p.n * p.D * (2.0 * p.Hq + p.Hkv + p.vin_heads); }
+
+// Ungrouped heads in 64-wide tiles, one tile, rows of a fibre 2 MB apart and more, calls that leave the last-level cache: each wave has 32 rows of four tensors under
+// way, and with the registers' five workgroups and more per CU they get in each other's way; with four (by their LDS) 64 hops of 36 to 60 features take 0.974 of the
+// time (fresh inputs each pass; 32 heads of 60, 32 x 1,024 112 -> 107 us, of 52 1.07 -> 1.03 of the serial requests before; three workgroups 1.03 of that up to
+// 48 features, below 280 MB no gain, up to 24 features 1.02).  Rows of up to 72 bytes want one run per XCD besides (xcd_order; 16 heads of 36 and more, from 280 MB on 1.05 -> 1.01 of
+// the serial requests, of 28 1.03 -> 1.01; of 40 2 per cent behind).
+constexpr size_t kFourPerCu = 33 * 1024;
+template <int D, int KT, FwdRows ROWS>
+bool far_rows(const HopParams& p, const TileParams& tp) { return D == 64 && KT == 1 && ROWS != kWhole && p.G == 1 && p.stride * tp.q_row >= 2 << 20; }
+
 template <int D, int KT, FwdRows ROWS>
 hipError_t launch(const HopParams& p, const TileParams& tp, hipStream_t s) {
-    const size_t smem = (size_t)kWavesPerBlock * (Geo<D>::kBufBytes + kTile * KT * 16);
+    const bool far = far_rows<D, KT, ROWS>(p, tp);
+    size_t smem = (size_t)kWavesPerBlock * (Geo<D>::kBufBytes + kTile * KT * 16);
+    if (far && p.D > 24 && call_bytes(p) >= 280e6) smem = kFourPerCu;
     const dim3 grid((unsigned)((p.Hq + kWavesPerBlock - 1) / kWavesPerBlock), tp.tiles_lo, (unsigned)p.B * tp.tiles_hi);
     const void* kf = p.rope ? (const void*)mfma_fwd_kernel<D, KT, ROWS, true> : (const void*)mfma_fwd_kernel<D, KT, ROWS, false>;
     HopParams pc = p;
     TileParams tc = tp;
-    tc.run_log2 = narrow_run_log2(kWavesPerBlock, grid);
+    tc.run_log2 = far && p.D <= 36 ? kLongestRun : narrow_run_log2(kWavesPerBlock, grid);
     void* args[2] = {&pc, &tc};
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }
@@ -724,7 +737,7 @@ namespace {
 // (1.2 GB) 247 and 256, 32 / 8 of 40, 25 x 28 x 24 x 8 (1.1 GB) 217 and 250.  In 64-wide tiles cached rows are level or ahead on one tile and where a group shares
 // the value input too (8 / 2 heads of 40, 1,765 x 37 x 3 135 and 145).
 FwdRows narrow_rows(const HopParams& p, int KT) {
-    const double bytes = 2.0 * p.B * p.fibres * p.n * p.D * (2.0 * p.Hq + p.Hkv + p.vin_heads);
+    const double bytes = call_bytes(p);
     if (p.D > 64) return bytes < 16e6 || (bytes >= 282e6 && bytes < 480e6) ? kNarrowStreamed : kNarrow;
     return KT == 2 && p.vin_heads == p.Hq && bytes >= 282e6 && bytes < 390e6 ? kNarrowStreamed : kNarrow;
 }

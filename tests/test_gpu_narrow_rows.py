@@ -112,3 +112,24 @@ def test_streamed_wide_rows_give_the_bits_of_cached_ones(n, H, Hkv, D, vin, rope
         cached = hop("rows_cached", *(t[b:b + 1].contiguous() for t in (q, k, x)))
         few = hop("rows_streamed", *(t[b:b + 1, :7 * n].contiguous() for t in (q, k, x)))
         assert torch.equal(whole[b:b + 1], cached) and torch.equal(cached[:, :7 * n], few)
+
+
+@pytest.mark.parametrize("D,n,H", [(36, 10, 16), (28, 32, 24), (60, 32, 12), (48, 9, 16), (20, 31, 16)])
+def test_rows_far_apart_give_the_bits_of_rows_nearby(D, n, H):
+    """Rows of a fibre 2 MB apart, in a call that leaves the last-level cache (and one that does not): the forward of one tile by heads alone, whose rows are nearer."""
+    fibres = -(-(2 << 20) // (H * D * 2)) + 3
+    for B in (1, -(-290000000 // (8 * n * fibres * H * D))):
+        gen = torch.Generator(device="cuda").manual_seed(D + n)
+        q, k, x = (torch.randn((B, n * fibres, H, D), generator=gen, device="cuda").bfloat16() for _ in range(3))
+
+        def hop(*rows):
+            plan = ta.ta_plan_create(rows[0].shape[0], rows[0].shape[2], rows[0].shape[2], D, (n, fibres), ta.TA_BF16, True)
+            assert plan.hop_function(0, ta.TA_VIN_O) == "mfma_fwd_kernel"
+            o = torch.full_like(rows[0], float("nan"))
+            ta.ta_axis_attn_forward(plan, 0, *rows[:2], rows[2], ta.TA_VIN_O, o)
+            return o
+        whole = hop(q, k, x)
+        assert torch.isfinite(whole).all()
+        for b in {0, B // 2, B - 1}:
+            for h in (0, 1, H // 2, H - 1):
+                assert torch.equal(whole[b:b + 1, :, h:h + 1], hop(*(t[b:b + 1, :, h:h + 1].contiguous() for t in (q, k, x)))), (B, b, h)
