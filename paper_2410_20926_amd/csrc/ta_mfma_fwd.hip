@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, KT == 1 && ROWS != kWhole ? 3 
         for (int i = 0; i < G::kPasses; ++i) {
             // Passes past the last row stay as they are; with two tiles the choice costs more than it saves (12 heads of width 100, 64 x 40 x 9, first hop
             // 77 us without it, 91 with; one tile, 2 x 20 x 28 x 23 80 and 75).
-            if (KT == 1 && i * G::kRowsPerPass >= rows_valid) break;
+            if (KT == 1 && i * G::kRowsPerPass >= rows_valid) continue;
             float c[4], sn[4];
             rope_sincos(row_pos(qt * kTile + i * G::kRowsPerPass + lrow), rev, c, sn);
             qreg[i] = rope_apply(qreg[i], c, sn);
@@ -352,6 +352,8 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, KT == 1 && ROWS != kWhole ? 3 
 #pragma unroll
     for (int i = 0; i < G::kPasses; ++i) {
         const int row = qt * kTile + i * G::kRowsPerPass + lrow;
+        // (passes without a row are left out, as under whole rows' branch: nothing is waited for behind these stores)
+        if (NARROW && qt * kTile + i * G::kRowsPerPass >= rows_valid) continue;
         if constexpr (NARROW)
             buffer_store_row_chunk<true, G::kChunks>(row_buffer(ob), rowoff[row].w, row < rows_valid, stg + i * G::kRowsPerPass * G::kPitch, lbyte, dbytes, o_whole);
         else if (row < rows_valid)
