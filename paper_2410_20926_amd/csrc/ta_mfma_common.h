@@ -392,8 +392,8 @@ inline uint32_t narrow_run_log2(int heads) {
     return r;
 }
 // The same for kernels with a form for fewer workgroups than CUs: such a call is as long as one workgroup, which the order's divisions come first in
-// (38 forward hops without them 0.955 of the time, 19 backward ones 0.96; 8 heads of 36, 16 x 100, 5.5 -> 5.2 us; 18 of 256 to 512 workgroups 1.02).
-// Workgroups that share a group's K are not among them: 21 forward hops 1.006 (9 x 51 x 2, 16 / 4 heads of 40, 4.5 -> 4.6).
+// (38 forward hops without them 0.955 of the time, 19 backward ones 0.96; 8 heads of 36, 16 x 100, 5.5 -> 5.2 us; 240 forward hops of groups 0.98;
+// 18 of 256 to 512 workgroups 1.02).
 inline uint32_t narrow_run_log2(int heads, const dim3& grid) {
     return (uint64_t)grid.x * grid.y * grid.z < 256 ? kAsTheyCome : narrow_run_log2(heads);
 }

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, KT == 1 && ROWS != kWhole ? 3 
         for (int i = 0; i < G::kPasses; ++i) {
             // Passes past the last row stay as they are; with two tiles the choice costs more than it saves (12 heads of width 100, 64 x 40 x 9, first hop
             // 77 us without it, 91 with; one tile, 2 x 20 x 28 x 23 80 and 75).
-            if (KT == 1 && i * G::kRowsPerPass >= rows_valid) continue;
+            if (KT == 1 && i * G::kRowsPerPass >= rows_valid) break;
             float c[4], sn[4];
             rope_sincos(row_pos(qt * kTile + i * G::kRowsPerPass + lrow), rev, c, sn);
             qreg[i] = rope_apply(qreg[i], c, sn);
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     uint32_t bx, by;
-    workgroup_xy<NARROW>(bx, by, tp.run_log2);
+    workgroup_xy<NARROW, true>(bx, by, tp.run_log2);
     const int h = (int)bx * kWavesPerBlock + w;                             // host guarantees Hq % 4 == 0 and G % 4 == 0
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
     const uint32_t tt = (blockIdx.z - zb * tp.tiles_hi) * tp.tiles_lo + by;
@@ -491,13 +491,26 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    gather_ready_all<NARROW>(qreg, qmis, qb, tp.q_row, lbyte, dbytes);
+    // One choice for all tensors: one for each is a wait for each, which a call that is as long as one workgroup shows (144 small hops up to 64 features 1.00 -> 0.974
+    // of the time of requests in one piece, 128-wide 0.92 -> 0.91; without a choice, every row put together, larger calls of whole units take 2 per cent longer).
+    if constexpr (NARROW) {
+        auto ready = [&](auto whole) {
+            auto all = [&](auto& raw, uint32_t mis) {
 #pragma unroll
-    for (int j = 0; j < KT; ++j)
-        if (j < kt_end) {
-            gather_ready_all<NARROW>(ksh[j], kmis[j], kb, tp.k_row, lbyte, dbytes);
-            if (v_shared) gather_ready_all<NARROW>(vsh[j], vmis[j], vb, tp.v_row, lbyte, dbytes);
-        }
+                for (int i = 0; i < (int)(sizeof(raw) / sizeof(raw[0])); ++i)
+                    raw[i] = decltype(whole)::value ? row_only(raw[i], lbyte, dbytes) : gather_ready<true>(raw[i], (mis >> i) & 1u, lbyte, dbytes);
+            };
+            all(qreg, qmis);
+#pragma unroll
+            for (int j = 0; j < KT; ++j)
+                if (j < kt_end) {
+                    all(ksh[j], kmis[j]);
+                    if (v_shared) all(vsh[j], vmis[j]);
+                }
+        };
+        if (whole_units(qb, tp.q_row, dbytes) && whole_units(kb, tp.k_row, dbytes) && whole_units(vb, tp.v_row, dbytes)) ready(std::true_type{});
+        else ready(std::false_type{});
+    }
 
     // ---- rotary encoding of the gathered rows, by their position on the axis: Q (private) and this
     //      wave's quarter of every K tile, before they enter LDS ---------------------------------
@@ -677,7 +690,7 @@ hipError_t launch_shared(const HopParams& p, const TileParams& tp, hipStream_t s
                             : (vs ? (const void*)mfma_fwd_shared_kernel<D, KT, true, ROWS, false> : (const void*)mfma_fwd_shared_kernel<D, KT, false, ROWS, false>);
     HopParams pc = p;
     TileParams tc = tp;
-    tc.run_log2 = narrow_run_log2(kWavesPerBlock);
+    tc.run_log2 = narrow_run_log2(kWavesPerBlock, grid);
     void* args[2] = {&pc, &tc};
     return hipLaunchKernel(kf, grid, dim3(kWavesPerBlock * 64), args, smem, s);
 }
