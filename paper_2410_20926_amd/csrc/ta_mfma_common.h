@@ -64,11 +64,17 @@ __device__ inline bool whole_units(const char* base, uint32_t pitch, uint32_t db
 // backward waited for memory five times one after the other, and the two of the two-tile forward twice.  In two parts (32 / 8 heads of 96, 32 x 32 x 32, the
 // backward hop along the second axis 338 -> 276 us, forward 122 -> 104; 12 heads of 96, 134 x 57 x 8, forward 196 -> 124; 8 / 2 heads of 96, 4 x 3 x 6 x 5 x 3,
 // a backward hop 15.3 -> 11.9).  `mis`: the row starts 8 bytes into an aligned unit.
-template <bool NARROW, bool NT>
+// PER_LANE: a 64-bit address per lane instead, for a kernel that has no registers left for the uniform part.
+template <bool NARROW, bool NT, bool PER_LANE = false>
 __device__ inline u32x4 gather_request(const char* base, uint32_t rowoff, uint32_t lbyte, uint32_t dbytes, uint32_t& mis) {
     if constexpr (!NARROW) {
         mis = 0u;
         const u32x4* src = reinterpret_cast<const u32x4*>(base + (rowoff + lbyte));
+        return NT ? __builtin_nontemporal_load(src) : *src;
+    } else if constexpr (PER_LANE) {
+        const char* row = base + rowoff;
+        mis = (uint32_t)reinterpret_cast<uintptr_t>(row) & 8u;
+        const u32x4* src = reinterpret_cast<const u32x4*>(row + (int32_t)(lbyte + 16 <= mis + dbytes ? lbyte - mis : dbytes - 16));
         return NT ? __builtin_nontemporal_load(src) : *src;
     } else {
         // `base` is uniform: a uniform 16-byte boundary and 32-bit offsets from it, so that no address takes two registers

@@ -121,6 +121,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
     if (qb * tiles * kTile >= nreal) je = jb;
 
     // this wave's share of a block: rows w * kRowsPerPass + lrow + i * kRows; rows past the fibre's end: its last one, never visible
+    // (Up to 60 features in step spilled a register at three waves per SIMD: 32 heads of 40, 176 x 207 x 2, 357 -> 370 us, now 359)
+    constexpr bool kPerLane = D == 64 && NW == 4 && FORM == kBlocks && !ROPE;
     struct Raw { u32x4 v[kMine]; uint32_t mis; };
     const int myrow = w * G::kRowsPerPass + lrow;
     auto request = [&](const char* base, uint32_t pitch, int j, Raw& raw) {
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
         for (int i = 0; i < kMine; ++i) {
             const uint32_t r = (uint32_t)min(j * kKeys + i * kRows + myrow, n - 1);
             uint32_t mis;
-            raw.v[i] = gather_request<NARROW, false>(base, (tok0 + r * stride) * pitch, lbyte, dbytes, mis);
+            raw.v[i] = gather_request<NARROW, false, kPerLane>(base, (tok0 + r * stride) * pitch, lbyte, dbytes, mis);
             raw.mis |= mis ? 1u << i : 0u;
         }
     };
@@ -141,7 +143,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && FORM != kPhases ? 3 : 2) void m
 #pragma unroll
         for (int i = 0; i < kMine; ++i) {
             uint32_t mis;
-            raw.v[i] = gather_request<NARROW, false>(base, min(__builtin_elementwise_add_sat(off, (uint32_t)(i * kRows) * hop), last), lbyte, dbytes, mis);
+            raw.v[i] = gather_request<NARROW, false, kPerLane>(base, min(__builtin_elementwise_add_sat(off, (uint32_t)(i * kRows) * hop), last), lbyte, dbytes, mis);
             raw.mis |= mis ? 1u << i : 0u;
         }
         off = min(__builtin_elementwise_add_sat(off, (uint32_t)kKeys * hop), last);
