@@ -68,7 +68,8 @@ struct UnRope {
 template <typename PosFn>
 __device__ inline UnRope<PosFn> unrope(const HopParams* p, PosFn fn) { return UnRope<PosFn>{p, fn}; }
 
-template <int D, bool NARROW = false, typename Enc = NoRope>
+// BRANCH: narrow rows that do not exist are left out under a branch.
+template <int D, bool NARROW = false, bool BRANCH = !NARROW, typename Enc = NoRope>
 __device__ inline void store_tile(const f32x16 (&acc)[Geo<D>::kDTiles], float mult, char* buf, const u32x4* rowoff,
                                   int which, char* gbase, const u32x4 (&old)[Geo<D>::kDTiles * 2], bool add_old, int rows_valid, int lane,
                                   uint32_t dbytes = 0, const Enc enc = Enc{}) {
@@ -110,7 +111,10 @@ __device__ inline void store_tile(const f32x16 (&acc)[Geo<D>::kDTiles], float mu
                 }
                 return u32x4{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])};
             };
-            if constexpr (NARROW) {
+            if constexpr (NARROW && BRANCH) {
+                const uint32_t fbyte = (uint32_t)(half * 64 + (lane & 7) * 8) * 2;
+                if (row < rows_valid) store_chunk<true>(gbase, tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, fbyte, dbytes, value());
+            } else if constexpr (NARROW) {
                 const uint32_t fbyte = (uint32_t)(half * 64 + (lane & 7) * 8) * 2;
                 buffer_store_chunk<true>(row_buffer(gbase), tile_out_offset<D>(rowoff, which, half, i, lane) - fbyte, row < rows_valid, fbyte, dbytes, value(), dbytes % 16 == 0);
             } else {

@@ -45,6 +45,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     using L = LongGeo<D>;
     constexpr int kRowsPass = kWaves * G::kRowsPerPass;   // rows the workgroup fetches per pass
     constexpr int kMine = kRowsB / kRowsPass;
+    // Narrow rows in 64-wide tiles, the value input shared: a third of the scalar registers that the loops spill belongs to row buffers and to the two ways of putting
+    // rows together, so that a tile of its own is put together row by row and stored under a branch (32 / 8 heads of 40, 67 x 463 x 2, 1,550 -> 1,596 us with them, 1,527
+    // now; of 60, 100 x 200 113 -> 116, now 111; per-head values and 128-wide tiles 1 to 3 per cent behind that way).
+    constexpr bool kRowByRow = NARROW && VS && D == 64, kBranch = !NARROW || kRowByRow;
     const HopParams& p = bp.hop;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63;
@@ -85,9 +89,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
         const int lane_ = again(lane), lrow = lane_ / G::kChunks, r32 = lane_ & 31, hf = lane_ >> 5;
         const uint32_t lbyte = (uint32_t)(lane_ % G::kChunks) * 16u;
 #pragma unroll
-        for (int i = 0; i < G::kPasses; ++i)
+        for (int i = 0; i < G::kPasses; ++i) {
             raw[i] = gather_noted<NARROW, false>(base, (tok0 + (uint32_t)min(kTile * t + i * G::kRowsPerPass + lrow, n - 1) * stride) * pitch, lbyte, dbytes, i, mis);
-        gather_ready_all<NARROW>(raw, mis, base, pitch, lbyte, dbytes);
+            if constexpr (kRowByRow) raw[i] = gather_ready<NARROW>(raw[i], (mis >> i) & 1u, lbyte, dbytes);
+        }
+        if constexpr (!kRowByRow) gather_ready_all<NARROW>(raw, mis, base, pitch, lbyte, dbytes);
         if (ROPE && turn) {
             float rev[4];
             rope_rates(p, lane_ % G::kChunks, rev);
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
                 set_rowoff(a);
                 u32x4 old[G::kDTiles * 2] = {};
                 if (bp.accumulate) prefetch_tile<D, NARROW>(old, rowoff, 0, dqb, again(lane), dbytes);
-                store_tile<D, NARROW>(acc, p.scale, transit, rowoff, 0, dqb, old, bp.accumulate != 0, min(kTile, n - kTile * a), again(lane), dbytes,
+                store_tile<D, NARROW, kBranch>(acc, p.scale, transit, rowoff, 0, dqb, old, bp.accumulate != 0, min(kTile, n - kTile * a), again(lane), dbytes,
                                       unrope(&p, [&](int r) { return (float)(kTile * a + r); }));
             }
         }
@@ -376,11 +382,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
             if (VS) {
                 char* dxb = slice(bp.d_vin, g);
                 if (bp.acc_x) prefetch_tile<D, NARROW>(old, rowoff, 2, dxb, again(lane), dbytes);
-                store_tile<D, NARROW>(dx, 1.f, transit, rowoff, 2, dxb, old, bp.acc_x != 0, rows_c, again(lane), dbytes);
+                store_tile<D, NARROW, kBranch>(dx, 1.f, transit, rowoff, 2, dxb, old, bp.acc_x != 0, rows_c, again(lane), dbytes);
             }
             char* dkb = slice(bp.dk, g);
             if (bp.acc_k) prefetch_tile<D, NARROW>(old, rowoff, 1, dkb, again(lane), dbytes);
-            store_tile<D, NARROW>(dk, p.scale, transit, rowoff, 1, dkb, old, bp.acc_k != 0, rows_c, again(lane), dbytes,
+            store_tile<D, NARROW, kBranch>(dk, p.scale, transit, rowoff, 1, dkb, old, bp.acc_k != 0, rows_c, again(lane), dbytes,
                                   unrope(&p, [&](int r) { return (float)(kTile * c + r); }));
         }
     }
