@@ -508,7 +508,15 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void mfma_fwd_shared_kernel
                     if (v_shared) all(vsh[j], vmis[j]);
                 }
         };
-        if (whole_units(qb, tp.q_row, dbytes) && whole_units(kb, tp.k_row, dbytes) && whole_units(vb, tp.v_row, dbytes)) ready(std::true_type{});
+        if constexpr (D == 128 && ROPE && VS) {           // (128 registers, four waves per SIMD; 129 with one choice: 32 / 8 heads of 96, 3 per cent)
+            gather_ready_all<true>(qreg, qmis, qb, tp.q_row, lbyte, dbytes);
+#pragma unroll
+            for (int j = 0; j < KT; ++j)
+                if (j < kt_end) {
+                    gather_ready_all<true>(ksh[j], kmis[j], kb, tp.k_row, lbyte, dbytes);
+                    gather_ready_all<true>(vsh[j], vmis[j], vb, tp.v_row, lbyte, dbytes);
+                }
+        } else if (whole_units(qb, tp.q_row, dbytes) && whole_units(kb, tp.k_row, dbytes) && whole_units(vb, tp.v_row, dbytes)) ready(std::true_type{});
         else ready(std::false_type{});
     }
 
