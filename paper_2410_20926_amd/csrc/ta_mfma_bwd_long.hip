@@ -80,6 +80,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
         if (D == 128) asm volatile("" : "+v"(x));
         return x;
     };
+    // But for the two products of a step where the heads of a group share the value input: whole rows have the registers there, and the arithmetic is in the chain (16 / 4
+    // heads of 128, 1,000 x 40, 1,482 -> 1,535 us with it, 1,471 now; 8 / 2, 700 x 60, encoded, 938 -> 981, now 929; 32 / 8, 200 x 64, 328 -> 319, now 312).
+    auto hot = [&](int x) { return VS && !NARROW ? x : again(x); };
     auto chunk_byte = [&]() { return (uint32_t)(again(lane) % G::kChunks) * 16u; };
     auto slice = [&](const Tensor& t, int head) { return reinterpret_cast<char*>(t.p) + ((int64_t)b * t.sb + (int64_t)head * t.sh) * 2; };
     // rows of tile t as operands contracted over the features, through this wave's transit tile
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     };
     auto scores = [&](const char* tile, const u32x4 (&op)[G::kKSteps]) {
         f32x16 x = {};
-        const int l = again(lane);
+        const int l = hot(lane);
         const char* at = tile + (l & 31) * G::kPitch + (l >> 5) * 16;
 #pragma unroll
         for (int s = 0; s < G::kKSteps; ++s) x = mma(*reinterpret_cast<const u32x4*>(at + 32 * s), op[s], x);
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_bwd_long_kernel(BwdParams
     };
     // acc^T += (tile)^T w, contracted over the tile's rows
     auto contract = [&](const char* tile, const u32x4 (&wt)[2], f32x16 (&acc)[G::kDTiles]) {
-        const int l = again(lane);
+        const int l = hot(lane);
         const char* from = tile + (4 * (l >> 5) + ((l & 15) >> 2)) * G::kPitch + (16 * ((l >> 4) & 1) + 4 * (l & 3)) * 2;
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2)
