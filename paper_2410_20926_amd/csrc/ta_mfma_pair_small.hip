@@ -17,6 +17,14 @@ namespace ta {
 namespace {
 
 using namespace mfma;
+template <bool NARROW, int N>
+__device__ inline void ready_rows(u32x4 (&raw)[N], uint32_t mis, const char*, uint32_t, uint32_t lbyte, uint32_t dbytes) {
+    if constexpr (NARROW) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) raw[i] = gather_ready<NARROW>(raw[i], (mis >> i) & 1u, lbyte, dbytes);
+    }
+}
+
 
 constexpr int kWaves = 4;
 constexpr int kMaxSlab = 256;
@@ -115,8 +123,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_fwd_pair_small_kernel(Hop
         }
         __builtin_amdgcn_sched_barrier(0);
         auto scores = [&](u32x4 (&q)[G::kPasses], u32x4 (&k)[G::kPasses], uint32_t mq, uint32_t mk, int n, int count) {
-            gather_ready_all<NARROW>(q, mq, qb, sp.q_row, lbyte, dbytes);
-            gather_ready_all<NARROW>(k, mk, kb, sp.k_row, lbyte, dbytes);
+            ready_rows<NARROW>(q, mq, qb, sp.q_row, lbyte, dbytes);
+            ready_rows<NARROW>(k, mk, kb, sp.k_row, lbyte, dbytes);
             if constexpr (ROPE) {
 #pragma unroll
                 for (int j = 0; j < G::kPasses; ++j) {
@@ -143,7 +151,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void mfma_fwd_pair_small_kernel(Hop
         const int fa = r32 / n1, aa = r32 - fa * n1;
         const f32x16 s1 = scores(q1, k1, mq1, mk1, n1, c1);
         const float inv1 = softmax(s1, visible(h1, fa, aa, c1 / n1, tok0 + (uint32_t)(ta * sp.fpt1 + fa), (int64_t)slab * n2 + ta * sp.fpt1 + fa), pop);
-        gather_ready_all<NARROW>(x1, mx1, xb, sp.v_row, lbyte, dbytes);
+        ready_rows<NARROW>(x1, mx1, xb, sp.v_row, lbyte, dbytes);
         lds_wave_sync();
         stage_rows<D>(stg, x1);
         lds_wave_sync();
