@@ -397,11 +397,11 @@ inline uint32_t narrow_run_log2(int heads) {
     for (; heads > 1 && r > 4; heads /= 2) --r;
     return r;
 }
-// The same for kernels with a form for fewer workgroups than CUs: such a call is as long as one workgroup, which the order's divisions come first in
-// (38 forward hops without them 0.955 of the time, 19 backward ones 0.96; 8 heads of 36, 16 x 100, 5.5 -> 5.2 us; 240 forward hops of groups 0.98;
-// 18 of 256 to 512 workgroups 1.02).
+// The same for kernels with a form for few workgroups: such a call is as long as one workgroup, which the order's divisions come first in (300 drawn calls of up to 8 MB: 0.985 of
+// the time up to 180 workgroups, of groups 0.98).  From there to 252 the order is worth as much: taken as they come, a hop's workgroups find the last hop's output in another XCD's
+// L2 (0.998; 12 heads of 36, 16 x 27 x 5, 204 to 240 workgroups, 15.2 -> 16.6 us), and from 256 on more (1.005).
 inline uint32_t narrow_run_log2(int heads, const dim3& grid) {
-    return (uint64_t)grid.x * grid.y * grid.z < 256 ? kAsTheyCome : narrow_run_log2(heads);
+    return (uint64_t)grid.x * grid.y * grid.z < 192 ? kAsTheyCome : narrow_run_log2(heads);
 }
 
 // Launch geometry computed on the host.
