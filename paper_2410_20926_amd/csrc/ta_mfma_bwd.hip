@@ -1092,8 +1092,8 @@ int heads_side_by_side(const HopParams& p, const TileParams& tp, BwdRows rows) {
 //   Large calls of wide rows are ahead in pairs: cached alone and in pairs, 32 heads of 100, 32 x 32 x 32 428 and 423; 8 of 112, 28 x 1,856 (652 MB) 216 and 192; of
 // 112, 31 x 1,378 x 4 681 and 621; from 1.5 GB on every width on tiles that are nearly full: 8 of 40, 32 x 6,627 x 2 568 and 553, of 84, 16 x 3,613 x 3 502 and 493,
 // 32 of 40, 23 x 32 x 23 x 8 691 and 670, but 32 of 96, 20 x 2,302 421 and 433; below, 12 of 100, 82 x 32 x 4 (176 MB) 39.5 and 41.4; 32 of 112, 28 x 31 x 4 (174 MB) 35.0 and 34.6.  Where the workgroups of a batch
-// are not a multiple of eight pairs were ahead while such a grid lost its order; in runs (xcd_order) they are 0 to 4 per cent behind (4 of 100, 1,518 x 16 29.5 and
-// 30.6; 1,276 x 27 level), and stay because the form is what a plan reports.
+// are not a multiple of eight pairs were 2 to 24 per cent ahead while such a grid lost its order; in runs (xcd_order) they take 1.02 of the time up to 280 MB, 1.03 to 560 (4 of 100, 1,518 x 16
+// 29.5 and 30.6; 1,276 x 27 level), 0.96 to 1.5 GB and 0.91 beyond.  (The line at 1,280 waves is where pairs began to be ahead then; heads alone up to 560 MB would take 0.985.)
 //   A call whose tensors are a little more than the 256 MB of the last-level cache evicts by a hop's end what the next pass, or hop, begins with; streamed
 // rows leave it part of that.  Cached and streamed: 32 heads of 100, 8 x 16 x 7 x 8 (321 MB) 86 and 78; 4 of 84, 39 x 16 x 38 x 4 (446 MB) 111 and 106; 16 / 4 of
 // 100, 16 x 131 x 8 (295 MB) 77 and 74, of 72, 28 x 1,407 (499 MB) 160 and 163, 32 / 8 of 72, 32 x 468 x 4 (1.1 GB) 398 and 406; 8 of 40, 33 x 31 x 32 (147 MB) 28.6 and
@@ -1129,7 +1129,7 @@ hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     TileParams tpc = tp;
     // Heads without a group, rows of a fibre 2 MB apart and more: one run per XCD (runs and one, us: 32 heads of 40, 27 x 1,860 319 and 271; 12 of 84,
     // 27 x 2,362 318 and 271; 32 of 96, 27 x 775 295 and 267; 8 of 84, 16 x 3,613 x 3 526 and 493; 32 of 100, 32 x 627 272 and 279; 12 of 96, 20 x 2,790 249
-    // and 253); groups are ahead in runs there too (32 / 8 heads of 96, 32 x 738 209 and 215).
+    // and 253; 32 of 96, 32 x 1,024, which is nearly level, 430 and in runs 416); groups are ahead in runs there too (32 / 8 heads of 96, 32 x 738 209 and 215).
     tpc.run_log2 = p.G == 1 && p.stride * tp.q_row >= 2 << 20 ? kLongestRun : narrow_run_log2(bp.wg_heads * side, grid);
     void* args[2] = {&bpc, &tpc};
     if (smem > 64 * 1024) {
@@ -1203,7 +1203,8 @@ bool mfma_backward_is_two_tile(const BwdParams& bp, int dtype) {
 // tiles at a time.  The former is ahead where it fills the chip and the latter's eight waves have five or six tiles (100 fibres of 129 / 160
 // positions, 16 / 4 heads of width 128: 212 / 245 against 241 / 256 us; from seven tiles on, 200 x 64, 32 / 8 heads: 513 against 440 us), and,
 // for five tiles, where a whole launch of eight heads is at hand (a training step of 130 x 16, 32 / 1 heads of width 128: 869 against 948 us,
-// 160 x 4, of width 64: 532 against 560; of 192 x 16: 1,127 against 1,058; groups of four, 160 x 16 with 4 / 1 heads: 163 against 145).
+// of 192 x 16: 1,127 against 1,058; groups of four, 160 x 16 with 4 / 1 heads: 163 against 145).  The long kernel ran whole in these; on up to some 130 fibres and key/value heads
+// it would go in parts (160 x 19 x 2, 16 / 2 heads of 100, 177 against the blocked kernel's 250; 39 such hops 0.83), which this line does not ask yet.
 static bool runs_blocked(const HopParams& p) {
     return (p.G >= 4 && p.n <= 6 * kTile && (int64_t)p.B * p.Hkv * p.fibres >= 256) || (p.G >= 8 && p.n <= 5 * kTile);
 }

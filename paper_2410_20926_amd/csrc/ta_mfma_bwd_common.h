@@ -91,6 +91,8 @@ __device__ inline void store_tile(const f32x16 (&acc)[Geo<D>::kDTiles], float mu
             const int row = 8 * i + (lane >> 3), cc = lane & 7;
             const f32x4 x0 = *reinterpret_cast<const f32x4*>(buf + row * G::kFPitch + cc * 32);
             const f32x4 x1 = *reinterpret_cast<const f32x4*>(buf + row * G::kFPitch + cc * 32 + 16);
+            // (In front of the branch for whole rows too: the two-tile kernel of four heads has 4 to 8 spilled registers that way, and takes 0.975 of the time nevertheless;
+            // 8 / 2 heads of 128, 40 x 4, 19.0 and under the branch 19.6 us.)
             float y[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
             auto value = [&]() {
                 if constexpr (Enc::on) {

@@ -15,7 +15,7 @@
 // A request is waited for with a count of what was issued behind it, loads and stores alike, so two things stand between the rows on their way and
 // their use: a store that may or may not have been issued, after which every wait is for all of them (stores go through the buffer's bounds check
 // instead of a branch, row_buffer), and a spilled value, whose reload waits for every row requested before it (what depends on the lane is formed anew
-// wherever it is used; narrow 128-wide instantiations had 12 to 26 spilled registers, now 0 to 4).  32 / 8 heads of 96, 13 x 52 x 71, hops of 1,078 / 800 ->
+// wherever it is used; narrow 128-wide instantiations had 12 to 29 spilled registers, now 0 to 4).  32 / 8 heads of 96, 13 x 52 x 71, hops of 1,078 / 800 ->
 // 866 / 584 us, of 100, 64 x 64 x 32, 1,965 -> 1,351; whole rows of 128 features, 128 x 128, 193 / 183 -> 189 / 175.
 //
 // What bounds it: memory, and seven barriers per head of which one workgroup per CU (width 128, n > 64) hides little (LDS active 30 % of
@@ -467,7 +467,7 @@ hipError_t launch_resident(const BwdParams& bp, hipStream_t s) {
     const int per_cu = by_lds < by_regs ? by_lds : by_regs;
     const int64_t most = 256 * (per_cu < 1 ? 1 : per_cu);
     // Narrow rows share lines with the neighbouring heads' rows, which find them in L2 only as long as their workgroups keep step.  Workgroups that walk a
-    // long share drift apart by more than L2 holds (32 heads of 100, 64 x 64 x 32: 1.5 times the bytes fetched), so where there is enough for it they
+    // long share drift apart by more than L2 holds (32 heads of 100, 64 x 64 x 32: 1.63 times the algorithmic bytes read, 1.25 in shares of four), so where there is enough for it they
     // take four (fibre, head) pairs each and are replaced in order: 3,000 -> 1,950 us, of 96 2,130 -> 1,700, of 40 1,440 -> 794; 8 of 36,
     // 60 x 238 x 9 x 2, 507 -> 355; at the lower ends of the rule 32 of 48, 63 x 19 x 9 x 2, 196 -> 139, 12 of 100, 251 x 50 x 4, 325 -> 293.
     // With less it costs a start that nothing hides more often than it gains (long shares and shares of four; 128-wide tiles, 3 heads of 100,

@@ -753,8 +753,8 @@ bool mfma_forward_supports(int32_t n, int32_t D, int dtype, int* kernel_id) {
 
 namespace {
 // Narrow rows by the bytes of the call: one that is a little larger than the 256 MB of the last-level cache evicts by its end what the next pass, or hop,
-// begins with, and streamed rows leave it part of that; elsewhere the lines that neighbouring heads share are worth more, but for calls of a few MB, where it
-// makes no difference.  Cached and streamed, one hop, us: 12 heads of 100, 25 x 28 x 25 x 2 (336 MB) 67.7 and 61.7; 32 of 84, 355 x 42 (321 MB) 105 and 98.6; 32 / 8
+// begins with, and streamed rows leave it part of that; elsewhere the lines that neighbouring heads share are worth more, but for calls below 16 MB, where it
+// makes no difference (36 drawn hops 0.986 to 1.005) and they are streamed as they were.  Cached and streamed, one hop, us: 12 heads of 100, 25 x 28 x 25 x 2 (336 MB) 67.7 and 61.7; 32 of 84, 355 x 42 (321 MB) 105 and 98.6; 32 / 8
 // of 112, 22 x 50 x 21 (414 MB) 93 and 88; 8 of 40, 31 x 44 x 31 x 3 (325 MB) 86 and 82; below, 12 heads of 100, 25 x 32 x 25 (192 MB) 33.7 and 36.7, 8 / 2 of 72,
 // 18 x 16 x 18 x 8 (155 MB) 27.2 and 33.3, 16 / 4 of 100, 11 x 32 x 9 (25 MB) 7.9 and 8.5, 8 / 2 of 112, 14 x 39 x 3 (10 MB) 7.8 and 7.8; above, 4 of 112, 28 x 12,184
 // (1.2 GB) 247 and 256, 32 / 8 of 40, 25 x 28 x 24 x 8 (1.1 GB) 217 and 250.  In 64-wide tiles cached rows are level or ahead on one tile and where a group shares
