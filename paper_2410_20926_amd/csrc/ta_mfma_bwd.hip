@@ -46,7 +46,7 @@ __global__ __launch_bounds__(512, 2) void mfma_bwd_kernel(BwdParams bp, TilePara
     const int w = SIDE && nw == 1 ? 0 : wave;             // heads without a group stand side by side in a workgroup, each on its own
 
     uint32_t bx, ty;
-    workgroup_xy<NARROW, true>(bx, ty, tp.run_log2);
+    workgroup_xy<NARROW, !ROPE>(bx, ty, tp.run_log2);     // (encoded rows: no form for few workgroups, which costs them 1 per cent and gains nothing)
     const int g = SIDE && nw == 1 ? (int)bx * bp.side + wave : (int)bx;
     const int h = g * p.G + (MULTI ? bp.head_base : 0) + w;
     const uint32_t zb = blockIdx.z / tp.tiles_hi;
@@ -1130,7 +1130,7 @@ hipError_t launch(const BwdParams& bp, const TileParams& tp, hipStream_t s) {
     // Heads without a group, rows of a fibre 2 MB apart and more: one run per XCD (runs and one, us: 32 heads of 40, 27 x 1,860 319 and 271; 12 of 84,
     // 27 x 2,362 318 and 271; 32 of 96, 27 x 775 295 and 267; 8 of 84, 16 x 3,613 x 3 526 and 493; 32 of 100, 32 x 627 272 and 279; 12 of 96, 20 x 2,790 249
     // and 253; 32 of 96, 32 x 1,024, which is nearly level, 430 and in runs 416); groups are ahead in runs there too (32 / 8 heads of 96, 32 x 738 209 and 215).
-    tpc.run_log2 = p.G == 1 && p.stride * tp.q_row >= 2 << 20 ? kLongestRun : narrow_run_log2(bp.wg_heads * side, grid);
+    tpc.run_log2 = p.G == 1 && p.stride * tp.q_row >= 2 << 20 ? kLongestRun : p.rope ? narrow_run_log2(bp.wg_heads * side) : narrow_run_log2(bp.wg_heads * side, grid);
     void* args[2] = {&bpc, &tpc};
     if (smem > 64 * 1024) {
         const hipError_t e = allow_dynamic_lds(kf, (int)smem);
