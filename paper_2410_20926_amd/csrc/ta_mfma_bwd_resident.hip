@@ -117,7 +117,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
     // What depends on the lane is formed anew wherever it is used, from a copy of the lane's number that the compiler cannot look
     // through: kept over the loop it would be spilled, and a reload waits for every row requested before it.  64-wide tiles have more room: narrow or
     // encoded rows form it once per head (32 / 8 heads of 40, 9 x 38 x 42 x 8, 803 -> 754 us), whole rows of three and four tiles keep it (8 / 2 heads, 50 x 70, 23.3 -> 22.2 us
-    // against new row addresses, 32 / 8, 100 x 200, 176 -> 168), of two all but row addresses (kept, they take 27 registers more and a wave per SIMD: 32 / 8 heads, 500 x 40, 113 against 145).
+    // against new row addresses, 32 / 8, 100 x 200, 176 -> 168; encoded, 128 x 128, 116.5 before any was formed anew, 117.9 once per head, 104.0), of two all but row addresses (kept, they take 27 registers more and a wave per SIMD: 32 / 8 heads, 500 x 40, 113 against 145).
     int head_lane = threadIdx.x & 63;
     auto fresh_lane = [&]() {
         int l = head_lane;
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(128 * TM, 2) void mfma_bwd_resident_kernel(BwdParam
         for (int hl = 0; hl < (MODE == kOne ? 1 : p.G); ++hl) {
             const int h = at.g * p.G + hl, hv = VS ? at.g : h;
             const bool last_head = MODE == kOne || hl + 1 == p.G;
-            if (D == 64 && (NARROW || ROPE)) asm volatile("" : "+v"(head_lane));
+            if (D == 64 && (NARROW || (ROPE && TM == 2))) asm volatile("" : "+v"(head_lane));
             const int l_ = fresh_lane(), r32 = kept_lane() & 31, hf = kept_lane() >> 5;
             const int qr = kTile * w + r32;               // this lane's query row
             const uint32_t nat = (uint32_t)((l_ & 31) * G::kPitch + (l_ >> 5) * 16);
